@@ -2,7 +2,7 @@
 """Benchmark of the LASER-KV prefill-compression hot path on one MI355X.
 
 A step is one pass of the whole path (score + LSH + top-k + gather-append) over one layer of one
-synthetic context: every block of the workload, issued back to back on one stream with no host
+synthetic context: every block of the workload, enqueued on one stream with no host
 synchronisation, inputs resident in HBM.  Prints ONE JSON line: context tokens per second per layer,
 the roofline position of the dominant kernel (timed live with HIP events around every kernel launch)
 and the CPU oracle's rate on the same box as a reported baseline.
@@ -23,7 +23,7 @@ PEAK_HBM_GBS = 8000.0
 
 
 def algorithmic_work(wl, B):
-    """Per-launch algorithmic work of every kernel: (bound, amount, unit). One launch = one block, all KV heads.
+    """Algorithmic work of every kernel per block, all KV heads: (bound, amount, unit).
     flops: 2*d*rows*S per contraction (look-back keys and the query projections are extras, not counted);
     bytes: what the step must move at least once."""
     d, s, hk = wl.head_dim, wl.s_block, wl.n_kv_heads
@@ -161,12 +161,15 @@ def measure(wl, args, dev, cpu_seconds):
                            n_kv_heads=wl.n_kv_heads, head_dim=wl.head_dim, budget_per_block=comp.B,
                            blocks=wl.n_blocks, layers_timed=1, launch=args.mode, sequences=args.batch,
                            step_time="median of the timed steps", row_statistics=args.lse,
-                           entry="laserkv_select_block+laserkv_append" if args.unfused else "laserkv_compress_block"),
+                           entry="laserkv_select_block+laserkv_append" if args.unfused else
+                           ("laserkv_compress_layer" if len(plan) < wl.n_blocks else "laserkv_compress_block")),
                roofline=None, cpu_baseline=None)
 
     work = algorithmic_work(wl, comp.B)
     if not args.unfused:  # the last kernel selects and appends
         work["select"] = ("hbm", work["select"][1] + work["append"][1])
+    if len(plan) < wl.n_blocks:  # one call for the layer: the key projection is part of the second sweep
+        work["sweep1"], work["sweep2"] = work["sweep2"], work["sweep1"]
     if args.attend:
         res["attend_cache"] = measure_attend(wl, comp, ddev, dev, cases=args.attend_case.split(","))
     if args.pipeline and args.batch == 1 and args.lse == "own":
@@ -179,6 +182,7 @@ def measure(wl, args, dev, cpu_seconds):
         if not v["launches"]:
             continue
         bound, amount = work[name]
+        amount *= wl.n_blocks / v["launches"]
         dur_s = v["avg_us"] * 1e-6
         if bound == "mfma":
             peak, achieved, unit = peak_mfma, amount / dur_s / 1e12, "TFLOP/s"

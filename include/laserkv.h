@@ -154,6 +154,38 @@ int laserkv_compress_block(laserkv_ctx* ctx,
                            int64_t cache_len, int64_t cache_cap,
                            void* hip_stream);
 
+/* Every block of a layer in one call, for callers that hold the layer's keys, values and window queries of the whole
+ * context: the results of laserkv_compress_block called block by block (block t covers tokens [t*s_block,
+ * min((t+1)*s_block, n_tok)), its window is its last w tokens under the causal mask, its budget is
+ * laserkv_partition(B, n, alpha, block length), its look-back keys are the previous block's local window, Sec. 3.2),
+ * appended to an empty cache.  The look-back keys are read from k itself (the local window is always kept), so the
+ * blocks are independent and share a few launches.  Scores are summed in another order than in the block call.
+ *   q_win        DEVICE [n_blocks, H_q, w, d]
+ *   k, v         DEVICE [H_kv, n_tok, d]
+ *   row_lse_complete  DEVICE array of n_blocks DEVICE pointers to [H_q, w] float tensors as laserkv_set_row_lse_complete
+ *                takes (one per block), or NULL: then the context's own row_lse setting holds for every block
+ *   keep_last    DEVICE out [H_kv, B_last] int32, the last block's kept indices, or NULL
+ *   k_cache, v_cache, cache_pos   as for laserkv_append; rows [0, sum of the blocks' B_t) are written
+ *   workspace    DEVICE scratch of at least laserkv_layer_workspace_bytes(ctx, n_tok, s_block, w, n_local) bytes, n_local
+ *                being that of a full block; 256-byte aligned, owned by the caller, dead after the call's kernels
+ * The call allocates nothing and is asynchronous on hip_stream.  Errors: those of laserkv_compress_block; LKV_EINVAL for
+ * shapes without layer kernels (laserkv_layer_workspace_bytes returns -1 for them: rows beyond 256 bytes,
+ * G * w > 512) and for a last block shorter than the window. */
+int64_t laserkv_layer_workspace_bytes(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_block, int32_t w, int32_t n_local);
+int laserkv_compress_layer(laserkv_ctx* ctx,
+                           const void* q_win, int64_t q_stride_block, int64_t q_stride_head, int64_t q_stride_tok,
+                           const void* k, int64_t k_stride_head, int64_t k_stride_tok,
+                           const void* v, int64_t v_stride_head, int64_t v_stride_tok,
+                           const void* hyperplanes,
+                           int64_t n_tok, int32_t s_block, int32_t w,
+                           int32_t B, int32_t n, double alpha,
+                           const float* const* row_lse_complete,
+                           int32_t* keep_last,
+                           void* k_cache, void* v_cache, int64_t cache_stride_head,
+                           int64_t* cache_pos, int64_t pos_stride_head, int64_t cache_cap,
+                           void* workspace, int64_t workspace_bytes,
+                           void* hip_stream);
+
 /* laserkv_compress_block for callers that cannot allocate device memory or hold a context: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, checks, kernels
  * and results as laserkv_compress_block on a context created from *cfg, but the workspace is a fixed

@@ -24,6 +24,7 @@ EXPORTS = (
     "laserkv_score_block", "laserkv_select_consensus", "laserkv_append_shared", "laserkv_set_row_lse",
     "laserkv_set_row_lse_complete", "laserkv_attend_workspace_bytes", "laserkv_attend_cache",
     "laserkv_attend_block_workspace_bytes", "laserkv_attend_block",
+    "laserkv_layer_workspace_bytes", "laserkv_compress_layer",
     "laserkv_static_init", "laserkv_static_workspace_bytes", "laserkv_compress_block_static",
 )
 LKV_STATIC_SCRATCH_BYTES = 32 << 20
@@ -80,6 +81,11 @@ def load():
         i32, i32, i32, i64, i64, i32, i32, i32, i32, i32,
         vp, vp, vp, i64, vp, i64, i64, i64, vp]
     lib.laserkv_compress_block.restype = C.c_int
+    lib.laserkv_layer_workspace_bytes.argtypes = [vp, i64, i32, i32, i32]
+    lib.laserkv_layer_workspace_bytes.restype = i64
+    lib.laserkv_compress_layer.argtypes = [vp, vp, i64, i64, i64, vp, i64, i64, vp, i64, i64, vp, i64, i32, i32,
+                                           i32, i32, C.c_double, vp, vp, vp, vp, i64, vp, i64, i64, vp, i64, vp]
+    lib.laserkv_compress_layer.restype = C.c_int
     lib.laserkv_static_init.argtypes = []
     lib.laserkv_static_init.restype = C.c_int
     lib.laserkv_static_workspace_bytes.argtypes = [C.POINTER(Config)]

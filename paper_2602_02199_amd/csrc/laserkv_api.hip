@@ -248,6 +248,7 @@ int laserkv_create(const laserkv_config* cfg, laserkv_ctx** out) {
   e = lkv::init_kernel_attributes();
   if (e == hipSuccess) e = lkv::init_attend_attributes();
   if (e == hipSuccess) e = lkv::init_single_attributes();
+  if (e == hipSuccess) e = lkv::init_layer_attributes();
   if (e != hipSuccess) {
     laserkv_destroy(ctx);
     return fail_hip(nullptr, e, "create: kernel attribute");
@@ -310,6 +311,37 @@ void laserkv_destroy(laserkv_ctx* ctx) {
 }  // extern "C"
 
 namespace {
+
+// Launch geometry of the count kernel over n_groups groups of cp.s_t keys.
+void plan_count(const laserkv_ctx* ctx, int w, int n_groups, int wg_target, lkv::CountParams& cp) {
+  const laserkv_config& c = ctx->cfg;
+  const int m_rows = ctx->group * w, s_t = cp.s_t;
+  cp.group = ctx->group;
+  cp.w = w;
+  cp.n_tables = c.lsh_tables;
+  cp.n_bits = c.lsh_bits;
+  // tables per group: keep the histogram within 64 KiB of LDS (one table at K = 16 takes 128 KiB)
+  int tg = (64 * 1024) / ((1 << c.lsh_bits) * 2);
+  if (tg < 1) tg = 1;
+  if (tg > c.lsh_tables) tg = c.lsh_tables;
+  cp.tables_per_group = tg;
+  const int n_tg = (c.lsh_tables + tg - 1) / tg;
+  // Several table groups per workgroup (taken one after the other) save global atomics; as many as
+  // still leave about one workgroup per compute unit with key ranges of at least 1024 keys.
+  int gpw = 1;
+  while (gpw * 2 <= n_tg && (int64_t)n_groups * ((n_tg + 2 * gpw - 1) / (2 * gpw)) * ((s_t + 1023) / 1024) >= wg_target) gpw *= 2;
+  const int n_wg_t = (n_tg + gpw - 1) / gpw;
+  int n_kr = wg_target / (n_groups * n_wg_t);
+  if (n_kr < 1) n_kr = 1;
+  int kpr = ((s_t + n_kr - 1) / n_kr + 1023) / 1024 * 1024;
+  if (kpr > lkv::count_max_keys_per_range()) kpr = lkv::count_max_keys_per_range();
+  // the workgroup stages its tables' codes of all window queries and of its keys in LDS beside the histogram:
+  // fewer table groups per workgroup, then shorter key ranges, until that fits
+  while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows, kpr) > 156 * 1024 && gpw > 1) gpw /= 2;
+  while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows, kpr) > 156 * 1024 && kpr > 64) kpr /= 2;
+  cp.groups_per_wg = gpw;
+  cp.keys_per_range = kpr;
+}
 
 // Steps a1-a4, and a5 in the same last kernel when `fused` is given.
 int select_impl(laserkv_ctx* ctx,
@@ -439,35 +471,10 @@ int select_impl(laserkv_ctx* ctx,
   cp.sig_k = ctx->sig_k;
   cp.sig_q = ctx->sig_q;
   cp.cnt = ctx->cnt;
-  cp.group = G;
-  cp.w = w;
-  cp.s_t = s_t;
-  cp.n_tables = c.lsh_tables;
-  cp.n_bits = c.lsh_bits;
-  {
-    // tables per group: keep the histogram within 64 KiB of LDS (one table at K = 16 takes 128 KiB)
-    int tg = (64 * 1024) / ((1 << c.lsh_bits) * 2);
-    if (tg < 1) tg = 1;
-    if (tg > c.lsh_tables) tg = c.lsh_tables;
-    cp.tables_per_group = tg;
-    const int n_tg = (c.lsh_tables + tg - 1) / tg;
-    // Several table groups per workgroup (taken one after the other) save global atomics; as many as
-    // still leave about one workgroup per compute unit with key ranges of at least 1024 keys.
-    int gpw = 1;
-    while (gpw * 2 <= n_tg && (int64_t)c.n_kv_heads * ((n_tg + 2 * gpw - 1) / (2 * gpw)) * ((s_t + 1023) / 1024) >= wg_target) gpw *= 2;
-    cp.groups_per_wg = gpw;
-    const int n_wg_t = (n_tg + gpw - 1) / gpw;
-    int n_kr = wg_target / (c.n_kv_heads * n_wg_t);
-    if (n_kr < 1) n_kr = 1;
-    int kpr = ((s_t + n_kr - 1) / n_kr + 1023) / 1024 * 1024;
-    if (kpr > lkv::count_max_keys_per_range()) kpr = lkv::count_max_keys_per_range();
-    // the workgroup stages its tables' codes of all window queries and of its keys in LDS beside the histogram:
-    // fewer table groups per workgroup, then shorter key ranges, until that fits
-    while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows, kpr) > 156 * 1024 && gpw > 1) gpw /= 2;
-    while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows, kpr) > 156 * 1024 && kpr > 64) kpr /= 2;
-    cp.groups_per_wg = gpw;
-    cp.keys_per_range = kpr;
-  }
+  cp.s_t = cp.key_stride = s_t;
+  cp.last_group = c.n_kv_heads;
+  cp.last_s_t = 0;
+  plan_count(ctx, w, c.n_kv_heads, wg_target, cp);
 
   lkv::SelectParams lp;
   lp.s_part = ctx->s_part;
@@ -696,6 +703,155 @@ int laserkv_compress_block(laserkv_ctx* ctx,
   return select_impl(ctx, q_win, q_stride_head, q_stride_tok, k_blk, k_stride_head, k_stride_tok,
                      k_ctx, c_stride_head, c_stride_tok, hyperplanes, s_t, w, t_ctx, block_pos0, q_pos0, causal,
                      n_anchor, n_local, k_exact, k_lsh, keep_idx, nullptr, nullptr, nullptr, nullptr, &ap, hip_stream);
+}
+
+// Launch geometry of laserkv_compress_layer; false when the shape has no layer kernels.
+static bool layer_geometry(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_block, int32_t w, int32_t n_local, lkv::LayerParams& p,
+                           lkv::LayerPlan& plan) {
+  const laserkv_config& c = ctx->cfg;
+  if (n_tok < 1 || n_tok > (int64_t(1) << 30) || s_block < 1 || s_block > c.max_block || w < 1 || w > c.max_window || n_local < 0) return false;
+  if (!lkv::layer_supports(c.dtype, c.head_dim, ctx->group * w)) return false;
+  p.group = ctx->group;
+  p.w = w;
+  p.w_magic = (uint32_t)(((uint64_t(1) << 32) + (uint64_t)w - 1) / (uint64_t)w);
+  p.m_rows = ctx->group * w;
+  p.n_kv_heads = c.n_kv_heads;
+  p.n_blocks = (int)((n_tok + s_block - 1) / s_block);
+  p.s_block = s_block;
+  p.n_tok = (int)n_tok;
+  p.n_ctx = n_local;
+  p.n_tables = c.lsh_tables;
+  p.n_bits = c.lsh_bits;
+  p.n_planes = c.lsh_tables * c.lsh_bits;
+  lkv::layer_plan(c.dtype, c.head_dim, ctx->n_cu, &p, &plan);
+  return true;
+}
+
+int64_t laserkv_layer_workspace_bytes(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_block, int32_t w, int32_t n_local) {
+  lkv::LayerParams p = {};
+  lkv::LayerPlan plan = {};
+  if (!ctx || !layer_geometry(ctx, n_tok, s_block, w, n_local, p, plan)) return -1;
+  // a call in which the rows come with their complete log-sum-exp has no look-back keys and may split differently
+  lkv::LayerParams p0 = {};
+  lkv::LayerPlan plan0 = {};
+  layer_geometry(ctx, n_tok, s_block, w, 0, p0, plan0);
+  return (int64_t)std::max(plan.bytes, plan0.bytes);
+}
+
+int laserkv_compress_layer(laserkv_ctx* ctx,
+                           const void* q_win, int64_t q_stride_block, int64_t q_stride_head, int64_t q_stride_tok,
+                           const void* k, int64_t k_stride_head, int64_t k_stride_tok,
+                           const void* v, int64_t v_stride_head, int64_t v_stride_tok,
+                           const void* hyperplanes,
+                           int64_t n_tok, int32_t s_block, int32_t w,
+                           int32_t B, int32_t n, double alpha,
+                           const float* const* row_lse_complete,
+                           int32_t* keep_last,
+                           void* k_cache, void* v_cache, int64_t cache_stride_head,
+                           int64_t* cache_pos, int64_t pos_stride_head, int64_t cache_cap,
+                           void* workspace, int64_t workspace_bytes,
+                           void* hip_stream) {
+  if (!ctx) return fail(nullptr, LKV_EINVAL, "compress_layer: null context");
+  const laserkv_config& c = ctx->cfg;
+  const int es = ctx->elem_size, d = c.head_dim, G = ctx->group;
+  if (!q_win || !hyperplanes || !workspace) return fail(ctx, LKV_EINVAL, "compress_layer: null tensor");
+  const bool lse_complete = row_lse_complete || (ctx->row_lse && ctx->row_lse_complete);
+  int32_t na, nl, ke, kl, na1, nl1, ke1, kl1;
+  if (s_block < 1 || laserkv_partition(B, n, alpha, s_block, &na, &nl, &ke, &kl) != LKV_OK)
+    return fail(ctx, LKV_EINVAL, "compress_layer: bad block length, budget, divisor or alpha");
+  lkv::LayerParams p = {};
+  lkv::LayerPlan plan = {};
+  if (!layer_geometry(ctx, n_tok, s_block, w, lse_complete ? 0 : nl, p, plan))
+    return fail(ctx, LKV_EINVAL, "compress_layer: sizes outside the context's configuration, or a shape without layer kernels "
+                "(rows of at most 256 bytes, G * w <= %d)", 512);
+  const int n_blocks = p.n_blocks, s_last = (int)(n_tok - (int64_t)(n_blocks - 1) * s_block);
+  if (s_last < w) return fail(ctx, LKV_EINVAL, "compress_layer: the last block (%d tokens) is shorter than the window", s_last);
+  if (laserkv_partition(B, n, alpha, s_last, &na1, &nl1, &ke1, &kl1) != LKV_OK) return fail(ctx, LKV_EINVAL, "compress_layer: bad partition");
+  const int b_full = na + nl + ke + kl, b_last = na1 + nl1 + ke1 + kl1;
+  auto bad_stride = [&](int64_t sh, int64_t st) { return st < d || sh < 0 || ((st * es) & 15) || ((sh * es) & 15); };
+  if (bad_stride(q_stride_head, q_stride_tok) || q_stride_block < 0 || ((q_stride_block * es) & 15))
+    return fail(ctx, LKV_EINVAL, "compress_layer: query strides must cover a row and keep rows 16-byte aligned");
+  if (!aligned16(q_win) || !aligned16(hyperplanes) || (reinterpret_cast<uintptr_t>(workspace) & 255u))
+    return fail(ctx, LKV_EINVAL, "compress_layer: tensors must be 16-byte aligned, the workspace 256-byte aligned");
+  if (((int64_t)s_block + p.n_ctx) * k_stride_tok * es >= (int64_t(1) << 31))
+    return fail(ctx, LKV_EINVAL, "compress_layer: a block's keys must span less than 2 GiB per head");
+  if (workspace_bytes < (int64_t)plan.bytes)
+    return fail(ctx, LKV_EINVAL, "compress_layer: workspace of %lld bytes, %zu needed", (long long)workspace_bytes, plan.bytes);
+  const int64_t rows = (int64_t)(n_blocks - 1) * b_full + b_last;
+  lkv::AppendParams ap;
+  int rc = append_params(ctx, k, k_stride_head, k_stride_tok, v, v_stride_head, v_stride_tok, b_full, s_block, 0, k_cache, v_cache,
+                         cache_stride_head, cache_pos, pos_stride_head, 0, cache_cap, ap);
+  if (rc != LKV_OK) return rc;
+  if (rows > cache_cap) return fail(ctx, LKV_ECAP, "compress_layer: %lld rows exceed the capacity %lld", (long long)rows, (long long)cache_cap);
+
+  char* ws = static_cast<char*>(workspace);
+  p.q = {(const char*)q_win, q_stride_head * es, q_stride_tok * es};
+  p.q_stride_block = q_stride_block * es;
+  p.k = {(const char*)k, k_stride_head * es, k_stride_tok * es};
+  p.planes = (const char*)hyperplanes;
+  p.scale2 = (float)(1.4426950408889634 / std::sqrt((double)d));
+  p.row_lse = ctx->row_lse;
+  p.row_lse_blk = row_lse_complete;
+  p.lse_complete = lse_complete ? 1 : 0;
+  p.part = reinterpret_cast<float2*>(ws + plan.off_part);
+  p.score = reinterpret_cast<float*>(ws + plan.off_score);
+  p.cnt = reinterpret_cast<int32_t*>(ws + plan.off_cnt);
+  p.cells = plan.use_cells ? reinterpret_cast<uint32_t*>(ws + plan.off_cells) : nullptr;
+  p.heavy = plan.use_cells ? reinterpret_cast<uint32_t*>(ws + plan.off_heavy) : nullptr;
+  p.sig_k = plan.use_cells ? nullptr : reinterpret_cast<uint16_t*>(ws + plan.off_sig_k);
+  p.sig_q = plan.use_cells ? nullptr : reinterpret_cast<uint16_t*>(ws + plan.off_sig_q);
+
+  hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
+  const int dt = c.dtype, n_groups = n_blocks * c.n_kv_heads;
+  hipError_t e;
+  if (!lse_complete) {
+    e = timed(ctx, LKV_KERN_SWEEP1, st, [&] {
+      hipError_t r = lkv::launch_layer_codes(dt, d, p, plan, st);
+      return r != hipSuccess ? r : lkv::launch_layer_stats(dt, d, p, plan, st);
+    });
+    if (e != hipSuccess) return fail_hip(ctx, e, "compress_layer: window-row codes and row statistics");
+    e = timed(ctx, LKV_KERN_SWEEP2, st, [&] { return lkv::launch_layer_score(dt, d, p, plan, st); });
+  } else {
+    e = timed(ctx, LKV_KERN_SINGLE, st, [&] {
+      hipError_t r = lkv::launch_layer_codes(dt, d, p, plan, st);
+      return r != hipSuccess ? r : lkv::launch_layer_score(dt, d, p, plan, st);
+    });
+  }
+  if (e != hipSuccess) return fail_hip(ctx, e, "compress_layer: scores, codes and counts");
+  if (!plan.use_cells) {
+    lkv::CountParams cp;
+    cp.sig_k = p.sig_k;
+    cp.sig_q = p.sig_q;
+    cp.cnt = p.cnt;
+    cp.s_t = s_block;
+    cp.key_stride = p.s_stride;
+    cp.last_group = (n_blocks - 1) * c.n_kv_heads;
+    cp.last_s_t = s_last;
+    plan_count(ctx, w, n_groups, ctx->n_cu, cp);
+    if ((e = timed(ctx, LKV_KERN_COUNT, st, [&] { return lkv::launch_count(cp, n_groups, st); })) != hipSuccess)
+      return fail_hip(ctx, e, "compress_layer: count kernel");
+  }
+  lkv::SelectParams lp;
+  lp.s_part = p.score;
+  lp.n_qgroups = 1;
+  lp.n_kv_heads = c.n_kv_heads;
+  lp.inv_m = 1.0f / (float)(G * w);
+  lp.cnt = p.cnt;
+  lp.n_cnt_parts = 1;
+  lp.cnt_out = nullptr;
+  lp.s_t = s_block;
+  lp.n_anchor = na;
+  lp.n_local = nl;
+  lp.k_exact = ke;
+  lp.k_lsh = kl;
+  lp.cnt_bits = bits_for((int64_t)G * w * c.lsh_tables);
+  lp.s_exact = nullptr;
+  lp.keep = nullptr;
+  const lkv::SelectLayer ly = {p.s_stride, n_blocks - 1, s_last, na1, nl1, ke1, kl1, keep_last};
+  const int n_cu = ctx->n_cu;
+  if ((e = timed(ctx, LKV_KERN_SELECT, st, [&] { return lkv::launch_select_layer(lp, ap, ly, n_cu, st); })) != hipSuccess)
+    return fail_hip(ctx, e, "compress_layer: select + append kernel");
+  return LKV_OK;
 }
 
 int laserkv_set_row_lse(laserkv_ctx* ctx, const float* row_lse) {

@@ -96,10 +96,6 @@ __device__ __forceinline__ uint2 ds_read_tr16(const void* lds_ptr) {
   return __builtin_bit_cast(uint2, v);
 }
 
-// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS traffic, not for its
-// global loads, so the next chunk's prefetch stays in flight across it (__syncthreads would wait for it).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   bf16x2 t = {(__bf16)lo, (__bf16)hi};  // round to nearest even

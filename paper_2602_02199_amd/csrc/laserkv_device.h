@@ -117,6 +117,7 @@ __device__ __forceinline__ float lane_xor1(float v) { return __uint_as_float(lan
 __device__ __forceinline__ float lane_xor2(float v) { return __uint_as_float(lane_xor2(__float_as_uint(v))); }
 __device__ __forceinline__ int lane_xor1(int v) { return (int)lane_xor1((uint32_t)v); }
 __device__ __forceinline__ int lane_xor2(int v) { return (int)lane_xor2((uint32_t)v); }
+__device__ __forceinline__ float lane_xor4(float v, bool bit2) { return __uint_as_float(lane_xor4(__float_as_uint(v), bit2)); }
 __device__ __forceinline__ int lane_xor4(int v, bool bit2) { return (int)lane_xor4((uint32_t)v, bit2); }
 // Value of lane (l ^ 32): one swap of the wave's halves (upper: the lane is in the upper half), no LDS round trip.
 __device__ __forceinline__ uint32_t half_other(uint32_t v, bool upper) {
@@ -134,6 +135,10 @@ __device__ __forceinline__ float half_pair_max(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));  // r[0]: the lower half's values in all lanes, r[1]: the upper half's
 }
+
+// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS traffic, not for its
+// global loads, so the next chunk's prefetch stays in flight across it (__syncthreads would wait for it).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // (m, s) pairs describe sum_i 2^(x_i) as s * 2^m.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {

@@ -65,10 +65,12 @@ struct PassParams {
 };
 
 struct CountParams {
-  const uint16_t* sig_k;  // [H_kv, S, L]
-  const uint16_t* sig_q;  // [H_q, W, L]
-  int32_t* cnt;           // [H_kv, S]
+  const uint16_t* sig_k;  // [groups, key_stride, L]; a group is a KV head, or a (block, KV head) pair of a layer
+  const uint16_t* sig_q;  // [groups, G * W, L]
+  int32_t* cnt;           // [groups, key_stride]
   int group, w, s_t;
+  int key_stride;         // keys per group in sig_k and cnt
+  int last_group, last_s_t;  // groups from last_group on have last_s_t keys (a layer's short last block)
   int n_tables, n_bits;
   int tables_per_group;   // TG: tables whose histograms share the LDS at one time
   int groups_per_wg;      // table groups a workgroup takes one after the other
@@ -88,6 +90,15 @@ struct SelectParams {
   int cnt_bits;         // bits needed to hold G * W * L
   float* s_exact;       // [H_kv, S] final scores (optional, for the stage outputs)
   int32_t* keep;        // [H_kv, B_t]
+};
+
+// The selection of all blocks of a layer in one launch: group = (block, KV head), scores and counts [n_blocks * H_kv, s_stride].
+// The numbers in SelectParams / AppendParams are those of a full block; the last block may be shorter.
+struct SelectLayer {
+  int s_stride;
+  int last;             // index of the last block
+  int last_s_t, last_anchor, last_local, last_exact, last_lsh;
+  int32_t* keep_last;   // [H_kv, B_last] kept indices of the last block, or null (the positions say it all)
 };
 
 // Adds one layer's scores and counts, summed over its KV heads, into [S] accumulators.
@@ -153,6 +164,48 @@ bool single_supports(int dtype, int head_dim);
 hipError_t launch_single(int dtype, int head_dim, const SingleParams& p, hipStream_t st);
 hipError_t init_single_attributes();
 
+// All blocks of a layer (laserkv_layer.hip).  Group = (block, KV head), group index = block * H_kv + head.
+struct LayerParams {
+  RowSrc q;              // [H_q, W, d] of block 0
+  int64_t q_stride_block;  // bytes
+  RowSrc k;              // [H_kv, n_tok, d]
+  const char* planes;    // [L*K, d] contiguous
+  int group, w;
+  uint32_t w_magic;
+  int m_rows;            // G * W
+  int n_kv_heads, n_blocks, s_block, n_tok;
+  int n_ctx;             // look-back keys of every block but the first: the rows in front of the block
+  float scale2;
+  const float* row_lse;             // [H_q, W] natural log-sum-exp of outside keys (or complete), the same for all blocks; or null
+  const float* const* row_lse_blk;  // DEVICE array of n_blocks pointers to such tensors, or null
+  int lse_complete;
+  int n_tables, n_bits, n_planes;
+  int wr_log;            // statistics: log2 of the waves that share the rows; the other factor of the eight takes different key tiles
+  int stat_splits, stat_keys, score_splits, score_keys;  // key ranges per group and keys per range
+  int n_parts;           // statistics partials per row
+  float2* part;          // [groups, M, n_parts]
+  int code_tables, code_tiles;  // tables per pass of the code kernel, 32-plane tiles they take
+  int cell_log, cell_words;  // log2 of the cells per word of a table's histogram (16, 8 or 4 bits each), words per table
+  uint32_t* cells;       // [groups, L, cell_words] histograms of the window-row codes, counts clamped to a cell; or null
+  uint32_t* heavy;       // [groups, L, 36] bins whose narrow cell is full: their number, then (code << 16 | count)
+  int s_stride;          // keys per group in score / cnt / sig_k
+  float* score;          // [groups, s_stride] pooled probabilities (sum over the rows)
+  int32_t* cnt;          // [groups, s_stride]
+  uint16_t* sig_k;       // [groups, s_stride, L] when cells is null
+  uint16_t* sig_q;       // [groups, M, L] when cells is null
+};
+struct LayerPlan {
+  int rt, use_cells;
+  size_t codes_lds, stats_lds, score_lds;
+  size_t off_part, off_score, off_cnt, off_cells, off_heavy, off_sig_k, off_sig_q, bytes;  // workspace
+};
+bool layer_supports(int dtype, int head_dim, int m_rows);
+void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* plan);  // fills the launch geometry of both
+hipError_t launch_layer_codes(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
+hipError_t launch_layer_stats(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
+hipError_t launch_layer_score(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
+hipError_t init_layer_attributes();
+
 // Attention of n_q queries per query head over the first cache_len rows of each KV head's compacted cache.
 struct AttendParams {
   RowSrc q;            // [H_q, n_q, d]
@@ -198,10 +251,11 @@ hipError_t init_attend_attributes();
 
 hipError_t launch_sweep1(int dtype, int head_dim, const PassParams& p, hipStream_t st);
 hipError_t launch_sweep2(int dtype, int head_dim, const PassParams& p, hipStream_t st);
-hipError_t launch_count(const CountParams& p, int n_kv_heads, hipStream_t st);
+hipError_t launch_count(const CountParams& p, int n_groups, hipStream_t st);
 hipError_t launch_select(const SelectParams& p, hipStream_t st);
 // split_override > 0: workgroups per head (tuning); otherwise n_cu / heads
 hipError_t launch_select_append(const SelectParams& p, const AppendParams& ap, int n_cu, int split_override, hipStream_t st);
+hipError_t launch_select_layer(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_cu, hipStream_t st);
 hipError_t launch_append(const AppendParams& p, int n_kv_heads, hipStream_t st);
 hipError_t launch_accumulate(const AccumParams& p, hipStream_t st);
 hipError_t init_kernel_attributes();

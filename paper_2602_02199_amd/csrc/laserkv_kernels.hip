@@ -706,7 +706,9 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
   const int kr = blockIdx.x, h = blockIdx.z;
   const int nq = p.group * p.w;
   const int i0 = kr * p.keys_per_range;
-  const int i1 = min(i0 + p.keys_per_range, p.s_t);
+  const int s_t = h >= p.last_group ? p.last_s_t : p.s_t;
+  if (i0 >= s_t) return;  // a short last block
+  const int i1 = min(i0 + p.keys_per_range, s_t);
   const int n_keys = i1 - i0;
   const int t_first = blockIdx.y * p.groups_per_wg * p.tables_per_group;            // the workgroup's tables
   const int ntw = min(p.groups_per_wg * p.tables_per_group, p.n_tables - t_first);  // > 0 by the grid's construction
@@ -715,7 +717,7 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
   uint16_t* sKc = sQ + ((ntw * nq + 7) & ~7);                                   // [n_keys][ntw]
   // 1. everything from memory, issued back to back: query codes (transposed to table-major), key codes
   const uint16_t* gq = p.sig_q + (size_t)h * nq * p.n_tables + t_first;
-  const uint16_t* gk = p.sig_k + ((size_t)h * p.s_t + i0) * p.n_tables + t_first;
+  const uint16_t* gk = p.sig_k + ((size_t)h * p.key_stride + i0) * p.n_tables + t_first;
   const bool vec8 = (ntw & 7) == 0 && (p.n_tables & 7) == 0 && (t_first & 7) == 0;  // rows of whole aligned 16-byte groups
   if (vec8) {
     const int g8 = ntw >> 3;
@@ -784,7 +786,7 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
 #pragma unroll
   for (int k = 0; k < COUNT_KEYS_PER_THREAD; ++k) {
     const int key = tid + k * COUNT_THREADS;
-    if (key < n_keys) atomicAdd(&p.cnt[(size_t)h * p.s_t + i0 + key], sum[k]);
+    if (key < n_keys) atomicAdd(&p.cnt[(size_t)h * p.key_stride + i0 + key], sum[k]);
   }
 }
 
@@ -809,8 +811,9 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
 constexpr int SEL_COPIES = 4;
 constexpr int SEL_BUFFERS = 3;
 
-template <int EPT, bool FUSED>
-__global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendParams ap, int split) {
+// LAYER = true (with FUSED): the groups are all (block, KV head) pairs of a layer.
+template <int EPT, bool FUSED, bool LAYER>
+__global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendParams ap, SelectLayer ly, int split) {
   __shared__ __align__(16) uint32_t sHist[SEL_BUFFERS][SEL_COPIES][256];
   __shared__ int sWave[16];
   __shared__ uint32_t sList[64];  // keys that share the threshold's leading digits
@@ -818,11 +821,30 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
   __shared__ uint32_t sMaxCnt;  // largest collision count among the candidates
   __shared__ int sKeep[FUSED ? 1024 : 1];  // FUSED: the kept indices this workgroup copies
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int n_sel_wg = p.n_kv_heads * split;
   // the workgroups that share a head (and read the same scores and counts) sit on one XCD
-  const int sel_id = xcd_major(blockIdx.x, n_sel_wg);
-  const int h = FUSED ? sel_id / split : sel_id;
-  const int part = FUSED ? sel_id - h * split : 0;
+  const int sel_id = xcd_major(blockIdx.x, gridDim.x);
+  const int grp = FUSED ? sel_id / split : sel_id;
+  const int part = FUSED ? sel_id - grp * split : 0;
+  int h = grp;
+  const size_t hoff = (size_t)grp * (LAYER ? ly.s_stride : p.s_t);
+  if (LAYER) {
+    const int blk = grp / p.n_kv_heads;
+    h = grp - blk * p.n_kv_heads;
+    const int64_t first = (int64_t)blk * p.s_t;  // the block's first token
+    ap.kb.base += first * ap.kb.stride_row;
+    ap.vb.base += first * ap.vb.stride_row;
+    ap.block_pos0 += first;
+    ap.cache_len += (int64_t)blk * (p.n_anchor + p.n_local + p.k_exact + p.k_lsh);
+    p.keep = nullptr;
+    if (blk == ly.last) {
+      p.s_t = ly.last_s_t;
+      p.n_anchor = ly.last_anchor;
+      p.n_local = ly.last_local;
+      p.k_exact = ly.last_exact;
+      p.k_lsh = ly.last_lsh;
+      p.keep = ly.keep_last;
+    }
+  }
   uint32_t key[EPT], c2[EPT];
   bool inr[EPT], cand[EPT], sel[EPT];
   {
@@ -830,9 +852,9 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
     // first use (a loop with a run-time part count would serialise one memory round trip per load)
     float sc[EPT];
     int cc[EPT];
-    const size_t hoff = (size_t)h * p.s_t, poff = (size_t)p.n_kv_heads * p.s_t;
+    const size_t poff = LAYER ? 0 : (size_t)p.n_kv_heads * p.s_t;
     // 16-byte loads when a thread's EPT positions are whole aligned quads inside the block
-    const bool quads = EPT % 4 == 0 && (p.s_t & 3) == 0 && (tid + 1) * EPT <= p.s_t;
+    const bool quads = EPT % 4 == 0 && (LAYER || (p.s_t & 3) == 0) && (tid + 1) * EPT <= p.s_t;
     if (p.n_qgroups <= 2 && p.n_cnt_parts <= 2 && __all(quads)) {
       constexpr int NQ = EPT >= 4 ? EPT / 4 : 1;
       const bool s2 = p.n_qgroups > 1, c2p = p.n_cnt_parts > 1;
@@ -859,7 +881,7 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
           }
       }
     } else if (EPT == 2 && p.n_qgroups <= 2 && p.n_cnt_parts <= 2 &&
-               __all((p.s_t & 1) == 0 && (tid + 1) * EPT <= p.s_t)) {
+               __all((LAYER || (p.s_t & 1) == 0) && (tid + 1) * EPT <= p.s_t)) {
       // two positions per thread: 8-byte loads
       const bool s2 = p.n_qgroups > 1, c2p = p.n_cnt_parts > 1;
       const uint2* ps = reinterpret_cast<const uint2*>(p.s_part + hoff + (size_t)tid * 2);
@@ -1081,7 +1103,7 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
     if (kept) {
       const int pos = n_sure + min(n_tie, need2);
       if (pos >= r0 && pos < r1) {
-        p.keep[(size_t)h * b_t + pos] = tid * EPT + e;
+        if (!LAYER || p.keep) p.keep[(size_t)h * b_t + pos] = tid * EPT + e;
         if (FUSED) sKeep[pos - r0] = tid * EPT + e;
       }
     }
@@ -1098,7 +1120,8 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
       const bool two = t1 < n_copy;
       const int row0 = t0 / cpr, c0 = t0 - row0 * cpr;
       const int row1 = two ? t1 / cpr : row0, c1 = two ? t1 - row1 * cpr : c0;
-      const int src0 = sKeep[row0], src1 = sKeep[row1];
+      // an index from LDS never addresses past the block, whatever the counts held
+      const int src0 = min((uint32_t)sKeep[row0], (uint32_t)p.s_t - 1u), src1 = min((uint32_t)sKeep[row1], (uint32_t)p.s_t - 1u);
       const char* kh = ap.kb.base + (int64_t)h * ap.kb.stride_head;
       const char* vh = ap.vb.base + (int64_t)h * ap.vb.stride_head;
       const uint4 k0v = ld16(kh + (int64_t)src0 * ap.kb.stride_row + c0 * 16);
@@ -1241,14 +1264,14 @@ size_t count_lds_bytes(int n_bits, int tables_per_group, int groups_per_wg, int 
   return bin_words * 4 + ((ntw * n_query_rows + 7) & ~(size_t)7) * 2 + ntw * keys_per_range * 2 + 16;
 }
 
-hipError_t launch_count(const CountParams& p, int n_kv_heads, hipStream_t st) {
+hipError_t launch_count(const CountParams& p, int n_groups, hipStream_t st) {
   const int n_tg = (p.n_tables + p.tables_per_group - 1) / p.tables_per_group;
   const int n_wg_t = (n_tg + p.groups_per_wg - 1) / p.groups_per_wg;
   const int n_kr = (p.s_t + p.keys_per_range - 1) / p.keys_per_range;
   if (p.keys_per_range > COUNT_THREADS * COUNT_KEYS_PER_THREAD) return hipErrorInvalidValue;
   const size_t lds = count_lds_bytes(p.n_bits, p.tables_per_group, p.groups_per_wg, p.group * p.w, p.keys_per_range);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
-  dim3 grid(n_kr, n_wg_t, n_kv_heads);
+  dim3 grid(n_kr, n_wg_t, n_groups);
   hipLaunchKernelGGL(count_kernel, grid, dim3(COUNT_THREADS), lds, st, p);
   return hipGetLastError();
 }
@@ -1260,32 +1283,42 @@ hipError_t launch_accumulate(const AccumParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <bool FUSED>
-static hipError_t launch_select_t(const SelectParams& p, const AppendParams& ap, int split, hipStream_t st) {
+template <bool FUSED, bool LAYER>
+static hipError_t launch_select_t(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_groups, int split, hipStream_t st) {
   const int ept = (p.s_t + 1023) / 1024;
-  // `split` workgroups per head select (and, fused, copy)
-  dim3 grid(p.n_kv_heads * split);
-  if (ept <= 1) hipLaunchKernelGGL((select_kernel<1, FUSED>), grid, dim3(1024), 0, st, p, ap, split);
-  else if (ept <= 2) hipLaunchKernelGGL((select_kernel<2, FUSED>), grid, dim3(1024), 0, st, p, ap, split);
-  else if (ept <= 4) hipLaunchKernelGGL((select_kernel<4, FUSED>), grid, dim3(1024), 0, st, p, ap, split);
-  else if (ept <= 8) hipLaunchKernelGGL((select_kernel<8, FUSED>), grid, dim3(1024), 0, st, p, ap, split);
-  else if (ept <= 16) hipLaunchKernelGGL((select_kernel<16, FUSED>), grid, dim3(1024), 0, st, p, ap, split);
+  // `split` workgroups per group select (and, fused, copy)
+  dim3 grid(n_groups * split);
+  if (ept <= 1) hipLaunchKernelGGL((select_kernel<1, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
+  else if (ept <= 2) hipLaunchKernelGGL((select_kernel<2, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
+  else if (ept <= 4) hipLaunchKernelGGL((select_kernel<4, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
+  else if (ept <= 8) hipLaunchKernelGGL((select_kernel<8, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
+  else if (ept <= 16) hipLaunchKernelGGL((select_kernel<16, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_select(const SelectParams& p, hipStream_t st) {
-  AppendParams none = {};
-  return launch_select_t<false>(p, none, 1, st);
+  return launch_select_t<false, false>(p, AppendParams{}, SelectLayer{}, p.n_kv_heads, 1, st);
+}
+
+// enough workgroups per group to fill the chip, each copying at most 1024 rows
+static int select_split(int n_groups, int b_t, int n_cu, int split_override) {
+  int split = split_override > 0 ? split_override : n_cu / n_groups;
+  if (split < 1) split = 1;
+  while ((b_t + split - 1) / split > 1024) ++split;
+  return split;
 }
 
 hipError_t launch_select_append(const SelectParams& p, const AppendParams& ap, int n_cu, int split_override, hipStream_t st) {
-  // enough workgroups per head to fill the chip, each copying at most 1024 rows
   const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
-  int split = split_override > 0 ? split_override : n_cu / p.n_kv_heads;
-  if (split < 1) split = 1;
-  while ((b_t + split - 1) / split > 1024) ++split;
-  return launch_select_t<true>(p, ap, split, st);
+  return launch_select_t<true, false>(p, ap, SelectLayer{}, p.n_kv_heads, select_split(p.n_kv_heads, b_t, n_cu, split_override), st);
+}
+
+hipError_t launch_select_layer(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_cu, hipStream_t st) {
+  const int n_groups = (ly.last + 1) * p.n_kv_heads;
+  const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
+  // two workgroups fit a compute unit
+  return launch_select_t<true, true>(p, ap, ly, n_groups, select_split(n_groups, b_t, 2 * n_cu, 0), st);
 }
 
 hipError_t launch_append(const AppendParams& p, int n_kv_heads, hipStream_t st) {

@@ -1,0 +1,745 @@
+// A layer whose blocks are all in memory, compressed with a few launches for all of its blocks together
+// (laserkv_compress_layer).  The blocks of a layer do not depend on each other: the look-back keys of block t are
+// the local window of block t - 1 (Sec. 3.2), which is always kept, so they are simply the rows in front of the
+// block in the layer's own key tensor.  Every (block, KV head) pair is one independent group of work; with a layer's
+// worth of groups in a launch the chip is full, and what a launch per block pays once per block (launch, loads of the
+// window rows and hyperplanes, tail) is paid once per layer.
+//
+//   layer_codes_kernel   SimHash codes of the window rows (Sec. 3.3 "Recall") and their histograms, compact enough
+//                        for the score kernel's LDS                                                           [MFMA]
+//   layer_stats_kernel   per window row, partial (reference, sum) of 2^(logit) over a key range (Alg. 1 step 3) [MFMA]
+//   layer_score_kernel   one pass over the block's keys: pooled probabilities (Alg. 1 step 3), sign bits against all
+//                        hyperplanes, collision counts (Alg. 1 step 6)                                        [MFMA]
+//   then the select + append kernel of laserkv_kernels.hip over all groups.
+//
+// In both sweeps the window rows stay in registers for the whole key range (two 32-row tiles per wave, so a key
+// fragment read from LDS feeds two matrix instructions) and the keys stream through two LDS stages, the next chunk's
+// loads in flight in registers while the current one is worked on: one barrier per chunk.
+#include "laserkv_device.h"
+#include "laserkv_kernels.h"
+
+#include <limits.h>
+
+namespace lkv {
+
+constexpr int LY_WAVES = 8;
+constexpr int LY_THREADS = LY_WAVES * 64;
+constexpr int LY_ROWS = 512;         // window rows per group at most
+constexpr int LY_STAT_KC = 256;      // keys per LDS chunk: statistics
+constexpr int LY_KC = 128;           // scores
+constexpr int LY_HEAVY = 36;         // words per table's list of heavy bins: at most LY_ROWS / 15 = 34 of them
+constexpr int LY_CODE_PLANES = 256;  // hyperplanes per pass of layer_codes_kernel at most
+
+struct LayerGroup {
+  int g, b, h, lo, s_t, n_ctx;
+};
+__device__ __forceinline__ LayerGroup layer_group(const LayerParams& p, int g) {
+  LayerGroup r;
+  r.g = g;
+  r.b = g / p.n_kv_heads;
+  r.h = g - r.b * p.n_kv_heads;
+  r.lo = r.b * p.s_block;
+  r.s_t = min(p.s_block, p.n_tok - r.lo);
+  r.n_ctx = r.b ? p.n_ctx : 0;
+  return r;
+}
+
+__device__ __forceinline__ const char* layer_row(const LayerParams& p, const LayerGroup& gr, int m) {
+  const int g = div_w(m, p.w_magic), j = m - g * p.w;
+  return p.q.base + gr.b * p.q_stride_block + (int64_t)(gr.h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Codes of a group's window rows.  Workgroup = group; wave w holds rows 64w .. 64w+63 as MFMA operands and the tables
+// pass by in sets whose hyperplanes and histograms fit the LDS.  A set's codes are counted in LDS histograms (16-bit
+// bins, 32 bins per 17 words against bank conflicts), which leave as cells of 16, 8 or 4 bits per bin, the widest with
+// which a group's tables fit 64 KiB of the score kernel's LDS (4 bits at K = 12, L = 32).  A narrow cell that is full
+// stands for a count the table's list of heavy bins holds: (code << 16 | count) each, their number in front.
+// Codes wider than 12 bits: the codes themselves are stored (count_kernel does the counting).
+// ---------------------------------------------------------------------------------------------
+template <int DT, int D>
+__global__ __launch_bounds__(LY_THREADS) void layer_codes_kernel(LayerParams p) {
+  constexpr int ES = DT == DT_BF16 ? 2 : 4;
+  constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const LayerGroup gr = layer_group(p, blockIdx.x);
+  const bool wide = p.cells == nullptr;
+  const int words = (1 << p.n_bits) >= 32 ? (1 << p.n_bits) >> 5 : 1;  // bitmap words per table
+  const int hp = words * 17;
+
+  extern __shared__ uint4 smem[];
+  uint4* sP = smem;                                                                  // [code_tiles * 32][CHP]
+  uint32_t* sH = reinterpret_cast<uint32_t*>(smem + (size_t)p.code_tiles * 32 * CHP);  // [code_tables][hp]
+  int* sHeavy = reinterpret_cast<int*>(sH + p.code_tables * hp);                     // [code_tables]
+
+  uint4 b[2][NCH];
+  const bool active = wave * 64 < p.m_rows;
+  if (active) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const char* ptr = layer_row(p, gr, min(wave * 64 + r * 32 + rl, p.m_rows - 1));
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) b[r][i] = ld16(ptr + (2 * i + kg) * 16);
+    }
+  }
+  const uint32_t code_mask = (1u << p.n_bits) - 1u;
+  for (int t0 = 0; t0 < p.n_tables; t0 += p.code_tables) {
+    const int n_tab = min(p.code_tables, p.n_tables - t0);
+    const int np = n_tab * p.n_bits, n_tile = (np + 31) >> 5;
+    __syncthreads();  // the previous set's histograms have been read
+    for (int q = tid; q < n_tile * 32 * CH; q += LY_THREADS) {
+      const int row = q / CH, c = q % CH;
+      sP[row * CHP + c] = ld16(p.planes + (size_t)(t0 * p.n_bits + min(row, np - 1)) * (D * ES) + c * 16);
+    }
+    if (!wide) {
+      for (int i = tid; i < n_tab * hp; i += LY_THREADS) sH[i] = 0u;
+      for (int i = tid; i < n_tab; i += LY_THREADS) sHeavy[i] = 0;
+    }
+    __syncthreads();
+    if (active) {
+      uint32_t prev[2] = {0u, 0u};
+      int tt0 = 0;  // first table of the set whose bits are not complete yet
+#pragma unroll 1
+      for (int t = 0; t < n_tile; ++t) {
+        const uint4* prow = sP + (size_t)(t * 32 + plane_row(rl)) * CHP + kg;
+        f32x16 acc[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[r][e] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+          const uint4 pf = prow[2 * i];
+#pragma unroll
+          for (int r = 0; r < 2; ++r) Mma<DT>::run(acc[r], pf, b[r][i]);
+        }
+        const int tt1 = min(32 * (t + 1), np) / p.n_bits;  // tables complete after this tile
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          uint32_t neg = 0u;
+#pragma unroll
+          for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[r][e]), 31);
+          const uint32_t pos = ~neg & 0xffffu;  // bit = projection >= 0
+          const uint32_t other = half_other(pos, kg);
+          const uint32_t word = kg ? (other | (pos << 16)) : (pos | (other << 16));
+          const uint64_t two = ((uint64_t)word << 32) | prev[r];
+          prev[r] = word;
+          const int row = wave * 64 + r * 32 + rl;
+          if (row < p.m_rows)
+            for (int tt = tt0 + ((tt0 ^ kg) & 1); tt < tt1; tt += 2) {  // tables alternate between the two lanes of a row
+              const uint32_t code = (uint32_t)(two >> (tt * p.n_bits - 32 * t + 32)) & code_mask;
+              if (wide) p.sig_q[((size_t)gr.g * p.m_rows + row) * p.n_tables + t0 + tt] = (uint16_t)code;
+              else atomicAdd(sH + tt * hp + (code >> 5) * 17 + ((code & 31u) >> 1), 1u << ((code & 1u) * 16));
+            }
+        }
+        tt0 = tt1;
+      }
+    }
+    if (wide) continue;
+    __syncthreads();
+    const int cpw = 1 << p.cell_log, cbits = 32 >> p.cell_log;
+    const uint32_t cmax = cbits == 16 ? 0xffffu : (1u << cbits) - 1u;
+    for (int i = tid; i < n_tab * p.cell_words; i += LY_THREADS) {
+      const int tt = i / p.cell_words, c0 = (i - tt * p.cell_words) << p.cell_log;
+      const uint32_t* hist = sH + tt * hp + (c0 >> 5) * 17 + ((c0 & 31) >> 1);
+      const size_t table = (size_t)gr.g * p.n_tables + t0 + tt;
+      uint32_t out = 0u;
+      for (int u = 0; u < cpw; u += 2) {
+        const uint32_t v = hist[u >> 1], lo = v & 0xffffu, hi = v >> 16;
+        out |= (min(lo, cmax) << (u * cbits)) | (min(hi, cmax) << ((u + 1) * cbits));
+        if (lo >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u) << 16 | lo;
+        if (hi >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u + 1) << 16 | hi;
+      }
+      p.cells[table * p.cell_words + (i - tt * p.cell_words)] = out;
+    }
+    __syncthreads();
+    for (int tt = tid; tt < n_tab; tt += LY_THREADS) p.heavy[((size_t)gr.g * p.n_tables + t0 + tt) * LY_HEAVY] = (uint32_t)sHeavy[tt];
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Row statistics.  Workgroup = (group, key range); waves share the rows (2^wr_log waves of RT tiles) and, where the
+// rows need fewer than eight waves, different key tiles.  Keys are the A operand and window rows the B operand, so a
+// lane owns a row per tile and keeps (reference, sum of 2^(x - reference)) privately.  The reference is the maximum
+// over the lane's first tile; complete tiles after it cost one fma, one exponential and one add per logit.  When a sum
+// has grown past 1e30 after a chunk, the wave repeats that chunk from LDS with a reference that follows the maximum.
+// ---------------------------------------------------------------------------------------------
+template <int DT, int D, int RT>
+__global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) {
+  constexpr int ES = DT == DT_BF16 ? 2 : 4;
+  constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
+  constexpr int KC = LY_STAT_KC, TPC = KC / 32;
+  constexpr int KL = KC * CH / LY_THREADS;
+  constexpr int RPL = LY_THREADS / CH;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int lin = xcd_major(blockIdx.x, gridDim.x);
+  const int sp = lin % p.stat_splits;
+  const LayerGroup gr = layer_group(p, lin / p.stat_splits);
+  const int wk = LY_WAVES >> p.wr_log;                     // waves over different key tiles
+  const int wi = wave & ((1 << p.wr_log) - 1), ks = wave >> p.wr_log;
+  const int row0 = wi * RT * 32;
+  const bool active = row0 < p.m_rows;
+  const int n_keys = gr.n_ctx + gr.s_t;                    // look-back keys first
+  const int k_lo = min(sp * p.stat_keys, n_keys), k_hi = min(k_lo + p.stat_keys, n_keys);
+  const int lim0 = gr.n_ctx + gr.s_t - p.w;                // key k is visible to window row j iff k <= lim0 + j
+
+  extern __shared__ uint4 smem[];
+
+  uint4 q[RT][NCH];
+  int lim[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int m = min(row0 + r * 32 + rl, p.m_rows - 1);
+    lim[r] = lim0 + m - div_w(m, p.w_magic) * p.w + 1;     // end of the visible keys
+    const char* ptr = layer_row(p, gr, m);
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) q[r][i] = ld16(ptr + (2 * i + kg) * 16);
+  }
+  const uint32_t kstride = (uint32_t)p.k.stride_row;
+  const __amdgpu_buffer_rsrc_t ksrd = make_srd(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)(gr.lo - gr.n_ctx) * p.k.stride_row,
+                                               (uint32_t)n_keys * kstride);
+  const uint32_t k_row = tid / CH, k_col = tid % CH;
+  uint4 kpre[KL];
+  auto prefetch = [&](int kc0) {
+#pragma unroll
+    for (int u = 0; u < KL; ++u) kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * RPL) * kstride + k_col * 16);
+  };
+  auto store = [&](uint4* buf) {
+#pragma unroll
+    for (int u = 0; u < KL; ++u) buf[(k_row + u * RPL) * CHP + k_col] = kpre[u];
+  };
+
+  float ref[RT], sum[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    ref[r] = NEG_BIG;
+    sum[r] = 0.0f;
+  }
+  bool first = true;  // no tile yet: the lane has no reference
+  prefetch(k_lo);
+  store(smem);
+  lds_barrier();
+  int cur = 0;
+  for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
+    const bool more = kc0 + KC < k_hi;
+    if (more) prefetch(kc0 + KC);
+    const uint4* sK = smem + (size_t)cur * KC * CHP;
+    float kept[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) kept[r] = sum[r];
+    bool fixed_ref = !first;  // wave-uniform
+#pragma unroll 1
+    for (int attempt = active ? 0 : 2; attempt < 2; ++attempt) {
+#pragma unroll 1
+      for (int nt = ks; nt < TPC; nt += wk) {
+        const int kbase = kc0 + nt * 32;
+        if (kbase >= k_hi) break;  // wave-uniform
+        f32x16 acc[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[r][e] = 0.0f;
+        const uint4* krow = sK + (size_t)(nt * 32 + rl) * CHP + kg;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+          const uint4 kf = krow[2 * i];
+#pragma unroll
+          for (int r = 0; r < RT; ++r) Mma<DT>::run(acc[r], kf, q[r][i]);
+        }
+        const bool whole = kbase + 32 <= k_hi && kbase + 31 <= lim0;  // every row sees every key
+        if (whole && fixed_ref) {
+#pragma unroll
+          for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sum[r] += fast_exp2(fmaf(acc[r][e], p.scale2, -ref[r]));
+        } else {
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            const int n_vis = whole ? 32 : min(k_hi, lim[r]) - kbase;
+            if (acc_row(0, kg) < n_vis) {  // a lane that sees none of its keys keeps its state
+              float mx = acc[r][0];
+#pragma unroll
+              for (int e = 1; e < 16; ++e) mx = acc_row(e, kg) < n_vis ? fmaxf(mx, acc[r][e]) : mx;
+              const float nref = fmaxf(ref[r], mx * p.scale2);  // scale2 > 0
+              sum[r] *= fast_exp2(ref[r] - nref);
+              ref[r] = nref;
+#pragma unroll
+              for (int e = 0; e < 16; ++e)
+                sum[r] += acc_row(e, kg) < n_vis ? fast_exp2(fmaf(acc[r][e], p.scale2, -nref)) : 0.0f;
+            }
+          }
+          if (first) fixed_ref = true;
+          first = false;
+        }
+      }
+      // sums that have grown too large against the fixed reference: the chunk (still in LDS) once more, the reference
+      // following the maximum
+      bool over = false;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) over |= !(sum[r] < 1.0e30f);
+      if (attempt || !__any(over)) break;
+      fixed_ref = false;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const float nref = kept[r] > 1.0e10f ? ref[r] + fast_log2(kept[r]) : ref[r];
+        sum[r] = kept[r] * fast_exp2(ref[r] - nref);
+        ref[r] = nref;
+      }
+    }
+    if (more) store(smem + (size_t)(cur ^ 1) * KC * CHP);
+    cur ^= 1;
+    lds_barrier();
+  }
+  if (!active) return;
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    lse_merge(ref[r], sum[r], half_other(ref[r], kg), half_other(sum[r], kg));  // the two halves hold the same rows over different keys
+    const int row = row0 + r * 32 + rl;
+    if (kg == 0 && row < p.m_rows)
+      p.part[((size_t)gr.g * p.m_rows + row) * p.n_parts + sp * wk + ks] = make_float2(ref[r], sum[r]);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Scores, sign bits and counts.  Workgroup = (group, range of block keys).  Window rows and hyperplanes are A operands
+// that stay in registers, keys the B operand: lane = key.  Waves 0-3 hold the window rows (RT tiles each) and pool the
+// probabilities of a key in-lane over their rows; they do nothing else, and the exponentials of one pair of row tiles
+// run beside the matrix work of the next.  Waves 4-7 hold the hyperplanes (PT tiles each): they take the sign bits,
+// bring the keys into LDS, and finish the previous chunk (sums and sign bits meet in LDS, two buffers): the sum over
+// the score waves, and per key and table one probe of the table's cells.  Every SIMD runs one wave of either kind.
+// ---------------------------------------------------------------------------------------------
+constexpr int LY_HALF = LY_WAVES / 2;  // waves of either kind
+
+template <int DT, int D, int RT, int PT>
+__global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) {
+  constexpr int ES = DT == DT_BF16 ? 2 : 4;
+  constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
+  constexpr int KC = LY_KC, TPC = KC / 32;
+  constexpr int NLD = LY_THREADS / 2;        // threads that load keys
+  constexpr int KL = KC * CH / NLD;
+  constexpr int RPL = NLD / CH;
+  constexpr int AT = RT > PT ? RT : PT;
+  constexpr int TP = RT > 1 ? 2 : 1;         // row tiles per step
+  constexpr int NP = RT / TP;                // steps per key tile
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int lin = xcd_major(blockIdx.x, gridDim.x);
+  const LayerGroup gr = layer_group(p, lin / p.score_splits);
+  const int k_lo = (lin % p.score_splits) * p.score_keys, k_hi = min(k_lo + p.score_keys, gr.s_t);
+  if (k_lo >= k_hi) return;  // a short last block may leave ranges empty
+  const int lim0 = gr.s_t - p.w;  // block key i is visible to window row j iff i <= lim0 + j
+  const int n_rt = (p.m_rows + 31) >> 5, n_pt = (p.n_planes + 31) >> 5;
+  const bool hash = wave >= LY_HALF;
+  const int idx = wave & (LY_HALF - 1);
+  // tiles of this wave: first, first + 4, ...; with fewer than three tiles several waves share one over different key
+  // tiles (k0, k0 + kstep, ...)
+  const int n_own = hash ? n_pt : n_rt;
+  const int share = n_own >= 3 ? LY_HALF : n_own;
+  const int kstep = LY_HALF / share, first = idx % share, k0 = idx / share;
+  const bool active = first < n_own;
+  const int n_sum = min(n_rt, LY_HALF);  // score waves whose sums make up a key's
+
+  const int bits_pitch = (n_pt + 1) | 1;  // words per key in the sign-bit scratch: odd, and one past the last tile
+  extern __shared__ uint4 smem[];
+  uint4* sK = smem;                                                                         // [2][KC][CHP]
+  uint32_t* sBits = reinterpret_cast<uint32_t*>(smem + (size_t)2 * KC * CHP);               // [2][KC][bits_pitch]
+  float* sCol = reinterpret_cast<float*>(sBits + 2 * KC * bits_pitch);                      // [2][LY_HALF][KC]
+  int* sLim = reinterpret_cast<int*>(sCol + 2 * LY_HALF * KC);                              // [LY_ROWS]
+  float* sLse = reinterpret_cast<float*>(sLim + LY_ROWS);                                   // [LY_ROWS]
+  uint32_t* sCells = reinterpret_cast<uint32_t*>(sLse + LY_ROWS);                             // [n_tables][cell_words]
+
+  const uint32_t kstride = (uint32_t)p.k.stride_row;
+  const __amdgpu_buffer_rsrc_t ksrd =
+      make_srd(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)gr.lo * p.k.stride_row, (uint32_t)gr.s_t * kstride);
+  const uint32_t k_row = (tid & (NLD - 1)) / CH, k_col = tid % CH;
+  uint4 kpre[KL];
+  auto prefetch = [&](int kc0) {
+#pragma unroll
+    for (int u = 0; u < KL; ++u) kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * RPL) * kstride + k_col * 16);
+  };
+  auto store = [&](uint4* buf) {
+#pragma unroll
+    for (int u = 0; u < KL; ++u) buf[(k_row + u * RPL) * CHP + k_col] = kpre[u];
+  };
+  if (hash) prefetch(k_lo);
+
+  // the row's log-sum-exp (exp2 domain): merged from the partials of layer_stats_kernel and the caller's outside
+  // keys, or the caller's complete one
+  {
+    const int m = tid;
+    float lse = 1.0e30f;  // padding rows: probability 0
+    if (m < p.m_rows) {
+      const float* outside = p.row_lse_blk ? p.row_lse_blk[gr.b] : p.row_lse;
+      const float ext = outside ? outside[(size_t)gr.h * p.m_rows + m] * 1.4426950408889634f : 0.0f;
+      if (p.lse_complete) {
+        lse = ext;
+      } else {
+        float mm = NEG_BIG, ss = 0.0f;
+        const float2* part = p.part + ((size_t)gr.g * p.m_rows + m) * p.n_parts;
+        for (int i = 0; i < p.n_parts; ++i) {
+          const float2 v = part[i];
+          lse_merge(mm, ss, v.x, v.y);
+        }
+        if (outside) lse_merge(mm, ss, ext, 1.0f);
+        lse = mm + fast_log2(ss);
+      }
+    }
+    sLse[m] = lse;
+    const int mc = min(m, p.m_rows - 1);
+    sLim[m] = lim0 + mc - div_w(mc, p.w_magic) * p.w;
+  }
+  if (p.cells) {
+    const int n_cw = p.n_tables * p.cell_words;
+    const uint32_t* src = p.cells + (size_t)gr.g * n_cw;
+    if ((n_cw & 3) == 0) {
+      for (int i = tid; i < n_cw / 4; i += LY_THREADS) *reinterpret_cast<uint4*>(sCells + 4 * i) = ld16(src + 4 * i);
+    } else {
+      for (int i = tid; i < n_cw; i += LY_THREADS) sCells[i] = src[i];
+    }
+  }
+  uint4 a[AT][NCH];
+#pragma unroll
+  for (int t = 0; t < AT; ++t) {
+    const int tile = first + LY_HALF * t;
+    const char* ptr = hash ? p.planes + (size_t)min(tile * 32 + plane_row(rl), p.n_planes - 1) * (D * ES)
+                           : layer_row(p, gr, min(tile * 32 + rl, p.m_rows - 1));
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) a[t][i] = ld16(ptr + (2 * i + kg) * 16);
+  }
+  if (hash) store(sK);
+  __syncthreads();
+
+  if (!hash) {
+    // logits of one step: row tiles t0, t0 + 1 against the 32 keys at LDS rows kt * 32 ..
+    auto logits = [&](const uint4* stage, int kt, int t0, f32x16* acc) {
+#pragma unroll
+      for (int t = 0; t < TP; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
+      const uint4* brow = stage + (kt * 32 + rl) * CHP + kg;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        const uint4 kf = brow[2 * i];
+#pragma unroll
+        for (int t = 0; t < TP; ++t) Mma<DT>::run(acc[t], a[t0 + t][i], kf);
+      }
+    };
+    // their probabilities, summed over the rows
+    auto pooled = [&](const f32x16* acc, int t0) -> float {
+      float c[TP];
+#pragma unroll
+      for (int t = 0; t < TP; ++t) {
+        const int row = min((first + LY_HALF * (t0 + t)) * 32, LY_ROWS - 32);
+        c[t] = 0.0f;
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const float4 l4 = *reinterpret_cast<const float4*>(&sLse[row + acc_row(4 * g4, kg)]);
+          const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) c[t] += fast_exp2(fmaf(acc[t][4 * g4 + u], p.scale2, -ls[u]));
+        }
+      }
+      return TP > 1 ? c[0] + c[TP - 1] : c[0];
+    };
+    auto pooled_masked = [&](const f32x16* acc, int t0, int kidx) -> float {
+      float c = 0.0f;
+#pragma unroll
+      for (int t = 0; t < TP; ++t) {
+        const int row = min((first + LY_HALF * (t0 + t)) * 32, LY_ROWS - 32);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const float v = fast_exp2(fmaf(acc[t][e], p.scale2, -sLse[row + acc_row(e, kg)]));
+          c += kidx <= sLim[row + acc_row(e, kg)] ? v : 0.0f;
+        }
+      }
+      return c;
+    };
+    int cur = 0;
+    for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
+      const uint4* stage = sK + (size_t)cur * KC * CHP;
+      float* col_dst = sCol + (size_t)(cur * LY_HALF + first) * KC;
+      auto put = [&](int kt, float col) {
+        col = half_pair_sum(col);
+        if (kg == 0) col_dst[kt * 32 + rl] = col;
+      };
+      if (kstep == 1 && kc0 + KC <= k_hi && kc0 + KC - 1 <= lim0) {  // workgroup-uniform: a complete chunk that every row sees
+        f32x16 acc[2][TP];
+        float col = 0.0f;
+        logits(stage, 0, 0, acc[0]);
+#pragma unroll
+        for (int s = 0; s < TPC * NP; ++s) {
+          if (s + 1 < TPC * NP) logits(stage, (s + 1) / NP, (s + 1) % NP * TP, acc[(s + 1) & 1]);
+          col += pooled(acc[s & 1], s % NP * TP);
+          if (DT == DT_BF16) {
+            // a matrix instruction, then what the vector unit can do beside it
+#pragma unroll
+            for (int q = 0; q < NCH * TP; ++q) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // MFMA
+              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // LDS read
+              __builtin_amdgcn_sched_group_barrier(0x002, 32 / NCH, 0);      // VALU
+              __builtin_amdgcn_sched_group_barrier(0x400, 16 / NCH, 0);      // exponentials
+            }
+          }
+          if (s % NP == NP - 1) {
+            put(s / NP, col);
+            col = 0.0f;
+          }
+        }
+      } else if (active) {
+#pragma unroll 1
+        for (int kt = k0; kt < TPC; kt += kstep) {
+          const int kbase = kc0 + kt * 32;
+          if (kbase >= k_hi) break;  // wave-uniform
+          float col = 0.0f;
+#pragma unroll
+          for (int t0 = 0; t0 < RT; t0 += TP) {
+            f32x16 acc[TP];
+            logits(stage, kt, t0, acc);
+            col += kbase + 31 <= lim0 ? pooled(acc, t0) : pooled_masked(acc, t0, kbase + rl);
+          }
+          put(kt, col);
+        }
+      }
+      cur ^= 1;
+      lds_barrier();
+    }
+    return;
+  }
+
+  // the hashing waves
+  const uint32_t code_mask = (1u << p.n_bits) - 1u;
+  const uint32_t cpw = 1u << p.cell_log, cb_log = 5 - p.cell_log, cbits = 1u << cb_log;  // cells per word, their width
+  const uint32_t cell_max = (1u << cbits) - 1u;
+  // sums over the score waves and collision counts of the chunk whose first key is kc0: two lanes per key
+  auto finish = [&](int buf, int kc0) {
+    const int key = (tid - NLD) >> 1, sub = tid & 1;
+    const int kidx = kc0 + key;
+    const uint32_t* bits = sBits + (buf * KC + key) * bits_pitch;
+    const size_t at = (size_t)gr.g * p.s_stride + kidx;
+    if (sub == 0 && kidx < k_hi) {
+      const float* col = sCol + (size_t)buf * LY_HALF * KC + key;
+      float v = col[0];
+      for (int w = 1; w < n_sum; ++w) v += col[w * KC];
+      p.score[at] = v;
+    }
+    if (p.cells) {
+      uint32_t n = 0u, fullest = 0u;
+      auto code_of = [&](int t) {
+        const int bitpos = t * p.n_bits, w0 = bitpos >> 5;
+        return __builtin_amdgcn_alignbit(bits[w0 + 1], bits[w0], bitpos & 31) & code_mask;
+      };
+      auto cell_of = [&](int t, uint32_t code) {
+        return __builtin_amdgcn_ubfe(sCells[t * p.cell_words + (code >> p.cell_log)], (code & (cpw - 1)) << cb_log, cbits);
+      };
+#pragma unroll 8
+      for (int t = sub; t < p.n_tables; t += 2) {
+        const uint32_t c = cell_of(t, code_of(t));
+        n += c;
+        fullest = max(fullest, c);
+      }
+      if (cbits < 16 && __any(fullest == cell_max)) {  // some key met a heavy bin: its count is in the table's list
+        for (int t = sub; t < p.n_tables; t += 2) {
+          const uint32_t code = code_of(t);
+          if (cell_of(t, code) != cell_max) continue;
+          const uint32_t* list = p.heavy + ((size_t)gr.g * p.n_tables + t) * LY_HEAVY;
+          const int len = (int)list[0];
+          for (int i = 1; i <= len; ++i)
+            if (list[i] >> 16 == code) n += (list[i] & 0xffffu) - cell_max;
+        }
+      }
+      n += lane_xor1(n);
+      if (sub == 0 && kidx < k_hi) p.cnt[at] = (int)n;
+    } else if (kidx < k_hi) {
+      uint16_t* dst = p.sig_k + ((size_t)gr.g * p.s_stride + kidx) * p.n_tables;
+      for (int t = sub; t < p.n_tables; t += 2) {
+        const int bitpos = t * p.n_bits, w0 = bitpos >> 5;
+        dst[t] = (uint16_t)(__builtin_amdgcn_alignbit(bits[w0 + 1], bits[w0], bitpos & 31) & code_mask);
+      }
+      if (sub == 1) p.cnt[at] = 0;  // count_kernel accumulates with atomics
+    }
+  };
+  int cur = 0;
+  for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
+    const bool more = kc0 + KC < k_hi;
+    if (more) prefetch(kc0 + KC);
+    const uint4* stage = sK + (size_t)cur * KC * CHP;
+    if (active) {
+#pragma unroll 1
+      for (int vt = k0; vt < TPC; vt += kstep) {
+        if (kc0 + vt * 32 >= k_hi) break;
+        const uint4* brow = stage + (vt * 32 + rl) * CHP + kg;
+        auto signs = [&](const f32x16& acc, int t) {
+          // 16 consecutive planes per lane (see plane_row): their sign bits shift into one word
+          uint32_t neg = 0u;
+#pragma unroll
+          for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[e]), 31);
+          const uint32_t pos = ~neg & 0xffffu;
+          const uint32_t mask = pos | (half_other(pos, kg) << 16);
+          const int tile = first + LY_HALF * t;
+          if (kg == 0 && tile < n_pt) sBits[(cur * KC + vt * 32 + rl) * bits_pitch + tile] = mask;
+        };
+        constexpr int HT = PT == 4 ? 2 : PT;  // tiles at a time (registers)
+#pragma unroll
+        for (int t0 = 0; t0 < PT; t0 += HT) {
+          f32x16 acc[HT];
+#pragma unroll
+          for (int t = 0; t < HT; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) {
+            const uint4 kf = brow[2 * i];
+#pragma unroll
+            for (int t = 0; t < HT; ++t) Mma<DT>::run(acc[t], a[t0 + t][i], kf);
+          }
+#pragma unroll
+          for (int t = 0; t < HT; ++t) signs(acc[t], t0 + t);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if (kc0 > k_lo) finish(cur ^ 1, kc0 - KC);
+    if (more) store(sK + (size_t)(cur ^ 1) * KC * CHP);
+    cur ^= 1;
+    lds_barrier();
+  }
+  finish(cur ^ 1, k_lo + (k_hi - k_lo - 1) / KC * KC);
+}
+
+// ---- host side ----
+bool layer_supports(int dtype, int head_dim, int m_rows) {
+  return head_dim * (dtype == DT_BF16 ? 2 : 4) <= 256 && m_rows <= LY_ROWS;
+}
+
+static size_t score_lds(int head_dim, int es, int n_planes, int cell_total_words) {
+  const int bits_pitch = ((n_planes + 31) / 32 + 1) | 1;
+  return (size_t)2 * LY_KC * (head_dim * es / 16 + 1) * 16 + (size_t)2 * LY_KC * bits_pitch * 4 +
+         (size_t)2 * LY_HALF * LY_KC * 4 + (size_t)LY_ROWS * 8 + (size_t)cell_total_words * 4 + 16;
+}
+
+// Key ranges per group: workgroups come in rounds of n_cu (one per compute unit); a workgroup costs its keys plus
+// `ovh` (its loads of rows and hyperplanes, in units of keys).
+static int best_splits(int n_groups, int keys, int n_cu, int ovh, int* per) {
+  int best = 1;
+  long best_cost = -1;
+  for (int s = 1; s <= 16; ++s) {
+    const int kps = (keys + s - 1) / s, k32 = (kps + 31) / 32 * 32;
+    const long cost = (long)((n_groups * s + n_cu - 1) / n_cu) * (k32 + ovh);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = s;
+      *per = k32;
+    }
+  }
+  return best;
+}
+
+void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* plan) {
+  const int es = dtype == DT_BF16 ? 2 : 4;
+  const int n_groups = p->n_blocks * p->n_kv_heads;
+  const int n_rt = (p->m_rows + 31) / 32;
+  plan->rt = n_rt > 4 ? 2 : 1;
+  const int need = (n_rt + plan->rt - 1) / plan->rt;
+  p->wr_log = 0;
+  while ((1 << p->wr_log) < need) ++p->wr_log;
+  p->stat_splits = best_splits(n_groups, p->s_block + p->n_ctx, n_cu, 160, &p->stat_keys);
+  p->score_splits = best_splits(n_groups, p->s_block, n_cu, 128, &p->score_keys);
+  p->n_parts = p->stat_splits * (LY_WAVES >> p->wr_log);
+  p->s_stride = (p->s_block + 3) & ~3;
+  // tables per pass of the code kernel: histograms within 68 KiB, at most 256 hyperplanes
+  const int words = p->n_bits >= 5 ? 1 << (p->n_bits - 5) : 1;
+  int cw = 0;
+  plan->use_cells = 0;
+  for (p->cell_log = 1; p->n_bits <= 12 && p->cell_log <= 3 && !plan->use_cells; ++p->cell_log) {
+    cw = max(1, (1 << p->n_bits) >> p->cell_log);
+    plan->use_cells = (size_t)cw * p->n_tables * 4 <= 64 * 1024 && score_lds(head_dim, es, p->n_planes, cw * p->n_tables) <= 160 * 1024;
+    if (plan->use_cells) break;
+  }
+  p->cell_words = plan->use_cells ? cw : 0;
+  int nt = LY_CODE_PLANES / p->n_bits;
+  if (plan->use_cells) nt = min(nt, 1024 / words);
+  p->code_tables = max(1, min(nt, p->n_tables));
+  p->code_tiles = (p->code_tables * p->n_bits + 31) / 32;
+  plan->codes_lds = (size_t)p->code_tiles * 32 * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)p->code_tables * (words * 17 + 1) * 4 : 0);
+  plan->stats_lds = (size_t)2 * LY_STAT_KC * (head_dim * es / 16 + 1) * 16 + 16;
+  plan->score_lds = score_lds(head_dim, es, p->n_planes, plan->use_cells ? cw * p->n_tables : 0);
+  // workspace
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t g = n_groups;
+  size_t off = 0;
+  plan->off_part = off;   off += up(g * p->m_rows * p->n_parts * sizeof(float2));
+  plan->off_score = off;  off += up(g * p->s_stride * sizeof(float));
+  plan->off_cnt = off;    off += up(g * p->s_stride * sizeof(int32_t));
+  plan->off_cells = off;    off += plan->use_cells ? up(g * p->n_tables * cw * sizeof(uint32_t)) : 0;
+  plan->off_heavy = off;  off += plan->use_cells ? up(g * p->n_tables * LY_HEAVY * sizeof(uint32_t)) : 0;
+  plan->off_sig_k = off;  off += plan->use_cells ? 0 : up(g * p->s_stride * p->n_tables * sizeof(uint16_t));
+  plan->off_sig_q = off;  off += plan->use_cells ? 0 : up(g * p->m_rows * p->n_tables * sizeof(uint16_t));
+  plan->bytes = off + 256;
+}
+
+template <int DT, int D>
+static hipError_t launch_codes_t(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
+  hipLaunchKernelGGL((layer_codes_kernel<DT, D>), dim3(p.n_blocks * p.n_kv_heads), dim3(LY_THREADS), plan.codes_lds, st, p);
+  return hipGetLastError();
+}
+template <int DT, int D>
+static hipError_t launch_stats_t(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
+  const dim3 grid(p.n_blocks * p.n_kv_heads * p.stat_splits);
+  if (plan.rt == 2) hipLaunchKernelGGL((layer_stats_kernel<DT, D, 2>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
+  else hipLaunchKernelGGL((layer_stats_kernel<DT, D, 1>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
+  return hipGetLastError();
+}
+template <int DT, int D, int RT>
+static hipError_t launch_score_rt(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
+  const dim3 grid(p.n_blocks * p.n_kv_heads * p.score_splits), blk(LY_THREADS);
+  const int pt = (p.n_planes + 32 * LY_HALF - 1) / (32 * LY_HALF);
+  if (pt == 1) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 1>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 2) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 2>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 3) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 3>), grid, blk, plan.score_lds, st, p);
+  else hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 4>), grid, blk, plan.score_lds, st, p);
+  return hipGetLastError();
+}
+template <int DT, int D>
+static hipError_t launch_score_t(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
+  const int n_rt = (p.m_rows + 31) / 32;
+  if (n_rt <= LY_HALF) return launch_score_rt<DT, D, 1>(p, plan, st);
+  if (n_rt <= 2 * LY_HALF) return launch_score_rt<DT, D, 2>(p, plan, st);
+  return launch_score_rt<DT, D, 4>(p, plan, st);
+}
+
+#define LY_DISPATCH(fn)                                                              \
+  if (dtype == DT_BF16 && head_dim == 128) return fn<DT_BF16, 128>(p, plan, st);     \
+  if (dtype == DT_BF16 && head_dim == 64) return fn<DT_BF16, 64>(p, plan, st);       \
+  if (dtype == DT_F32 && head_dim == 64) return fn<DT_F32, 64>(p, plan, st);         \
+  return hipErrorInvalidValue
+
+hipError_t launch_layer_codes(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st) { LY_DISPATCH(launch_codes_t); }
+hipError_t launch_layer_stats(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st) { LY_DISPATCH(launch_stats_t); }
+hipError_t launch_layer_score(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st) { LY_DISPATCH(launch_score_t); }
+
+static hipError_t allow_lds(const void* kernel) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); }
+template <int DT, int D, int RT>
+static hipError_t score_attrs() {
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 1>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 2>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 3>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 4>));
+  return e;
+}
+template <int DT, int D>
+static hipError_t layer_attrs() {
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&layer_codes_kernel<DT, D>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 1>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 2>));
+  if (e == hipSuccess) e = score_attrs<DT, D, 1>();
+  if (e == hipSuccess) e = score_attrs<DT, D, 2>();
+  if (e == hipSuccess) e = score_attrs<DT, D, 4>();
+  return e;
+}
+hipError_t init_layer_attributes() {
+  hipError_t e = layer_attrs<DT_BF16, 128>();
+  if (e == hipSuccess) e = layer_attrs<DT_BF16, 64>();
+  if (e == hipSuccess) e = layer_attrs<DT_F32, 64>();
+  return e;
+}
+
+}  // namespace lkv

@@ -12,6 +12,11 @@ import torch
 from . import binding
 
 
+class _Plan(list):
+    """A call list and the device tensors its arguments point to."""
+    tensors = ()
+
+
 class LayerCompressor:
     def __init__(self, wl, device="cuda:0", max_blocks=None, budget=None, tail=0, lib=None):
         """budget: per-block budget B of this layer (default: the App. B equation for the workload; a
@@ -34,6 +39,7 @@ class LayerCompressor:
         self.v_cache = torch.zeros_like(self.k_cache)
         self.cache_pos = torch.full((wl.n_kv_heads, self.cap), -1, dtype=torch.int64, device=self.device)
         self.keep = torch.empty(wl.n_kv_heads, min(self.B, wl.s_block), dtype=torch.int32, device=self.device)
+        self._layer_ws = None  # scratch of laserkv_compress_layer, sized by the first layer that needs it
         self.cache_len = 0
 
     def reset(self):
@@ -112,13 +118,43 @@ class LayerCompressor:
         self.cache_len += b_t
         return nl, keep
 
+    def _layer_call(self, data, nb, row_lse_complete=None):
+        """(c_function, argument tuple without the stream) of one laserkv_compress_layer over the first nb blocks and
+        the rows it leaves in the cache, or None for shapes it has no kernels for.  row_lse_complete: device tensor
+        of per-block pointers, or None."""
+        wl, lib = self.wl, self.lib
+        n_tok = min(nb * wl.s_block, data["k"].shape[1])
+        last = n_tok - (nb - 1) * wl.s_block
+        size = lib._lib.laserkv_layer_workspace_bytes(lib._ctx, n_tok, wl.s_block, wl.window, self.parts[1]) if last >= wl.window else -1
+        if size < 0:
+            return None
+        if self._layer_ws is None or self._layer_ws.numel() < size:
+            self._layer_ws = torch.empty(size, dtype=torch.uint8, device=self.device)
+        q, k, v = data["q_win"], data["k"], data["v"]
+        b_last = sum(self.block_budget(last))
+        keep = self.keep if b_last == self.keep.shape[1] else None
+        args = (lib._ctx, q.data_ptr(), q.stride(0), q.stride(1), q.stride(2), k.data_ptr(), k.stride(0), k.stride(1),
+                v.data_ptr(), v.stride(0), v.stride(1), data["planes"].data_ptr(), n_tok, wl.s_block, wl.window,
+                self.B, wl.n_div, wl.alpha, None if row_lse_complete is None else row_lse_complete.data_ptr(),
+                None if keep is None else keep.data_ptr(), self.k_cache.data_ptr(), self.v_cache.data_ptr(),
+                self.k_cache.stride(0), self.cache_pos.data_ptr(), self.cache_pos.stride(0), self.cap,
+                self._layer_ws.data_ptr(), self._layer_ws.numel())
+        return lib._lib.laserkv_compress_layer, args, (nb - 1) * sum(self.parts) + b_last
+
     def run_layer(self, data, n_blocks=None):
-        """All blocks of one layer, back to back, no host sync.  data: device tensors from synth.make_layer."""
+        """All blocks of one layer, no host sync: one laserkv_compress_layer call, or, where a block's shape has no
+        layer kernels, block by block.  data: device tensors from synth.make_layer."""
         wl = self.wl
         self.reset()
         nb = data["q_win"].shape[0] if n_blocks is None else n_blocks
         prev_local = 0
         l_tot = data["k"].shape[1]
+        call = self._layer_call(data, nb) if nb > 1 else None
+        if call is not None:
+            fn, args, n = call
+            self.lib._check(fn(*args, torch.cuda.current_stream().cuda_stream))
+            self.cache_len = n
+            return n
         for t in range(nb):
             lo, hi = t * wl.s_block, min((t + 1) * wl.s_block, l_tot)
             prev_local, _ = self.step(data["q_win"][t], data["k"][:, lo:hi], data["v"][:, lo:hi], data["planes"],
@@ -169,10 +205,12 @@ class LayerCompressor:
         The tensors in `data`, the cache and the keep buffer must stay alive and in place while the
         plan is used.  run_plan() then issues the calls back to back with no per-call Python work
         beyond the foreign call itself (and can be captured into a HIP graph).  fused=True uses
-        laserkv_compress_block (one call per block), else laserkv_select_block + laserkv_append.
+        laserkv_compress_layer (one call for all blocks) where it has kernels for the shape, else
+        laserkv_compress_block (one call per block); fused=False laserkv_select_block + laserkv_append.
         row_lse_complete: optional list of per-block float32 [H_q, W] device tensors with the window rows'
-        complete log-sum-exp (what the model's attention kernel reports); each block's call is then preceded
-        by laserkv_set_row_lse_complete, and look-back keys are not passed.
+        complete log-sum-exp (what the model's attention kernel reports): handed to laserkv_compress_layer as a
+        table of pointers, or set by laserkv_set_row_lse_complete in front of each block's call, and look-back
+        keys are not passed.
         """
         import ctypes as C
         wl, lib = self.wl, self.lib._lib
@@ -181,7 +219,23 @@ class LayerCompressor:
         nb = data["q_win"].shape[0] if n_blocks is None else n_blocks
         l_tot = data["k"].shape[1]
         d = wl.head_dim
-        calls, cache_len, prev_local = [], 0, 0
+        calls, cache_len, prev_local = _Plan(), 0, 0
+        if row_lse_complete is not None:
+            for lse in row_lse_complete[:nb]:
+                assert lse.is_contiguous() and lse.dtype == torch.float32 and lse.shape == (wl.n_q_heads, wl.window)
+        if fused and nb > 1:
+            table = None
+            if row_lse_complete is not None:
+                table = torch.tensor([t.data_ptr() for t in row_lse_complete[:nb]], dtype=torch.int64, device=self.device)
+            call = self._layer_call(data, nb, table)
+            if call is not None:
+                assert min(nb * wl.s_block, l_tot) == nb * wl.s_block, "plans cover equal-sized blocks only"
+                calls.tensors = (table, self._layer_ws)
+                calls.append((call[0], call[1], True))
+                if row_lse_complete is not None:
+                    calls.append((lib.laserkv_set_row_lse_complete, (ctx, None), False))
+                self._plan_len = call[2]
+                return calls
         kc_sh, kc_st = self.k_cache.stride(0), self.k_cache.stride(1)
         es = self.k_cache.element_size()
         for t in range(nb):
@@ -194,7 +248,6 @@ class LayerCompressor:
             t_ctx = prev_local if cache_len else 0
             if row_lse_complete is not None:
                 lse = row_lse_complete[t]
-                assert lse.is_contiguous() and lse.dtype == torch.float32 and lse.shape == (wl.n_q_heads, wl.window)
                 calls.append((lib.laserkv_set_row_lse_complete, (ctx, vp(lse.data_ptr())), False))
                 t_ctx = 0
             ctx_ptr = vp(self.k_cache.data_ptr() + (cache_len - t_ctx) * kc_st * es) if t_ctx else None

@@ -1,0 +1,145 @@
+"""laserkv_compress_layer (all blocks of a layer in one call) against the block-by-block loop and the oracle, at the
+shapes where its kernels change: row tiles and plane tiles that do not fill the waves, block lengths that are no
+multiple of a chunk, a short last block, cell widths of 16, 8 and 4 bits, codes wider than 12 bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import laserkv_oracle as O
+from paper_2602_02199_amd import binding, synth
+from paper_2602_02199_amd.driver import LayerCompressor
+from tests.test_gpu_parity import DEV, f64, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def oracle_positions(wl, data, B, nb, outside=None):
+    """Kept positions per head of the first nb blocks, and how close each block's thresholds are to a tie."""
+    k, planes = f64(data["k"]), f64(data["planes"])
+    l_tot = k.shape[1]
+    pos, prev = [], 0
+    for t in range(nb):
+        lo, hi = t * wl.s_block, min((t + 1) * wl.s_block, l_tot)
+        parts = O.partition(B, wl.n_div, wl.alpha, hi - lo)
+        st = O.select_block(f64(data["q_win"][t]), k[:, lo:hi], k[:, lo - prev:lo] if prev else None, planes, wl.lsh_tables,
+                            wl.lsh_bits, *parts, block_pos0=lo)
+        pos.append(np.asarray(st["keep"]) + lo)
+        prev = parts[1]
+    return np.concatenate(pos, axis=1)
+
+
+def loop_positions(wl, dev, B, nb):
+    comp = LayerCompressor(wl, DEV, budget=B)
+    l_tot, prev = dev["k"].shape[1], 0
+    for t in range(nb):
+        lo, hi = t * wl.s_block, min((t + 1) * wl.s_block, l_tot)
+        prev, _ = comp.step(dev["q_win"][t], dev["k"][:, lo:hi], dev["v"][:, lo:hi], dev["planes"], lo, prev)
+    torch.cuda.synchronize()
+    return comp
+
+
+def check_layer(wl, mutate=None, with_oracle=True, tol=2e-3):
+    B = O.budget(wl.s_block, wl.l_ctx, wl.r_num, wl.r_den)
+    data = synth.make_layer(wl, 1, O.partition(B, wl.n_div, wl.alpha, wl.s_block)[0])
+    if mutate is not None:
+        mutate(data)
+    dev = to_dev(data)
+    nb = wl.n_blocks
+    comp = LayerCompressor(wl, DEV)
+    comp.lib.laserkv_profile_begin()
+    n = comp.run_layer(dev)
+    torch.cuda.synchronize()
+    launches = {k: v[1] for k, v in comp.lib.laserkv_profile_end().items() if v[1]}
+    assert launches["select"] == 1 and launches["sweep1"] == 1 and "append" not in launches, launches
+    ref = loop_positions(wl, dev, B, nb)
+    assert n == ref.cache_len
+    pos, want = comp.cache_pos[:, :n], ref.cache_pos[:, :n]
+    assert bool((pos[:, 1:] > pos[:, :-1]).all()) and bool((comp.cache_pos[:, n:] == -1).all())
+    idx = pos[:, :, None].expand(-1, -1, wl.head_dim)
+    assert torch.equal(torch.gather(dev["k"], 1, idx), comp.k_cache[:, :n])
+    assert torch.equal(torch.gather(dev["v"], 1, idx), comp.v_cache[:, :n])
+    swapped = sum(len(set(pos[h].tolist()) - set(want[h].tolist())) for h in range(wl.n_kv_heads))
+    say(f"[layer {wl.name}] rows {n}, tokens kept that the block loop does not keep: {swapped}")
+    assert swapped <= tol * n * wl.n_kv_heads
+    if with_oracle:
+        o = oracle_positions(wl, data, B, nb)
+        got = pos.cpu().numpy()
+        off = sum(len(set(got[h].tolist()) - set(o[h].tolist())) for h in range(wl.n_kv_heads))
+        say(f"[layer {wl.name}] tokens kept that the oracle does not keep: {off}")
+        assert off <= tol * n * wl.n_kv_heads
+    return launches
+
+
+@pytest.mark.parametrize("case", [
+    dict(name="two-row-tiles", n_q_heads=4, n_kv_heads=2, head_dim=64, dtype="f32", l_ctx=2048, s_block=512, window=32, n_div=4,
+         lsh_tables=8, lsh_bits=8),
+    dict(name="one-row-tile-one-plane", n_q_heads=2, n_kv_heads=2, head_dim=64, dtype="bf16", l_ctx=390, s_block=130, window=3,
+         n_div=2, lsh_tables=1, lsh_bits=1),
+    dict(name="three-tiles-of-each", n_q_heads=6, n_kv_heads=2, head_dim=128, dtype="bf16", l_ctx=2077, s_block=701, window=27,
+         n_div=5, lsh_tables=7, lsh_bits=11),
+    dict(name="five-plane-tiles-short-last-block", n_q_heads=32, n_kv_heads=8, head_dim=128, dtype="bf16", l_ctx=5000, s_block=2048,
+         window=64, n_div=4, lsh_tables=16, lsh_bits=10),
+    dict(name="four-bit-cells", n_q_heads=16, n_kv_heads=4, head_dim=128, dtype="bf16", l_ctx=3000, s_block=1000, window=128, n_div=8,
+         lsh_tables=32, lsh_bits=12),
+    dict(name="odd-row-tiles", n_q_heads=10, n_kv_heads=2, head_dim=64, dtype="bf16", l_ctx=1500, s_block=500, window=29, n_div=4,
+         lsh_tables=9, lsh_bits=9),
+    dict(name="wide-codes", n_q_heads=16, n_kv_heads=2, head_dim=128, dtype="bf16", l_ctx=2600, s_block=1100, window=40, n_div=4,
+         lsh_tables=31, lsh_bits=16),
+    dict(name="blocks-shorter-than-a-tile", n_q_heads=2, n_kv_heads=1, head_dim=128, dtype="bf16", l_ctx=80, s_block=19, window=4,
+         n_div=2, lsh_tables=2, lsh_bits=2),
+])
+def test_layer_call_against_block_loop_and_oracle(case):
+    check_layer(synth.shrink(synth.WORKLOADS["tiny"], index=41, needles_per_block=2, outlier_channels=2, **case))
+
+
+@pytest.mark.parametrize("kw", [dict(lsh_tables=32, lsh_bits=12), dict(lsh_tables=32, lsh_bits=11)])
+def test_layer_call_with_heavy_bins(kw):
+    """Window rows that are nearly one vector share their codes: bins hold more rows than a narrow cell can say."""
+    wl = synth.shrink(synth.WORKLOADS["llama8b-128k"], index=43, name=f"heavy-{kw['lsh_bits']}", l_ctx=2048, s_block=1024,
+                      n_q_heads=16, n_kv_heads=4, **kw)
+
+    def mutate(data):
+        q = data["q_win"].float()
+        data["q_win"] = (q[:, :, :1] + 0.1 * q).to(torch.bfloat16).contiguous()
+
+    check_layer(wl, mutate)
+
+
+def test_layer_call_with_a_dominant_late_key():
+    """A key deep inside a range whose logit lies far above everything before it: the statistics of that chunk are repeated."""
+    wl = synth.shrink(synth.WORKLOADS["llama8b-16k"], index=44, name="dominant", l_ctx=4096, needles_per_block=2)
+
+    def mutate(data):
+        k = data["k"].float()
+        for t in range(2):
+            for h in range(wl.n_kv_heads):
+                qv = data["q_win"][t, h * wl.group, 5].float()
+                k[h, t * wl.s_block + 1201 + 3 * h] = qv * (130.0 * wl.head_dim ** 0.5 / float(qv @ qv))
+        data["k"] = k.to(torch.bfloat16).contiguous()
+
+    check_layer(wl, mutate)
+
+
+def test_layer_call_falls_back_where_it_has_no_kernels():
+    wl = synth.shrink(synth.WORKLOADS["tiny"], index=45, name="f32-d128", head_dim=128, l_ctx=1024)
+    comp = LayerCompressor(wl, DEV)
+    assert comp.lib._lib.laserkv_layer_workspace_bytes(comp.lib._ctx, 1024, wl.s_block, wl.window, comp.parts[1]) == -1
+    dev = to_dev(synth.make_layer(wl, 0, comp.parts[0]))
+    n = comp.run_layer(dev)
+    ref = loop_positions(wl, dev, comp.B, wl.n_blocks)
+    assert n == ref.cache_len and torch.equal(comp.cache_pos, ref.cache_pos)
+
+
+def test_layer_call_rejects_what_does_not_fit():
+    wl = synth.shrink(synth.WORKLOADS["tiny"], index=46, l_ctx=1024)
+    comp = LayerCompressor(wl, DEV)
+    dev = to_dev(synth.make_layer(wl, 0, comp.parts[0]))
+    fn, args, _ = comp._layer_call(dev, 2)
+    stream = torch.cuda.current_stream().cuda_stream
+    before = comp.cache_pos.clone()
+    for at, value, code in ((25, 10, binding.LKV_ECAP), (27, 256, binding.LKV_EINVAL), (13, 100000, binding.LKV_EINVAL)):
+        bad = list(args)
+        bad[at] = value
+        assert fn(*bad, stream) == code, (at, comp.lib._lib.laserkv_last_error(comp.lib._ctx))
+    torch.cuda.synchronize()
+    assert torch.equal(before, comp.cache_pos)
