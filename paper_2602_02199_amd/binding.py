@@ -156,30 +156,43 @@ def laserkv_compress_block_static(cfg: Config, q_win, k_blk, v_blk, k_ctx, hyper
     """laserkv_compress_block on the library's static scratch (no context, no allocation).  stream: raw handle."""
     lib = load()
     d = cfg.head_dim
-    s_t, w = k_blk.shape[1], q_win.shape[1]
-    t_ctx = 0 if k_ctx is None else k_ctx.shape[1]
-    if q_pos0 is None:
-        q_pos0 = LKV_WINDOW_AT_BLOCK_END
-    qs, ks, vs = _strides3(q_win, d), _strides3(k_blk, d), _strides3(v_blk, d)
-    cs = _strides3(k_ctx, d) if k_ctx is not None else (0, 0)
+    q, qsh, qst, w = _rows3(q_win, d)
+    k, ksh, kst, s_t = _rows3(k_blk, d)
+    v, vsh, vst, _ = _rows3(v_blk, d)
+    c, csh, cst, t_ctx = _context3(k_ctx, d)
+    kc, vc, cache_sh, cap = _cache(k_cache, v_cache, d)
     assert hyperplanes.is_contiguous()
-    assert k_cache.stride(2) == 1 and k_cache.stride(1) == d and v_cache.stride() == k_cache.stride()
     rc = lib.laserkv_compress_block_static(
-        C.byref(cfg), _ptr(q_win), qs[0], qs[1], _ptr(k_blk), ks[0], ks[1], _ptr(v_blk), vs[0], vs[1],
-        _ptr(k_ctx), cs[0], cs[1], _ptr(hyperplanes), s_t, w, t_ctx, block_pos0, q_pos0, 1 if causal else 0,
-        n_anchor, n_local, k_exact, k_lsh, _ptr(keep_idx), _ptr(k_cache), _ptr(v_cache), k_cache.stride(0),
-        _ptr(cache_pos), cache_pos.stride(0), cache_len, k_cache.shape[1], C.c_void_p(stream))
+        C.byref(cfg), q, qsh, qst, k, ksh, kst, v, vsh, vst, c, csh, cst, hyperplanes.data_ptr(), s_t, w, t_ctx, block_pos0,
+        LKV_WINDOW_AT_BLOCK_END if q_pos0 is None else q_pos0, 1 if causal else 0, n_anchor, n_local, k_exact, k_lsh,
+        _ptr(keep_idx), kc, vc, cache_sh, _ptr(cache_pos), cache_pos.stride(0), cache_len, cap, stream)
     if rc != LKV_OK:
         raise LaserKVError(rc, lib.laserkv_last_error(None).decode())
 
 
+# Small calls cost what their marshalling costs: every attribute of a tensor is read once (about 0.1 us each), addresses
+# go to ctypes as plain integers.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _strides3(t, d):
-    assert t.dim() == 3 and t.stride(2) == 1 and t.shape[2] == d, "expected [heads, rows, d] with d contiguous"
-    return t.stride(0), t.stride(1)
+def _rows3(t, d):
+    """(address, head stride, row stride, rows) of a [heads, rows, d] tensor with d contiguous."""
+    sh, st, one = t.stride()
+    _, n, dd = t.shape
+    assert one == 1 and dd == d, "expected [heads, rows, d] with d contiguous"
+    return t.data_ptr(), sh, st, n
+
+
+def _context3(t, d):
+    return (None, 0, 0, 0) if t is None else _rows3(t, d)
+
+
+def _cache(k_cache, v_cache, d):
+    """(K address, V address, head stride, capacity) of a cache pair [H_kv, cap, d] with contiguous rows."""
+    ks = k_cache.stride()
+    assert ks[2] == 1 and ks[1] == d and v_cache.stride() == ks
+    return k_cache.data_ptr(), v_cache.data_ptr(), ks[0], k_cache.shape[1]
 
 
 class LaserKV:
@@ -195,6 +208,8 @@ class LaserKV:
         self.cfg = Config(n_q_heads, n_kv_heads, head_dim,
                           {"f32": LKV_F32, "bf16": LKV_BF16}[dtype] if isinstance(dtype, str) else dtype,
                           lsh_tables, lsh_bits, max_block, max_window, max_ctx_keys)
+        self._head_dim = head_dim
+        self._raw_stream, self._current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
         self._ctx = C.c_void_p()
         rc = self._lib.laserkv_create(C.byref(self.cfg), C.byref(self._ctx))
         if rc != LKV_OK:
@@ -216,74 +231,70 @@ class LaserKV:
             raise LaserKVError(rc, self._lib.laserkv_last_error(self._ctx).decode())
 
     def _stream(self, stream):
-        if stream is None:
-            stream = self._torch.cuda.current_stream().cuda_stream
-        return C.c_void_p(stream)
+        # the raw handle without a Stream object around it (0.3 instead of 2.8 us)
+        return self._raw_stream(self._current_device()) if stream is None else stream
 
     def laserkv_select_block(self, q_win, k_blk, k_ctx, hyperplanes, *, block_pos0, q_pos0=None, causal=True,
                              n_anchor, n_local, k_exact, k_lsh, keep_idx,
                              dbg_s_exact=None, dbg_sig_k=None, dbg_sig_q=None, dbg_count=None, stream=None):
-        d = self.cfg.head_dim
-        s_t, w = k_blk.shape[1], q_win.shape[1]
-        t_ctx = 0 if k_ctx is None else k_ctx.shape[1]
-        if q_pos0 is None:
-            q_pos0 = LKV_WINDOW_AT_BLOCK_END
-        qs, ks = _strides3(q_win, d), _strides3(k_blk, d)
-        cs = _strides3(k_ctx, d) if k_ctx is not None else (0, 0)
+        d = self._head_dim
+        q, qsh, qst, w = _rows3(q_win, d)
+        k, ksh, kst, s_t = _rows3(k_blk, d)
+        c, csh, cst, t_ctx = _context3(k_ctx, d)
         assert hyperplanes.is_contiguous()
         rc = self._lib.laserkv_select_block(
-            self._ctx, _ptr(q_win), qs[0], qs[1], _ptr(k_blk), ks[0], ks[1], _ptr(k_ctx), cs[0], cs[1],
-            _ptr(hyperplanes), s_t, w, t_ctx, block_pos0, q_pos0, 1 if causal else 0,
-            n_anchor, n_local, k_exact, k_lsh, _ptr(keep_idx),
-            _ptr(dbg_s_exact), _ptr(dbg_sig_k), _ptr(dbg_sig_q), _ptr(dbg_count), self._stream(stream))
-        self._check(rc)
+            self._ctx, q, qsh, qst, k, ksh, kst, c, csh, cst, hyperplanes.data_ptr(), s_t, w, t_ctx, block_pos0,
+            LKV_WINDOW_AT_BLOCK_END if q_pos0 is None else q_pos0, 1 if causal else 0, n_anchor, n_local, k_exact, k_lsh,
+            _ptr(keep_idx), _ptr(dbg_s_exact), _ptr(dbg_sig_k), _ptr(dbg_sig_q), _ptr(dbg_count), self._stream(stream))
+        if rc:
+            self._check(rc)
+
+    def _append(self, fn, k_blk, v_blk, keep_idx, b_t, block_pos0, k_cache, v_cache, cache_pos, cache_len, stream):
+        d = self._head_dim
+        k, ksh, kst, s_t = _rows3(k_blk, d)
+        v, vsh, vst, _ = _rows3(v_blk, d)
+        kc, vc, cache_sh, cap = _cache(k_cache, v_cache, d)
+        rc = fn(self._ctx, k, ksh, kst, v, vsh, vst, _ptr(keep_idx), b_t, s_t, block_pos0, kc, vc, cache_sh,
+                _ptr(cache_pos), cache_pos.stride(0), cache_len, cap, self._stream(stream))
+        if rc:
+            self._check(rc)
 
     def laserkv_append(self, k_blk, v_blk, keep_idx, *, b_t, block_pos0, k_cache, v_cache, cache_pos,
                        cache_len, stream=None):
-        d = self.cfg.head_dim
-        ks, vs = _strides3(k_blk, d), _strides3(v_blk, d)
-        assert k_cache.stride(2) == 1 and k_cache.stride(1) == d and v_cache.stride() == k_cache.stride()
-        rc = self._lib.laserkv_append(
-            self._ctx, _ptr(k_blk), ks[0], ks[1], _ptr(v_blk), vs[0], vs[1], _ptr(keep_idx), b_t, k_blk.shape[1],
-            block_pos0, _ptr(k_cache), _ptr(v_cache), k_cache.stride(0), _ptr(cache_pos), cache_pos.stride(0),
-            cache_len, k_cache.shape[1], self._stream(stream))
-        self._check(rc)
+        self._append(self._lib.laserkv_append, k_blk, v_blk, keep_idx, b_t, block_pos0, k_cache, v_cache, cache_pos,
+                     cache_len, stream)
 
     def laserkv_compress_block(self, q_win, k_blk, v_blk, k_ctx, hyperplanes, *, block_pos0, q_pos0=None, causal=True,
                                n_anchor, n_local, k_exact, k_lsh, keep_idx, k_cache, v_cache, cache_pos, cache_len,
                                stream=None):
-        d = self.cfg.head_dim
-        s_t, w = k_blk.shape[1], q_win.shape[1]
-        t_ctx = 0 if k_ctx is None else k_ctx.shape[1]
-        if q_pos0 is None:
-            q_pos0 = LKV_WINDOW_AT_BLOCK_END
-        qs, ks, vs = _strides3(q_win, d), _strides3(k_blk, d), _strides3(v_blk, d)
-        cs = _strides3(k_ctx, d) if k_ctx is not None else (0, 0)
+        d = self._head_dim
+        q, qsh, qst, w = _rows3(q_win, d)
+        k, ksh, kst, s_t = _rows3(k_blk, d)
+        v, vsh, vst, _ = _rows3(v_blk, d)
+        c, csh, cst, t_ctx = _context3(k_ctx, d)
+        kc, vc, cache_sh, cap = _cache(k_cache, v_cache, d)
         assert hyperplanes.is_contiguous()
-        assert k_cache.stride(2) == 1 and k_cache.stride(1) == d and v_cache.stride() == k_cache.stride()
         rc = self._lib.laserkv_compress_block(
-            self._ctx, _ptr(q_win), qs[0], qs[1], _ptr(k_blk), ks[0], ks[1], _ptr(v_blk), vs[0], vs[1],
-            _ptr(k_ctx), cs[0], cs[1], _ptr(hyperplanes), s_t, w, t_ctx, block_pos0, q_pos0, 1 if causal else 0,
-            n_anchor, n_local, k_exact, k_lsh, _ptr(keep_idx), _ptr(k_cache), _ptr(v_cache), k_cache.stride(0),
-            _ptr(cache_pos), cache_pos.stride(0), cache_len, k_cache.shape[1], self._stream(stream))
-        self._check(rc)
+            self._ctx, q, qsh, qst, k, ksh, kst, v, vsh, vst, c, csh, cst, hyperplanes.data_ptr(), s_t, w, t_ctx, block_pos0,
+            LKV_WINDOW_AT_BLOCK_END if q_pos0 is None else q_pos0, 1 if causal else 0, n_anchor, n_local, k_exact, k_lsh,
+            _ptr(keep_idx), kc, vc, cache_sh, _ptr(cache_pos), cache_pos.stride(0), cache_len, cap, self._stream(stream))
+        if rc:
+            self._check(rc)
 
     def laserkv_score_block(self, q_win, k_blk, k_ctx, hyperplanes, *, block_pos0, q_pos0=None, causal=True,
                             score_acc, count_acc, accumulate, stream=None):
-        d = self.cfg.head_dim
-        s_t, w = k_blk.shape[1], q_win.shape[1]
-        t_ctx = 0 if k_ctx is None else k_ctx.shape[1]
-        if q_pos0 is None:
-            q_pos0 = LKV_WINDOW_AT_BLOCK_END
-        qs, ks = _strides3(q_win, d), _strides3(k_blk, d)
-        cs = _strides3(k_ctx, d) if k_ctx is not None else (0, 0)
+        d = self._head_dim
+        q, qsh, qst, w = _rows3(q_win, d)
+        k, ksh, kst, s_t = _rows3(k_blk, d)
+        c, csh, cst, t_ctx = _context3(k_ctx, d)
         assert hyperplanes.is_contiguous() and score_acc.is_contiguous() and count_acc.is_contiguous()
         assert score_acc.numel() >= s_t and count_acc.numel() >= s_t
         rc = self._lib.laserkv_score_block(
-            self._ctx, _ptr(q_win), qs[0], qs[1], _ptr(k_blk), ks[0], ks[1], _ptr(k_ctx), cs[0], cs[1],
-            _ptr(hyperplanes), s_t, w, t_ctx, block_pos0, q_pos0, 1 if causal else 0,
-            _ptr(score_acc), _ptr(count_acc), 1 if accumulate else 0, self._stream(stream))
-        self._check(rc)
+            self._ctx, q, qsh, qst, k, ksh, kst, c, csh, cst, hyperplanes.data_ptr(), s_t, w, t_ctx, block_pos0,
+            LKV_WINDOW_AT_BLOCK_END if q_pos0 is None else q_pos0, 1 if causal else 0,
+            score_acc.data_ptr(), count_acc.data_ptr(), 1 if accumulate else 0, self._stream(stream))
+        if rc:
+            self._check(rc)
 
     def laserkv_select_consensus(self, score_acc, count_acc, *, s_t, n_anchor, n_local, k_exact, k_lsh, keep_idx,
                                  stream=None):
@@ -294,14 +305,8 @@ class LaserKV:
 
     def laserkv_append_shared(self, k_blk, v_blk, keep_idx, *, b_t, block_pos0, k_cache, v_cache, cache_pos,
                               cache_len, stream=None):
-        d = self.cfg.head_dim
-        ks, vs = _strides3(k_blk, d), _strides3(v_blk, d)
-        assert k_cache.stride(2) == 1 and k_cache.stride(1) == d and v_cache.stride() == k_cache.stride()
-        rc = self._lib.laserkv_append_shared(
-            self._ctx, _ptr(k_blk), ks[0], ks[1], _ptr(v_blk), vs[0], vs[1], _ptr(keep_idx), b_t, k_blk.shape[1],
-            block_pos0, _ptr(k_cache), _ptr(v_cache), k_cache.stride(0), _ptr(cache_pos), cache_pos.stride(0),
-            cache_len, k_cache.shape[1], self._stream(stream))
-        self._check(rc)
+        self._append(self._lib.laserkv_append_shared, k_blk, v_blk, keep_idx, b_t, block_pos0, k_cache, v_cache, cache_pos,
+                     cache_len, stream)
 
     def laserkv_set_row_lse(self, row_lse):
         """row_lse: contiguous float32 [H_q, w] device tensor, or None to switch the feature off.  The tensor
@@ -329,17 +334,20 @@ class LaserKV:
         """q [H_q, n_q, d]; k_cache / v_cache [H_kv, cap, d]; out float32 [H_q, n_q, d] or None (normaliser only),
         out_lse float32 [H_q, n_q];
         workspace: uint8 device tensor of at least laserkv_attend_workspace_bytes(n_q, cache_len) bytes."""
-        d = self.cfg.head_dim
-        qs = _strides3(q, d)
-        assert k_cache.stride(2) == 1 and k_cache.stride(1) == d and v_cache.stride() == k_cache.stride()
+        d = self._head_dim
+        qp, qsh, qst, n_q = _rows3(q, d)
+        ks = k_cache.stride()
+        assert ks[2] == 1 and ks[1] == d and v_cache.stride() == ks
         f32 = self._torch.float32
-        assert out is None or (out.is_contiguous() and out.dtype == f32 and out.shape == q.shape)
-        assert out_lse.is_contiguous() and out_lse.dtype == f32 and out_lse.shape == q.shape[:2]
+        shape = q.shape
+        assert out is None or (out.is_contiguous() and out.dtype is f32 and out.shape == shape)
+        assert out_lse.is_contiguous() and out_lse.dtype is f32 and out_lse.shape == shape[:2]
         assert workspace.is_contiguous() and workspace.element_size() == 1
         rc = self._lib.laserkv_attend_cache(
-            self._ctx, _ptr(q), qs[0], qs[1], q.shape[1], _ptr(k_cache), _ptr(v_cache), k_cache.stride(0), cache_len,
-            _ptr(out), _ptr(out_lse), _ptr(workspace), workspace.numel(), self._stream(stream))
-        self._check(rc)
+            self._ctx, qp, qsh, qst, n_q, k_cache.data_ptr(), v_cache.data_ptr(), ks[0], cache_len,
+            _ptr(out), out_lse.data_ptr(), workspace.data_ptr(), workspace.numel(), self._stream(stream))
+        if rc:
+            self._check(rc)
 
     def laserkv_attend_block_workspace_bytes(self, n_q, cache_len, s_t):
         n = int(self._lib.laserkv_attend_block_workspace_bytes(self._ctx, n_q, cache_len, s_t))
@@ -353,24 +361,26 @@ class LaserKV:
         [H_kv, s_t, d] (views with strides allowed); out float32 [H_q, n_q, d], out_lse float32 [H_q, n_q];
         q_pos0 defaults to the block's last n_q positions;
         workspace: uint8 device tensor of at least laserkv_attend_block_workspace_bytes(n_q, cache_len, s_t) bytes."""
-        d = self.cfg.head_dim
-        qs, ks, vs = _strides3(q, d), _strides3(k_blk, d), _strides3(v_blk, d)
-        s_t = k_blk.shape[1]
+        d = self._head_dim
+        qp, qsh, qst, n_q = _rows3(q, d)
+        k, ksh, kst, s_t = _rows3(k_blk, d)
+        v, vsh, vst, _ = _rows3(v_blk, d)
         assert v_blk.shape == k_blk.shape
+        kc = vc = None
+        cache_sh = 0
         if k_cache is not None:
-            assert k_cache.stride(2) == 1 and k_cache.stride(1) == d and v_cache.stride() == k_cache.stride()
+            kc, vc, cache_sh, _ = _cache(k_cache, v_cache, d)
         f32 = self._torch.float32
-        assert out.is_contiguous() and out.dtype == f32 and out.shape == q.shape
-        assert out_lse.is_contiguous() and out_lse.dtype == f32 and out_lse.shape == q.shape[:2]
+        shape = q.shape
+        assert out.is_contiguous() and out.dtype is f32 and out.shape == shape
+        assert out_lse.is_contiguous() and out_lse.dtype is f32 and out_lse.shape == shape[:2]
         assert workspace.is_contiguous() and workspace.element_size() == 1
-        if q_pos0 is None:
-            q_pos0 = block_pos0 + s_t - q.shape[1]
         rc = self._lib.laserkv_attend_block(
-            self._ctx, _ptr(q), qs[0], qs[1], q.shape[1], _ptr(k_cache), _ptr(v_cache),
-            k_cache.stride(0) if k_cache is not None else 0, cache_len,
-            _ptr(k_blk), ks[0], ks[1], _ptr(v_blk), vs[0], vs[1], s_t, block_pos0, q_pos0, 1 if causal else 0,
-            _ptr(out), _ptr(out_lse), _ptr(workspace), workspace.numel(), self._stream(stream))
-        self._check(rc)
+            self._ctx, qp, qsh, qst, n_q, kc, vc, cache_sh, cache_len, k, ksh, kst, v, vsh, vst, s_t, block_pos0,
+            block_pos0 + s_t - n_q if q_pos0 is None else q_pos0, 1 if causal else 0,
+            out.data_ptr(), out_lse.data_ptr(), workspace.data_ptr(), workspace.numel(), self._stream(stream))
+        if rc:
+            self._check(rc)
 
     def laserkv_profile_begin(self):
         self._check(self._lib.laserkv_profile_begin(self._ctx))

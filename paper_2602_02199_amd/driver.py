@@ -152,7 +152,7 @@ class LayerCompressor:
         call = self._layer_call(data, nb) if nb > 1 else None
         if call is not None:
             fn, args, n = call
-            self.lib._check(fn(*args, torch.cuda.current_stream().cuda_stream))
+            self.lib._check(fn(*args, self.lib._stream(None)))
             self.cache_len = n
             return n
         for t in range(nb):
@@ -278,9 +278,7 @@ class LayerCompressor:
 
     def run_plan(self, calls, stream=None):
         import ctypes as C
-        if stream is None:
-            stream = torch.cuda.current_stream().cuda_stream
-        sp = C.c_void_p(stream)
+        sp = self.lib._stream(stream)
         for fn, args, takes_stream in calls:
             rc = fn(*args, sp) if takes_stream else fn(*args)
             if rc != 0:
