@@ -46,6 +46,7 @@ struct laserkv_ctx {
   int32_t* cnt_sum;  // [H_kv, max_block] summed counts (stage output)
   uint32_t* qhist;   // [H_kv, L, 2^K / 2, n_qgroups] or null when the tables are too large
   uint32_t* sync;    // single sweep: [0] epoch, [1] finished workgroups, [64 ..] per-table flags [H_kv, L]; null without qhist
+  uint32_t* attend_sync;  // [H_kv] counters of attend_decode_kernel, zero between launches
   uint16_t* sig_k;   // [H_kv, max_block, L]
   uint16_t* sig_q;   // [H_q, max_window, L]
   int m_pad;
@@ -132,9 +133,9 @@ int check_config(const laserkv_config& c, const char* who) {
   return LKV_OK;
 }
 
-// The device workspace of a configuration: nine buffers, in the order of WsIndex.
-constexpr int kWsBuffers = 9;
-enum WsIndex { WS_PART, WS_S_PART, WS_S_EXACT, WS_CNT, WS_CNT_SUM, WS_SIG_K, WS_SIG_Q, WS_QHIST, WS_SYNC };
+// The device workspace of a configuration: ten buffers, in the order of WsIndex.
+constexpr int kWsBuffers = 10;
+enum WsIndex { WS_PART, WS_S_PART, WS_S_EXACT, WS_CNT, WS_CNT_SUM, WS_SIG_K, WS_SIG_Q, WS_QHIST, WS_SYNC, WS_ATTEND_SYNC };
 struct WsPlan {
   int m_pad, max_ranges;
   size_t bytes[kWsBuffers];  // 0: buffer not used by this configuration
@@ -168,6 +169,7 @@ void plan_workspace(const laserkv_config& c, bool allow_qhist, WsPlan& w) {
   w.bytes[WS_SIG_Q] = (size_t)c.n_q_heads * c.max_window * c.lsh_tables * sizeof(uint16_t);
   w.bytes[WS_QHIST] = use_qhist ? n_qg_max * hk * hist_bytes_head : 0;
   // the single sweep's per-table flags and its two launch counters (zero before the first launch)
+  w.bytes[WS_ATTEND_SYNC] = hk * sizeof(uint32_t);
   w.bytes[WS_SYNC] = use_qhist ? (hk * c.lsh_tables + 64) * sizeof(uint32_t) : 0;
 }
 
@@ -191,6 +193,7 @@ void bind_workspace(laserkv_ctx* ctx, const WsPlan& w, void* const ptr[kWsBuffer
   ctx->sig_q = (uint16_t*)ptr[WS_SIG_Q];
   ctx->qhist = (uint32_t*)ptr[WS_QHIST];
   ctx->sync = (uint32_t*)ptr[WS_SYNC];
+  ctx->attend_sync = (uint32_t*)ptr[WS_ATTEND_SYNC];
 }
 
 }  // namespace
@@ -283,13 +286,12 @@ int laserkv_create(const laserkv_config* cfg, laserkv_ctx** out) {
       return fail_hip(nullptr, e, "create: workspace fill");
     }
   }
-  if (ptr[WS_SYNC]) {
-    e = hipMemset(ptr[WS_SYNC], 0, ws.bytes[WS_SYNC]);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
-      laserkv_destroy(ctx);
-      return fail_hip(nullptr, e, "create: clearing the flags of the single sweep");
-    }
+  e = hipMemset(ptr[WS_ATTEND_SYNC], 0, ws.bytes[WS_ATTEND_SYNC]);
+  if (e == hipSuccess && ptr[WS_SYNC]) e = hipMemset(ptr[WS_SYNC], 0, ws.bytes[WS_SYNC]);
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e != hipSuccess) {
+    laserkv_destroy(ctx);
+    return fail_hip(nullptr, e, "create: clearing flags and counters");
   }
   *out = ctx;
   return LKV_OK;
@@ -297,7 +299,7 @@ int laserkv_create(const laserkv_config* cfg, laserkv_ctx** out) {
 
 void laserkv_destroy(laserkv_ctx* ctx) {
   if (!ctx) return;
-  void* ptrs[] = {ctx->part, ctx->s_part, ctx->s_exact, ctx->cnt, ctx->cnt_sum, ctx->qhist, ctx->sig_k, ctx->sig_q, ctx->sync};
+  void* ptrs[] = {ctx->part, ctx->s_part, ctx->s_exact, ctx->cnt, ctx->cnt_sum, ctx->qhist, ctx->sig_k, ctx->sig_q, ctx->sync, ctx->attend_sync};
   if (ctx->owns_workspace)
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
@@ -967,15 +969,17 @@ static int attend_impl(laserkv_ctx* ctx, const char* fn, int64_t n_q_max,
   p.n_qgroups = plan.n_qgroups;
   p.n_kv_heads = c.n_kv_heads;
   p.scale2 = (float)(1.4426950408889634 / sqrt((double)d));
-  const size_t rows = (size_t)c.n_kv_heads * plan.n_parts * m_rows;
+  const size_t rows = (size_t)c.n_kv_heads * plan.n_parts * (plan.decode ? lkv::decode_rows(m_rows) : m_rows);
   p.part_o = lse_only ? nullptr : reinterpret_cast<float*>(workspace);
   p.part_ml = lse_only ? reinterpret_cast<float2*>(workspace)
                        : reinterpret_cast<float2*>(reinterpret_cast<char*>(workspace) + ((rows * d * 4 + 255) & ~(size_t)255));
   p.out = out;
   p.out_lse = out_lse;
+  p.counters = ctx->attend_sync;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   hipError_t e = timed(ctx, LKV_KERN_ATTEND, st, [&] {
-    return lse_only ? lkv::launch_attend_lse((int)c.dtype, d, p, st) : lkv::launch_attend((int)c.dtype, d, p, st);
+    return lse_only ? lkv::launch_attend_lse((int)c.dtype, d, p, st)
+                    : plan.decode ? lkv::launch_decode((int)c.dtype, d, p, st) : lkv::launch_attend((int)c.dtype, d, p, st);
   });
   if (e != hipSuccess) return fail(ctx, LKV_EHIP, "%s: kernels: %s", fn, hipGetErrorString(e));
   return LKV_OK;

@@ -808,6 +808,8 @@ __global__ __launch_bounds__(256) void attend_lse_combine_kernel(AttendParams p)
 
 // ---- host side ----
 void attend_plan(int m_rows, int64_t cache_len, int s_t, int n_kv_heads, int n_cu, AttendPlan* plan) {
+  if (decode_supports(m_rows, cache_len, s_t)) return decode_plan(cache_len, n_kv_heads, n_cu, plan);
+  plan->decode = 0;
   const int n_qg = (m_rows + ATT_ROWS - 1) / ATT_ROWS;
   const int n_rt = (min(m_rows, ATT_ROWS) + 31) / 32;
   int rt_pow2 = 1, wprt_log = 3;
@@ -843,12 +845,12 @@ void attend_lse_plan(int m_rows, int64_t cache_len, int n_kv_heads, int n_cu, At
   plan->keys_per_split = (int)kps;
   plan->blk_keys_per_split = 32;
   plan->n_parts = n_splits;
-  plan->direct = 0;
+  plan->direct = plan->decode = 0;
 }
 
 size_t attend_workspace_bytes(const AttendPlan& plan, int m_rows, int n_kv_heads, int head_dim) {
   if (plan.direct) return 256;  // the kernel writes the result itself
-  const size_t rows = (size_t)n_kv_heads * plan.n_parts * m_rows;
+  const size_t rows = (size_t)n_kv_heads * plan.n_parts * (plan.decode ? decode_rows(m_rows) : m_rows);
   return ((rows * head_dim * 4 + 255) & ~(size_t)255) + rows * 8 + 256;
 }
 

@@ -235,12 +235,18 @@ struct AttendParams {
   float scale2;        // log2(e) / sqrt(d)
   float* part_o;       // [H_kv, n_parts, M, d] unnormalised partial outputs
   float2* part_ml;     // [H_kv, n_parts, M] (reference, sum) in the exp2 domain
+  uint32_t* counters;  // attend_decode_kernel: [H_kv] finished key splits, zero between launches
   float* out;          // [H_kv * M, d]
   float* out_lse;      // [H_kv * M] natural log
 };
 struct AttendPlan {
-  int n_qgroups, wprt_log, n_splits, keys_per_split, blk_keys_per_split, n_parts, direct;
+  int n_qgroups, wprt_log, n_splits, keys_per_split, blk_keys_per_split, n_parts, direct, decode;
 };
+// few rows (decoding): one launch on the vector unit
+bool decode_supports(int m_rows, int64_t cache_len, int s_t);
+int decode_rows(int m_rows);  // rows per head and split in the workspace
+void decode_plan(int64_t cache_len, int n_kv_heads, int n_cu, AttendPlan* plan);
+hipError_t launch_decode(int dtype, int head_dim, const AttendParams& p, hipStream_t st);
 void attend_plan(int m_rows, int64_t cache_len, int s_t, int n_kv_heads, int n_cu, AttendPlan* plan);
 size_t attend_workspace_bytes(const AttendPlan& plan, int m_rows, int n_kv_heads, int head_dim);  // part_o, then part_ml
 hipError_t launch_attend(int dtype, int head_dim, const AttendParams& p, hipStream_t st);
