@@ -16,6 +16,7 @@
 //   attend_lse_kernel (+ attend_lse_combine_kernel)  the normaliser alone, for callers that want nothing else
 #include "laserkv_device.h"
 #include "laserkv_kernels.h"
+#include "laserkv_rowstats.h"
 
 namespace lkv {
 
@@ -665,144 +666,78 @@ __global__ __launch_bounds__((D / 4) * COMB_SLICES) void attend_combine_kernel(A
 
 // ---------------------------------------------------------------------------------------------
 // The normaliser alone (out == null): log sum_i exp(q.k_i / sqrt(d)) of every query over the cache, which is
-// all laserkv_set_row_lse needs.  No values are read, no output accumulators are kept, so 16 waves of 32
-// rows each share a workgroup (512 rows: a GQA group's whole window reads the keys once).  Workgroup = (key
-// split, group of 512 rows, KV head).  Keys pass through two LDS buffers in chunks (the next chunk's loads are
-// issued before the current one is worked on and stored after it: one barrier per chunk).  K Q^T with the
-// keys as the A operand puts a query row in a lane: each lane keeps (reference, sum of 2^(x - reference))
-// over its keys; the reference is the maximum over the split's first tile, and a pass whose sums overflow is
-// repeated with a reference that follows the running maximum.
+// all laserkv_set_row_lse needs.  No values are read and no output accumulators kept, so a workgroup takes up to 512
+// rows (a GQA group's whole window reads the keys once; with fewer rows the eight waves share them over different key
+// tiles).  Workgroup = (key split, group of 512 rows, KV head); the arithmetic is laserkv_rowstats.h.
+// 256 rows over 31 681 keys, 8 heads: 36.6 -> 24 us (before: sixteen waves of 32 rows, half of them without rows).
 // ---------------------------------------------------------------------------------------------
-constexpr int LSE_WAVES = 16;
-constexpr int LSE_THREADS = LSE_WAVES * 64;
-constexpr int LSE_ROWS = 32 * LSE_WAVES;
+constexpr int LSE_ROWS = 512;
 
-template <int DT>
-__host__ __device__ constexpr int lse_chunk_keys() { return DT == DT_BF16 ? 256 : 128; }
-
-template <int DT, int D>
-__global__ __launch_bounds__(LSE_THREADS) void attend_lse_kernel(AttendParams p) {
-  constexpr int ES = DT == DT_BF16 ? 2 : 4;
-  constexpr int CH = D * ES / 16;
-  constexpr int NCH = CH / 2;
-  constexpr int CHP = CH + 1;
-  constexpr int KC = lse_chunk_keys<DT>();
-  constexpr int KL = KC * CH / LSE_THREADS;
-  constexpr int TPC = KC / 32;
-  constexpr int ROWS_PER_LOAD = LSE_THREADS / CH;
-  static_assert(KL >= 1 && KL * LSE_THREADS == KC * CH, "chunk not a whole number of loads per thread");
-
+template <int DT, int D, int RT>
+__global__ __launch_bounds__(RS_THREADS) void attend_lse_kernel(AttendParams p) {
+  constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
-  const int split = blockIdx.x, rg = blockIdx.y, h = blockIdx.z;
-  const int k_lo = split * p.keys_per_split;
-  const int k_hi = min(k_lo + p.keys_per_split, p.cache_len);
-  const int row = rg * LSE_ROWS + wave * 32 + rl;
+  const int idx = xcd_major(blockIdx.x, gridDim.x);
+  const int split = idx % p.n_splits, rg = idx / p.n_splits % p.n_qgroups, h = idx / (p.n_splits * p.n_qgroups);
+  const int k_lo = split * p.keys_per_split, k_hi = min(k_lo + p.keys_per_split, p.cache_len);
+  const int wk = RS_WAVES >> p.wprt_log, wi = wave & ((1 << p.wprt_log) - 1), ks = wave >> p.wprt_log;
+  const int row0 = rg * LSE_ROWS + wi * RT * 32;
+  const bool active = row0 < p.m_rows;
 
-  extern __shared__ uint4 smem[];  // two key buffers [KC][CHP]
-
-  uint4 a[NCH];
-  {
-    const int m = min(row, p.m_rows - 1);
+  extern __shared__ uint4 smem[];
+  uint4 q[RT][NCH];
+  int lim[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int m = min(row0 + r * 32 + rl, p.m_rows - 1);
     const int g = div_w(m, p.nq_magic), j = m - g * p.n_q;
     const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row;
+    lim[r] = k_hi;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + (2 * i + kg) * 16);
+    for (int i = 0; i < NCH; ++i) q[r][i] = ld16(ptr + (2 * i + kg) * 16);
   }
   const __amdgpu_buffer_rsrc_t ksrd =
       make_srd(p.k_cache + (int64_t)h * p.cache_stride_head, (uint32_t)p.cache_len * (uint32_t)p.row_bytes);
-  const uint32_t k_row = tid / CH, k_col = tid % CH;
-  uint4 kpre[KL];
-  auto prefetch = [&](int kc0) {
+  float ref[RT], sum[RT];
+  row_stats<DT, D, RT>(smem, ksrd, (uint32_t)p.row_bytes, k_lo, k_hi, k_hi, lim, q, p.scale2, ks, wk, active, ref, sum);
+  // the waves that shared rows meet in LDS (free after row_stats)
+  float2* sP = reinterpret_cast<float2*>(smem);  // [wk][rows of the group]
+  const int n_rows = RT * 32 << p.wprt_log;
 #pragma unroll
-    for (int u = 0; u < KL; ++u)
-      kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * ROWS_PER_LOAD) * (uint32_t)p.row_bytes + k_col * 16);
-  };
-  auto store = [&](uint4* buf) {
-#pragma unroll
-    for (int u = 0; u < KL; ++u) buf[(k_row + u * ROWS_PER_LOAD) * CHP + k_col] = kpre[u];
-  };
-
-  // One pass over the split's keys.  fixed_ref: the reference is the lane's maximum over the split's first tile and
-  // is not raised by later complete tiles (one fma, one exponential, one add per logit and nothing else); a later
-  // logit 2^7 above it overflows the sum, which the caller detects.  Otherwise the reference follows the maximum.
-  float ref, sum;
-  auto pass = [&](bool fixed_ref) {
-    ref = NEG_BIG;
-    sum = 0.0f;
-    prefetch(k_lo);
-    store(smem);
-    lds_barrier();
-    int cur = 0;
-    for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
-      const bool more = kc0 + KC < k_hi;
-      if (more) prefetch(kc0 + KC);
-      const uint4* sK = smem + (size_t)cur * KC * CHP;
-#pragma unroll 1
-      for (int nt = 0; nt < TPC; ++nt) {
-        const int kbase = kc0 + nt * 32;
-        if (kbase >= k_hi) break;  // workgroup-uniform
-        f32x16 acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-        const uint4* krow = sK + (size_t)(nt * 32 + rl) * CHP + kg;
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) Mma<DT>::run(acc, krow[2 * i], a[i]);
-        const int n_vis = k_hi - kbase;  // keys of this tile inside the split (>= 32: all)
-        if (n_vis >= 32 && fixed_ref && kbase > k_lo) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[r], p.scale2, -ref));
-        } else if (n_vis >= 32) {
-          float mx = acc[0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-          const float nref = fmaxf(ref, mx * p.scale2);  // scale2 > 0
-          sum *= fast_exp2(ref - nref);
-          ref = nref;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[r], p.scale2, -ref));
-        } else if (acc_row(0, kg) < n_vis) {  // the split's last tile: a lane that sees none of its keys keeps its state
-          float mx = acc[0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) mx = acc_row(r, kg) < n_vis ? fmaxf(mx, acc[r]) : mx;
-          const float nref = fmaxf(ref, mx * p.scale2);
-          sum *= fast_exp2(ref - nref);
-          ref = nref;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += acc_row(r, kg) < n_vis ? fast_exp2(fmaf(acc[r], p.scale2, -ref)) : 0.0f;
-        }
-      }
-      if (more) store(smem + (size_t)(cur ^ 1) * KC * CHP);
-      cur ^= 1;
-      lds_barrier();
-    }
-  };
-  int* redo = reinterpret_cast<int*>(smem + (size_t)2 * KC * CHP);  // one word behind the two key buffers
-  if (tid == 0) *redo = 0;  // ordered before the writes below by the barriers of the pass
-  pass(true);
-  // an overflowed sum (inf, or NaN once it was rescaled) anywhere in the workgroup: once more with a running maximum
-  // (the decision is taken for the workgroup as a whole: the pass has barriers)
-  if (!(sum < 3.0e38f)) *redo = 1;
+  for (int r = 0; r < RT; ++r)
+    if (kg == 0) sP[ks * n_rows + wi * RT * 32 + r * 32 + rl] = make_float2(ref[r], sum[r]);
   __syncthreads();
-  if (*redo) pass(false);
-  lse_merge(ref, sum, half_other(ref, kg), half_other(sum, kg));  // the two halves hold the same rows over different keys
-  if (kg == 0 && row < p.m_rows) p.part_ml[((size_t)h * p.n_parts + split) * p.m_rows + row] = make_float2(ref, sum);
+  const int row = rg * LSE_ROWS + tid;
+  if (tid >= n_rows || row >= p.m_rows) return;
+  float2 v = sP[tid];
+  for (int k = 1; k < wk; ++k) lse_merge(v.x, v.y, sP[k * n_rows + tid].x, sP[k * n_rows + tid].y);
+  p.part_ml[((size_t)h * p.n_parts + split) * p.m_rows + row] = v;
 }
 
-// lse = (M + log2 sum_p l_p 2^(m_p - M)) ln 2 per row; -inf without any partial (empty cache)
-__global__ __launch_bounds__(256) void attend_lse_combine_kernel(AttendParams p) {
-  const int row_lin = blockIdx.x * 256 + threadIdx.x;
-  if (row_lin >= p.n_kv_heads * p.m_rows) return;
-  const int h = row_lin / p.m_rows, m = row_lin - h * p.m_rows;
+// lse = (M + log2 sum_p l_p 2^(m_p - M)) ln 2 per row; -inf without any partial (empty cache).  32 rows per workgroup,
+// eight threads per row over the partials (one pass, their loads in flight together: 4.6 -> 2.5 us at 32 splits).
+constexpr int LSEC_ROWS = 32, LSEC_SLICES = 8;
+__global__ __launch_bounds__(LSEC_ROWS * LSEC_SLICES) void attend_lse_combine_kernel(AttendParams p) {
+  __shared__ float2 sP[LSEC_SLICES][LSEC_ROWS];
+  const int r = threadIdx.x % LSEC_ROWS, sl = threadIdx.x / LSEC_ROWS;
+  const int row_lin = blockIdx.x * LSEC_ROWS + r, n_rows = p.n_kv_heads * p.m_rows;
+  const int rc = min(row_lin, n_rows - 1);
+  const int h = rc / p.m_rows, m = rc - h * p.m_rows;
   const float2* ml = p.part_ml + (size_t)h * p.n_parts * p.m_rows + m;
-  float mx = NEG_BIG;
-#pragma unroll 8
-  for (int q = 0; q < p.n_parts; ++q) mx = fmaxf(mx, ml[(size_t)q * p.m_rows].x);
-  float l = 0.0f;
-#pragma unroll 8
-  for (int q = 0; q < p.n_parts; ++q) {
-    const float2 v = ml[(size_t)q * p.m_rows];
-    l = fmaf(v.y, fast_exp2(v.x - mx), l);
+  float mx = NEG_BIG, l = 0.0f;
+  for (int q0 = sl; q0 < p.n_parts; q0 += 8 * LSEC_SLICES) {
+    float2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = ml[(size_t)min(q0 + u * LSEC_SLICES, p.n_parts - 1) * p.m_rows];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (q0 + u * LSEC_SLICES < p.n_parts) lse_merge(mx, l, v[u].x, v[u].y);
   }
+  sP[sl][r] = make_float2(mx, l);
+  __syncthreads();
+  if (sl || row_lin >= n_rows) return;
+#pragma unroll
+  for (int s = 1; s < LSEC_SLICES; ++s) lse_merge(mx, l, sP[s][r].x, sP[s][r].y);
   p.out_lse[row_lin] = l > 0.0f ? (mx + fast_log2(l)) * 0.6931471805599453f : -__builtin_inff();
 }
 
@@ -840,7 +775,10 @@ void attend_lse_plan(int m_rows, int64_t cache_len, int n_kv_heads, int n_cu, At
   kps = max((int64_t)32, (kps + 31) / 32 * 32);
   n_splits = cache_len > 0 ? (int)((cache_len + kps - 1) / kps) : 0;
   plan->n_qgroups = n_rg;
+  // waves over different rows: two row tiles each (one where there are at most four); the others take other key tiles
+  const int n_rt = (min(m_rows, LSE_ROWS) + 31) / 32, need = n_rt > 4 ? (n_rt + 1) / 2 : n_rt;
   plan->wprt_log = 0;
+  while ((1 << plan->wprt_log) < need) ++plan->wprt_log;
   plan->n_splits = n_splits;
   plan->keys_per_split = (int)kps;
   plan->blk_keys_per_split = 32;
@@ -888,16 +826,16 @@ static hipError_t launch_attend_t(const AttendParams& p, hipStream_t st) {
 
 template <int DT, int D>
 static hipError_t launch_attend_lse_t(const AttendParams& p, hipStream_t st) {
-  constexpr int ES = DT == DT_BF16 ? 2 : 4;
-  constexpr size_t lds = (size_t)2 * lse_chunk_keys<DT>() * (D * ES / 16 + 1) * 16 + 16;  // two key buffers and the redo flag
-  static_assert(lds <= 160 * 1024, "two key chunks do not fit the LDS");
   if (p.n_splits > 0) {
-    hipLaunchKernelGGL((attend_lse_kernel<DT, D>), dim3(p.n_splits, p.n_qgroups, p.n_kv_heads), dim3(LSE_THREADS), lds, st, p);
+    const dim3 grid(p.n_splits * p.n_qgroups * p.n_kv_heads), blk(RS_THREADS);
+    const size_t lds = row_stats_lds(D * (DT == DT_BF16 ? 2 : 4));
+    if (min(p.m_rows, LSE_ROWS) > 128) hipLaunchKernelGGL((attend_lse_kernel<DT, D, 2>), grid, blk, lds, st, p);
+    else hipLaunchKernelGGL((attend_lse_kernel<DT, D, 1>), grid, blk, lds, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   const int n_rows = p.n_kv_heads * p.m_rows;
-  hipLaunchKernelGGL(attend_lse_combine_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, p);
+  hipLaunchKernelGGL(attend_lse_combine_kernel, dim3((n_rows + LSEC_ROWS - 1) / LSEC_ROWS), dim3(LSEC_ROWS * LSEC_SLICES), 0, st, p);
   return hipGetLastError();
 }
 
@@ -923,7 +861,9 @@ static hipError_t attend_attr() {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_rows_kernel<DT, D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
 }
 

@@ -17,6 +17,7 @@
 // loads in flight in registers while the current one is worked on: one barrier per chunk.
 #include "laserkv_device.h"
 #include "laserkv_kernels.h"
+#include "laserkv_rowstats.h"
 
 #include <limits.h>
 
@@ -25,8 +26,7 @@ namespace lkv {
 constexpr int LY_WAVES = 8;
 constexpr int LY_THREADS = LY_WAVES * 64;
 constexpr int LY_ROWS = 512;         // window rows per group at most
-constexpr int LY_STAT_KC = 256;      // keys per LDS chunk: statistics
-constexpr int LY_KC = 128;           // scores
+constexpr int LY_KC = 128;           // keys per LDS chunk of the score kernel
 constexpr int LY_HEAVY = 36;         // words per table's list of heavy bins: at most LY_ROWS / 15 = 34 of them
 constexpr int LY_CODE_PLANES = 256;  // hyperplanes per pass of layer_codes_kernel at most
 
@@ -158,19 +158,13 @@ __global__ __launch_bounds__(LY_THREADS) void layer_codes_kernel(LayerParams p) 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Row statistics.  Workgroup = (group, key range); waves share the rows (2^wr_log waves of RT tiles) and, where the
-// rows need fewer than eight waves, different key tiles.  Keys are the A operand and window rows the B operand, so a
-// lane owns a row per tile and keeps (reference, sum of 2^(x - reference)) privately.  The reference is the maximum
-// over the lane's first tile; complete tiles after it cost one fma, one exponential and one add per logit.  When a sum
-// has grown past 1e30 after a chunk, the wave repeats that chunk from LDS with a reference that follows the maximum.
+// Row statistics (laserkv_rowstats.h).  Workgroup = (group, key range); 2^wr_log waves share the rows (RT tiles each) and,
+// where the rows need fewer than eight waves, the others take different key tiles.
 // ---------------------------------------------------------------------------------------------
 template <int DT, int D, int RT>
 __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) {
-  constexpr int ES = DT == DT_BF16 ? 2 : 4;
-  constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
-  constexpr int KC = LY_STAT_KC, TPC = KC / 32;
-  constexpr int KL = KC * CH / LY_THREADS;
-  constexpr int RPL = LY_THREADS / CH;
+  constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
+  static_assert(LY_THREADS == RS_THREADS, "row_stats works with eight waves");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const int lin = xcd_major(blockIdx.x, gridDim.x);
   const int sp = lin % p.stat_splits;
@@ -198,102 +192,11 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
   const uint32_t kstride = (uint32_t)p.k.stride_row;
   const __amdgpu_buffer_rsrc_t ksrd = make_srd(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)(gr.lo - gr.n_ctx) * p.k.stride_row,
                                                (uint32_t)n_keys * kstride);
-  const uint32_t k_row = tid / CH, k_col = tid % CH;
-  uint4 kpre[KL];
-  auto prefetch = [&](int kc0) {
-#pragma unroll
-    for (int u = 0; u < KL; ++u) kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * RPL) * kstride + k_col * 16);
-  };
-  auto store = [&](uint4* buf) {
-#pragma unroll
-    for (int u = 0; u < KL; ++u) buf[(k_row + u * RPL) * CHP + k_col] = kpre[u];
-  };
-
   float ref[RT], sum[RT];
-#pragma unroll
-  for (int r = 0; r < RT; ++r) {
-    ref[r] = NEG_BIG;
-    sum[r] = 0.0f;
-  }
-  bool first = true;  // no tile yet: the lane has no reference
-  prefetch(k_lo);
-  store(smem);
-  lds_barrier();
-  int cur = 0;
-  for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
-    const bool more = kc0 + KC < k_hi;
-    if (more) prefetch(kc0 + KC);
-    const uint4* sK = smem + (size_t)cur * KC * CHP;
-    float kept[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) kept[r] = sum[r];
-    bool fixed_ref = !first;  // wave-uniform
-#pragma unroll 1
-    for (int attempt = active ? 0 : 2; attempt < 2; ++attempt) {
-#pragma unroll 1
-      for (int nt = ks; nt < TPC; nt += wk) {
-        const int kbase = kc0 + nt * 32;
-        if (kbase >= k_hi) break;  // wave-uniform
-        f32x16 acc[RT];
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc[r][e] = 0.0f;
-        const uint4* krow = sK + (size_t)(nt * 32 + rl) * CHP + kg;
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-          const uint4 kf = krow[2 * i];
-#pragma unroll
-          for (int r = 0; r < RT; ++r) Mma<DT>::run(acc[r], kf, q[r][i]);
-        }
-        const bool whole = kbase + 32 <= k_hi && kbase + 31 <= lim0;  // every row sees every key
-        if (whole && fixed_ref) {
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) sum[r] += fast_exp2(fmaf(acc[r][e], p.scale2, -ref[r]));
-        } else {
-#pragma unroll
-          for (int r = 0; r < RT; ++r) {
-            const int n_vis = whole ? 32 : min(k_hi, lim[r]) - kbase;
-            if (acc_row(0, kg) < n_vis) {  // a lane that sees none of its keys keeps its state
-              float mx = acc[r][0];
-#pragma unroll
-              for (int e = 1; e < 16; ++e) mx = acc_row(e, kg) < n_vis ? fmaxf(mx, acc[r][e]) : mx;
-              const float nref = fmaxf(ref[r], mx * p.scale2);  // scale2 > 0
-              sum[r] *= fast_exp2(ref[r] - nref);
-              ref[r] = nref;
-#pragma unroll
-              for (int e = 0; e < 16; ++e)
-                sum[r] += acc_row(e, kg) < n_vis ? fast_exp2(fmaf(acc[r][e], p.scale2, -nref)) : 0.0f;
-            }
-          }
-          if (first) fixed_ref = true;
-          first = false;
-        }
-      }
-      // sums that have grown too large against the fixed reference: the chunk (still in LDS) once more, the reference
-      // following the maximum
-      bool over = false;
-#pragma unroll
-      for (int r = 0; r < RT; ++r) over |= !(sum[r] < 1.0e30f);
-      if (attempt || !__any(over)) break;
-      fixed_ref = false;
-#pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const float nref = kept[r] > 1.0e10f ? ref[r] + fast_log2(kept[r]) : ref[r];
-        sum[r] = kept[r] * fast_exp2(ref[r] - nref);
-        ref[r] = nref;
-      }
-    }
-    if (more) store(smem + (size_t)(cur ^ 1) * KC * CHP);
-    cur ^= 1;
-    lds_barrier();
-  }
+  row_stats<DT, D, RT>(smem, ksrd, kstride, k_lo, k_hi, lim0, lim, q, p.scale2, ks, wk, active, ref, sum);
   if (!active) return;
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    lse_merge(ref[r], sum[r], half_other(ref[r], kg), half_other(sum[r], kg));  // the two halves hold the same rows over different keys
     const int row = row0 + r * 32 + rl;
     if (kg == 0 && row < p.m_rows)
       p.part[((size_t)gr.g * p.m_rows + row) * p.n_parts + sp * wk + ks] = make_float2(ref[r], sum[r]);
@@ -660,7 +563,7 @@ void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* pl
   p->code_tables = max(1, min(nt, p->n_tables));
   p->code_tiles = (p->code_tables * p->n_bits + 31) / 32;
   plan->codes_lds = (size_t)p->code_tiles * 32 * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)p->code_tables * (words * 17 + 1) * 4 : 0);
-  plan->stats_lds = (size_t)2 * LY_STAT_KC * (head_dim * es / 16 + 1) * 16 + 16;
+  plan->stats_lds = row_stats_lds(head_dim * es);
   plan->score_lds = score_lds(head_dim, es, p->n_planes, plan->use_cells ? cw * p->n_tables : 0);
   // workspace
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
