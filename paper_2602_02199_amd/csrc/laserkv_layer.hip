@@ -50,110 +50,121 @@ __device__ __forceinline__ const char* layer_row(const LayerParams& p, const Lay
 }
 
 // ---------------------------------------------------------------------------------------------
-// Codes of a group's window rows.  Workgroup = group; wave w holds rows 64w .. 64w+63 as MFMA operands and the tables
+// Codes of a group's window rows.  Workgroup = group; a wave holds 32 rows as MFMA operands and the tables
 // pass by in sets whose hyperplanes and histograms fit the LDS.  A set's codes are counted in LDS histograms (16-bit
 // bins, 32 bins per 17 words against bank conflicts), which leave as cells of 16, 8 or 4 bits per bin, the widest with
 // which a group's tables fit 64 KiB of the score kernel's LDS (4 bits at K = 12, L = 32).  A narrow cell that is full
 // stands for a count the table's list of heavy bins holds: (code << 16 | count) each, their number in front.
 // Codes wider than 12 bits: the codes themselves are stored (count_kernel does the counting).
 // ---------------------------------------------------------------------------------------------
+constexpr int LY_CODE_THREADS = 1024;
+
 template <int DT, int D>
-__global__ __launch_bounds__(LY_THREADS) void layer_codes_kernel(LayerParams p) {
+__global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParams p) {
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
+  constexpr int NPL = LY_CODE_PLANES * CH / LY_CODE_THREADS;  // 16-byte pieces of hyperplanes per thread at most
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const LayerGroup gr = layer_group(p, blockIdx.x);
   const bool wide = p.cells == nullptr;
-  const int words = (1 << p.n_bits) >= 32 ? (1 << p.n_bits) >> 5 : 1;  // bitmap words per table
+  const int words = (1 << p.n_bits) >= 32 ? (1 << p.n_bits) >> 5 : 1;  // groups of 32 bins per table
   const int hp = words * 17;
 
   extern __shared__ uint4 smem[];
-  uint4* sP = smem;                                                                  // [code_tiles * 32][CHP]
+  uint4* sP = smem;                                                                    // [code_tiles * 32][CHP]
   uint32_t* sH = reinterpret_cast<uint32_t*>(smem + (size_t)p.code_tiles * 32 * CHP);  // [code_tables][hp]
-  int* sHeavy = reinterpret_cast<int*>(sH + p.code_tables * hp);                     // [code_tables]
+  int* sHeavy = reinterpret_cast<int*>(sH + ((p.code_tables * hp + 3) & ~3));          // [code_tables]
 
-  uint4 b[2][NCH];
-  const bool active = wave * 64 < p.m_rows;
-  if (active) {
+  uint4 pre[NPL];  // the next set's hyperplanes, on their way while the current set is worked on
+  auto fetch = [&](int t0) {
+    const int np = min(p.code_tables, p.n_tables - t0) * p.n_bits;
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const char* ptr = layer_row(p, gr, min(wave * 64 + r * 32 + rl, p.m_rows - 1));
-#pragma unroll
-      for (int i = 0; i < NCH; ++i) b[r][i] = ld16(ptr + (2 * i + kg) * 16);
+    for (int u = 0; u < NPL; ++u) {
+      const int row = (tid + u * LY_CODE_THREADS) / CH;
+      pre[u] = ld16(p.planes + (size_t)(t0 * p.n_bits + min(row, np - 1)) * (D * ES) + tid % CH * 16);
     }
+  };
+  fetch(0);
+  uint4 b[NCH];  // this wave's 32 window rows
+  const int row = wave * 32 + rl;
+  const bool active = wave * 32 < p.m_rows;
+  if (active) {
+    const char* ptr = layer_row(p, gr, min(row, p.m_rows - 1));
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) b[i] = ld16(ptr + (2 * i + kg) * 16);
   }
   const uint32_t code_mask = (1u << p.n_bits) - 1u;
+  const int cpw = 1 << p.cell_log, cbits = 32 >> p.cell_log, cw_log = max(p.n_bits - p.cell_log, 0);  // cell_words = 1 << cw_log
+  const uint32_t cmax = cbits == 16 ? 0xffffu : (1u << cbits) - 1u;
   for (int t0 = 0; t0 < p.n_tables; t0 += p.code_tables) {
     const int n_tab = min(p.code_tables, p.n_tables - t0);
     const int np = n_tab * p.n_bits, n_tile = (np + 31) >> 5;
     __syncthreads();  // the previous set's histograms have been read
-    for (int q = tid; q < n_tile * 32 * CH; q += LY_THREADS) {
-      const int row = q / CH, c = q % CH;
-      sP[row * CHP + c] = ld16(p.planes + (size_t)(t0 * p.n_bits + min(row, np - 1)) * (D * ES) + c * 16);
+#pragma unroll
+    for (int u = 0; u < NPL; ++u) {
+      const int r = (tid + u * LY_CODE_THREADS) / CH;
+      if (r < n_tile * 32) sP[r * CHP + tid % CH] = pre[u];
     }
     if (!wide) {
-      for (int i = tid; i < n_tab * hp; i += LY_THREADS) sH[i] = 0u;
-      for (int i = tid; i < n_tab; i += LY_THREADS) sHeavy[i] = 0;
+      uint4* h4 = reinterpret_cast<uint4*>(sH);
+      for (int i = tid; i < (n_tab * hp + 3) / 4; i += LY_CODE_THREADS) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (tid < n_tab) sHeavy[tid] = 0;
     }
     __syncthreads();
+    if (t0 + p.code_tables < p.n_tables) fetch(t0 + p.code_tables);
     if (active) {
-      uint32_t prev[2] = {0u, 0u};
+      uint32_t prev = 0u;
       int tt0 = 0;  // first table of the set whose bits are not complete yet
 #pragma unroll 1
       for (int t = 0; t < n_tile; ++t) {
         const uint4* prow = sP + (size_t)(t * 32 + plane_row(rl)) * CHP + kg;
-        f32x16 acc[2];
+        f32x16 acc;
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) acc[r][e] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-          const uint4 pf = prow[2 * i];
-#pragma unroll
-          for (int r = 0; r < 2; ++r) Mma<DT>::run(acc[r], pf, b[r][i]);
-        }
+        for (int i = 0; i < NCH; ++i) Mma<DT>::run(acc, prow[2 * i], b[i]);
         const int tt1 = min(32 * (t + 1), np) / p.n_bits;  // tables complete after this tile
+        uint32_t neg = 0u;
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          uint32_t neg = 0u;
-#pragma unroll
-          for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[r][e]), 31);
-          const uint32_t pos = ~neg & 0xffffu;  // bit = projection >= 0
-          const uint32_t other = half_other(pos, kg);
-          const uint32_t word = kg ? (other | (pos << 16)) : (pos | (other << 16));
-          const uint64_t two = ((uint64_t)word << 32) | prev[r];
-          prev[r] = word;
-          const int row = wave * 64 + r * 32 + rl;
-          if (row < p.m_rows)
-            for (int tt = tt0 + ((tt0 ^ kg) & 1); tt < tt1; tt += 2) {  // tables alternate between the two lanes of a row
-              const uint32_t code = (uint32_t)(two >> (tt * p.n_bits - 32 * t + 32)) & code_mask;
-              if (wide) p.sig_q[((size_t)gr.g * p.m_rows + row) * p.n_tables + t0 + tt] = (uint16_t)code;
-              else atomicAdd(sH + tt * hp + (code >> 5) * 17 + ((code & 31u) >> 1), 1u << ((code & 1u) * 16));
-            }
-        }
+        for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[e]), 31);
+        const uint32_t pos = ~neg & 0xffffu;  // bit = projection >= 0
+        const uint32_t other = half_other(pos, kg);
+        const uint32_t word = kg ? (other | (pos << 16)) : (pos | (other << 16));
+        const uint64_t two = ((uint64_t)word << 32) | prev;
+        prev = word;
+        if (row < p.m_rows)
+          for (int tt = tt0 + ((tt0 ^ kg) & 1); tt < tt1; tt += 2) {  // tables alternate between the two lanes of a row
+            const uint32_t code = (uint32_t)(two >> (tt * p.n_bits - 32 * t + 32)) & code_mask;
+            if (wide) p.sig_q[((size_t)gr.g * p.m_rows + row) * p.n_tables + t0 + tt] = (uint16_t)code;
+            else atomicAdd(sH + tt * hp + (code >> 5) * 17 + ((code & 31u) >> 1), 1u << ((code & 1u) * 16));
+          }
         tt0 = tt1;
       }
     }
     if (wide) continue;
     __syncthreads();
-    const int cpw = 1 << p.cell_log, cbits = 32 >> p.cell_log;
-    const uint32_t cmax = cbits == 16 ? 0xffffu : (1u << cbits) - 1u;
-    for (int i = tid; i < n_tab * p.cell_words; i += LY_THREADS) {
-      const int tt = i / p.cell_words, c0 = (i - tt * p.cell_words) << p.cell_log;
+    for (int i = tid; i < n_tab << cw_log; i += LY_CODE_THREADS) {
+      const int tt = i >> cw_log, cw = i & (p.cell_words - 1), c0 = cw << p.cell_log;
       const uint32_t* hist = sH + tt * hp + (c0 >> 5) * 17 + ((c0 & 31) >> 1);
       const size_t table = (size_t)gr.g * p.n_tables + t0 + tt;
-      uint32_t out = 0u;
-      for (int u = 0; u < cpw; u += 2) {
-        const uint32_t v = hist[u >> 1], lo = v & 0xffffu, hi = v >> 16;
-        out |= (min(lo, cmax) << (u * cbits)) | (min(hi, cmax) << ((u + 1) * cbits));
-        if (lo >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u) << 16 | lo;
-        if (hi >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u + 1) << 16 | hi;
+      uint32_t v[4], out = 0u;
+      bool full = false;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v[u] = 2 * u < cpw ? hist[u] : 0u;
+        const uint32_t lo = v[u] & 0xffffu, hi = v[u] >> 16;
+        full |= max(lo, hi) >= cmax;
+        out |= (min(lo, cmax) | (min(hi, cmax) << cbits)) << (2 * u * cbits & 31);  // words past the cells are zero
       }
-      p.cells[table * p.cell_words + (i - tt * p.cell_words)] = out;
+      p.cells[table * p.cell_words + cw] = out;
+      if (full)
+        for (int u = 0; u < cpw; ++u) {
+          const uint32_t c = hist[u >> 1] >> ((u & 1) * 16) & 0xffffu;
+          if (c >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u) << 16 | c;
+        }
     }
     __syncthreads();
-    for (int tt = tid; tt < n_tab; tt += LY_THREADS) p.heavy[((size_t)gr.g * p.n_tables + t0 + tt) * LY_HEAVY] = (uint32_t)sHeavy[tt];
+    if (tid < n_tab) p.heavy[((size_t)gr.g * p.n_tables + t0 + tid) * LY_HEAVY] = (uint32_t)sHeavy[tid];
   }
 }
 
@@ -562,7 +573,7 @@ void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* pl
   if (plan->use_cells) nt = min(nt, 1024 / words);
   p->code_tables = max(1, min(nt, p->n_tables));
   p->code_tiles = (p->code_tables * p->n_bits + 31) / 32;
-  plan->codes_lds = (size_t)p->code_tiles * 32 * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)p->code_tables * (words * 17 + 1) * 4 : 0);
+  plan->codes_lds = (size_t)p->code_tiles * 32 * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)(p->code_tables * (words * 17 + 1) + 4) * 4 : 0);
   plan->stats_lds = row_stats_lds(head_dim * es);
   plan->score_lds = score_lds(head_dim, es, p->n_planes, plan->use_cells ? cw * p->n_tables : 0);
   // workspace
@@ -581,7 +592,7 @@ void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* pl
 
 template <int DT, int D>
 static hipError_t launch_codes_t(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
-  hipLaunchKernelGGL((layer_codes_kernel<DT, D>), dim3(p.n_blocks * p.n_kv_heads), dim3(LY_THREADS), plan.codes_lds, st, p);
+  hipLaunchKernelGGL((layer_codes_kernel<DT, D>), dim3(p.n_blocks * p.n_kv_heads), dim3(LY_CODE_THREADS), plan.codes_lds, st, p);
   return hipGetLastError();
 }
 template <int DT, int D>

@@ -17,8 +17,9 @@ constexpr size_t row_stats_lds(int row_bytes) { return (size_t)2 * row_stats_chu
 // that share rows take different 32-key tiles (ks, ks + wk, ...).  Keys are the A operand and rows the B operand, so a
 // lane owns a row per tile; its two halves hold the same rows over different keys and are merged before the end.
 // A row sees the keys below its lim[r]; every row sees the keys up to lim_all.  The reference is the maximum over the
-// lane's first tile; complete tiles after it cost one fma, one exponential and one add per logit.  When a sum has grown
-// past 1e30 after a chunk, the wave repeats that chunk from LDS with a reference that follows the maximum.
+// lane's first tile plus 60; complete tiles after it cost one fma, one exponential and one add per logit.  When a sum
+// has grown past 1e30 after a chunk (a logit 160 above the first tile's, in powers of two), the wave repeats that
+// chunk from LDS with a reference that follows the maximum.
 // What bounds it: matrix and vector work of a SIMD hardly overlap (16 matrix instructions of 32 clocks and 64 vector
 // instructions of 4, 32 exponentials of 8 per pair of tiles): 870 - 1000 TFLOP/s of the 1140 a plain matrix product
 // reaches here.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
@@ -100,7 +101,14 @@ __device__ __forceinline__ void row_stats(uint4* smem, __amdgpu_buffer_rsrc_t ks
                 sum[r] += acc_row(e, kg) < n_vis ? fast_exp2(fmaf(acc[r][e], scale2, -nref)) : 0.0f;
             }
           }
-          if (first) fixed_ref = true;
+          if (first) {
+            fixed_ref = true;
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {  // 2^60 of headroom: the sums are relative, terms that vanish are below 2^-60 of them
+              ref[r] += 60.0f;
+              sum[r] *= 0x1p-60f;
+            }
+          }
           first = false;
         }
       }
