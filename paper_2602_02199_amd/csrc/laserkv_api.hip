@@ -881,7 +881,7 @@ static bool attend_sizes_ok(const laserkv_ctx* ctx, int64_t n_q, int64_t n_q_max
 static int64_t attend_workspace_need(const laserkv_ctx* ctx, int n_q, int64_t cache_len, int s_t, bool with_lse_only) {
   const int m_rows = ctx->group * n_q;
   lkv::AttendPlan plan;
-  lkv::attend_plan(m_rows, cache_len, s_t, ctx->cfg.n_kv_heads, ctx->n_cu, &plan);
+  lkv::attend_plan((int)ctx->cfg.dtype, ctx->cfg.head_dim, m_rows, n_q, cache_len, s_t, ctx->cfg.n_kv_heads, ctx->n_cu, &plan);
   size_t need = lkv::attend_workspace_bytes(plan, m_rows, ctx->cfg.n_kv_heads, ctx->cfg.head_dim);
   if (with_lse_only) {
     lkv::AttendPlan lplan;
@@ -936,7 +936,7 @@ static int attend_impl(laserkv_ctx* ctx, const char* fn, int64_t n_q_max,
   const int m_rows = ctx->group * n_q;
   lkv::AttendPlan plan;
   if (lse_only) lkv::attend_lse_plan(m_rows, cache_len, c.n_kv_heads, ctx->n_cu, &plan);
-  else lkv::attend_plan(m_rows, cache_len, s_t, c.n_kv_heads, ctx->n_cu, &plan);
+  else lkv::attend_plan((int)c.dtype, d, m_rows, n_q, cache_len, s_t, c.n_kv_heads, ctx->n_cu, &plan);
   const size_t need = lse_only ? (size_t)c.n_kv_heads * plan.n_parts * m_rows * 8 + 256
                                : lkv::attend_workspace_bytes(plan, m_rows, c.n_kv_heads, d);
   if (workspace_bytes < (int64_t)need)
@@ -963,13 +963,14 @@ static int attend_impl(laserkv_ctx* ctx, const char* fn, int64_t n_q_max,
   p.keys_per_split = plan.keys_per_split;
   p.blk_keys_per_split = plan.blk_keys_per_split;
   p.n_splits = plan.n_splits;
-  p.direct = plan.direct;
+  p.n_full = plan.n_full;
+  p.n_cut = plan.n_cut;
   p.wprt_log = plan.wprt_log;
   p.n_parts = plan.n_parts;
   p.n_qgroups = plan.n_qgroups;
   p.n_kv_heads = c.n_kv_heads;
   p.scale2 = (float)(1.4426950408889634 / sqrt((double)d));
-  const size_t rows = (size_t)c.n_kv_heads * plan.n_parts * (plan.decode ? lkv::decode_rows(m_rows) : m_rows);
+  const size_t rows = lkv::attend_part_rows(plan, m_rows, c.n_kv_heads);
   p.part_o = lse_only ? nullptr : reinterpret_cast<float*>(workspace);
   p.part_ml = lse_only ? reinterpret_cast<float2*>(workspace)
                        : reinterpret_cast<float2*>(reinterpret_cast<char*>(workspace) + ((rows * d * 4 + 255) & ~(size_t)255));

@@ -8,9 +8,9 @@
 //                          values pass through LDS in chunks; each wave keeps 32 query rows in registers and an
 //                          online-softmax state (reference, sum, unnormalised output) per row; the waves'
 //                          states meet in LDS and leave one partial per split                          [MFMA]
-//   attend_rows_kernel     a row tile per wave (window rows, whole blocks): two LDS stages, the next tile's
-//                          logits issued before the current tile's softmax; writes the result itself when a
-//                          workgroup sees all keys of its rows                                         [MFMA]
+//   attend_rows_kernel     more than four row tiles (window rows, whole blocks): two waves per pair of row tiles that
+//                          together see the same number of keys, keys and values straight into two LDS stages; writes
+//                          the result itself when a workgroup sees all keys of its rows                      [MFMA]
 //   attend_combine_kernel  merges the partials of a row through their references and writes the output and
 //                          the natural-log normaliser, the number laserkv_set_row_lse takes
 //   attend_lse_kernel (+ attend_lse_combine_kernel)  the normaliser alone, for callers that want nothing else
@@ -92,8 +92,8 @@ __device__ __forceinline__ void store_vt(uint4* row, int group, const uint4& t) 
 
 // ds_read_b64_tr_b16: four 16-bit values per lane, transposed within groups of 16 lanes (see its use)
 typedef short s16x4_lds __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 ds_read_tr16(const void* lds_ptr) {
-  const s16x4_lds v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_lds*)lds_ptr);
+__device__ __forceinline__ uint2 ds_read_tr16(uint32_t at) {
+  const s16x4_lds v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_lds*)(uintptr_t)at);
   return __builtin_bit_cast(uint2, v);
 }
 
@@ -332,22 +332,34 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
   }
 }
 
-// The same pass for launches in which every wave owns a row tile (8 or more query rows tiles per KV head: window
-// rows, whole blocks), arranged so that the matrix unit and the vector unit work at the same time.  The keys of
-// a chunk are complete tiles (hidden keys are masked, a tile nobody sees costs its arithmetic), so the tile loop
-// has no early exits and is unrolled: the logits of tile t+1 are issued before the softmax of tile t, whose
-// exponentials then run while the matrix unit multiplies.  Chunks alternate between two LDS stages: the next
-// chunk, prefetched into registers while the current one is worked on, is stored after the chunk's last tile,
-// so one barrier per chunk suffices (every wave has left the stage that is overwritten a barrier ago).
+// The same pass for launches with more than four row tiles per KV head (window rows, whole blocks), arranged so that the
+// matrix unit and the vector unit work at the same time and that every workgroup has the same work.
+//   Pairs.  Waves w and w + 4 (one SIMD) take the row tiles i and n_tiles - 1 - i.  Row m = g n_q + j mirrors to the query
+//   n_q - 1 - j, so under the causal mask of a whole block the two tiles see the block's first L and H keys with L + H the
+//   same for all pairs.  The wave with fewer keys writes its result when the keys pass L and joins the other tile: from
+//   then on the two waves take alternate 32-key tiles, and their states meet in LDS at the end.  (With
+//   consecutive tiles in a workgroup a launch took as long as the block's last rows: a 16k prefill of 32 heads in blocks
+//   of 2048 rows 169 us a block on average, now 151.)
+//   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  References are
+//   fixed, so that the output accumulators see nothing but matrix instructions (a rescaling in the loop doubles their
+//   registers), and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
+//   instructions hardly overlap with matrix instructions here).
+//   Chunks alternate between two LDS stages and arrive through async_ld16, the next one while the current one is worked
+//   on, so one barrier per chunk suffices.
+// Bound by power: at 1.1 PFLOP/s it runs at the rate of a plain bf16 matrix product on this card.
 template <int DT>
 __host__ __device__ constexpr int rows_chunk_keys() { return DT == DT_BF16 ? 128 : 64; }
+
+// the order of V's 32-byte pieces by key: 16 lanes read four keys at one piece, 32 lanes at two neighbouring ones, and
+// both sets are to lie in different banks
+template <int CH>
+__device__ __forceinline__ uint32_t v_swz(uint32_t key) { return CH == 8 ? key : 2 * key + (key >> 1); }
 
 template <int DT, int D>
 __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p) {
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int CH = D * ES / 16;             // 16-byte chunks per row
   constexpr int NCH = CH / 2;
-  constexpr int CHP = CH + 1;                 // K row pitch in chunks (odd)
   constexpr int KC = rows_chunk_keys<DT>();   // keys per LDS chunk
   constexpr int EPC = 16 / ES;                // elements per 16-byte chunk
   constexpr int VTP = KC / EPC + 1;           // V^T row pitch in chunks (odd)
@@ -355,88 +367,154 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   constexpr int NDT = D / 32;                 // 32-wide tiles of the head dimension
   constexpr int TPC = KC / 32;                // key tiles per chunk
   constexpr int RUNS = 32 / (2 * EPC);        // operand chunks per lane and 32-key tile in P.V
-  constexpr int K_ROWS_PER_LOAD = ATT_THREADS / CH;
+  constexpr int ROWS_PER_LOAD = ATT_THREADS / CH;
   constexpr int V_GROUPS_PER_LOAD = ATT_THREADS / (EPC * CH);
-  // bf16: V stays key-major in LDS (rows of CH chunks + 2: a 4-key x 32-byte transposing read touches every bank
-  // once) and ds_read_b64_tr_b16 delivers it transposed; fp32 has no such read: V^T is built in registers
+  // Rows of K lie in LDS without padding (they arrive through async_ld16); chunk c of row r at position c ^ (r & KX), so
+  // that consecutive rows of one operand chunk lie in different banks.
+  constexpr int KX = CH < 16 ? CH - 1 : 15;
+  // bf16: V stays key-major too and ds_read_b64_tr_b16 delivers it transposed; its 32-byte pieces are permuted by the
+  // key (v_swz): a transposing read of four keys touches every bank once.  fp32 has no such read: V^T is built in
+  // registers
   constexpr bool TR = DT == DT_BF16;
-  constexpr int VP = CH + 2;                  // V row pitch in chunks (bf16)
-  constexpr int STAGE = KC * CHP + (TR ? KC * VP : D * VTP);   // uint4 per LDS stage: K [KC][CHP], then V [KC][VP] or V^T [D][VTP]
+  constexpr int STAGE = KC * CH + (TR ? KC * CH : D * VTP);   // uint4 per LDS stage: K [KC][CH], then V [KC][CH] or V^T [D][VTP]
   static_assert(KL >= 1 && KL * ATT_THREADS == KC * CH, "chunk not a whole number of loads per thread");
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
-  // consecutive indices stay on one XCD: the row groups and splits of a head share that XCD's L2
-  const int idx = xcd_major(blockIdx.x, gridDim.x);
-  const int split = idx % p.n_splits, qg = (idx / p.n_splits) % p.n_qgroups, h = idx / (p.n_splits * p.n_qgroups);
-  const int row = qg * ATT_ROWS + wave * 32 + rl;
+  // The first n_full workgroups take all keys of their rows, the others the n_splits key ranges of the last n_cut row
+  // groups.  Consecutive indices stay on one XCD: the row groups and splits of a head share that XCD's L2
+  const bool full = (int)blockIdx.x < p.n_full;
+  const int idx = full ? xcd_major(blockIdx.x, p.n_full) : xcd_major(blockIdx.x - p.n_full, p.n_cut * p.n_splits);
+  const int n_splits = full ? 1 : p.n_splits, split = full ? 0 : idx % n_splits, cut_wg = full ? 0 : idx / n_splits;
+  const int wg = full ? idx : p.n_full + cut_wg, pg = wg % p.n_qgroups, h = wg / p.n_qgroups;
+  const bool direct = n_splits == 1;
+
+  // end of the block keys that some row of a tile sees
+  const int n_tiles = (p.m_rows + 31) >> 5, n_pairs = (n_tiles + 1) >> 1;
+  auto tile_end = [&](int t) {
+    if (p.s_t == 0) return 0;
+    const int m0 = t * 32, m1 = min(m0 + 32, p.m_rows) - 1;
+    const int g0 = div_w(m0, p.nq_magic), g1 = div_w(m1, p.nq_magic);
+    const int j_max = g0 == g1 ? m1 - g1 * p.n_q : p.n_q - 1;
+    return max(0, min(p.s_t, p.diag + j_max + 1));
+  };
+  const int upper = __builtin_amdgcn_readfirstlane(wave >> 2);  // the pair's wave whose tile sees more keys
+  const int pr = pg * 4 + (__builtin_amdgcn_readfirstlane(wave) & 3);
+  const bool present = pr < n_pairs;
+  int t_lo = min(pr, n_pairs - 1), t_hi = n_tiles - 1 - t_lo;
+  const bool single = t_lo == t_hi;           // the middle tile of an odd number: both waves work on it
+  int end_lo = tile_end(t_lo), end_hi = tile_end(t_hi);
+  if (end_lo > end_hi) {
+    int t = t_lo; t_lo = t_hi; t_hi = t;
+    t = end_lo; end_lo = end_hi; end_hi = t;
+  }
+  // This split's keys: an equal share of the time the workgroup takes, which passes one key per unit where both waves of
+  // a pair work on their own tiles and two where they share one (the workgroup's first pair stands for all).
+  int lo0, hi0, lo1, hi1;
+  {
+    const int pr0 = pg * 4, ea = tile_end(pr0), eb = tile_end(n_tiles - 1 - pr0);
+    const int both = p.cache_len + min(ea, eb);
+    int wg_end = max(ea, eb);
+    for (int q = 1; q < 4; ++q)
+      if (pr0 + q < n_pairs) wg_end = max(wg_end, max(tile_end(pr0 + q), tile_end(n_tiles - 1 - pr0 - q)));
+    const int total = both + (max(ea, eb) - min(ea, eb) + 1) / 2;
+    const int share = ((total + n_splits - 1) / n_splits + 31) & ~31;
+    auto cut = [&](int s, int& c, int& b) {  // the start of split s in the two segments, multiples of 32 (or their ends)
+      const int t = s * share, x = t <= both ? t : both + 2 * (t - both);
+      c = min(x, p.cache_len);
+      b = s >= n_splits ? wg_end : min(max(x - p.cache_len, 0) & ~31, wg_end);
+    };
+    cut(split, lo0, lo1);
+    cut(split + 1, hi0, hi1);
+    if (split + 1 >= n_splits) hi0 = p.cache_len;
+  }
 
   extern __shared__ uint4 smem[];
 
-  // the wave's 32 query rows, as the B operand of S^T
+  // the rows of the wave's current tile, as the B operand of S^T
   uint4 a[NCH];
   int blk_end_lane;  // block keys [0, blk_end_lane) are visible to this lane's row
-  {
-    const int m = min(row, p.m_rows - 1);
-    const int g = m / p.n_q, j = m - g * p.n_q;
+  auto load_rows = [&](int t) {
+    const int m = min(fresh(t * 32 + rl), p.m_rows - 1);
+    const int g = div_w(m, p.nq_magic), j = m - g * p.n_q;
     const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + (2 * i + kg) * 16);
     blk_end_lane = max(0, min(p.s_t, p.diag + j + 1));
-  }
-  const int lo0 = min(split * p.keys_per_split, p.cache_len), hi0 = min(lo0 + p.keys_per_split, p.cache_len);
-  int lo1 = 0, hi1 = 0;
-  if (p.s_t > 0) {
-    const int m0 = qg * ATT_ROWS, m1 = min(m0 + ATT_ROWS, p.m_rows) - 1;
-    const int g0 = m0 / p.n_q, g1 = m1 / p.n_q;
-    const int j_max = g0 == g1 ? m1 - g1 * p.n_q : p.n_q - 1;
-    const int wg_end = max(0, min(p.s_t, p.diag + j_max + 1));
-    lo1 = min(split * p.blk_keys_per_split, wg_end);
-    hi1 = min(lo1 + p.blk_keys_per_split, wg_end);
-  }
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) landed(a[i]);
+  };
 
-  const __amdgpu_buffer_rsrc_t ksrd0 = make_srd(p.k_cache + (int64_t)h * p.cache_stride_head, (uint32_t)p.cache_len * (uint32_t)p.row_bytes);
-  const __amdgpu_buffer_rsrc_t vsrd0 = make_srd(p.v_cache + (int64_t)h * p.cache_stride_head, (uint32_t)p.cache_len * (uint32_t)p.row_bytes);
+  // the segments: the cache (0) and the block's own rows (1)
   const uint32_t kb_bytes = p.s_t > 0 ? (uint32_t)(p.s_t - 1) * (uint32_t)p.kb_stride_row + (uint32_t)p.row_bytes : 0u;
   const uint32_t vb_bytes = p.s_t > 0 ? (uint32_t)(p.s_t - 1) * (uint32_t)p.vb_stride_row + (uint32_t)p.row_bytes : 0u;
-  const __amdgpu_buffer_rsrc_t ksrd1 = make_srd(p.k_blk + (int64_t)h * p.kb_stride_head, kb_bytes);
-  const __amdgpu_buffer_rsrc_t vsrd1 = make_srd(p.v_blk + (int64_t)h * p.vb_stride_head, vb_bytes);
-  const uint32_t k_row = tid / CH, k_col = tid % CH;
+  const char* k_base0 = p.k_cache + (int64_t)h * p.cache_stride_head;
+  const char* v_base0 = p.v_cache + (int64_t)h * p.cache_stride_head;
+  const char* k_base1 = p.k_blk + (int64_t)h * p.kb_stride_head;
+  const char* v_base1 = p.v_blk + (int64_t)h * p.vb_stride_head;
+  const uint32_t c_bytes = (uint32_t)p.cache_len * (uint32_t)p.row_bytes;
+  const uint32_t lds0 = lds_offset(smem);
+  // chunk lane % CH of row ld_row (+ ROWS_PER_LOAD per load)
+  const uint32_t ld_row = wave * (64 / CH) + lane / CH, ld_pos = lane % CH;
+  const uint32_t k_col = (ld_pos ^ (ld_row & KX)) * 16, v_col = (ld_pos ^ (2 * v_swz<CH>(ld_row & 3))) * 16;
   const uint32_t v_i = tid % EPC, v_c = (tid / EPC) % CH, v_grp = tid / (EPC * CH);
-  uint4 kpre[KL], vpre[KL];
-  auto prefetch = [&](int seg, int kc0) {
-    const __amdgpu_buffer_rsrc_t ksrd = seg ? ksrd1 : ksrd0, vsrd = seg ? vsrd1 : vsrd0;
+  uint4 vpre[TR ? 1 : KL];
+  // Starts the loads of a chunk into a stage.  Rows past the segment's last one repeat it (they weigh nothing).
+  auto prefetch = [&](int seg, int kc0, int stage) {
+    const srd_words ksrd = make_srd_words(seg ? k_base1 : k_base0, seg ? kb_bytes : c_bytes);
+    const srd_words vsrd = make_srd_words(seg ? v_base1 : v_base0, seg ? vb_bytes : c_bytes);
     const uint32_t kstride = seg ? (uint32_t)p.kb_stride_row : (uint32_t)p.row_bytes;
     const uint32_t vstride = seg ? (uint32_t)p.vb_stride_row : (uint32_t)p.row_bytes;
+    const uint32_t rows = (uint32_t)(seg ? p.s_t : p.cache_len);
+    const uint32_t dst = lds0 + stage * (STAGE * 16) + __builtin_amdgcn_readfirstlane(wave) * 1024;
+    const uint32_t r0 = fresh(ld_row);
+    if (kc0 + KC <= (int)rows) {
+      const uint32_t k_off = r0 * kstride + k_col, v_off = r0 * vstride + v_col;
 #pragma unroll
-    for (int u = 0; u < KL; ++u) {
-      kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * K_ROWS_PER_LOAD) * kstride + k_col * 16);
-      if (TR) {
-        vpre[u] = buf_ld16(vsrd, (uint32_t)(kc0 + k_row + u * K_ROWS_PER_LOAD) * vstride + k_col * 16);
-      } else {
+      for (int u = 0; u < KL; ++u) {
+        const uint32_t row = kc0 + u * ROWS_PER_LOAD;
+        async_ld16(ksrd, k_off, row * kstride, dst + u * (ATT_THREADS * 16));
+        if (TR) async_ld16(vsrd, v_off, row * vstride, dst + KC * CH * 16 + u * (ATT_THREADS * 16));
+      }
+    } else {
+#pragma unroll 1
+      for (int u = 0; u < KL; ++u) {
+        const uint32_t row = min((uint32_t)kc0 + r0 + u * ROWS_PER_LOAD, rows - 1u);
+        async_ld16(ksrd, row * kstride + k_col, 0u, dst + u * (ATT_THREADS * 16));
+        if (TR) async_ld16(vsrd, row * vstride + v_col, 0u, dst + KC * CH * 16 + u * (ATT_THREADS * 16));
+      }
+    }
+    if (!TR) {
+      const __amdgpu_buffer_rsrc_t vs = make_srd(seg ? v_base1 : v_base0, seg ? vb_bytes : c_bytes);
+#pragma unroll
+      for (int u = 0; u < KL; ++u) {
         const uint32_t key = (u * V_GROUPS_PER_LOAD + v_grp) * EPC + v_i;
-        vpre[u] = buf_ld16(vsrd, (uint32_t)(kc0 + key) * vstride + v_c * 16);
+        vpre[u] = buf_ld16(vs, (uint32_t)(kc0 + key) * vstride + v_c * 16);
       }
     }
   };
-  auto store = [&](uint4* stage) {
-    uint4* sK = stage;
-    uint4* sV = stage + KC * CHP;
+  // Completes them (fp32: V^T is written here).
+  auto land = [&](int stage) {
+    if (!TR) {
+      uint4* sV = smem + (size_t)stage * STAGE + KC * CH;
 #pragma unroll
-    for (int u = 0; u < KL; ++u) {
-      sK[(k_row + u * K_ROWS_PER_LOAD) * CHP + k_col] = kpre[u];
-      if (TR) {
-        sV[(k_row + u * K_ROWS_PER_LOAD) * VP + k_col] = vpre[u];
-      } else {
+      for (int u = 0; u < KL; ++u)
         store_vt<DT>(sV + (v_c * EPC + v_i) * VTP, u * V_GROUPS_PER_LOAD + v_grp, transpose_4x4_b32(vpre[u], lane));
-      }
     }
+    async_wait();
   };
   // Transposing read of V (bf16).  Within 16 lanes, lane i hands in the address of 4 consecutive 16-bit values and
   // lane 4c + e receives value e of lanes c, c + 4, c + 8, c + 12.  Lane i points at key (i >> 2) of a run of four
   // keys and head-dimension offset 4 (i & 3), so lane l of the sixteen receives the four keys at head-dimension
   // offset l: the A operand of O^T += V^T P^T.  Byte offset of this lane's piece within a V stage, for key 0 of the
   // tile's first 16-key block and head-dimension tile 0:
-  const uint32_t tr_off = (uint32_t)((4 * kg + ((lane & 15) >> 2)) * VP * 16 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+  // LDS addresses of a lane's pieces for a tile in the first rows of a stage: K, to be xored with 32 i for operand chunk
+  // pair i, and V, to be xored with 64 dt for head-dimension tile dt (rows are powers of two, so rows are added and
+  // positions within them xored)
+  const uint32_t k_at = lds0 + rl * (CH * 16) + ((kg ^ (rl & KX)) * 16);
+  const uint32_t v_at = TR ? lds0 + KC * CH * 16 + (4 * kg + ((lane & 15) >> 2)) * CH * 16 + (lane & 3) * 8 +
+                                 (((2 * ((lane >> 4) & 1)) ^ (2 * v_swz<CH>((lane & 15) >> 2))) * 16)
+                           : lds0 + KC * CH * 16 + rl * (VTP * 16) + kg * 16;
+  constexpr uint32_t K_TILE = 32 * CH * 16, V_TILE = TR ? 32 * CH * 16 : 32 / EPC * 16;  // bytes from one 32-key tile to the next
   // the chunk after (seg, kc0): the next of the segment, else the first of the block's keys
   auto advance = [&](int& seg, int& kc0) -> bool {
     kc0 += KC;
@@ -448,212 +526,397 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     }
     return false;
   };
-  auto logits = [&](const uint4* stage, int nt, f32x16& acc) {
-    const uint4* krow = stage + (size_t)(nt * 32 + rl) * CHP + kg;
+  auto load_k = [&](uint32_t at, uint4* kf) {  // a key tile's operand chunks
+    at = opaque(at);
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(at ^ (32 * i));
+  };
+  auto logits = [&](const uint4* kf, f32x16& acc) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) Mma<DT>::run(acc, krow[2 * i], a[i]);
+    for (int i = 0; i < NCH; ++i) Mma<DT>::run(acc, kf[i], a[i]);
   };
 
-  // Two attempts at most.  In the first, a row's reference is its maximum over the first tile of the cache rows
-  // and complete tiles of cache rows after it skip the maximum, the comparison and the rescaling (an fma, an
-  // exponential and an add per logit are all that is left); sums that grow past 2^100 (a later logit far above
-  // the first tile's) make the workgroup repeat the pass with a reference that follows the running maximum
-  // everywhere, as the block's own keys (masked, and possibly a row's first visible keys) always do.
+  constexpr float HEADROOM = 60.0f;  // of a fixed reference over the maximum of its first tile, in powers of two
   float m_ref, l_sum;
   f32x16 o[NDT];
-  int* redo = reinterpret_cast<int*>(smem + (size_t)2 * STAGE);  // one word behind the two stages
-  if (tid == 0) *redo = 0;  // ordered before the writes after the first attempt by the barriers in between
-#pragma unroll 1
-  for (int attempt = 0; attempt < 2; ++attempt) {
-  const bool fixed_ref = attempt == 0 && DT == DT_BF16;  // fp32 rows (512 bytes) leave no registers for a second tile body
-  m_ref = NEG_BIG;
-  l_sum = 0.0f;
+  auto clear = [&]() {
+    m_ref = NEG_BIG;
+    l_sum = 0.0f;
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
-
-  int seg = lo0 < hi0 ? 0 : 1;
-  int kc0 = seg ? lo1 : lo0;
-  bool have = seg ? lo1 < hi1 : true;
-  int nseg = seg, nkc = kc0;
-  bool nhave = false;
-  int cur = 0;
-  if (have) {
-    prefetch(seg, kc0);
-    store(smem);
-    nhave = advance(nseg, nkc);
-    if (nhave) prefetch(nseg, nkc);  // in flight while the first chunk is worked on
-    lds_barrier();
-  }
-  while (have) {
-    const uint4* stage = smem + (size_t)cur * STAGE;
-    const uint4* sVT = stage + KC * CHP;
-    const char* sVb = reinterpret_cast<const char*>(sVT) + tr_off;
-    const int lane_end = seg ? min(hi1, blk_end_lane) : hi0;  // end of the keys of this segment the lane's row sees
-    f32x16 acc, acc_next;
-    logits(stage, 0, acc);
+      for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
+  };
+  auto load_v = [&](uint32_t vat, uint4* vf) {  // fp32
 #pragma unroll
-    for (int nt = 0; nt < TPC; ++nt) {
-      if (nt + 1 < TPC) logits(stage, nt + 1, acc_next);  // the matrix unit works on these during the exponentials below
-      const int n_vis = lane_end - (kc0 + nt * 32);  // keys of this tile the lane's row sees (>= 32: all)
-      // workgroup-uniform: a complete tile of cache rows that is not the pass's first
-      if (fixed_ref && seg == 0 && kc0 + nt * 32 > lo0 && kc0 + nt * 32 + 32 <= hi0) {
+    for (int s = 0; s < RUNS; ++s)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[r] = fast_exp2(fmaf(acc[r], p.scale2, -m_ref));
-          l_sum += acc[r];
-        }
+      for (int dt = 0; dt < NDT; ++dt) vf[s * NDT + dt] = lds_ld16(vat + dt * (32 * VTP * 16) + 2 * s * 16);  // registers 4s .. 4s+3 are keys 8s + 4kg + (0..3)
+  };
+  auto load_v_tr = [&](const uint32_t* vx, uint32_t off, uint4* vf) {  // bf16
+#pragma unroll
+    for (int s = 0; s < RUNS; ++s)
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+        // registers 8s .. 8s+3 of the logits are keys 16s + 4kg + (0..3), registers 8s+4 .. 8s+7 the same + 8
+        const uint32_t at = vx[dt] + off + 16 * s * CH * 16;
+        const uint2 lo = ds_read_tr16(at), hi = ds_read_tr16(at + 8 * CH * 16);
+        vf[s * NDT + dt] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+  };
+  auto weigh = [&](const f32x16& acc, const uint4* vf) {  // O^T += V^T P^T
+#pragma unroll
+    for (int s = 0; s < RUNS; ++s) {
+      uint4 pb;
+      if (DT == DT_BF16) {
+        pb = make_uint4(pack_bf16(acc[8 * s], acc[8 * s + 1]), pack_bf16(acc[8 * s + 2], acc[8 * s + 3]),
+                        pack_bf16(acc[8 * s + 4], acc[8 * s + 5]), pack_bf16(acc[8 * s + 6], acc[8 * s + 7]));
       } else {
-      if (!__all(n_vis >= 32)) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = acc_row(r, kg) < n_vis ? acc[r] : NEG_BIG;
-      }
-      float mx = acc[0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-      mx = half_pair_max(mx);  // both halves of the wave use one reference per row
-      mx = mx > NEG_BIG ? mx * p.scale2 : NEG_BIG;  // the reference lives in the scaled (log2) domain; scale2 > 0
-      if (__any(mx > m_ref)) {
-        const float m_new = fmaxf(m_ref, mx);
-        const float alpha = fast_exp2(m_ref - m_new);
-        l_sum *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-        m_ref = m_new;
-      }
-      // a row without a visible key so far subtracts nothing: its hidden logits give 2^(NEG_BIG * scale2) = 0
-      const float m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        acc[r] = fast_exp2(fmaf(acc[r], p.scale2, -m_sub));
-        l_sum += acc[r];
-      }
+        pb = make_uint4(__float_as_uint(acc[4 * s]), __float_as_uint(acc[4 * s + 1]),
+                        __float_as_uint(acc[4 * s + 2]), __float_as_uint(acc[4 * s + 3]));
       }
 #pragma unroll
-      for (int s = 0; s < RUNS; ++s) {
-        uint4 pb;
-        if (DT == DT_BF16) {
-          pb = make_uint4(pack_bf16(acc[8 * s], acc[8 * s + 1]), pack_bf16(acc[8 * s + 2], acc[8 * s + 3]),
-                          pack_bf16(acc[8 * s + 4], acc[8 * s + 5]), pack_bf16(acc[8 * s + 6], acc[8 * s + 7]));
-        } else {
-          pb = make_uint4(__float_as_uint(acc[4 * s]), __float_as_uint(acc[4 * s + 1]),
-                          __float_as_uint(acc[4 * s + 2]), __float_as_uint(acc[4 * s + 3]));
-        }
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-          const uint4* vrow = sVT + (size_t)(dt * 32 + rl) * VTP;
-          uint4 va;
-          if (TR) {
-            // registers 8s .. 8s+3 are keys 16s + 4kg + (0..3), registers 8s+4 .. 8s+7 the same + 8
-            const char* at = sVb + (size_t)((nt * 32 + 16 * s) * VP) * 16 + dt * 64;
-            const uint2 lo = ds_read_tr16(at), hi = ds_read_tr16(at + 8 * VP * 16);
-            va = make_uint4(lo.x, lo.y, hi.x, hi.y);
-          } else if (DT == DT_BF16) {
-            va = vrow[nt * 4 + 2 * s + kg];  // registers 8s .. 8s+7 are keys 16s + 4kg + (0..3) and the same + 8: see store_vt
-          } else {
-            va = vrow[nt * 8 + 2 * s + kg];  // registers 4s .. 4s+3 are keys 8s + 4kg + (0..3)
-          }
-          Mma<DT>::run(o[dt], va, pb);
-        }
-      }
-      if (nt + 1 < TPC) acc = acc_next;
+      for (int dt = 0; dt < NDT; ++dt) Mma<DT>::run(o[dt], vf[s * NDT + dt], pb);
     }
-    // the next chunk goes into the other stage, which every wave left before the previous barrier
+  };
+  // The result of tile t from the wave's complete state: with one split out = O / l and lse = (m + log2 l) ln 2 (a row
+  // that saw no key gives zero and -inf), else the split's partial (reference, sum, unnormalised output).  A lane holds 16
+  // bytes of every 32 of its row; groups of four lanes exchange them so that a store instruction writes whole 128-byte
+  // lines of eight rows (with 32-byte pieces of
+  // 32 rows the 33 MB of 65536 rows took 3.6 us longer).
+  auto write_tile = [&](int t) {
+    const int row = fresh(t * 32 + rl);
+    const float l = half_pair_sum(l_sum);
+    float scale = 1.0f, *dst;
+    if (direct) {
+      const size_t at = (size_t)h * p.m_rows + row;
+      scale = l > 0.0f ? 1.0f / l : 0.0f;
+      const float up = l < 1.0f ? HEADROOM : 0.0f;  // the headroom comes off exactly, before the logarithm
+      if (kg == 0 && row < p.m_rows)
+        p.out_lse[at] = l > 0.0f ? ((m_ref - up) + fast_log2(l < 1.0f ? l * 0x1p60f : l)) * 0.6931471805599453f : -__builtin_inff();
+      dst = p.out + (size_t)h * p.m_rows * D;
+    } else {
+      // [cut row groups][splits][256 rows: the pairs in order, of each the tile with the lower number first]
+      const size_t at = ((size_t)cut_wg * n_splits + split) * ATT_ROWS + ((wave & 3) * 2 + (t != pr)) * 32;
+      if (kg == 0) p.part_ml[at + rl] = make_float2(m_ref, l);
+      dst = p.part_o + at * D - (size_t)t * 32 * D;
+    }
+    const int row4 = row & ~3;
+    dst += (int64_t)row4 * D + 8 * (rl & 3) + 4 * kg;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) {
+      uint4 x[4];  // component u of the lane's four pieces, then of its piece of four rows
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        x[u] = transpose_4x4_b32(make_uint4(__float_as_uint(o[dt][u] * scale), __float_as_uint(o[dt][4 + u] * scale),
+                                            __float_as_uint(o[dt][8 + u] * scale), __float_as_uint(o[dt][12 + u] * scale)), lane);
+      const uint4 piece[4] = {make_uint4(x[0].x, x[1].x, x[2].x, x[3].x), make_uint4(x[0].y, x[1].y, x[2].y, x[3].y),
+                              make_uint4(x[0].z, x[1].z, x[2].z, x[3].z), make_uint4(x[0].w, x[1].w, x[2].w, x[3].w)};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (row4 + e >= p.m_rows) continue;
+        if (direct) st16_stream(dst + (size_t)e * D + dt * 32, piece[e]);
+        else *reinterpret_cast<uint4*>(dst + (size_t)e * D + dt * 32) = piece[e];
+      }
+    }
+  };
+
+  // A row's reference is fixed: its maximum over the first tile of keys that it sees, plus HEADROOM (what a row sees is a prefix of
+  // the keys: a row that sees none of a wave's first tile sees none of the others).  Each logit then costs an fma, an
+  // exponential and an add, and the output accumulators nothing but matrix instructions.  Sums that grow past 1e30 (a
+  // logit 160 above the first tile's, in powers of two) make the workgroup repeat the pass with the exact maxima, which a
+  // sweep over the keys finds first.
+  int* redo = reinterpret_cast<int*>(smem + (size_t)2 * STAGE);  // one word behind the two stages
+  if (tid == 0) *redo = 0;  // ordered before the writes after the first pass by the barriers in between
+  // position in the split's chunks
+  int seg, kc0, nseg, nkc, cur;
+  bool have, nhave;
+  auto start = [&]() {  // the first chunk's loads
+    seg = lo0 < hi0 ? 0 : 1;
+    kc0 = seg ? lo1 : lo0;
+    have = seg ? lo1 < hi1 : true;
+    nseg = seg;
+    nkc = kc0;
+    nhave = false;
+    cur = 0;
+    if (have) {
+      prefetch(seg, kc0, 0);
+      nhave = advance(nseg, nkc);
+    }
+  };
+  auto next = [&]() {  // on to the next chunk
     have = nhave;
     if (have) {
-      store(smem + (size_t)(cur ^ 1) * STAGE);
+      land(cur ^ 1);
       seg = nseg;
       kc0 = nkc;
       nhave = advance(nseg, nkc);
-      if (nhave) prefetch(nseg, nkc);
       cur ^= 1;
       lds_barrier();
     }
+  };
+  auto hide = [&](f32x16& acc, int n_vis) {  // hidden keys (past the end of the split or the row's causal limit) weigh nothing
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = acc_row(r, 0) < n_vis - 4 * kg ? acc[r] : NEG_BIG;
+  };
+  auto maximum = [&](uint32_t at, int n_vis) {  // of a tile's visible logits, in the scaled (log2) domain; scale2 > 0
+    f32x16 acc;
+    uint4 kf[NCH];
+    load_k(at, kf);
+    logits(kf, acc);
+    hide(acc, n_vis);
+    float mx = acc[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+    mx = half_pair_max(mx);  // both halves of the wave use one reference per row
+    return mx > NEG_BIG ? mx * p.scale2 : NEG_BIG;
+  };
+  bool joined;  // the pair's waves share the upper tile
+  float ref_own = NEG_BIG, ref_join = NEG_BIG;  // the second pass's references for the wave's own tile and the shared one
+  // The wave's key tiles in a chunk are nt0, nt0 + 1, ..., up to the last key that some row sees; sharing waves take half a
+  // chunk each.
+  int nt0;
+  // LDS addresses of the lane's operand chunks in the wave's first tile of the current chunk (bf16; kept and moved from
+  // stage to stage: computed where they are used they cost a vector instruction per LDS read)
+  uint32_t kx[NCH], vx[NDT];
+  auto place = [&]() {
+    nt0 = joined && !upper ? TPC / 2 : 0;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) kx[i] = opaque((k_at + cur * (STAGE * 16) + nt0 * K_TILE) ^ (32 * i));
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) vx[dt] = opaque((v_at + cur * (STAGE * 16) + nt0 * V_TILE) ^ (64 * dt));
+  };
+#pragma unroll 1
+  for (int pass = 0;; ++pass) {
+    start();
+    joined = single && have;
+    place();
+    load_rows(upper || single ? t_hi : t_lo);
+    clear();
+    bool has_ref = pass != 0, bad = false;
+    if (pass) m_ref = ref_own;
+    if (have) {
+      land(0);
+      lds_barrier();
+    }
+    while (have) {
+      if (nhave) prefetch(nseg, nkc, cur ^ 1);  // in flight while this chunk is worked on; every wave left that stage before the barrier
+      if (!joined && seg && kc0 >= end_lo) {
+        joined = true;
+        if (!upper) {
+          bad = !(l_sum < 1.0e30f);
+          if (present) write_tile(t_lo);
+          load_rows(t_hi);
+          clear();
+          place();
+          has_ref = pass != 0;
+          if (pass) m_ref = ref_join;
+        }
+      }
+      const int wave_end = seg ? min(hi1, upper || joined ? end_hi : end_lo) : hi0;
+      int left = present ? min(min(max((wave_end - kc0 + 31) >> 5, 0), TPC) - nt0, joined ? TPC / 2 : TPC) : 0;
+      const int lane_end = seg ? min(hi1, blk_end_lane) : hi0;  // end of the keys of this segment the lane's row sees
+      const int n_vis = lane_end - (kc0 + nt0 * 32);  // keys from the wave's first on that the lane's row sees
+      const bool whole = __all(n_vis >= KC - nt0 * 32);
+      if (left > 0 && !has_ref) {
+        has_ref = true;
+        m_ref = maximum(k_at + cur * (STAGE * 16) + nt0 * K_TILE, n_vis);
+        m_ref += m_ref > NEG_BIG ? HEADROOM : 0.0f;
+      }
+      // a row without a visible key subtracts nothing: its hidden logits give 2^(NEG_BIG * scale2) = 0
+      const float m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
+      auto soft = [&](f32x16& acc) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc[r] = fast_exp2(fmaf(acc[r], p.scale2, -m_sub));
+          l_sum += acc[r];
+        }
+      };
+      if (DT == DT_BF16) {
+        // two key tiles: the exponentials of one run beside the other's products
+#pragma unroll
+        for (int T = 0; T < TPC; T += 2) {
+          if (left <= T) break;
+          const int vis = n_vis - T * 32;
+          f32x16 acc0, acc1;
+          uint4 ka[NCH], kb[NCH], va[RUNS * NDT], vb[RUNS * NDT];
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) ka[i] = lds_ld16(kx[i] + T * K_TILE);
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) kb[i] = lds_ld16(kx[i] + (T + 1) * K_TILE);
+          logits(ka, acc0);
+          if (!whole) hide(acc0, vis);
+          load_v_tr(vx, T * V_TILE, va);
+          logits(kb, acc1);
+          soft(acc0);
+          if (!whole) hide(acc1, vis - 32);
+          load_v_tr(vx, (T + 1) * V_TILE, vb);
+          weigh(acc0, va);
+          soft(acc1);
+          weigh(acc1, vb);
+        }
+      } else {
+        uint32_t kr = k_at + cur * (STAGE * 16) + nt0 * K_TILE, vr = v_at + cur * (STAGE * 16) + nt0 * V_TILE;
+        int vis = n_vis;
+#pragma unroll 1
+        for (; left > 0; --left) {
+          f32x16 acc;
+          uint4 kf[NCH], vf[RUNS * NDT];
+          load_k(kr, kf);
+          logits(kf, acc);
+          if (!whole) hide(acc, vis);
+          soft(acc);
+          load_v(vr, vf);
+          weigh(acc, vf);
+          kr += K_TILE;
+          vr += V_TILE;
+          vis -= 32;
+        }
+      }
+      next();
+      if (DT == DT_BF16) {
+        const uint32_t move = cur ? STAGE * 16 : -STAGE * 16;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) kx[i] = opaque(kx[i] + move);
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) vx[dt] = opaque(vx[dt] + move);
+      }
+    }
+    if (pass) {
+      lds_barrier();  // every wave has left the stages
+      break;
+    }
+    // inf, NaN or large enough for O = sum p v to overflow next: once more (decided for the workgroup: the pass has barriers)
+    if (bad || !(l_sum < 1.0e30f)) *redo = 1;
+    __syncthreads();
+    if (!*redo) break;
+    start();
+    joined = single && have;
+    nt0 = joined && !upper ? TPC / 2 : 0;
+    load_rows(upper || single ? t_hi : t_lo);
+    if (have) {
+      land(0);
+      lds_barrier();
+    }
+    while (have) {
+      if (nhave) prefetch(nseg, nkc, cur ^ 1);
+      if (!joined && seg && kc0 >= end_lo) {
+        joined = true;
+        if (!upper) load_rows(t_hi);
+        nt0 = upper ? 0 : TPC / 2;
+      }
+      const int wave_end = seg ? min(hi1, upper || joined ? end_hi : end_lo) : hi0;
+      int left = present ? min(min(max((wave_end - kc0 + 31) >> 5, 0), TPC) - nt0, joined ? TPC / 2 : TPC) : 0;
+      const int lane_end = seg ? min(hi1, blk_end_lane) : hi0;
+      for (int nt = nt0; left > 0; --left, ++nt) {
+        const float mx = maximum(k_at + cur * (STAGE * 16) + nt * K_TILE, lane_end - (kc0 + nt * 32));
+        float& ref = joined && !upper && !single ? ref_join : ref_own;
+        ref = fmaxf(ref, mx);
+      }
+      next();
+    }
+    lds_barrier();
   }
-  if (!fixed_ref) break;
-  // inf, NaN or large enough for O = sum p v to overflow next: repeat (decided for the workgroup: the pass has barriers)
-  if (!(l_sum < 1.0e30f)) *redo = 1;
-  __syncthreads();
-  if (!*redo) break;
-  }
-
-  l_sum = half_pair_sum(l_sum);
-  if (row >= p.m_rows) return;
-  if (p.direct) {
-    // one split: the state is final.  out = O / l, lse = (m + log2 l) ln 2; a row that saw no key gives zero and -inf
-    const size_t at = (size_t)h * p.m_rows + row;
-    const float inv = l_sum > 0.0f ? 1.0f / l_sum : 0.0f;
-    if (kg == 0) p.out_lse[at] = l_sum > 0.0f ? (m_ref + fast_log2(l_sum)) * 0.6931471805599453f : -__builtin_inff();
-    float* dst = p.out + at * D;
+  // every wave has left the stages: the states of pairs that shared a tile meet there (rows padded by four floats
+  // against bank conflicts)
+  constexpr int OP = D + 4;
+  static_assert((size_t)4 * 32 * (OP + 2) * 4 <= (size_t)2 * STAGE * 16, "the states do not fit the stages");
+  float* so = reinterpret_cast<float*>(smem) + (size_t)((wave & 3) * 32 + rl) * OP;
+  float2* sml = reinterpret_cast<float2*>(reinterpret_cast<float*>(smem) + (size_t)4 * 32 * OP) + (wave & 3) * 64 + lane;
+  if (joined && !upper) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
-        st16_stream(dst + dt * 32 + 8 * q4 + 4 * kg,
-                    make_uint4(__float_as_uint(o[dt][4 * q4] * inv), __float_as_uint(o[dt][4 * q4 + 1] * inv),
-                               __float_as_uint(o[dt][4 * q4 + 2] * inv), __float_as_uint(o[dt][4 * q4 + 3] * inv)));
-    return;
+        *reinterpret_cast<float4*>(so + dt * 32 + 8 * q4 + 4 * kg) =
+            make_float4(o[dt][4 * q4], o[dt][4 * q4 + 1], o[dt][4 * q4 + 2], o[dt][4 * q4 + 3]);
+    *sml = make_float2(m_ref, l_sum);
   }
-  // the split's partial (reference, sum, unnormalised output)
-  const size_t at = ((size_t)h * p.n_parts + split) * p.m_rows + row;
-  if (kg == 0) p.part_ml[at] = make_float2(m_ref, l_sum);
-  float* dst = p.part_o + at * D;
+  lds_barrier();
+  if (!present) return;
+  if (joined && upper) {
+    const float2 ml = *sml;
+    const float mn = fmaxf(m_ref, ml.x), wa = fast_exp2(m_ref - mn), wb = fast_exp2(ml.x - mn);
+    m_ref = mn;
+    l_sum = l_sum * wa + ml.y * wb;
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4)
-      *reinterpret_cast<float4*>(dst + dt * 32 + 8 * q4 + 4 * kg) =
-          make_float4(o[dt][4 * q4], o[dt][4 * q4 + 1], o[dt][4 * q4 + 2], o[dt][4 * q4 + 3]);
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const float4 ov = *reinterpret_cast<const float4*>(so + dt * 32 + 8 * q4 + 4 * kg);
+        const float of[4] = {ov.x, ov.y, ov.z, ov.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[dt][4 * q4 + u] = o[dt][4 * q4 + u] * wa + of[u] * wb;
+      }
+  }
+  if (upper) write_tile(t_hi);
+  else if (!joined && !single) write_tile(t_lo);
 }
 
-// out = sum_p O_p 2^(m_p - M) / sum_p l_p 2^(m_p - M), lse = (M + log2 of that sum) ln 2.  One workgroup per row:
-// D / 4 lanes across the head dimension times COMB_SLICES slices of the partials, each slice merged on the fly
-// and the slices then through LDS.  Without any partial (empty cache) the output is zero, the normaliser -inf.
+// out = sum_p O_p 2^(m_p - M) / sum_p l_p 2^(m_p - M), lse = (M + log2 of that sum) ln 2.  A row takes D / 4 lanes across
+// the head dimension times S slices of its partials, each slice merged on the fly and the slices then through LDS; a
+// workgroup takes 8 / S rows, S growing with the partials (two partials of 24 000 rows with eight slices: 15 - 18 us,
+// six of the slices idle; with two 9 us).  Without any partial (empty cache) the output is zero, the normaliser -inf.
 constexpr int COMB_SLICES = 8;
-template <int D>
+template <int D, int S>
 __global__ __launch_bounds__((D / 4) * COMB_SLICES) void attend_combine_kernel(AttendParams p) {
   constexpr int LPR = D / 4;  // lanes per row
+  constexpr int ROWS = COMB_SLICES / S;
   __shared__ float4 sAcc[COMB_SLICES][LPR];
   __shared__ float2 sMl[COMB_SLICES];
-  const int row_lin = blockIdx.x;
-  const int d4 = threadIdx.x % LPR, sl = threadIdx.x / LPR;
-  const int h = row_lin / p.m_rows, m = row_lin - h * p.m_rows;
-  const float2* ml = p.part_ml + (size_t)h * p.n_parts * p.m_rows + m;
-  const float* po = p.part_o + ((size_t)h * p.n_parts * p.m_rows + m) * D + d4 * 4;
+  const int d4 = threadIdx.x % LPR, sl = threadIdx.x / LPR % S, rw = threadIdx.x / (LPR * S);
+  // rows per split in the workspace, this row's first partial, and the row of the output (none: -1)
+  int pitch = p.m_rows, row_lin = blockIdx.x * ROWS + rw;
+  size_t first = 0;
+  if (p.n_cut) {  // attend_rows_kernel's layout
+    const int cut_wg = row_lin / ATT_ROWS, r = row_lin % ATT_ROWS, wg = p.n_full + cut_wg;
+    const int h = wg / p.n_qgroups, pr = (wg - h * p.n_qgroups) * 4 + r / 64, n_tiles = (p.m_rows + 31) >> 5;
+    const int t = r & 32 ? n_tiles - 1 - pr : pr, m = t * 32 + (r & 31);
+    const bool none = pr >= (n_tiles + 1) / 2 || ((r & 32) && t == pr) || m >= p.m_rows;
+    pitch = ATT_ROWS;
+    row_lin = none ? -1 : h * p.m_rows + m;
+    first = (size_t)cut_wg * p.n_parts * ATT_ROWS + r;
+  } else if (row_lin < p.n_kv_heads * p.m_rows) {
+    const int h = row_lin / p.m_rows;
+    first = (size_t)h * p.n_parts * p.m_rows + (row_lin - h * p.m_rows);
+  } else {
+    row_lin = -1;
+  }
+  const float2* ml = p.part_ml + first;
+  const float* po = p.part_o + first * D + d4 * 4;
   float mx = NEG_BIG, l = 0.0f;
   float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (row_lin >= 0) {
 #pragma unroll 4
-  for (int q = sl; q < p.n_parts; q += COMB_SLICES) {
-    const float2 v = ml[(size_t)q * p.m_rows];
-    const float4 ov = *reinterpret_cast<const float4*>(po + (size_t)q * p.m_rows * D);
-    const float mn = fmaxf(mx, v.x);
-    const float wa = fast_exp2(mx - mn), wb = fast_exp2(v.x - mn);
-    l = l * wa + v.y * wb;
-    acc.x = acc.x * wa + ov.x * wb;
-    acc.y = acc.y * wa + ov.y * wb;
-    acc.z = acc.z * wa + ov.z * wb;
-    acc.w = acc.w * wa + ov.w * wb;
-    mx = mn;
+    for (int q = sl; q < p.n_parts; q += S) {
+      const float2 v = ml[(size_t)q * pitch];
+      const float4 ov = *reinterpret_cast<const float4*>(po + (size_t)q * pitch * D);
+      const float mn = fmaxf(mx, v.x);
+      const float wa = fast_exp2(mx - mn), wb = fast_exp2(v.x - mn);
+      l = l * wa + v.y * wb;
+      acc.x = acc.x * wa + ov.x * wb;
+      acc.y = acc.y * wa + ov.y * wb;
+      acc.z = acc.z * wa + ov.z * wb;
+      acc.w = acc.w * wa + ov.w * wb;
+      mx = mn;
+    }
   }
-  sAcc[sl][d4] = acc;
-  if (d4 == 0) sMl[sl] = make_float2(mx, l);
+  sAcc[rw * S + sl][d4] = acc;
+  if (d4 == 0) sMl[rw * S + sl] = make_float2(mx, l);
   __syncthreads();
-  if (sl != 0) return;
+  if (sl != 0 || row_lin < 0) return;
   float mt = NEG_BIG;
 #pragma unroll
-  for (int k = 0; k < COMB_SLICES; ++k) mt = fmaxf(mt, sMl[k].x);
+  for (int k = 0; k < S; ++k) mt = fmaxf(mt, sMl[rw * S + k].x);
   float lt = 0.0f;
   float4 at = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-  for (int k = 0; k < COMB_SLICES; ++k) {
-    const float wgt = fast_exp2(sMl[k].x - mt);
-    const float4 ov = sAcc[k][d4];
-    lt = fmaf(sMl[k].y, wgt, lt);
+  for (int k = 0; k < S; ++k) {
+    const float wgt = fast_exp2(sMl[rw * S + k].x - mt);
+    const float4 ov = sAcc[rw * S + k][d4];
+    lt = fmaf(sMl[rw * S + k].y, wgt, lt);
     at.x = fmaf(ov.x, wgt, at.x);
     at.y = fmaf(ov.y, wgt, at.y);
     at.z = fmaf(ov.z, wgt, at.z);
@@ -742,14 +1005,48 @@ __global__ __launch_bounds__(LSEC_ROWS * LSEC_SLICES) void attend_lse_combine_ke
 }
 
 // ---- host side ----
-void attend_plan(int m_rows, int64_t cache_len, int s_t, int n_kv_heads, int n_cu, AttendPlan* plan) {
+// Key splits for n_wg workgroups of attend_rows_kernel (one per compute unit at a time) that take t keys each.  The time is
+// a line in t for every number of splits: rounds * (t keys / splits + a start), and with more than one the partials' way
+// through memory and the merging launch.  The slopes fall as the splits that pay grow, so the choice grows with t and with
+// it the workspace.
+static int rows_splits(int n_wg, int n_cu, double t, int dtype, int head_dim) {
+  const double key_us = 0.038 * head_dim / 128 * (dtype == DT_F32 ? 7.4 : 1.0);  // 256 rows; 0.030 over long ranges, 0.05 over 400 keys
+  int best = 1;
+  double best_cost = 0.0;
+  for (int s = 1; s <= ATT_MAX_SPLITS; ++s) {
+    const int rounds = (int)(((int64_t)n_wg * s + n_cu - 1) / n_cu);
+    const double part_us = (double)n_wg * ATT_ROWS * head_dim * 8.0 / 6.0e6;  // a partial of every row written and read
+    const double cost = rounds * (t / s * key_us + 4.0) + (s > 1 ? 4.0 + s * part_us : 0.0);
+    if (s == 1 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+void attend_plan(int dtype, int head_dim, int m_rows, int n_q, int64_t cache_len, int s_t, int n_kv_heads, int n_cu, AttendPlan* plan) {
   if (decode_supports(m_rows, cache_len, s_t)) return decode_plan(cache_len, n_kv_heads, n_cu, plan);
   plan->decode = 0;
-  const int n_qg = (m_rows + ATT_ROWS - 1) / ATT_ROWS;
-  const int n_rt = (min(m_rows, ATT_ROWS) + 31) / 32;
+  const int n_rt = (m_rows + 31) / 32;
+  if (n_rt > 4) {
+    // a pair of waves per pair of row tiles.  The queries of a whole block see half of its keys on average
+    const int n_pg = ((n_rt + 1) / 2 + 3) / 4;
+    const double t = (double)cache_len + (2 * n_q > s_t ? 0.5 : 1.0) * s_t;
+    // whole rounds of workgroups take all their keys; the workgroups of the last, incomplete round are cut by keys
+    const int n_wg = n_kv_heads * n_pg, n_rest = n_wg % n_cu;
+    const int s = n_rest ? min(rows_splits(n_rest, n_cu, t, dtype, head_dim), max(1, (int)((t + 31.0) / 32.0))) : 1;
+    plan->n_qgroups = n_pg;
+    plan->wprt_log = 0;
+    plan->keys_per_split = plan->blk_keys_per_split = 0;  // the kernel cuts the ranges itself
+    plan->n_cut = s > 1 ? n_rest : 0;
+    plan->n_full = n_wg - plan->n_cut;
+    plan->n_splits = plan->n_parts = s;
+    return;
+  }
   int rt_pow2 = 1, wprt_log = 3;
   while (rt_pow2 < n_rt) { rt_pow2 <<= 1; --wprt_log; }
-  int n_splits = n_cu / (n_kv_heads * n_qg);
+  int n_splits = n_cu / n_kv_heads;
   n_splits = max(1, min(n_splits, ATT_MAX_SPLITS));
   // every split takes a share of the cache rows and a share of the block's keys
   int64_t kps = (cache_len + n_splits - 1) / n_splits;
@@ -758,13 +1055,13 @@ void attend_plan(int m_rows, int64_t cache_len, int s_t, int n_kv_heads, int n_c
   bps = max(32, (bps + 31) / 32 * 32);
   const int need_c = (int)((cache_len + kps - 1) / kps), need_b = (s_t + bps - 1) / bps;
   n_splits = max(need_c, need_b);  // 0: no key at all
-  plan->n_qgroups = n_qg;
+  plan->n_qgroups = 1;
   plan->wprt_log = wprt_log;
   plan->n_splits = n_splits;
   plan->keys_per_split = (int)kps;
   plan->blk_keys_per_split = bps;
   plan->n_parts = n_splits;
-  plan->direct = n_splits == 1 && wprt_log == 0;
+  plan->n_full = plan->n_cut = 0;
 }
 
 void attend_lse_plan(int m_rows, int64_t cache_len, int n_kv_heads, int n_cu, AttendPlan* plan) {
@@ -783,12 +1080,17 @@ void attend_lse_plan(int m_rows, int64_t cache_len, int n_kv_heads, int n_cu, At
   plan->keys_per_split = (int)kps;
   plan->blk_keys_per_split = 32;
   plan->n_parts = n_splits;
-  plan->direct = plan->decode = 0;
+  plan->n_full = plan->n_cut = plan->decode = 0;
+}
+
+size_t attend_part_rows(const AttendPlan& plan, int m_rows, int n_kv_heads) {
+  if (plan.decode) return (size_t)n_kv_heads * plan.n_parts * decode_rows(m_rows);
+  if (plan.n_full + plan.n_cut) return (size_t)plan.n_cut * plan.n_parts * ATT_ROWS;  // attend_rows_kernel
+  return (size_t)n_kv_heads * plan.n_parts * m_rows;
 }
 
 size_t attend_workspace_bytes(const AttendPlan& plan, int m_rows, int n_kv_heads, int head_dim) {
-  if (plan.direct) return 256;  // the kernel writes the result itself
-  const size_t rows = (size_t)n_kv_heads * plan.n_parts * (plan.decode ? decode_rows(m_rows) : m_rows);
+  const size_t rows = attend_part_rows(plan, m_rows, n_kv_heads);
   return ((rows * head_dim * 4 + 255) & ~(size_t)255) + rows * 8 + 256;
 }
 
@@ -805,22 +1107,24 @@ static hipError_t launch_attend_kc(const AttendParams& p, hipStream_t st) {
 
 template <int DT, int D>
 static hipError_t launch_attend_t(const AttendParams& p, hipStream_t st) {
-  if (p.n_splits > 0) {
-    hipError_t e;
-    if (p.wprt_log == 0) {
-      constexpr int ES = DT == DT_BF16 ? 2 : 4;
-      constexpr int KC = rows_chunk_keys<DT>();
-      constexpr size_t v_stage = DT == DT_BF16 ? (size_t)KC * (D * ES / 16 + 2) : (size_t)D * (KC / (16 / ES) + 1);
-      constexpr size_t lds = (size_t)2 * ((size_t)KC * (D * ES / 16 + 1) + v_stage) * 16 + 16;  // two stages and the redo flag
-      static_assert(lds <= 160 * 1024, "two attention chunks do not fit the LDS");
-      hipLaunchKernelGGL((attend_rows_kernel<DT, D>), dim3(p.n_splits * p.n_qgroups * p.n_kv_heads), dim3(ATT_THREADS), lds, st, p);
-      e = hipGetLastError();
-    } else {
-      e = launch_attend_kc<DT, D, att_chunk_keys<DT>()>(p, st);
-    }
-    if (e != hipSuccess || p.direct) return e;
+  if (p.n_full + p.n_cut) {
+    constexpr int ES = DT == DT_BF16 ? 2 : 4;
+    constexpr int KC = rows_chunk_keys<DT>();
+    constexpr size_t v_stage = DT == DT_BF16 ? (size_t)KC * (D * ES / 16) : (size_t)D * (KC / (16 / ES) + 1);
+    constexpr size_t lds = (size_t)2 * ((size_t)KC * (D * ES / 16) + v_stage) * 16 + 16;  // two stages and the redo flag
+    static_assert(lds <= 160 * 1024, "two attention chunks do not fit the LDS");
+    hipLaunchKernelGGL((attend_rows_kernel<DT, D>), dim3(p.n_full + p.n_cut * p.n_splits), dim3(ATT_THREADS), lds, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !p.n_cut) return e;
+  } else if (p.n_splits > 0) {
+    const hipError_t e = launch_attend_kc<DT, D, att_chunk_keys<DT>()>(p, st);
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((attend_combine_kernel<D>), dim3(p.n_kv_heads * p.m_rows), dim3((D / 4) * COMB_SLICES), 0, st, p);
+  const int n_rows = p.n_cut ? p.n_cut * ATT_ROWS : p.n_kv_heads * p.m_rows;
+  const dim3 blk((D / 4) * COMB_SLICES);
+  if (p.n_parts <= 3) hipLaunchKernelGGL((attend_combine_kernel<D, 2>), dim3((n_rows + 3) / 4), blk, 0, st, p);
+  else if (p.n_parts <= 7) hipLaunchKernelGGL((attend_combine_kernel<D, 4>), dim3((n_rows + 1) / 2), blk, 0, st, p);
+  else hipLaunchKernelGGL((attend_combine_kernel<D, 8>), dim3(n_rows), blk, 0, st, p);
   return hipGetLastError();
 }
 

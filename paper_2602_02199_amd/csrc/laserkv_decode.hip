@@ -420,7 +420,7 @@ void decode_plan(int64_t cache_len, int n_kv_heads, int n_cu, AttendPlan* plan) 
   plan->keys_per_split = (int)kps;
   plan->blk_keys_per_split = 32;
   plan->n_parts = n_splits;
-  plan->direct = 0;
+  plan->n_full = plan->n_cut = 0;
   plan->decode = 1;
 }
 

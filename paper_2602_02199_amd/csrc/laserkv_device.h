@@ -80,6 +80,48 @@ __device__ __forceinline__ uint4 buf_ld16(__amdgpu_buffer_rsrc_t r, uint32_t byt
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// Asynchronous 16-byte loads straight into LDS: no registers hold the data and no LDS write instructions are issued.
+// A wave's 64 chunks land at LDS bytes lds .. lds + 1023 in lane order (lds is wave-uniform; so rows cannot be padded,
+// and a layout free of bank conflicts comes from permuting which chunk of its row a lane fetches).  The compiler does
+// not track these loads: async_wait() before the barrier that publishes the data.
+typedef int srd_words __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ srd_words make_srd_words(const void* base, uint32_t bytes) {
+  const uint64_t b = (uint64_t)base;
+  const srd_words r = {__builtin_amdgcn_readfirstlane((int)b), __builtin_amdgcn_readfirstlane((int)(b >> 32) & 0xffff),
+                       __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+  return r;
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+__device__ __forceinline__ uint4 lds_ld16(uint32_t at) {
+  typedef uint32_t u32x4_lds __attribute__((ext_vector_type(4)));
+  const u32x4_lds v = *(__attribute__((address_space(3))) const u32x4_lds*)(uintptr_t)at;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void async_ld16(srd_words srd, uint32_t lane_offset, uint32_t uniform_offset, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_offset), "s"(srd), "s"(__builtin_amdgcn_readfirstlane((int)uniform_offset))
+               : "memory");  // the kernels here use m0 for nothing else
+}
+// Makes the compiler complete its own loads of v here (registers loaded before a loop would otherwise be waited for at
+// their first use inside it, and with them every asynchronous load in flight there).
+__device__ __forceinline__ void landed(uint4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+// An opaque copy: what is computed from it inside a loop is not kept in registers across the loop.
+template <typename T>
+__device__ __forceinline__ T fresh(T x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// The same for values that change with the loop: only derived addresses (an xor per operand chunk) are kept from
+// becoming induction variables, the scheduler stays free to move the instructions.
+__device__ __forceinline__ uint32_t opaque(uint32_t x) {
+  asm("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ void async_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Streaming stores: data that no later instruction of the same kernel reads goes out without waiting
 // for the end-of-kernel write-back of the L2.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

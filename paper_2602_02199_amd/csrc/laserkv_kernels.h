@@ -224,30 +224,31 @@ struct AttendParams {
   int kb_stride_row, vb_stride_row;        // bytes
   int s_t;
   int diag;            // block key i is visible to query j iff i <= diag + j (>= s_t: no mask); |diag| <= 2^30
-  int keys_per_split;  // cache rows per split, multiple of 32
-  int blk_keys_per_split;  // block keys per split, multiple of 32
+  int keys_per_split;  // cache rows per split, multiple of 32 (attend_rows_kernel cuts its ranges itself)
+  int blk_keys_per_split;  // block keys per split, multiple of 32 (attend_kernel)
   int n_splits;        // every split takes its share of both segments; 0: no key at all
-  int direct;          // one split and a wave per row tile: attend_kernel writes out / out_lse itself
+  int n_full, n_cut;   // attend_rows_kernel: workgroups over all keys, and row groups cut into n_splits key ranges (both 0: attend_kernel)
   int wprt_log;        // log2 of the waves that share a 32-row tile (over different key tiles)
   int n_parts;         // partials per row: one per key split
-  int n_qgroups;       // ceil(M / 256)
+  int n_qgroups;       // workgroups over the rows of a KV head and split
   int n_kv_heads;
   float scale2;        // log2(e) / sqrt(d)
-  float* part_o;       // [H_kv, n_parts, M, d] unnormalised partial outputs
-  float2* part_ml;     // [H_kv, n_parts, M] (reference, sum) in the exp2 domain
+  float* part_o;       // [H_kv, n_parts, M, d] unnormalised partial outputs (attend_rows_kernel: [n_cut, n_parts, 256, d])
+  float2* part_ml;     // the same rows: (reference, sum) in the exp2 domain
   uint32_t* counters;  // attend_decode_kernel: [H_kv] finished key splits, zero between launches
   float* out;          // [H_kv * M, d]
   float* out_lse;      // [H_kv * M] natural log
 };
 struct AttendPlan {
-  int n_qgroups, wprt_log, n_splits, keys_per_split, blk_keys_per_split, n_parts, direct, decode;
+  int n_qgroups, wprt_log, n_splits, keys_per_split, blk_keys_per_split, n_parts, n_full, n_cut, decode;
 };
 // few rows (decoding): one launch on the vector unit
 bool decode_supports(int m_rows, int64_t cache_len, int s_t);
 int decode_rows(int m_rows);  // rows per head and split in the workspace
 void decode_plan(int64_t cache_len, int n_kv_heads, int n_cu, AttendPlan* plan);
 hipError_t launch_decode(int dtype, int head_dim, const AttendParams& p, hipStream_t st);
-void attend_plan(int m_rows, int64_t cache_len, int s_t, int n_kv_heads, int n_cu, AttendPlan* plan);
+void attend_plan(int dtype, int head_dim, int m_rows, int n_q, int64_t cache_len, int s_t, int n_kv_heads, int n_cu, AttendPlan* plan);
+size_t attend_part_rows(const AttendPlan& plan, int m_rows, int n_kv_heads);  // rows of partials in the workspace
 size_t attend_workspace_bytes(const AttendPlan& plan, int m_rows, int n_kv_heads, int head_dim);  // part_o, then part_ml
 hipError_t launch_attend(int dtype, int head_dim, const AttendParams& p, hipStream_t st);
 // the normaliser alone (out unused): 512 rows per workgroup, keys only
