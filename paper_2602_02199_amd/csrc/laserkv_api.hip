@@ -328,19 +328,15 @@ void plan_count(const laserkv_ctx* ctx, int w, int n_groups, int wg_target, lkv:
   if (tg > c.lsh_tables) tg = c.lsh_tables;
   cp.tables_per_group = tg;
   const int n_tg = (c.lsh_tables + tg - 1) / tg;
-  // Several table groups per workgroup (taken one after the other) save global atomics; as many as
-  // still leave about one workgroup per compute unit with key ranges of at least 1024 keys.
+  // A workgroup pays per table, hardly per key: ranges as long as they come, and as many table groups (one after the
+  // other) as still leave a workgroup per compute unit; shorter ranges only where the tables do not give as many.
+  int n_kr = (s_t + lkv::count_max_keys_per_range() - 1) / lkv::count_max_keys_per_range();
   int gpw = 1;
-  while (gpw * 2 <= n_tg && (int64_t)n_groups * ((n_tg + 2 * gpw - 1) / (2 * gpw)) * ((s_t + 1023) / 1024) >= wg_target) gpw *= 2;
-  const int n_wg_t = (n_tg + gpw - 1) / gpw;
-  int n_kr = wg_target / (n_groups * n_wg_t);
-  if (n_kr < 1) n_kr = 1;
-  int kpr = ((s_t + n_kr - 1) / n_kr + 1023) / 1024 * 1024;
-  if (kpr > lkv::count_max_keys_per_range()) kpr = lkv::count_max_keys_per_range();
-  // the workgroup stages its tables' codes of all window queries and of its keys in LDS beside the histogram:
-  // fewer table groups per workgroup, then shorter key ranges, until that fits
-  while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows, kpr) > 156 * 1024 && gpw > 1) gpw /= 2;
-  while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows, kpr) > 156 * 1024 && kpr > 64) kpr /= 2;
+  while (gpw * 2 <= n_tg && (int64_t)n_groups * ((n_tg + 2 * gpw - 1) / (2 * gpw)) * n_kr >= wg_target) gpw *= 2;
+  n_kr = std::max(n_kr, std::min(wg_target / (n_groups * ((n_tg + gpw - 1) / gpw)), (s_t + 1023) / 1024));
+  const int kpr = ((s_t + n_kr - 1) / n_kr + 1023) / 1024 * 1024;
+  // the codes of the window queries lie in LDS beside the histogram
+  while (lkv::count_lds_bytes(c.lsh_bits, tg, gpw, m_rows) > 156 * 1024 && gpw > 1) gpw /= 2;
   cp.groups_per_wg = gpw;
   cp.keys_per_range = kpr;
 }

@@ -271,6 +271,6 @@ int sweep_rows_per_group();  // window rows one sweep workgroup covers
 int score_max_range();  // most keys one score workgroup takes (its LDS holds the whole range)
 int count_max_keys_per_range();
 // LDS of a count workgroup: the histogram of one table group plus the staged query and key codes of all its tables
-size_t count_lds_bytes(int n_bits, int tables_per_group, int groups_per_wg, int n_query_rows, int keys_per_range);
+size_t count_lds_bytes(int n_bits, int tables_per_group, int groups_per_wg, int n_query_rows);
 
 }  // namespace lkv

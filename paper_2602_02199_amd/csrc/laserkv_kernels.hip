@@ -691,35 +691,49 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
 
 // ---------------------------------------------------------------------------------------------
 // Collision counts as a kernel of their own (codes too wide for resident histograms).  Workgroup =
-// (key range, set of table groups, KV head).  All codes the workgroup needs -- its tables' codes of
-// the G*W window queries and of the range's keys -- are fetched into LDS once, so that only one
-// round trip to memory lies on the kernel's critical path.  Then, one table group after the other
-// through the same LDS histogram (two 16-bit bins per word): the query codes are histogrammed, every
-// key looks its own codes up, and the bins that were touched are cleared again.  A key's count over
-// all the workgroup's tables meets in a register and costs one global atomic.
+// (key range, set of table groups, KV head).  The codes of the G*W window queries are staged in LDS, table-major; then,
+// one table group after the other through the same LDS histogram (two 16-bit bins per word), the query codes are
+// histogrammed, every key looks its own codes up, and the bins that were touched are cleared again.  A thread owns up to
+// eight keys and keeps their codes in registers: eight tables at a time, the next eight in flight, where the workgroup
+// takes whole aligned groups of eight tables (VEC), else one.  A key's count over all the workgroup's tables meets in a
+// register and costs one global atomic.
+// What a table costs is three barriers, 512 atomics and the lookups of a range: long ranges, few tables.  (Key codes
+// staged in LDS were read with a stride of a whole key, sixteen lanes to a bank, and left room for 1024 keys only: 145 us
+// for a layer of 131 072 keys, 8 heads, 32 tables of 16 bits, now 53.)
 // ---------------------------------------------------------------------------------------------
 constexpr int COUNT_THREADS = 1024;
 constexpr int COUNT_KEYS_PER_THREAD = 8;  // keys_per_range <= COUNT_THREADS * COUNT_KEYS_PER_THREAD
+template <bool VEC>
 __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
-  extern __shared__ uint32_t bins[];  // [tables_per_group << n_bits] / 2 words, then the staged codes
+  extern __shared__ uint32_t bins[];  // [tables_per_group << n_bits] / 2 words, then the query codes
+  constexpr int KPT = COUNT_KEYS_PER_THREAD;
+  constexpr int STEP = VEC ? 8 : 1;   // tables whose key codes are fetched at a time
   const int tid = threadIdx.x;
   const int kr = blockIdx.x, h = blockIdx.z;
   const int nq = p.group * p.w;
   const int i0 = kr * p.keys_per_range;
   const int s_t = h >= p.last_group ? p.last_s_t : p.s_t;
   if (i0 >= s_t) return;  // a short last block
-  const int i1 = min(i0 + p.keys_per_range, s_t);
-  const int n_keys = i1 - i0;
+  const int n_keys = min(i0 + p.keys_per_range, s_t) - i0;
   const int t_first = blockIdx.y * p.groups_per_wg * p.tables_per_group;            // the workgroup's tables
   const int ntw = min(p.groups_per_wg * p.tables_per_group, p.n_tables - t_first);  // > 0 by the grid's construction
   const int n_bin_words = (p.tables_per_group << p.n_bits) >> 1;
   uint16_t* sQ = reinterpret_cast<uint16_t*>(bins + ((n_bin_words + 3) & ~3));  // [ntw][nq]
-  uint16_t* sKc = sQ + ((ntw * nq + 7) & ~7);                                   // [n_keys][ntw]
-  // 1. everything from memory, issued back to back: query codes (transposed to table-major), key codes
   const uint16_t* gq = p.sig_q + (size_t)h * nq * p.n_tables + t_first;
   const uint16_t* gk = p.sig_k + ((size_t)h * p.key_stride + i0) * p.n_tables + t_first;
-  const bool vec8 = (ntw & 7) == 0 && (p.n_tables & 7) == 0 && (t_first & 7) == 0;  // rows of whole aligned 16-byte groups
-  if (vec8) {
+
+  uint4 next[KPT];  // VEC: the codes of eight tables; else .x: of one
+  auto fetch = [&](int t) {
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) {
+      if (k * COUNT_THREADS >= n_keys) break;  // workgroup-uniform
+      const uint16_t* at = gk + (size_t)min(tid + k * COUNT_THREADS, n_keys - 1) * p.n_tables + t;
+      if (VEC) next[k] = ld16(at);
+      else next[k].x = *at;
+    }
+  };
+  fetch(0);
+  if (VEC) {
     const int g8 = ntw >> 3;
     for (int e = tid; e < nq * g8; e += COUNT_THREADS) {
       const int qrow = e / g8, gi = e - qrow * g8;
@@ -728,18 +742,10 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) sQ[(gi * 8 + u) * nq + qrow] = (uint16_t)(wv[u >> 1] >> ((u & 1) * 16));
     }
-    for (int e = tid; e < n_keys * g8; e += COUNT_THREADS) {
-      const int key = e / g8, gi = e - key * g8;
-      *reinterpret_cast<uint4*>(sKc + (size_t)key * ntw + gi * 8) = ld16(gk + (size_t)key * p.n_tables + gi * 8);
-    }
   } else {
     for (int e = tid; e < nq * ntw; e += COUNT_THREADS) {
       const int qrow = e / ntw, tl = e - qrow * ntw;
       sQ[tl * nq + qrow] = gq[(size_t)qrow * p.n_tables + tl];
-    }
-    for (int e = tid; e < n_keys * ntw; e += COUNT_THREADS) {
-      const int key = e / ntw, tl = e - key * ntw;
-      sKc[(size_t)key * ntw + tl] = gk[(size_t)key * p.n_tables + tl];
     }
   }
   if ((n_bin_words & 3) == 0) {
@@ -748,43 +754,49 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
   } else {
     for (int i = tid; i < n_bin_words; i += COUNT_THREADS) bins[i] = 0u;
   }
-  int sum[COUNT_KEYS_PER_THREAD];
-#pragma unroll
-  for (int k = 0; k < COUNT_KEYS_PER_THREAD; ++k) sum[k] = 0;
-  __syncthreads();
-  // 2. the table groups, one after the other, in LDS only
-  for (int g0 = 0; g0 < ntw; g0 += p.tables_per_group) {
+  // the query codes of the table group from g0 on: into the bins, or the bins they touched back to zero
+  auto each_query = [&](int g0, bool add) {
     const int tga = min(p.tables_per_group, ntw - g0);
-    for (int e = tid; e < nq * tga; e += COUNT_THREADS) {
-      const int tl = e / nq, qrow = e - tl * nq;
-      const uint32_t idx = ((uint32_t)tl << p.n_bits) | sQ[(g0 + tl) * nq + qrow];
-      atomicAdd(&bins[idx >> 1], 1u << ((idx & 1u) * 16));
-    }
-    __syncthreads();
+    for (int tl = 0; tl < tga; ++tl)
+      for (int q = tid; q < nq; q += COUNT_THREADS) {
+        const uint32_t idx = ((uint32_t)tl << p.n_bits) | sQ[(g0 + tl) * nq + q];
+        if (add) atomicAdd(&bins[idx >> 1], 1u << ((idx & 1u) * 16));
+        else bins[idx >> 1] = 0u;
+      }
+  };
+  int sum[KPT];
 #pragma unroll
-    for (int k = 0; k < COUNT_KEYS_PER_THREAD; ++k) {
-      const int key = tid + k * COUNT_THREADS;
-      if (key < n_keys) {
-        const uint16_t* kc = sKc + (size_t)key * ntw + g0;
-        for (int tl = 0; tl < tga; ++tl) {
-          const uint32_t idx = ((uint32_t)tl << p.n_bits) | kc[tl];
-          sum[k] += (bins[idx >> 1] >> ((idx & 1u) * 16)) & 0xffffu;
+  for (int k = 0; k < KPT; ++k) sum[k] = 0;
+  __syncthreads();
+  int g0 = -p.tables_per_group;  // first table of the group in the bins
+  for (int tb = 0; tb < ntw; tb += STEP) {
+    uint4 codes[KPT];
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) codes[k] = next[k];
+    if (tb + STEP < ntw) fetch(tb + STEP);
+#pragma unroll
+    for (int u = 0; u < STEP; ++u) {
+      if (tb + u >= g0 + p.tables_per_group) {  // workgroup-uniform: the next group's turn
+        if (g0 >= 0) {
+          lds_barrier();  // lookups done before the bins are cleared
+          each_query(g0, false);
+          lds_barrier();
         }
+        g0 += p.tables_per_group;
+        each_query(g0, true);
+        lds_barrier();
       }
-    }
-    if (g0 + p.tables_per_group < ntw) {  // block-uniform: another group follows
-      __syncthreads();                    // lookups done before the bins are cleared
-      // only the bins of this group's query codes are non-zero
-      for (int e = tid; e < nq * tga; e += COUNT_THREADS) {
-        const int tl = e / nq, qrow = e - tl * nq;
-        const uint32_t idx = ((uint32_t)tl << p.n_bits) | sQ[(g0 + tl) * nq + qrow];
-        bins[idx >> 1] = 0u;
+      const uint32_t base = (uint32_t)(tb + u - g0) << p.n_bits;
+#pragma unroll
+      for (int k = 0; k < KPT; ++k) {
+        if (k * COUNT_THREADS >= n_keys) break;  // workgroup-uniform
+        const uint32_t w = (u >> 1) == 0 ? codes[k].x : (u >> 1) == 1 ? codes[k].y : (u >> 1) == 2 ? codes[k].z : codes[k].w;
+        sum[k] += reinterpret_cast<const uint16_t*>(bins)[base + ((u & 1) ? w >> 16 : w & 0xffffu)];
       }
-      __syncthreads();
     }
   }
 #pragma unroll
-  for (int k = 0; k < COUNT_KEYS_PER_THREAD; ++k) {
+  for (int k = 0; k < KPT; ++k) {
     const int key = tid + k * COUNT_THREADS;
     if (key < n_keys) atomicAdd(&p.cnt[(size_t)h * p.key_stride + i0 + key], sum[k]);
   }
@@ -1246,8 +1258,9 @@ static hipError_t pass_attrs() {
 }
 
 hipError_t init_kernel_attributes() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&count_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&count_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&count_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess) e = pass_attrs<DT_BF16, 128>();
   if (e == hipSuccess) e = pass_attrs<DT_BF16, 64>();
   if (e == hipSuccess) e = pass_attrs<DT_F32, 128>();
@@ -1258,10 +1271,10 @@ hipError_t init_kernel_attributes() {
 int score_max_range() { return SCORE_MAX_RANGE; }
 int sweep_rows_per_group() { return PASS_ROWS; }
 
-size_t count_lds_bytes(int n_bits, int tables_per_group, int groups_per_wg, int n_query_rows, int keys_per_range) {
+size_t count_lds_bytes(int n_bits, int tables_per_group, int groups_per_wg, int n_query_rows) {
   const size_t bin_words = (((size_t)tables_per_group << n_bits) / 2 + 3) & ~(size_t)3;
   const size_t ntw = (size_t)groups_per_wg * tables_per_group;
-  return bin_words * 4 + ((ntw * n_query_rows + 7) & ~(size_t)7) * 2 + ntw * keys_per_range * 2 + 16;
+  return bin_words * 4 + ((ntw * n_query_rows + 7) & ~(size_t)7) * 2 + 16;
 }
 
 hipError_t launch_count(const CountParams& p, int n_groups, hipStream_t st) {
@@ -1269,10 +1282,13 @@ hipError_t launch_count(const CountParams& p, int n_groups, hipStream_t st) {
   const int n_wg_t = (n_tg + p.groups_per_wg - 1) / p.groups_per_wg;
   const int n_kr = (p.s_t + p.keys_per_range - 1) / p.keys_per_range;
   if (p.keys_per_range > COUNT_THREADS * COUNT_KEYS_PER_THREAD) return hipErrorInvalidValue;
-  const size_t lds = count_lds_bytes(p.n_bits, p.tables_per_group, p.groups_per_wg, p.group * p.w, p.keys_per_range);
+  const size_t lds = count_lds_bytes(p.n_bits, p.tables_per_group, p.groups_per_wg, p.group * p.w);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   dim3 grid(n_kr, n_wg_t, n_groups);
-  hipLaunchKernelGGL(count_kernel, grid, dim3(COUNT_THREADS), lds, st, p);
+  // every workgroup's tables are whole aligned groups of eight
+  const bool vec = (p.groups_per_wg * p.tables_per_group) % 8 == 0 && p.n_tables % 8 == 0;
+  if (vec) hipLaunchKernelGGL(count_kernel<true>, grid, dim3(COUNT_THREADS), lds, st, p);
+  else hipLaunchKernelGGL(count_kernel<false>, grid, dim3(COUNT_THREADS), lds, st, p);
   return hipGetLastError();
 }
 

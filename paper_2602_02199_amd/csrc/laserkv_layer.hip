@@ -383,16 +383,6 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
         for (int s = 0; s < TPC * NP; ++s) {
           if (s + 1 < TPC * NP) logits(stage, (s + 1) / NP, (s + 1) % NP * TP, acc[(s + 1) & 1]);
           col += pooled(acc[s & 1], s % NP * TP);
-          if (DT == DT_BF16) {
-            // a matrix instruction, then what the vector unit can do beside it
-#pragma unroll
-            for (int q = 0; q < NCH * TP; ++q) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // MFMA
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // LDS read
-              __builtin_amdgcn_sched_group_barrier(0x002, 32 / NCH, 0);      // VALU
-              __builtin_amdgcn_sched_group_barrier(0x400, 16 / NCH, 0);      // exponentials
-            }
-          }
           if (s % NP == NP - 1) {
             put(s / NP, col);
             col = 0.0f;
@@ -421,8 +411,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
 
   // the hashing waves
   const uint32_t code_mask = (1u << p.n_bits) - 1u;
-  const uint32_t cpw = 1u << p.cell_log, cb_log = 5 - p.cell_log, cbits = 1u << cb_log;  // cells per word, their width
-  const uint32_t cell_max = (1u << cbits) - 1u;
+  const uint32_t cell_max = p.cell_log == 2 ? 255u : 15u;  // full cells of 8 and 4 bits (cell_log 2, 3; those of 16 bits hold every count)
   // sums over the score waves and collision counts of the chunk whose first key is kc0: two lanes per key
   auto finish = [&](int buf, int kc0) {
     const int key = (tid - NLD) >> 1, sub = tid & 1;
@@ -441,19 +430,34 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
         const int bitpos = t * p.n_bits, w0 = bitpos >> 5;
         return __builtin_amdgcn_alignbit(bits[w0 + 1], bits[w0], bitpos & 31) & code_mask;
       };
-      auto cell_of = [&](int t, uint32_t code) {
-        return __builtin_amdgcn_ubfe(sCells[t * p.cell_words + (code >> p.cell_log)], (code & (cpw - 1)) << cb_log, cbits);
+      auto nibble_of = [&](int t, uint32_t code) {
+        return __builtin_amdgcn_ubfe(sCells[t * p.cell_words + (code >> 3)], (code & 7u) << 2, 4u);
       };
+      // cells are read at their own width: vector instructions hardly overlap with the score waves' matrix instructions
+      if (p.cell_log == 1) {
 #pragma unroll 8
-      for (int t = sub; t < p.n_tables; t += 2) {
-        const uint32_t c = cell_of(t, code_of(t));
-        n += c;
-        fullest = max(fullest, c);
+        for (int t = sub; t < p.n_tables; t += 2)
+          n += reinterpret_cast<const uint16_t*>(sCells + t * p.cell_words)[code_of(t)];
+      } else if (p.cell_log == 2) {
+#pragma unroll 8
+        for (int t = sub; t < p.n_tables; t += 2) {
+          const uint32_t c = reinterpret_cast<const uint8_t*>(sCells + t * p.cell_words)[code_of(t)];
+          n += c;
+          fullest = max(fullest, c);
+        }
+      } else {
+#pragma unroll 8
+        for (int t = sub; t < p.n_tables; t += 2) {
+          const uint32_t c = nibble_of(t, code_of(t));
+          n += c;
+          fullest = max(fullest, c);
+        }
       }
-      if (cbits < 16 && __any(fullest == cell_max)) {  // some key met a heavy bin: its count is in the table's list
+      if (p.cell_log > 1 && __any(fullest == cell_max)) {  // some key met a heavy bin: its count is in the table's list
         for (int t = sub; t < p.n_tables; t += 2) {
           const uint32_t code = code_of(t);
-          if (cell_of(t, code) != cell_max) continue;
+          const uint32_t c = p.cell_log == 2 ? reinterpret_cast<const uint8_t*>(sCells + t * p.cell_words)[code] : nibble_of(t, code);
+          if (c != cell_max) continue;
           const uint32_t* list = p.heavy + ((size_t)gr.g * p.n_tables + t) * LY_HEAVY;
           const int len = (int)list[0];
           for (int i = 1; i <= len; ++i)
