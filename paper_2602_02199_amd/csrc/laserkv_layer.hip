@@ -383,6 +383,17 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
         for (int s = 0; s < TPC * NP; ++s) {
           if (s + 1 < TPC * NP) logits(stage, (s + 1) / NP, (s + 1) % NP * TP, acc[(s + 1) & 1]);
           col += pooled(acc[s & 1], s % NP * TP);
+          if (DT == DT_BF16 && RT <= 2) {
+            // a matrix instruction, then what the vector unit can do beside it (two row tiles: 3.5 % of a layer; with four
+            // the compiler's own order is the faster one)
+#pragma unroll
+            for (int q = 0; q < NCH * TP; ++q) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // MFMA
+              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // LDS read
+              __builtin_amdgcn_sched_group_barrier(0x002, 32 / NCH, 0);      // VALU
+              __builtin_amdgcn_sched_group_barrier(0x400, 16 / NCH, 0);      // exponentials
+            }
+          }
           if (s % NP == NP - 1) {
             put(s / NP, col);
             col = 0.0f;
