@@ -195,7 +195,7 @@ struct LayerParams {
   uint16_t* sig_q;       // [groups, M, L] when cells is null
 };
 struct LayerPlan {
-  int rt, use_cells;
+  int rt, use_cells, code_split;  // code_split: workgroups a group's tables are shared out to in the code kernel
   size_t codes_lds, stats_lds, score_lds;
   size_t off_part, off_score, off_cnt, off_cells, off_heavy, off_sig_k, off_sig_q, bytes;  // workspace
 };

@@ -50,7 +50,7 @@ __device__ __forceinline__ const char* layer_row(const LayerParams& p, const Lay
 }
 
 // ---------------------------------------------------------------------------------------------
-// Codes of a group's window rows.  Workgroup = group; a wave holds 32 rows as MFMA operands and the tables
+// Codes of a group's window rows.  Workgroup = (group, share of its tables); a wave holds 32 rows as MFMA operands and the tables
 // pass by in sets whose hyperplanes and histograms fit the LDS.  A set's codes are counted in LDS histograms (16-bit
 // bins, 32 bins per 17 words against bank conflicts), which leave as cells of 16, 8 or 4 bits per bin, the widest with
 // which a group's tables fit 64 KiB of the score kernel's LDS (4 bits at K = 12, L = 32).  A narrow cell that is full
@@ -84,7 +84,8 @@ __global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParam
       pre[u] = ld16(p.planes + (size_t)(t0 * p.n_bits + min(row, np - 1)) * (D * ES) + tid % CH * 16);
     }
   };
-  fetch(0);
+  const int t_first = blockIdx.y * p.code_tables, t_step = gridDim.y * p.code_tables;  // this workgroup's sets of tables
+  fetch(t_first);
   uint4 b[NCH];  // this wave's 32 window rows
   const int row = wave * 32 + rl;
   const bool active = wave * 32 < p.m_rows;
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParam
   const uint32_t code_mask = (1u << p.n_bits) - 1u;
   const int cpw = 1 << p.cell_log, cbits = 32 >> p.cell_log, cw_log = max(p.n_bits - p.cell_log, 0);  // cell_words = 1 << cw_log
   const uint32_t cmax = cbits == 16 ? 0xffffu : (1u << cbits) - 1u;
-  for (int t0 = 0; t0 < p.n_tables; t0 += p.code_tables) {
+  for (int t0 = t_first; t0 < p.n_tables; t0 += t_step) {
     const int n_tab = min(p.code_tables, p.n_tables - t0);
     const int np = n_tab * p.n_bits, n_tile = (np + 31) >> 5;
     __syncthreads();  // the previous set's histograms have been read
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParam
       if (tid < n_tab) sHeavy[tid] = 0;
     }
     __syncthreads();
-    if (t0 + p.code_tables < p.n_tables) fetch(t0 + p.code_tables);
+    if (t0 + t_step < p.n_tables) fetch(t0 + t_step);
     if (active) {
       uint32_t prev = 0u;
       int tt0 = 0;  // first table of the set whose bits are not complete yet
@@ -587,6 +588,11 @@ void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* pl
   int nt = LY_CODE_PLANES / p->n_bits;
   if (plan->use_cells) nt = min(nt, 1024 / words);
   p->code_tables = max(1, min(nt, p->n_tables));
+  // groups that leave compute units idle share their tables out: smaller sets, one or more workgroups each (a 16k layer of
+  // 64 groups: 10.2 -> 6.4 us)
+  const int share = min(max(1, n_cu / n_groups), p->n_tables);
+  p->code_tables = min(p->code_tables, (p->n_tables + share - 1) / share);
+  plan->code_split = min(share, (p->n_tables + p->code_tables - 1) / p->code_tables);
   p->code_tiles = (p->code_tables * p->n_bits + 31) / 32;
   plan->codes_lds = (size_t)p->code_tiles * 32 * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)(p->code_tables * (words * 17 + 1) + 4) * 4 : 0);
   plan->stats_lds = row_stats_lds(head_dim * es);
@@ -607,7 +613,7 @@ void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* pl
 
 template <int DT, int D>
 static hipError_t launch_codes_t(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
-  hipLaunchKernelGGL((layer_codes_kernel<DT, D>), dim3(p.n_blocks * p.n_kv_heads), dim3(LY_CODE_THREADS), plan.codes_lds, st, p);
+  hipLaunchKernelGGL((layer_codes_kernel<DT, D>), dim3(p.n_blocks * p.n_kv_heads, plan.code_split), dim3(LY_CODE_THREADS), plan.codes_lds, st, p);
   return hipGetLastError();
 }
 template <int DT, int D>
