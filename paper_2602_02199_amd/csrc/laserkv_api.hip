@@ -401,7 +401,7 @@ int select_impl(laserkv_ctx* ctx,
   sp.m_rows = m_rows;
   sp.s_t = s_t;
   sp.t_ctx = t_ctx;
-  sp.w_magic = (uint32_t)(((uint64_t(1) << 32) + (uint64_t)w - 1) / (uint64_t)w);
+  sp.w_magic = lkv::div_magic(w);
   const int n_qg = (m_rows + lkv::sweep_rows_per_group() - 1) / lkv::sweep_rows_per_group();
   sp.n_qgroups = n_qg;
   sp.n_kv_heads = c.n_kv_heads;
@@ -711,7 +711,7 @@ static bool layer_geometry(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_bloc
   if (!lkv::layer_supports(c.dtype, c.head_dim, ctx->group * w)) return false;
   p.group = ctx->group;
   p.w = w;
-  p.w_magic = (uint32_t)(((uint64_t(1) << 32) + (uint64_t)w - 1) / (uint64_t)w);
+  p.w_magic = lkv::div_magic(w);
   p.m_rows = ctx->group * w;
   p.n_kv_heads = c.n_kv_heads;
   p.n_blocks = (int)((n_tok + s_block - 1) / s_block);
@@ -941,7 +941,7 @@ static int attend_impl(laserkv_ctx* ctx, const char* fn, int64_t n_q_max,
   p.q = {(const char*)q, q_stride_head * es, q_stride_tok * es};
   p.group = ctx->group;
   p.n_q = n_q;
-  p.nq_magic = n_q > 1 ? (uint32_t)(((uint64_t(1) << 32) + n_q - 1) / n_q) : 0u;
+  p.nq_magic = lkv::div_magic(n_q);
   p.m_rows = m_rows;
   p.k_cache = (const char*)k_cache;
   p.v_cache = (const char*)v_cache;

@@ -393,8 +393,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   auto tile_end = [&](int t) {
     if (p.s_t == 0) return 0;
     const int m0 = t * 32, m1 = min(m0 + 32, p.m_rows) - 1;
-    const int g0 = div_w(m0, p.nq_magic), g1 = div_w(m1, p.nq_magic);
-    const int j_max = g0 == g1 ? m1 - g1 * p.n_q : p.n_q - 1;
+    int j0, j1;
+    const int g0 = div_rem(m0, p.n_q, p.nq_magic, &j0), g1 = div_rem(m1, p.n_q, p.nq_magic, &j1);
+    const int j_max = g0 == g1 ? j1 : p.n_q - 1;
     return max(0, min(p.s_t, p.diag + j_max + 1));
   };
   const int upper = __builtin_amdgcn_readfirstlane(wave >> 2);  // the pair's wave whose tile sees more keys
@@ -435,7 +436,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   int blk_end_lane;  // block keys [0, blk_end_lane) are visible to this lane's row
   auto load_rows = [&](int t) {
     const int m = min(fresh(t * 32 + rl), p.m_rows - 1);
-    const int g = div_w(m, p.nq_magic), j = m - g * p.n_q;
+    int j;
+    const int g = div_rem(m, p.n_q, p.nq_magic, &j);
     const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + (2 * i + kg) * 16);

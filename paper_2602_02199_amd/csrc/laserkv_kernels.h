@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "laserkv_index.h"
+
 namespace lkv {
 
 // Rows of a [heads, rows, d] tensor with element strides; d contiguous.
@@ -23,7 +25,7 @@ struct PassParams {
                    // first row of query head h*G, and one buffer descriptor covers the group
   int group;       // G
   int w;           // W
-  uint32_t w_magic;  // ceil(2^32 / W) (0 for W == 1): row / W, see div_w
+  uint32_t w_magic;  // div_magic(W): row / W, see div_w
   int m_rows;      // M = G * W
   int s_t;         // S
   int t_ctx;       // T
@@ -210,7 +212,7 @@ hipError_t init_layer_attributes();
 struct AttendParams {
   RowSrc q;            // [H_q, n_q, d]
   int group, n_q;
-  uint32_t nq_magic;   // ceil(2^32 / n_q) (0 for n_q == 1): row / n_q, see div_w
+  uint32_t nq_magic;   // div_magic(n_q): row / n_q, see div_rem
   int m_rows;          // M = G * n_q rows per KV head, row m = g * n_q + j
   const char* k_cache; // [H_kv, cap, d] rows contiguous
   const char* v_cache;

@@ -49,3 +49,19 @@ def test_attend_rows_edges(case):
     again = run_block(lib, q.to(DEV), kc.to(DEV), vc.to(DEV), n, kb.to(DEV), vb.to(DEV), bp, qp)
     assert (again[0] == out).all() and (again[1] == lse).all()
     lib.close()
+
+
+def test_long_queries_of_many_heads_per_group():
+    """32 query heads per KV head, 15000 queries each: row indices beyond the range of the 32-bit multiplier alone."""
+    g, n_q, d, n, s_t = 32, 15000, 64, 40, 64
+    q, kk, vv = make_inputs(g, 1, d, n_q, n + s_t, "bf16", seed=32)
+    kc, vc, kb, vb = kk[:, :n].contiguous(), vv[:, :n].contiguous(), kk[:, n:].contiguous(), vv[:, n:].contiguous()
+    wide = torch.zeros(g, n_q + 2, d, dtype=torch.bfloat16, device=DEV)
+    wide[:, 1:1 + n_q] = q.to(DEV)
+    lib = binding.LaserKV(g, 1, d, "bf16", 8, 8, max_block=n_q, max_window=32, max_ctx_keys=0)
+    bp = 20000
+    qp = bp + s_t - n_q
+    out, lse = run_block(lib, wide[:, 1:1 + n_q], kc.to(DEV), vc.to(DEV), n, kb.to(DEV), vb.to(DEV), bp, qp)
+    for j0, j1 in ((0, 2), (n_q // 2, n_q // 2 + 1), (n_q - s_t - 1, n_q - s_t + 2), (n_q - 3, n_q)):
+        compare_block(out[:, j0:j1], lse[:, j0:j1], q[:, j0:j1], kc, vc, n, kb, vb, bp, qp + j0, True, "bf16", f"rows {j0}..{j1 - 1} of 32 heads")
+    lib.close()
