@@ -184,6 +184,14 @@ def _rows3(t, d):
     return t.data_ptr(), sh, st, n
 
 
+def _rows4(t, d):
+    """(address, block stride, head stride, row stride, blocks, rows) of a [blocks, heads, rows, d] tensor with d contiguous."""
+    sb, sh, st, one = t.stride()
+    nb, _, n, dd = t.shape
+    assert one == 1 and dd == d, "expected [blocks, heads, rows, d] with d contiguous"
+    return t.data_ptr(), sb, sh, st, nb, n
+
+
 def _context3(t, d):
     return (None, 0, 0, 0) if t is None else _rows3(t, d)
 

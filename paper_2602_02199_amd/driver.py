@@ -121,20 +121,31 @@ class LayerCompressor:
     def _layer_call(self, data, nb, row_lse_complete=None):
         """(c_function, argument tuple without the stream) of one laserkv_compress_layer over the first nb blocks and
         the rows it leaves in the cache, or None for shapes it has no kernels for.  row_lse_complete: device tensor
-        of per-block pointers, or None."""
+        of per-block pointers, or None.  The library is told what the tensors hold (a window shorter than the workload's
+        is one) and tensors that a block's own call refuses are refused here."""
         wl, lib = self.wl, self.lib
-        n_tok = min(nb * wl.s_block, data["k"].shape[1])
+        if not torch.is_tensor(data["q_win"]):  # windows as a list: no common stride
+            return None
+        q, qsb, qsh, qst, n_win, w = binding._rows4(data["q_win"], wl.head_dim)
+        k, ksh, kst, l_tot = binding._rows3(data["k"], wl.head_dim)
+        v, vsh, vst, l_v = binding._rows3(data["v"], wl.head_dim)
+        planes = data["planes"]
+        assert planes.is_contiguous()
+        if nb > n_win:
+            raise IndexError(f"{nb} blocks, but window queries of {n_win}")
+        n_tok = min(nb * wl.s_block, l_tot)
+        assert l_v >= n_tok, "fewer values than keys"
         last = n_tok - (nb - 1) * wl.s_block
-        size = lib._lib.laserkv_layer_workspace_bytes(lib._ctx, n_tok, wl.s_block, wl.window, self.parts[1]) if last >= wl.window else -1
+        # a block and its look-back keys go through one buffer descriptor; a block alone may just fit where both do not
+        one_span = (wl.s_block + self.parts[1]) * kst * self.k_cache.element_size() < 1 << 31
+        size = lib._lib.laserkv_layer_workspace_bytes(lib._ctx, n_tok, wl.s_block, w, self.parts[1]) if last >= w and one_span else -1
         if size < 0:
             return None
         if self._layer_ws is None or self._layer_ws.numel() < size:
             self._layer_ws = torch.empty(size, dtype=torch.uint8, device=self.device)
-        q, k, v = data["q_win"], data["k"], data["v"]
         b_last = sum(self.block_budget(last))
         keep = self.keep if b_last == self.keep.shape[1] else None
-        args = (lib._ctx, q.data_ptr(), q.stride(0), q.stride(1), q.stride(2), k.data_ptr(), k.stride(0), k.stride(1),
-                v.data_ptr(), v.stride(0), v.stride(1), data["planes"].data_ptr(), n_tok, wl.s_block, wl.window,
+        args = (lib._ctx, q, qsb, qsh, qst, k, ksh, kst, v, vsh, vst, planes.data_ptr(), n_tok, wl.s_block, w,
                 self.B, wl.n_div, wl.alpha, None if row_lse_complete is None else row_lse_complete.data_ptr(),
                 None if keep is None else keep.data_ptr(), self.k_cache.data_ptr(), self.v_cache.data_ptr(),
                 self.k_cache.stride(0), self.cache_pos.data_ptr(), self.cache_pos.stride(0), self.cap,
@@ -221,6 +232,7 @@ class LayerCompressor:
         d = wl.head_dim
         calls, cache_len, prev_local = _Plan(), 0, 0
         if row_lse_complete is not None:
+            assert all(q.shape[1] == wl.window for q in data["q_win"][:nb]), "statistics are those of the workload's window"
             for lse in row_lse_complete[:nb]:
                 assert lse.is_contiguous() and lse.dtype == torch.float32 and lse.shape == (wl.n_q_heads, wl.window)
         if fused and nb > 1:
@@ -236,6 +248,8 @@ class LayerCompressor:
                     calls.append((lib.laserkv_set_row_lse_complete, (ctx, None), False))
                 self._plan_len = call[2]
                 return calls
+        assert data["planes"].is_contiguous()
+        planes = data["planes"].data_ptr()
         kc_sh, kc_st = self.k_cache.stride(0), self.k_cache.stride(1)
         es = self.k_cache.element_size()
         for t in range(nb):
@@ -244,7 +258,9 @@ class LayerCompressor:
             na, nl, ke, kl = self.block_budget(s_t)
             b_t = na + nl + ke + kl
             assert b_t == self.keep.shape[1], "plans cover equal-sized blocks only"
-            q, k, v = data["q_win"][t], data["k"][:, lo:hi], data["v"][:, lo:hi]
+            q, qsh, qst, w = binding._rows3(data["q_win"][t], d)
+            k, ksh, kst, _ = binding._rows3(data["k"][:, lo:hi], d)
+            v, vsh, vst, _ = binding._rows3(data["v"][:, lo:hi], d)
             t_ctx = prev_local if cache_len else 0
             if row_lse_complete is not None:
                 lse = row_lse_complete[t]
@@ -253,20 +269,19 @@ class LayerCompressor:
             ctx_ptr = vp(self.k_cache.data_ptr() + (cache_len - t_ctx) * kc_st * es) if t_ctx else None
             if fused:
                 calls.append((lib.laserkv_compress_block, (
-                    ctx, vp(q.data_ptr()), q.stride(0), q.stride(1), vp(k.data_ptr()), k.stride(0), k.stride(1),
-                    vp(v.data_ptr()), v.stride(0), v.stride(1),
-                    ctx_ptr, kc_sh if t_ctx else 0, kc_st if t_ctx else 0, vp(data["planes"].data_ptr()),
-                    s_t, wl.window, t_ctx, lo, binding.LKV_WINDOW_AT_BLOCK_END, 1, na, nl, ke, kl,
+                    ctx, q, qsh, qst, k, ksh, kst, v, vsh, vst,
+                    ctx_ptr, kc_sh if t_ctx else 0, kc_st if t_ctx else 0, planes,
+                    s_t, w, t_ctx, lo, binding.LKV_WINDOW_AT_BLOCK_END, 1, na, nl, ke, kl,
                     vp(self.keep.data_ptr()), vp(self.k_cache.data_ptr()), vp(self.v_cache.data_ptr()), kc_sh,
                     vp(self.cache_pos.data_ptr()), self.cache_pos.stride(0), cache_len, self.cap), True))
             else:
                 calls.append((lib.laserkv_select_block, (
-                    ctx, vp(q.data_ptr()), q.stride(0), q.stride(1), vp(k.data_ptr()), k.stride(0), k.stride(1),
-                    ctx_ptr, kc_sh if t_ctx else 0, kc_st if t_ctx else 0, vp(data["planes"].data_ptr()),
-                    s_t, wl.window, t_ctx, lo, binding.LKV_WINDOW_AT_BLOCK_END, 1, na, nl, ke, kl,
+                    ctx, q, qsh, qst, k, ksh, kst,
+                    ctx_ptr, kc_sh if t_ctx else 0, kc_st if t_ctx else 0, planes,
+                    s_t, w, t_ctx, lo, binding.LKV_WINDOW_AT_BLOCK_END, 1, na, nl, ke, kl,
                     vp(self.keep.data_ptr()), None, None, None, None), True))
                 calls.append((lib.laserkv_append, (
-                    ctx, vp(k.data_ptr()), k.stride(0), k.stride(1), vp(v.data_ptr()), v.stride(0), v.stride(1),
+                    ctx, k, ksh, kst, v, vsh, vst,
                     vp(self.keep.data_ptr()), b_t, s_t, lo, vp(self.k_cache.data_ptr()), vp(self.v_cache.data_ptr()),
                     kc_sh, vp(self.cache_pos.data_ptr()), self.cache_pos.stride(0), cache_len, self.cap), True))
             cache_len += b_t

@@ -143,3 +143,19 @@ def test_layer_call_rejects_what_does_not_fit():
         assert fn(*bad, stream) == code, (at, comp.lib._lib.laserkv_last_error(comp.lib._ctx))
     torch.cuda.synchronize()
     assert torch.equal(before, comp.cache_pos)
+
+
+def test_layer_call_with_a_window_shorter_than_the_workloads():
+    """The window is the tensor's: one call, a plan and the block loop keep the same rows."""
+    wl = synth.shrink(synth.WORKLOADS["tiny"], index=47, l_ctx=2048)
+    comp = LayerCompressor(wl, DEV)
+    dev = to_dev(synth.make_layer(wl, 0, comp.parts[0]))
+    dev["q_win"] = dev["q_win"][:, :, 12:]
+    want = loop_positions(wl, dev, comp.B, wl.n_blocks)
+    for call in (lambda: comp.run_layer(dev), lambda: comp.run_plan(comp.plan_layer(dev)),
+                 lambda: comp.run_plan(comp.plan_layer(dev, fused=False))):
+        comp.cache_pos.fill_(-1)
+        n = call()
+        got = comp.cache_pos[:, :n]
+        swapped = sum(len(set(got[h].tolist()) - set(want.cache_pos[h].tolist())) for h in range(wl.n_kv_heads))
+        assert n == want.cache_len and swapped <= 2e-3 * n * wl.n_kv_heads
