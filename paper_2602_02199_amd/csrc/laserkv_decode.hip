@@ -222,8 +222,9 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void attend_decode_kernel(AttendPar
 #pragma unroll
     for (int u = 1; u < U; ++u) mx = fmaxf(mx, s[u]);
     mx *= p.scale2;  // scale2 > 0
-    // the reference is raised only when a logit exceeds it by 2^8: sums stay far from overflow
-    if (__any(mx > ref + 8.0f)) {
+    // the reference follows the maximum: the largest probability is exactly 1, also as the bf16 that weighs V, so a row
+    // that one key dominates gets that key's values unrounded (raised only past 2^8 it was off by up to 2^-9 of them)
+    if (__any(mx > ref)) {
       const float nref = fmaxf(ref, mx), f = fast_exp2(ref - nref);
       sum *= f;
       float fm[M];
