@@ -340,9 +340,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
 //   then on the two waves take alternate 32-key tiles, and their states meet in LDS at the end.  (With
 //   consecutive tiles in a workgroup a launch took as long as the block's last rows: a 16k prefill of 32 heads in blocks
 //   of 2048 rows 169 us a block on average, now 151.)
-//   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  References are
-//   fixed, so that the output accumulators see nothing but matrix instructions (a rescaling in the loop doubles their
-//   registers), and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
+//   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  Over the cache's
+//   rows references are fixed, so that the output accumulators see nothing but matrix instructions, and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
 //   instructions hardly overlap with matrix instructions here).
 //   Chunks alternate between two LDS stages and arrive through async_ld16, the next one while the current one is worked
 //   on, so one barrier per chunk suffices.
@@ -625,11 +624,15 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     }
   };
 
-  // A row's reference is fixed: its maximum over the first tile of keys that it sees, plus HEADROOM (what a row sees is a prefix of
-  // the keys: a row that sees none of a wave's first tile sees none of the others).  Each logit then costs an fma, an
-  // exponential and an add, and the output accumulators nothing but matrix instructions.  Sums that grow past 1e30 (a
-  // logit 160 above the first tile's, in powers of two) make the workgroup repeat the pass with the exact maxima, which a
-  // sweep over the keys finds first.
+  // Over the cache's rows (and in fp32) a row's reference is fixed: its maximum over the first tile of keys that it sees, plus
+  // HEADROOM (what a row sees is a prefix of the keys: a row that sees none of a wave's first tile sees none of the others).
+  // Each logit then costs an fma, an exponential and an add, and the output accumulators nothing but matrix instructions.
+  // Sums that grow past 1e30 (a logit 160 above the first tile's, in powers of two) make the workgroup repeat the pass with
+  // the exact maxima, which a sweep over the keys finds first.
+  // Over the block's own keys in bf16 it follows the maximum: the dominant key's probability is then a power of two and its
+  // bf16 exact, while against a fixed reference its rounding (up to 2^-8) goes into the output whole.  A maximum and a
+  // rescaling of the output per pair of tiles: 16k prefill in blocks of 2048 1358 -> 1378 us, causal blocks without a cache
+  // up to 7 %.
   int* redo = reinterpret_cast<int*>(smem + (size_t)2 * STAGE);  // one word behind the two stages
   if (tid == 0) *redo = 0;  // ordered before the writes after the first pass by the barriers in between
   // position in the split's chunks
@@ -703,87 +706,135 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
       land(0);
       lds_barrier();
     }
-    while (have) {
-      if (nhave) prefetch(nseg, nkc, cur ^ 1);  // in flight while this chunk is worked on; every wave left that stage before the barrier
-      if (!joined && seg && kc0 >= end_lo) {
-        joined = true;
-        if (!upper) {
-          bad = !(l_sum < 1.0e30f);
-          if (present) write_tile(t_lo);
-          load_rows(t_hi);
-          clear();
-          place();
-          has_ref = pass != 0;
-          if (pass) m_ref = ref_join;
+    // a loop for each segment: with one for both, what the second needs costs the first registers
+#pragma unroll
+    for (int SEG = 0; SEG < 2; ++SEG) {
+      constexpr bool BF16 = DT == DT_BF16;
+      const bool follows = SEG == 1 && BF16;  // the reference follows the maximum
+      while (have && seg == SEG) {
+        if (nhave) prefetch(nseg, nkc, cur ^ 1);  // in flight while this chunk is worked on; every wave left that stage before the barrier
+        if (SEG && !joined && kc0 >= end_lo) {
+          joined = true;
+          if (!upper) {
+            bad = !(l_sum < 1.0e30f);
+            if (present) write_tile(t_lo);
+            load_rows(t_hi);
+            clear();
+            place();
+            has_ref = pass != 0;
+            if (pass) m_ref = ref_join;
+          }
         }
-      }
-      const int wave_end = seg ? min(hi1, upper || joined ? end_hi : end_lo) : hi0;
-      int left = present ? min(min(max((wave_end - kc0 + 31) >> 5, 0), TPC) - nt0, joined ? TPC / 2 : TPC) : 0;
-      const int lane_end = seg ? min(hi1, blk_end_lane) : hi0;  // end of the keys of this segment the lane's row sees
-      const int n_vis = lane_end - (kc0 + nt0 * 32);  // keys from the wave's first on that the lane's row sees
-      const bool whole = __all(n_vis >= KC - nt0 * 32);
-      if (left > 0 && !has_ref) {
-        has_ref = true;
-        m_ref = maximum(k_at + cur * (STAGE * 16) + nt0 * K_TILE, n_vis);
-        m_ref += m_ref > NEG_BIG ? HEADROOM : 0.0f;
-      }
-      // a row without a visible key subtracts nothing: its hidden logits give 2^(NEG_BIG * scale2) = 0
-      const float m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
-      auto soft = [&](f32x16& acc) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[r] = fast_exp2(fmaf(acc[r], p.scale2, -m_sub));
-          l_sum += acc[r];
+        const int wave_end = SEG ? min(hi1, upper || joined ? end_hi : end_lo) : hi0;
+        int left = present ? min(min(max((wave_end - kc0 + 31) >> 5, 0), TPC) - nt0, joined ? TPC / 2 : TPC) : 0;
+        const int lane_end = SEG ? min(hi1, blk_end_lane) : hi0;  // end of the keys of this segment the lane's row sees
+        const int n_vis = lane_end - (kc0 + nt0 * 32);  // keys from the wave's first on that the lane's row sees
+        const bool whole = SEG ? __all(n_vis >= KC - nt0 * 32) : n_vis >= KC - nt0 * 32;
+        if (left > 0 && !has_ref && !follows) {
+          has_ref = true;
+          m_ref = maximum(k_at + cur * (STAGE * 16) + nt0 * K_TILE, n_vis);
+          m_ref += m_ref > NEG_BIG ? HEADROOM : 0.0f;
         }
-      };
-      if (DT == DT_BF16) {
-        // two key tiles: the exponentials of one run beside the other's products
+        // a row without a visible key subtracts nothing: its hidden logits give 2^(NEG_BIG * scale2) = 0
+        float m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
+        // Raises the reference to a pair of tiles' maximum, always: a branch around the rescaling doubles the output's registers.
+        auto raise = [&](const f32x16& acc0, const f32x16& acc1) {
+          float mx = acc0[0];
 #pragma unroll
-        for (int T = 0; T < TPC; T += 2) {
-          if (left <= T) break;
-          const int vis = n_vis - T * 32;
-          f32x16 acc0, acc1;
-          uint4 ka[NCH], kb[NCH], va[RUNS * NDT], vb[RUNS * NDT];
+          for (int r = 0; r < 16; ++r) mx = fmaxf(fmaxf(mx, acc0[r]), acc1[r]);
+          mx = half_pair_max(mx);
+          const float m_new = mx > NEG_BIG ? fmaxf(m_ref, fmaf(mx, p.scale2, HEADROOM)) : m_ref;
+          const float f = fast_exp2(m_ref - m_new);
+          m_ref = m_new;
+          m_sub = m_new > NEG_BIG ? m_new : 0.0f;
+          l_sum *= f;
 #pragma unroll
-          for (int i = 0; i < NCH; ++i) ka[i] = lds_ld16(kx[i] + T * K_TILE);
+          for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-          for (int i = 0; i < NCH; ++i) kb[i] = lds_ld16(kx[i] + (T + 1) * K_TILE);
-          logits(ka, acc0);
-          if (!whole) hide(acc0, vis);
-          load_v_tr(vx, T * V_TILE, va);
-          logits(kb, acc1);
-          soft(acc0);
-          if (!whole) hide(acc1, vis - 32);
-          load_v_tr(vx, (T + 1) * V_TILE, vb);
-          weigh(acc0, va);
-          soft(acc1);
-          weigh(acc1, vb);
-        }
-      } else {
-        uint32_t kr = k_at + cur * (STAGE * 16) + nt0 * K_TILE, vr = v_at + cur * (STAGE * 16) + nt0 * V_TILE;
-        int vis = n_vis;
+            for (int r = 0; r < 16; ++r) o[dt][r] *= f;
+        };
+        auto soft = [&](f32x16& acc) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            acc[r] = fast_exp2(fmaf(acc[r], p.scale2, -m_sub));
+            l_sum += acc[r];
+          }
+        };
+        if (BF16) {
+          if (!follows) {
+            // two key tiles: the exponentials of one run beside the other's products
+#pragma unroll
+            for (int T = 0; T < TPC; T += 2) {
+              if (left <= T) break;
+              const int vis = n_vis - T * 32;
+              f32x16 acc0, acc1;
+              uint4 ka[NCH], kb[NCH], va[RUNS * NDT], vb[RUNS * NDT];
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) ka[i] = lds_ld16(kx[i] + T * K_TILE);
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) kb[i] = lds_ld16(kx[i] + (T + 1) * K_TILE);
+              logits(ka, acc0);
+              if (!whole) hide(acc0, vis);
+              load_v_tr(vx, T * V_TILE, va);
+              logits(kb, acc1);
+              soft(acc0);
+              if (!whole) hide(acc1, vis - 32);
+              load_v_tr(vx, (T + 1) * V_TILE, vb);
+              weigh(acc0, va);
+              soft(acc1);
+              weigh(acc1, vb);
+            }
+          } else {
+#pragma unroll
+            for (int T = 0; T < TPC; T += 2) {
+              if (left <= T) break;
+              f32x16 acc0, acc1;
+              uint4 kf[NCH], vf[RUNS * NDT];
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(kx[i] + T * K_TILE);
+              logits(kf, acc0);
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(kx[i] + (T + 1) * K_TILE);
+              logits(kf, acc1);
+              if (!whole) {
+                hide(acc0, n_vis - T * 32);
+                hide(acc1, n_vis - T * 32 - 32);
+              }
+              raise(acc0, acc1);
+              load_v_tr(vx, T * V_TILE, vf);
+              soft(acc0);
+              weigh(acc0, vf);
+              load_v_tr(vx, (T + 1) * V_TILE, vf);
+              soft(acc1);
+              weigh(acc1, vf);
+            }
+          }
+        } else {
+          uint32_t kr = k_at + cur * (STAGE * 16) + nt0 * K_TILE, vr = v_at + cur * (STAGE * 16) + nt0 * V_TILE;
+          int vis = n_vis;
 #pragma unroll 1
-        for (; left > 0; --left) {
-          f32x16 acc;
-          uint4 kf[NCH], vf[RUNS * NDT];
-          load_k(kr, kf);
-          logits(kf, acc);
-          if (!whole) hide(acc, vis);
-          soft(acc);
-          load_v(vr, vf);
-          weigh(acc, vf);
-          kr += K_TILE;
-          vr += V_TILE;
-          vis -= 32;
+          for (; left > 0; --left) {
+            f32x16 acc;
+            uint4 kf[NCH], vf[RUNS * NDT];
+            load_k(kr, kf);
+            logits(kf, acc);
+            if (!whole) hide(acc, vis);
+            soft(acc);
+            load_v(vr, vf);
+            weigh(acc, vf);
+            kr += K_TILE;
+            vr += V_TILE;
+            vis -= 32;
+          }
         }
-      }
-      next();
-      if (DT == DT_BF16) {
-        const uint32_t move = cur ? STAGE * 16 : -STAGE * 16;
+        next();
+        if (DT == DT_BF16) {
+          const uint32_t move = cur ? STAGE * 16 : -STAGE * 16;
 #pragma unroll
-        for (int i = 0; i < NCH; ++i) kx[i] = opaque(kx[i] + move);
+          for (int i = 0; i < NCH; ++i) kx[i] = opaque(kx[i] + move);
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) vx[dt] = opaque(vx[dt] + move);
+          for (int dt = 0; dt < NDT; ++dt) vx[dt] = opaque(vx[dt] + move);
+        }
       }
     }
     if (pass) {
