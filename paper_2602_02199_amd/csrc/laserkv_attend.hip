@@ -539,7 +539,6 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     for (int i = 0; i < NCH; ++i) Mma<DT>::run(acc, kf[i], a[i]);
   };
 
-  constexpr float HEADROOM = 60.0f;  // of a fixed reference over the maximum of its first tile, in powers of two
   float m_ref, l_sum;
   f32x16 o[NDT];
   auto clear = [&]() {
@@ -582,6 +581,25 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
       for (int dt = 0; dt < NDT; ++dt) Mma<DT>::run(o[dt], vf[s * NDT + dt], pb);
     }
   };
+  auto finite = [&]() -> bool {  // the lane's sum and outputs below 2^127
+    uint32_t top = __float_as_uint(l_sum) << 1;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) top = max(top, __float_as_uint(o[dt][r]) << 1);
+    return top < 0xfe000000u;
+  };
+  // Moves a sum's growth past one into the reference: states are merged and divided as if the reference had been there.
+  auto settle = [&]() {
+    const float l = half_pair_max(l_sum);  // one reference for both halves
+    const int e = l > 1.0f ? __builtin_amdgcn_frexp_expf(l) : 0;
+    m_ref += (float)e;
+    l_sum = __builtin_amdgcn_ldexpf(l_sum, -e);
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] = __builtin_amdgcn_ldexpf(o[dt][r], -e);
+  };
   // The result of tile t from the wave's complete state: with one split out = O / l and lse = (m + log2 l) ln 2 (a row
   // that saw no key gives zero and -inf), else the split's partial (reference, sum, unnormalised output).  A lane holds 16
   // bytes of every 32 of its row; groups of four lanes exchange them so that a store instruction writes whole 128-byte
@@ -594,9 +612,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     if (direct) {
       const size_t at = (size_t)h * p.m_rows + row;
       scale = l > 0.0f ? 1.0f / l : 0.0f;
-      const float up = l < 1.0f ? HEADROOM : 0.0f;  // the headroom comes off exactly, before the logarithm
-      if (kg == 0 && row < p.m_rows)
-        p.out_lse[at] = l > 0.0f ? ((m_ref - up) + fast_log2(l < 1.0f ? l * 0x1p60f : l)) * 0.6931471805599453f : -__builtin_inff();
+      if (kg == 0 && row < p.m_rows) p.out_lse[at] = l > 0.0f ? lse_log2(m_ref, l) * 0.6931471805599453f : -__builtin_inff();
       dst = p.out + (size_t)h * p.m_rows * D;
     } else {
       // [cut row groups][splits][256 rows: the pairs in order, of each the tile with the lower number first]
@@ -627,8 +643,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // Over the cache's rows (and in fp32) a row's reference is fixed: its maximum over the first tile of keys that it sees, plus
   // HEADROOM (what a row sees is a prefix of the keys: a row that sees none of a wave's first tile sees none of the others).
   // Each logit then costs an fma, an exponential and an add, and the output accumulators nothing but matrix instructions.
-  // Sums that grow past 1e30 (a logit 160 above the first tile's, in powers of two) make the workgroup repeat the pass with
-  // the exact maxima, which a sweep over the keys finds first.
+  // Sums or outputs that overflow (from about a logit 145 above the first tile's on, in powers of two) make the workgroup
+  // repeat the pass with the exact maxima, which a sweep over the keys finds first.  (One workgroup in a round that repeats
+  // it costs three times the round; keys whose lengths spread by e^0.5 reach 140.)
   // Over the block's own keys in bf16 it follows the maximum: the dominant key's probability is then a power of two and its
   // bf16 exact, while against a fixed reference its rounding (up to 2^-8) goes into the output whole.  A maximum and a
   // rescaling of the output per pair of tiles: 16k prefill in blocks of 2048 1358 -> 1378 us, causal blocks without a cache
@@ -716,7 +733,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
         if (SEG && !joined && kc0 >= end_lo) {
           joined = true;
           if (!upper) {
-            bad = !(l_sum < 1.0e30f);
+            bad = !finite();
+            settle();
             if (present) write_tile(t_lo);
             load_rows(t_hi);
             clear();
@@ -841,8 +859,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
       lds_barrier();  // every wave has left the stages
       break;
     }
-    // inf, NaN or large enough for O = sum p v to overflow next: once more (decided for the workgroup: the pass has barriers)
-    if (bad || !(l_sum < 1.0e30f)) *redo = 1;
+    // once more (decided for the workgroup: the pass has barriers)
+    if (bad || !finite()) *redo = 1;
     __syncthreads();
     if (!*redo) break;
     start();
@@ -872,6 +890,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     }
     lds_barrier();
   }
+  settle();
   // every wave has left the stages: the states of pairs that shared a tile meet there (rows padded by four floats
   // against bank conflicts)
   constexpr int OP = D + 4;
@@ -977,7 +996,7 @@ __global__ __launch_bounds__((D / 4) * COMB_SLICES) void attend_combine_kernel(A
   }
   const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
   *reinterpret_cast<float4*>(p.out + (size_t)row_lin * D + d4 * 4) = make_float4(at.x * inv, at.y * inv, at.z * inv, at.w * inv);
-  if (d4 == 0) p.out_lse[row_lin] = lt > 0.0f ? (mt + fast_log2(lt)) * 0.6931471805599453f : -__builtin_inff();
+  if (d4 == 0) p.out_lse[row_lin] = lt > 0.0f ? lse_log2(mt, lt) * 0.6931471805599453f : -__builtin_inff();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1054,7 +1073,7 @@ __global__ __launch_bounds__(LSEC_ROWS * LSEC_SLICES) void attend_lse_combine_ke
   if (sl || row_lin >= n_rows) return;
 #pragma unroll
   for (int s = 1; s < LSEC_SLICES; ++s) lse_merge(mx, l, sP[s][r].x, sP[s][r].y);
-  p.out_lse[row_lin] = l > 0.0f ? (mx + fast_log2(l)) * 0.6931471805599453f : -__builtin_inff();
+  p.out_lse[row_lin] = l > 0.0f ? lse_log2(mx, l) * 0.6931471805599453f : -__builtin_inff();
 }
 
 // ---- host side ----

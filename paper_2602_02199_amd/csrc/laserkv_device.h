@@ -186,4 +186,18 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
   m = mn;
 }
 
+
+// Powers of two that a reference fixed at the first keys' maximum lies above it: room for later keys before a sum must be
+// taken again.  More room costs precision, since fma(logit, scale, -reference) rounds at the size of its result: with 24 a
+// row's log-sum-exp is as exact as with none (model of 2048 keys: mean error 3.1e-7 diffuse, 4.0e-7 with a key at e^9, 5.4e-7
+// with 60).
+constexpr float HEADROOM = 24.0f;
+
+// log2 of sum * 2^ref for sum > 0.  A sum below one holds headroom, which comes off the reference as an integer first: ref
+// and log2(sum) by themselves are larger than the result and round coarser.
+__device__ __forceinline__ float lse_log2(float ref, float sum) {
+  const int e = sum < 1.0f ? __builtin_amdgcn_frexp_expf(sum) : 0;
+  return (ref + (float)e) + fast_log2(__builtin_amdgcn_ldexpf(sum, -e));
+}
+
 }  // namespace lkv

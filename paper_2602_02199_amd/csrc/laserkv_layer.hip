@@ -295,7 +295,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
           lse_merge(mm, ss, v.x, v.y);
         }
         if (outside) lse_merge(mm, ss, ext, 1.0f);
-        lse = mm + fast_log2(ss);
+        lse = lse_log2(mm, ss);
       }
     }
     sLse[m] = lse;

@@ -17,9 +17,10 @@ constexpr size_t row_stats_lds(int row_bytes) { return (size_t)2 * row_stats_chu
 // that share rows take different 32-key tiles (ks, ks + wk, ...).  Keys are the A operand and rows the B operand, so a
 // lane owns a row per tile; its two halves hold the same rows over different keys and are merged before the end.
 // A row sees the keys below its lim[r]; every row sees the keys up to lim_all.  The reference is the maximum over the
-// lane's first tile plus 60; complete tiles after it cost one fma, one exponential and one add per logit.  When a sum
-// has grown past 1e30 after a chunk (a logit 160 above the first tile's, in powers of two), the wave repeats that
-// chunk from LDS with a reference that follows the maximum.
+// lane's first tile plus HEADROOM; complete tiles after it cost one fma, one exponential and one add per logit.  When a
+// sum has grown past 1e34 after a chunk (a logit 137 above the first tile's, in powers of two; a thousand such sums can
+// still be merged), the wave repeats that chunk from LDS with a reference that follows the maximum.  References are
+// whole numbers, so that moving one rescales its sum exactly.
 // What bounds it: matrix and vector work of a SIMD hardly overlap (16 matrix instructions of 32 clocks and 64 vector
 // instructions of 4, 32 exponentials of 8 per pair of tiles): 870 - 1000 TFLOP/s of the 1140 a plain matrix product
 // reaches here.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
@@ -93,7 +94,7 @@ __device__ __forceinline__ void row_stats(uint4* smem, __amdgpu_buffer_rsrc_t ks
               float mx = acc[r][0];
 #pragma unroll
               for (int e = 1; e < 16; ++e) mx = acc_row(e, kg) < n_vis ? fmaxf(mx, acc[r][e]) : mx;
-              const float nref = fmaxf(ref[r], mx * scale2);  // scale2 > 0
+              const float nref = fmaxf(ref[r], ceilf(mx * scale2));  // scale2 > 0
               sum[r] *= fast_exp2(ref[r] - nref);
               ref[r] = nref;
 #pragma unroll
@@ -104,9 +105,9 @@ __device__ __forceinline__ void row_stats(uint4* smem, __amdgpu_buffer_rsrc_t ks
           if (first) {
             fixed_ref = true;
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {  // 2^60 of headroom: the sums are relative, terms that vanish are below 2^-60 of them
-              ref[r] += 60.0f;
-              sum[r] *= 0x1p-60f;
+            for (int r = 0; r < RT; ++r) {
+              ref[r] += HEADROOM;
+              sum[r] = __builtin_amdgcn_ldexpf(sum[r], -(int)HEADROOM);
             }
           }
           first = false;
@@ -116,12 +117,12 @@ __device__ __forceinline__ void row_stats(uint4* smem, __amdgpu_buffer_rsrc_t ks
       // following the maximum
       bool over = false;
 #pragma unroll
-      for (int r = 0; r < RT; ++r) over |= !(sum[r] < 1.0e30f);
+      for (int r = 0; r < RT; ++r) over |= !(sum[r] < 1.0e34f);
       if (attempt || !__any(over)) break;
       fixed_ref = false;
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        const float nref = kept[r] > 1.0e10f ? ref[r] + fast_log2(kept[r]) : ref[r];
+        const float nref = kept[r] > 1.0e10f ? ref[r] + ceilf(fast_log2(kept[r])) : ref[r];
         sum[r] = kept[r] * fast_exp2(ref[r] - nref);
         ref[r] = nref;
       }

@@ -95,3 +95,29 @@ def test_rows_of_a_block_that_one_of_its_keys_dominates(case):
     hidden = np.arange(n + s_t)[None, :] > n + np.arange(s_t)[:, None]
     verdict([against_bound(out[i], weights(q[i], kk[i // g], hidden), vv[i // g], n) for i in range(0, h_q, 3)], f"block {s_t} after {n}")
     lib.close()
+
+
+@pytest.mark.parametrize("route", ["normaliser", "rows-split", "rows-whole"])
+def test_log_sum_exp_of_diffuse_rows(route):
+    """Values below 16: the last addition and the store round by at most half of 2^-20 each (mean 2.4e-7 and, times ln 2,
+    1.7e-7, together 3e-7), the logarithm of a number below one adds little, and so do sums of at most a thousand terms per
+    lane: a mean error of 4.5e-7 leaves half as much again."""
+    h_q, h_kv, d = 32, 8, 128
+    n_q, n = (2048, 2000) if route == "rows-whole" else (40, 9000)
+    q, k, v = make_inputs(h_q, h_kv, d, n_q, n, "bf16", seed=66, needles=False)
+    lib = binding.LaserKV(h_q, h_kv, d, "bf16", 8, 8, max_block=n_q, max_window=64, max_ctx_keys=0)
+    if route == "rows-whole":
+        assert lib.laserkv_attend_block_workspace_bytes(n_q, n, 0) == 256  # workgroups that see all keys of their rows
+        _, lse = run_block(lib, q.to(DEV), k.to(DEV), v.to(DEV), n, k[:, :0].to(DEV), v[:, :0].to(DEV), 0, 0)
+    else:
+        _, lse = run_attend(lib, q.to(DEV), k.to(DEV), v.to(DEV), n, lse_only=route == "normaliser")
+    err = []
+    for hq in range(0, h_q, 3):
+        x = f64(q[hq, :256]) @ f64(k[hq // (h_q // h_kv)]).T / d ** 0.5
+        m = x.max(axis=1)
+        want = m + np.log(np.exp(x - m[:, None]).sum(axis=1))
+        err.append(np.abs(lse[hq, :256] - want)[want < 16.0])
+    err = np.concatenate(err)
+    say(f"[precision lse {route}] mean error {err.mean():.2e}, max {err.max():.2e}")
+    assert err.mean() <= 4.5e-7
+    lib.close()

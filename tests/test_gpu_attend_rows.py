@@ -65,3 +65,22 @@ def test_long_queries_of_many_heads_per_group():
     for j0, j1 in ((0, 2), (n_q // 2, n_q // 2 + 1), (n_q - s_t - 1, n_q - s_t + 2), (n_q - 3, n_q)):
         compare_block(out[:, j0:j1], lse[:, j0:j1], q[:, j0:j1], kc, vc, n, kb, vb, bp, qp + j0, True, "bf16", f"rows {j0}..{j1 - 1} of 32 heads")
     lib.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("growth", [90, 122, 137, 143, 150, 170])
+def test_logits_far_above_the_first_tile(dtype, growth):
+    """A cache key whose logit lies that far above the first tile's (in powers of two): within the sums' range, at its end
+    and past it (the second pass), in split and in whole key ranges."""
+    for g, n_q, n in ((4, 90, 3000), (32, 2048, 300)):
+        q, kk, vv = make_inputs(g, 1, 64, n_q, n + 40, dtype, seed=growth, needles=False)
+        for i, j in ((0, 5), (g - 1, n_q - 3)):
+            qq = q[i, j].float()
+            kk[0, n - 50 - 3 * i] = (qq * (growth / 1.4427 * 8.0 / float(qq @ qq))).to(kk.dtype)
+        kc, vc, kb, vb = kk[:, :n].contiguous(), vv[:, :n].contiguous(), kk[:, n:].contiguous(), vv[:, n:].contiguous()
+        lib = binding.LaserKV(g, 1, 64, dtype, 8, 8, max_block=n_q, max_window=32, max_ctx_keys=0)
+        out, lse = run_block(lib, q.to(DEV), kc.to(DEV), vc.to(DEV), n, kb.to(DEV), vb.to(DEV), 5000, 5040 - n_q)
+        for rows in (slice(0, 8), slice(n_q - 8, n_q)):
+            compare_block(out[:, rows], lse[:, rows], q[:, rows], kc, vc, n, kb, vb, 5000, 5040 - n_q + rows.start, True, dtype,
+                          f"growth {growth}, {g * n_q} rows from {rows.start}")
+        lib.close()
