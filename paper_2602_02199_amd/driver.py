@@ -241,7 +241,7 @@ class LayerCompressor:
                 table = torch.tensor([t.data_ptr() for t in row_lse_complete[:nb]], dtype=torch.int64, device=self.device)
             call = self._layer_call(data, nb, table)
             if call is not None:
-                assert min(nb * wl.s_block, l_tot) == nb * wl.s_block, "plans cover equal-sized blocks only"
+                assert call[2] == nb * sum(self.parts), "plans cover blocks that keep equally many rows only"
                 calls.tensors = (table, self._layer_ws)
                 calls.append((call[0], call[1], True))
                 if row_lse_complete is not None:
@@ -257,7 +257,7 @@ class LayerCompressor:
             s_t = hi - lo
             na, nl, ke, kl = self.block_budget(s_t)
             b_t = na + nl + ke + kl
-            assert b_t == self.keep.shape[1], "plans cover equal-sized blocks only"
+            assert b_t == self.keep.shape[1], "plans cover blocks that keep equally many rows only"
             q, qsh, qst, w = binding._rows3(data["q_win"][t], d)
             k, ksh, kst, _ = binding._rows3(data["k"][:, lo:hi], d)
             v, vsh, vst, _ = binding._rows3(data["v"][:, lo:hi], d)

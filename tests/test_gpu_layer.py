@@ -159,3 +159,18 @@ def test_layer_call_with_a_window_shorter_than_the_workloads():
         got = comp.cache_pos[:, :n]
         swapped = sum(len(set(got[h].tolist()) - set(want.cache_pos[h].tolist())) for h in range(wl.n_kv_heads))
         assert n == want.cache_len and swapped <= 2e-3 * n * wl.n_kv_heads
+
+
+def test_plan_with_a_short_last_block():
+    """The last block is short but keeps the full budget: the plan keeps what the layer call keeps."""
+    wl = synth.shrink(synth.WORKLOADS["llama8b-16k"], index=48, l_ctx=7360)
+    comp = LayerCompressor(wl, DEV)
+    dev = to_dev(synth.make_layer(wl, 0, comp.parts[0]))
+    n = comp.run_layer(dev)
+    want = [t[:, :n].clone() for t in (comp.k_cache, comp.v_cache, comp.cache_pos)]
+    plan = comp.plan_layer(dev)
+    assert len(plan) == 1
+    comp.cache_pos.fill_(-1)
+    assert comp.run_plan(plan) == n
+    for a, b in zip(want, (comp.k_cache, comp.v_cache, comp.cache_pos)):
+        assert torch.equal(a, b[:, :n])

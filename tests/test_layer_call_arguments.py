@@ -96,6 +96,21 @@ def test_statistics_of_another_window_are_refused():
         comp.plan_layer(inputs(w=20), row_lse_complete=lse)
 
 
+def test_plans_take_a_short_last_block_that_keeps_the_full_budget():
+    wl = synth.Workload("short-last", 0, 4, 2, 64, "f32", 1900, 512, 32, 4, 8, 8)
+    comp = compressor(wl)
+    assert sum(comp.parts) <= 364  # the last block's tokens
+    plan = comp.plan_layer(inputs(l_ctx=1900))
+    assert len(plan) == 1 and plan[0][1][N_TOK] == 1900
+    assert len(compressor(wl).plan_layer(inputs(l_ctx=1900), fused=False)) == 2 * 4
+    wl = synth.Workload("too-short-last", 0, 4, 2, 64, "f32", 1640, 512, 32, 4, 8, 8)
+    comp = compressor(wl)
+    assert sum(comp.parts) > 104
+    for fused in (True, False):
+        with pytest.raises(AssertionError):
+            comp.plan_layer(inputs(l_ctx=1640), fused=fused)
+
+
 def test_windows_in_a_list_go_block_by_block():
     comp, data = compressor(), inputs()
     data["q_win"] = list(data["q_win"])
