@@ -17,6 +17,11 @@ class _Plan(list):
     tensors = ()
 
 
+class _Args(tuple):
+    """Arguments of a laserkv_compress_layer and the scratch they point to."""
+    workspace = None
+
+
 class LayerCompressor:
     def __init__(self, wl, device="cuda:0", max_blocks=None, budget=None, tail=0, lib=None):
         """budget: per-block budget B of this layer (default: the App. B equation for the workload; a
@@ -39,11 +44,18 @@ class LayerCompressor:
         self.v_cache = torch.zeros_like(self.k_cache)
         self.cache_pos = torch.full((wl.n_kv_heads, self.cap), -1, dtype=torch.int64, device=self.device)
         self.keep = torch.empty(wl.n_kv_heads, min(self.B, wl.s_block), dtype=torch.int32, device=self.device)
-        self._layer_ws = None  # scratch of laserkv_compress_layer, sized by the first layer that needs it
+        # scratch of laserkv_compress_layer for every number of blocks this object is made for: like the cache it is never
+        # replaced, so no call on any stream and no captured graph loses it while this object lives
+        size = max((self._layer_ws_bytes(n * wl.s_block, wl.window) for n in range(2, nb + 1)), default=-1)
+        self._layer_ws = torch.empty(size, dtype=torch.uint8, device=self.device) if size > 0 else None
         self.cache_len = 0
 
     def reset(self):
         self.cache_len = 0
+
+    def _layer_ws_bytes(self, n_tok, window):
+        """Scratch of laserkv_compress_layer; -1 for shapes it has no kernels for."""
+        return self.lib._lib.laserkv_layer_workspace_bytes(self.lib._ctx, n_tok, self.wl.s_block, window, self.parts[1])
 
     def run_layer_deferred(self, data, n_blocks=None, dbg_for=None):
         """The layer loop with each block's last `tail` tokens deferred to the next block's call (the look-back
@@ -138,18 +150,20 @@ class LayerCompressor:
         last = n_tok - (nb - 1) * wl.s_block
         # a block and its look-back keys go through one buffer descriptor; a block alone may just fit where both do not
         one_span = (wl.s_block + self.parts[1]) * kst * self.k_cache.element_size() < 1 << 31
-        size = lib._lib.laserkv_layer_workspace_bytes(lib._ctx, n_tok, wl.s_block, w, self.parts[1]) if last >= w and one_span else -1
+        size = self._layer_ws_bytes(n_tok, w) if last >= w and one_span else -1
         if size < 0:
             return None
-        if self._layer_ws is None or self._layer_ws.numel() < size:
-            self._layer_ws = torch.empty(size, dtype=torch.uint8, device=self.device)
+        ws = self._layer_ws
+        if ws is None or ws.numel() < size:  # more blocks or another window: this call's (or plan's) own
+            ws = torch.empty(size, dtype=torch.uint8, device=self.device)
         b_last = sum(self.block_budget(last))
         keep = self.keep if b_last == self.keep.shape[1] else None
-        args = (lib._ctx, q, qsb, qsh, qst, k, ksh, kst, v, vsh, vst, planes.data_ptr(), n_tok, wl.s_block, w,
+        args = _Args((lib._ctx, q, qsb, qsh, qst, k, ksh, kst, v, vsh, vst, planes.data_ptr(), n_tok, wl.s_block, w,
                 self.B, wl.n_div, wl.alpha, None if row_lse_complete is None else row_lse_complete.data_ptr(),
                 None if keep is None else keep.data_ptr(), self.k_cache.data_ptr(), self.v_cache.data_ptr(),
                 self.k_cache.stride(0), self.cache_pos.data_ptr(), self.cache_pos.stride(0), self.cap,
-                self._layer_ws.data_ptr(), self._layer_ws.numel())
+                ws.data_ptr(), ws.numel()))
+        args.workspace = ws
         return lib._lib.laserkv_compress_layer, args, (nb - 1) * sum(self.parts) + b_last
 
     def run_layer(self, data, n_blocks=None):
@@ -242,7 +256,7 @@ class LayerCompressor:
             call = self._layer_call(data, nb, table)
             if call is not None:
                 assert call[2] == nb * sum(self.parts), "plans cover blocks that keep equally many rows only"
-                calls.tensors = (table, self._layer_ws)
+                calls.tensors = (table, call[1].workspace)
                 calls.append((call[0], call[1], True))
                 if row_lse_complete is not None:
                     calls.append((lib.laserkv_set_row_lse_complete, (ctx, None), False))

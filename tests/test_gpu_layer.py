@@ -174,3 +174,34 @@ def test_plan_with_a_short_last_block():
     assert comp.run_plan(plan) == n
     for a, b in zip(want, (comp.k_cache, comp.v_cache, comp.cache_pos)):
         assert torch.equal(a, b[:, :n])
+
+
+def test_layer_calls_on_two_streams_and_a_first_call_under_capture():
+    """Nothing is allocated by a layer call: a short one on one stream, the whole layer on another, then a graph of a
+    compressor that has not run before, replayed between eager runs."""
+    wl = synth.shrink(synth.WORKLOADS["llama8b-16k"], index=49, l_ctx=8192)
+    comp, fresh = LayerCompressor(wl, DEV), LayerCompressor(wl, DEV)
+    dev = to_dev(synth.make_layer(wl, 0, comp.parts[0]))
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(one):
+        comp.run_layer(dev, n_blocks=2)
+    two.wait_stream(one)
+    with torch.cuda.stream(two):
+        n = comp.run_layer(dev)
+    torch.cuda.synchronize()
+    assert torch.cuda.memory_allocated() == before
+    want = comp.cache_pos[:, :n].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(two):
+        with torch.cuda.graph(graph, stream=two):
+            fresh.run_layer(dev)
+    for _ in range(3):
+        fresh.cache_pos.fill_(-1)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(want, fresh.cache_pos[:, :n])
+        comp.run_layer(dev)
+        assert torch.equal(want, comp.cache_pos[:, :n])

@@ -111,6 +111,22 @@ def test_plans_take_a_short_last_block_that_keeps_the_full_budget():
             comp.plan_layer(inputs(l_ctx=1640), fused=fused)
 
 
+def test_the_scratch_is_there_from_the_start_and_stays():
+    """Calls of growing length, a plan among them: one scratch tensor, sized for the longest; what the object was not made
+    for brings its own."""
+    comp = compressor()
+    first = comp._layer_ws
+    assert first is not None and first.numel() == 1000 + 100 * 4
+    for n in (2, 3, 4):
+        comp.run_layer(inputs(), n_blocks=n)
+    plan = comp.plan_layer(inputs())
+    assert all(a[-3] == first.data_ptr() and a[-2] == first.numel() for a in comp.lib.layer)
+    assert comp._layer_ws is first and plan.tensors[1] is first
+    longer = comp.plan_layer(inputs(n_win=6, l_ctx=3072))
+    assert comp._layer_ws is first and longer.tensors[1].numel() == 1000 + 100 * 6
+    assert longer[0][1][-2:] == (longer.tensors[1].data_ptr(), longer.tensors[1].numel())
+
+
 def test_windows_in_a_list_go_block_by_block():
     comp, data = compressor(), inputs()
     data["q_win"] = list(data["q_win"])
