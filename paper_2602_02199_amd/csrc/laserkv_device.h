@@ -97,10 +97,12 @@ __device__ __forceinline__ uint4 lds_ld16(uint32_t at) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ void async_ld16(srd_words srd, uint32_t lane_offset, uint32_t uniform_offset, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
+  // m0 is put back: it is reserved to the compiler, which takes no notice of a clobber
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0)
                : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_offset), "s"(srd), "s"(__builtin_amdgcn_readfirstlane((int)uniform_offset))
-               : "memory");  // the kernels here use m0 for nothing else
+               : "memory");
 }
 // Makes the compiler complete its own loads of v here (registers loaded before a loop would otherwise be waited for at
 // their first use inside it, and with them every asynchronous load in flight there).
