@@ -97,9 +97,11 @@ __device__ __forceinline__ uint4 lds_ld16(uint32_t at) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ void async_ld16(srd_words srd, uint32_t lane_offset, uint32_t uniform_offset, uint32_t lds) {
-  // m0 is put back: it is reserved to the compiler, which takes no notice of a clobber
+  // m0 is put back: it is reserved to the compiler, which takes no notice of a clobber.  The load is the sixth instruction
+  // slot: a vector instruction in front (a lane read of a spilled scalar) may have written the scalars it reads, which takes
+  // five wait states that the compiler counts for its own instructions only.
   uint32_t m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
                : "=&s"(m0)
                : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(lane_offset), "s"(srd), "s"(__builtin_amdgcn_readfirstlane((int)uniform_offset))
                : "memory");

@@ -1,5 +1,7 @@
-"""Inline assembly that writes m0 (LDS-direct loads take their address from it) leaves it as it was: the register is reserved
-to the compiler, which neither saves it nor heeds a clobber."""
+"""What the compiler does not see inside inline assembly.  m0 (LDS-direct loads take their address from it) is left as it was:
+the register is reserved to the compiler, which neither saves it nor heeds a clobber.  A scalar operand that a vector
+instruction has just written may be read by a memory instruction five wait states later only; the compiler counts them
+for its own instructions."""
 import glob
 import os
 import re
@@ -22,4 +24,16 @@ def test_writes_of_m0_are_taken_back():
         found += 1
         saved = re.fullmatch(r"s_mov_b32 (%\d), m0", lines[0])
         assert saved and lines[-1] == f"s_mov_b32 m0, {saved.group(1)}", f"{name}: {lines}"
+    assert found
+
+
+def test_loads_wait_for_scalars_from_vector_instructions():
+    found = 0
+    for name, lines in statements():
+        for at, line in enumerate(lines):
+            if not re.match(r"(buffer|global|flat|scratch)_", line):
+                continue
+            found += 1
+            waits = sum(1 + (int(i.split()[1]) if i.startswith("s_nop") else 0) for i in lines[:at])
+            assert waits >= 5, f"{name}: {lines}"
     assert found
