@@ -397,9 +397,9 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void attend_decode_kernel(AttendPar
     }
   }
   if (!own) return;
-  const float inv = 1.0f / l;  // every split holds a key: l > 0
+  const float inv = l > 0.0f ? 1.0f / l : 0.0f;  // all logits -inf (products that overflow): zero and -inf
   *reinterpret_cast<float2*>(p.out + (rows0 + m) * D + 2 * d2) = make_float2(acc.x * inv, acc.y * inv);
-  if (d2 == 0) p.out_lse[rows0 + m] = (mx + fast_log2(l)) * 0.6931471805599453f;
+  if (d2 == 0) p.out_lse[rows0 + m] = l > 0.0f ? (mx + fast_log2(l)) * 0.6931471805599453f : -__builtin_inff();
 }
 
 // ---- host side ----

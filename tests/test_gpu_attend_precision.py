@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import laserkv_oracle as O
 from paper_2602_02199_amd import binding
 from tests.test_gpu_attend import DEV, f64, make_inputs, run_attend, say
 from tests.test_gpu_attend_block import run_block
@@ -120,4 +121,22 @@ def test_log_sum_exp_of_diffuse_rows(route):
     err = np.concatenate(err)
     say(f"[precision lse {route}] mean error {err.mean():.2e}, max {err.max():.2e}")
     assert err.mean() <= 4.5e-7
+    lib.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 40, 4500])
+def test_decoding_row_whose_logits_all_overflow_to_minus_infinity(dtype, n):
+    """As every other attention kernel: zero and -inf for that row, the other heads untouched."""
+    h_q, h_kv, d = 8, 2, 64
+    q, k, v = make_inputs(h_q, h_kv, d, 1, n, dtype, seed=11, needles=False)
+    q[3], k[0, :, 0] = 0.0, -1.0e30
+    q[:4, :, 0] = 0.0
+    q[3, 0, 0] = 1.0e30
+    lib = binding.LaserKV(h_q, h_kv, d, dtype, 8, 8, max_block=64, max_window=8, max_ctx_keys=0)
+    out, lse = run_attend(lib, q.to(DEV), k.to(DEV), v.to(DEV), n)
+    assert not out[3].any() and np.isneginf(lse[3]).all()
+    o_out, o_lse = O.attend_cache(f64(q), f64(k), f64(v), n)
+    rest = [0, 1, 2, 4, 5, 6, 7]
+    assert np.abs(out[rest] - o_out[rest]).max() <= (1e-5 if dtype == "f32" else 2e-2) * 5 and np.abs(lse[rest] - o_lse[rest]).max() <= 1e-4
     lib.close()
