@@ -43,6 +43,14 @@ def algorithmic_work(wl, B):
     }
 
 
+def measured_traffic(workload, lse, whole_layer, kernel):
+    """HBM bytes per launch of a kernel kind as profiled, or None: a launch of the layer call takes all blocks, one of the
+    block calls a block."""
+    path = os.path.join(ROOT, "profiles", "" if whole_layer else "blocks",
+                        f"traffic_{workload}{'-lse-complete' if lse == 'complete' else ''}.json")
+    return json.load(open(path)).get(kernel) if os.path.exists(path) else None
+
+
 def measure(wl, args, dev, cpu_seconds):
     """Times one workload: returns the fields of the JSON line that depend on the workload."""
     import statistics
@@ -191,10 +199,7 @@ def measure(wl, args, dev, cpu_seconds):
         per_kernel[name] = dict(bound=bound, avg_us=round(v["avg_us"], 2), achieved=round(achieved, 3), peak=peak,
                                 unit=unit, frac=round(achieved / peak, 4), launches_per_step=v["launches"])
     dom = max(per_kernel, key=lambda k: per_kernel[k]["avg_us"])
-    traffic = None
-    tpath = os.path.join(ROOT, "profiles", f"traffic_{wl.name}{'-lse-complete' if args.lse == 'complete' else ''}.json")
-    if os.path.exists(tpath):
-        traffic = json.load(open(tpath)).get(dom)
+    traffic = measured_traffic(wl.name, args.lse, len(plan) < wl.n_blocks, dom)
     d = per_kernel[dom]
     roofline = dict(bound=d["bound"], kernel=dom, achieved=d["achieved"], peak=d["peak"], unit=d["unit"],
                     frac=d["frac"], traffic=traffic, avg_us=d["avg_us"], kernels=per_kernel,
