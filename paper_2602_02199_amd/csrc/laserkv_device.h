@@ -160,7 +160,6 @@ __device__ __forceinline__ float lane_xor1(float v) { return __uint_as_float(lan
 __device__ __forceinline__ float lane_xor2(float v) { return __uint_as_float(lane_xor2(__float_as_uint(v))); }
 __device__ __forceinline__ int lane_xor1(int v) { return (int)lane_xor1((uint32_t)v); }
 __device__ __forceinline__ int lane_xor2(int v) { return (int)lane_xor2((uint32_t)v); }
-__device__ __forceinline__ float lane_xor4(float v, bool bit2) { return __uint_as_float(lane_xor4(__float_as_uint(v), bit2)); }
 __device__ __forceinline__ int lane_xor4(int v, bool bit2) { return (int)lane_xor4((uint32_t)v, bit2); }
 // Value of lane (l ^ 32): one swap of the wave's halves (upper: the lane is in the upper half), no LDS round trip.
 __device__ __forceinline__ uint32_t half_other(uint32_t v, bool upper) {

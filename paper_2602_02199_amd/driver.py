@@ -306,7 +306,6 @@ class LayerCompressor:
         return calls
 
     def run_plan(self, calls, stream=None):
-        import ctypes as C
         sp = self.lib._stream(stream)
         for fn, args, takes_stream in calls:
             rc = fn(*args, sp) if takes_stream else fn(*args)
