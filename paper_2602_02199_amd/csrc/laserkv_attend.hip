@@ -3,8 +3,9 @@
 // cache rows, over the current block's own keys under the causal mask (the block's prefill attention, whose
 // log-sum-exp of the window rows is the complete statistic of Sec. 3.3 "Precision").
 //
-//   attend_kernel          few query rows (decoding).  Workgroup = (key split, group of 256 query rows, KV
-//                          head); the waves share row tiles over different key tiles.  The split's keys and
+//   attend_decode_kernel   at most eight query rows per KV head over the cache (decoding): laserkv_decode.hip
+//   attend_kernel          up to four row tiles otherwise (128 query rows per KV head).  Workgroup = (key split, KV head);
+//                          the waves share row tiles over different key tiles.  The split's keys and
 //                          values pass through LDS in chunks; each wave keeps 32 query rows in registers and an
 //                          online-softmax state (reference, sum, unnormalised output) per row; the waves'
 //                          states meet in LDS and leave one partial per split                          [MFMA]
@@ -338,14 +339,15 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
 //   n_q - 1 - j, so under the causal mask of a whole block the two tiles see the block's first L and H keys with L + H the
 //   same for all pairs.  The wave with fewer keys writes its result when the keys pass L and joins the other tile: from
 //   then on the two waves take alternate 32-key tiles, and their states meet in LDS at the end.  (With
-//   consecutive tiles in a workgroup a launch took as long as the block's last rows: a 16k prefill of 32 heads in blocks
-//   of 2048 rows 169 us a block on average, now 151.)
+//   consecutive tiles in a workgroup a launch takes as long as the block's last rows: a 16k prefill of 32 heads in blocks
+//   of 2048 rows took 169 us a block on average, with pairs 151.)
 //   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  Over the cache's
 //   rows references are fixed, so that the output accumulators see nothing but matrix instructions, and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
 //   instructions hardly overlap with matrix instructions here).
 //   Chunks alternate between two LDS stages and arrive through async_ld16, the next one while the current one is worked
 //   on, so one barrier per chunk suffices.
-// Bound by power: at 1.1 PFLOP/s it runs at the rate of a plain bf16 matrix product on this card.
+// Bound by the matrix unit, at the clock that power allows: 128k prefill, last block, 1136 TFLOP/s, and 1404 when all
+// operands are zero (a plain bf16 product of 8192: 1380 and 1800).
 template <int DT>
 __host__ __device__ constexpr int rows_chunk_keys() { return DT == DT_BF16 ? 128 : 64; }
 
@@ -1004,7 +1006,8 @@ __global__ __launch_bounds__((D / 4) * COMB_SLICES) void attend_combine_kernel(A
 // all laserkv_set_row_lse needs.  No values are read and no output accumulators kept, so a workgroup takes up to 512
 // rows (a GQA group's whole window reads the keys once; with fewer rows the eight waves share them over different key
 // tiles).  Workgroup = (key split, group of 512 rows, KV head); the arithmetic is laserkv_rowstats.h.
-// 256 rows over 31 681 keys, 8 heads: 36.6 -> 24 us (before: sixteen waves of 32 rows, half of them without rows).
+// 256 rows over 31 681 keys, 8 heads: 36.6 -> 24 us and 28.6 with the merge (before: sixteen waves of 32 rows, half of them
+// without rows); 512 rows over 63 520 keys 78 -> 76 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int LSE_ROWS = 512;
 

@@ -12,8 +12,8 @@
 // Workgroup = (key split, KV head), 8 waves that never wait for each other in the main loop.  K of the next tile is
 // requested as soon as the current tile's logits are done and V as soon as its sum is done.
 //
-// Measured (32/8 heads, d 128, bf16, one query): 7301 rows 13.3 -> 11.6 us (of which 1.8 launch, 8 until the keys are
-// worked off, 4 merging), 63 520 rows 52.4 -> 43.9 us = 5.9 TB/s (loads alone: 40 us).  The matrix-instruction kernel
+// Measured (32/8 heads, d 128, bf16, one query): 7301 rows 13.3 -> 11.5 us (of which 1.8 launch, 8 until the keys are
+// worked off, 4 merging), 63 520 rows 52.4 -> 43.4 us = 6.0 TB/s (loads alone: 40 us).  The matrix-instruction kernel
 // before it passed everything through LDS with a register transpose of V and two barriers per 256 keys.
 #include "laserkv_device.h"
 #include "laserkv_kernels.h"

@@ -22,8 +22,9 @@ constexpr size_t row_stats_lds(int row_bytes) { return (size_t)2 * row_stats_chu
 // still be merged), the wave repeats that chunk from LDS with a reference that follows the maximum.  References are
 // whole numbers, so that moving one rescales its sum exactly.
 // What bounds it: matrix and vector work of a SIMD hardly overlap (16 matrix instructions of 32 clocks and 64 vector
-// instructions of 4, 32 exponentials of 8 per pair of tiles): 870 - 1000 TFLOP/s of the 1140 a plain matrix product
-// reaches here.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
+// instructions of 4, 32 exponentials of 8 per pair of tiles).  512 rows over 63 520 keys of 8 heads 76 us = 870 TFLOP/s
+// with the merge, a 128k layer 181 us = 800, 256 rows over 31 681 keys 28.6 us = 580 (start and merge are a third); a
+// plain bf16 product reaches 1380.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
 template <int DT, int D, int RT>
 __device__ __forceinline__ void row_stats(uint4* smem, __amdgpu_buffer_rsrc_t ksrd, uint32_t kstride, int k_lo, int k_hi, int lim_all,
                                           const int (&lim)[RT], const uint4 (&q)[RT][D * (DT == DT_BF16 ? 2 : 4) / 32], float scale2,
