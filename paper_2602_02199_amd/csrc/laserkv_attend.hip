@@ -341,8 +341,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
 //   then on the two waves take alternate 32-key tiles, and their states meet in LDS at the end.  (With
 //   consecutive tiles in a workgroup a launch takes as long as the block's last rows: a 16k prefill of 32 heads in blocks
 //   of 2048 rows took 169 us a block on average, with pairs 151.)
-//   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  Over the cache's
-//   rows references are fixed, so that the output accumulators see nothing but matrix instructions, and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
+//   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  Over long key
+//   ranges references are fixed, so that the output accumulators see nothing but matrix instructions, and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
 //   instructions hardly overlap with matrix instructions here).
 //   Chunks alternate between two LDS stages and arrive through async_ld16, the next one while the current one is worked
 //   on, so one barrier per chunk suffices.
@@ -642,16 +642,23 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     }
   };
 
-  // Over the cache's rows (and in fp32) a row's reference is fixed: its maximum over the first tile of keys that it sees, plus
-  // HEADROOM (what a row sees is a prefix of the keys: a row that sees none of a wave's first tile sees none of the others).
-  // Each logit then costs an fma, an exponential and an add, and the output accumulators nothing but matrix instructions.
-  // Sums or outputs that overflow (from about a logit 145 above the first tile's on, in powers of two) make the workgroup
-  // repeat the pass with the exact maxima, which a sweep over the keys finds first.  (One workgroup in a round that repeats
-  // it costs three times the round; keys whose lengths spread by e^0.5 reach 140.)
-  // Over the block's own keys in bf16 it follows the maximum: the dominant key's probability is then a power of two and its
-  // bf16 exact, while against a fixed reference its rounding (up to 2^-8) goes into the output whole.  A maximum and a
-  // rescaling of the output per pair of tiles: 16k prefill in blocks of 2048 1358 -> 1378 us, causal blocks without a cache
-  // up to 7 %.
+  // In bf16 a row's reference follows the maximum, tile by tile: the dominant key's probability is then a power of two and
+  // its bf16 exact, while against another reference its rounding (up to 2^-8) goes into the output whole.  But where the
+  // key range has more than FIXED_KEYS cache rows, and in fp32, the reference over them is fixed: the row's maximum over the
+  // first tile of keys that it sees, plus HEADROOM (what a row sees is a prefix of the keys: a row that sees none of a
+  // wave's first tile sees none of the others).  Each logit then costs an fma, an exponential and an add, and the output
+  // accumulators nothing but matrix instructions.
+  // Measured: following costs 11 % over long ranges (window rows over 63 520 keys 147 -> 164 us, last block of a 128k
+  // prefill 3.71 -> 4.14 ms), 9 % over short ones (256 rows over 8000 keys, 288 a range: 28.2 -> 30.8 us) and over the
+  // block's own keys 3.4 % of a 16k prefill in blocks of 2048 (1330 -> 1375 us).  The line: up to there a fixed reference
+  // is the worse the longer the range (the first tile holds the maximum of fewer rows; 288 keys 1.6e-3 of the output
+  // against 2e-4), past it its error no longer changes.
+  // Sums or outputs that overflow against a fixed reference (from about a logit 145 above the first tile's on, in powers
+  // of two) make the workgroup repeat the pass with the exact maxima, which a sweep over the keys finds first.  (One
+  // workgroup in a round that repeats it costs three times the round; keys whose lengths spread by e^0.5 reach 140.)
+  constexpr int FIXED_KEYS = 320;
+  constexpr bool BF16 = DT == DT_BF16;
+  const bool fixed = !BF16 || hi0 - lo0 > FIXED_KEYS;
   int* redo = reinterpret_cast<int*>(smem + (size_t)2 * STAGE);  // one word behind the two stages
   if (tid == 0) *redo = 0;  // ordered before the writes after the first pass by the barriers in between
   // position in the split's chunks
@@ -725,14 +732,14 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
       land(0);
       lds_barrier();
     }
-    // a loop for each segment: with one for both, what the second needs costs the first registers
+    // A loop for fixed references, then one for those that follow the maximum (fp32: one for each segment): in a loop for
+    // both, what the second kind needs costs the first registers.
 #pragma unroll
-    for (int SEG = 0; SEG < 2; ++SEG) {
-      constexpr bool BF16 = DT == DT_BF16;
-      const bool follows = SEG == 1 && BF16;  // the reference follows the maximum
-      while (have && seg == SEG) {
+    for (int kind = 0; kind < 2; ++kind) {
+      const bool follows = kind == 1 && BF16;
+      while (have && (kind == 1 || (seg == 0 && fixed))) {
         if (nhave) prefetch(nseg, nkc, cur ^ 1);  // in flight while this chunk is worked on; every wave left that stage before the barrier
-        if (SEG && !joined && kc0 >= end_lo) {
+        if (kind && seg && !joined && kc0 >= end_lo) {
           joined = true;
           if (!upper) {
             bad = !finite();
@@ -745,11 +752,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
             if (pass) m_ref = ref_join;
           }
         }
-        const int wave_end = SEG ? min(hi1, upper || joined ? end_hi : end_lo) : hi0;
+        const int wave_end = kind && seg ? min(hi1, upper || joined ? end_hi : end_lo) : hi0;
         int left = present ? min(min(max((wave_end - kc0 + 31) >> 5, 0), TPC) - nt0, joined ? TPC / 2 : TPC) : 0;
-        const int lane_end = SEG ? min(hi1, blk_end_lane) : hi0;  // end of the keys of this segment the lane's row sees
+        const int lane_end = kind && seg ? min(hi1, blk_end_lane) : hi0;  // end of the keys of this segment the lane's row sees
         const int n_vis = lane_end - (kc0 + nt0 * 32);  // keys from the wave's first on that the lane's row sees
-        const bool whole = SEG ? __all(n_vis >= KC - nt0 * 32) : n_vis >= KC - nt0 * 32;
+        const bool whole = kind ? __all(n_vis >= KC - nt0 * 32) : n_vis >= KC - nt0 * 32;
         if (left > 0 && !has_ref && !follows) {
           has_ref = true;
           m_ref = maximum(k_at + cur * (STAGE * 16) + nt0 * K_TILE, n_vis);
@@ -757,21 +764,22 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
         }
         // a row without a visible key subtracts nothing: its hidden logits give 2^(NEG_BIG * scale2) = 0
         float m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
-        // Raises the reference to a pair of tiles' maximum, always: a branch around the rescaling doubles the output's registers.
-        auto raise = [&](const f32x16& acc0, const f32x16& acc1) {
-          float mx = acc0[0];
+        auto raise = [&](const f32x16& acc) {  // the reference, to the row's maximum in a tile
+          float mx = acc[0];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) mx = fmaxf(fmaxf(mx, acc0[r]), acc1[r]);
+          for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
           mx = half_pair_max(mx);
           const float m_new = mx > NEG_BIG ? fmaxf(m_ref, fmaf(mx, p.scale2, HEADROOM)) : m_ref;
-          const float f = fast_exp2(m_ref - m_new);
+          if (__any(m_new > m_ref && l_sum > 0.0f)) {  // nothing to rescale before the first keys
+            const float f = fast_exp2(m_ref - m_new);
+            l_sum *= f;
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) o[dt][r] *= f;
+          }
           m_ref = m_new;
           m_sub = m_new > NEG_BIG ? m_new : 0.0f;
-          l_sum *= f;
-#pragma unroll
-          for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[dt][r] *= f;
         };
         auto soft = [&](f32x16& acc) {
 #pragma unroll
@@ -820,11 +828,12 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
                 hide(acc0, n_vis - T * 32);
                 hide(acc1, n_vis - T * 32 - 32);
               }
-              raise(acc0, acc1);
               load_v_tr(vx, T * V_TILE, vf);
+              raise(acc0);
               soft(acc0);
               weigh(acc0, vf);
               load_v_tr(vx, (T + 1) * V_TILE, vf);
+              raise(acc1);
               soft(acc1);
               weigh(acc1, vf);
             }

@@ -1,9 +1,9 @@
 """How far attention is from 64 bits beyond what rounding probabilities to bf16 (relative error 2^-8 each) allows.
 
-Where a row's reference follows its maximum (decoding; the block's own keys in the kernel of many rows), the largest
-probability is a power of two and exact, so the output sum w_i v_i is off by at most 2^-8 sum over the OTHER keys of
-w_i |v_i|: far below 2^-8 of it for a row that one key dominates.  A row of the kernel of many rows whose largest weight is
-a key of the cache has no such key.  32-bit sums add at most 4e-6 of sum w_i |v_i|.
+Where a row's reference follows its maximum (decoding; in the kernel of many rows the block's own keys, and the cache's
+where a key range holds at most 320 of them), the largest probability is a power of two and exact, so the output
+sum w_i v_i is off by at most 2^-8 sum over the OTHER keys of w_i |v_i|: far below 2^-8 of it for a row that one key
+dominates.  32-bit sums add at most 4e-6 of sum w_i |v_i|.
 """
 import numpy as np
 import pytest
@@ -95,6 +95,17 @@ def test_rows_of_a_block_that_one_of_its_keys_dominates(case):
     out, _ = run_block(lib, q.to(DEV), kc.to(DEV), vc.to(DEV), n, kb.to(DEV), vb.to(DEV), 0, 0)
     hidden = np.arange(n + s_t)[None, :] > n + np.arange(s_t)[:, None]
     verdict([against_bound(out[i], weights(q[i], kk[i // g], hidden), vv[i // g], n) for i in range(0, h_q, 3)], f"block {s_t} after {n}")
+    lib.close()
+
+
+@pytest.mark.parametrize("h_q,h_kv,d,n_q,n", [(16, 4, 128, 64, 3000), (4, 1, 64, 40, 1900), (8, 2, 128, 300, 320)])
+def test_rows_over_a_short_cache_that_one_key_dominates(h_q, h_kv, d, n_q, n):
+    """Window rows whose key ranges hold few cache rows, and a block's rows over a small cache alone: the reference follows."""
+    g = h_q // h_kv
+    q, k, v = make_inputs(h_q, h_kv, d, n_q, n, "bf16", seed=n)
+    lib = binding.LaserKV(h_q, h_kv, d, "bf16", 8, 8, max_block=n_q, max_window=128, max_ctx_keys=0)
+    out, _ = run_block(lib, q.to(DEV), k.to(DEV), v.to(DEV), n, k[:, :0].to(DEV), v[:, :0].to(DEV), 0, 0)
+    verdict([against_bound(out[i], weights(q[i], k[i // g]), v[i // g]) for i in range(h_q)], f"rows {n_q} over {n}")
     lib.close()
 
 
