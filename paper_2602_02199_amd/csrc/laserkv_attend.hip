@@ -1015,15 +1015,15 @@ __global__ __launch_bounds__((D / 4) * COMB_SLICES) void attend_combine_kernel(A
 // all laserkv_set_row_lse needs.  No values are read and no output accumulators kept, so a workgroup takes up to 512
 // rows (a GQA group's whole window reads the keys once; with fewer rows the eight waves share them over different key
 // tiles).  Workgroup = (key split, group of 512 rows, KV head); the arithmetic is laserkv_rowstats.h.
-// 256 rows over 31 681 keys, 8 heads: 36.6 -> 24 us and 28.6 with the merge (before: sixteen waves of 32 rows, half of them
-// without rows); 512 rows over 63 520 keys 78 -> 76 us.
+// 256 rows over 31 681 keys, 8 heads: 25.4-27 us, 27.7 a call with the merge in a series of calls (31.2 before products and
+// exponentials were interleaved, 37 with sixteen waves of 32 rows, half of them without rows).
 // ---------------------------------------------------------------------------------------------
 constexpr int LSE_ROWS = 512;
 
 template <int DT, int D, int RT>
 __global__ __launch_bounds__(RS_THREADS) void attend_lse_kernel(AttendParams p) {
   constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const int idx = xcd_major(blockIdx.x, gridDim.x);
   const int split = idx % p.n_splits, rg = idx / p.n_splits % p.n_qgroups, h = idx / (p.n_splits * p.n_qgroups);
   const int k_lo = split * p.keys_per_split, k_hi = min(k_lo + p.keys_per_split, p.cache_len);
@@ -1043,8 +1043,7 @@ __global__ __launch_bounds__(RS_THREADS) void attend_lse_kernel(AttendParams p) 
 #pragma unroll
     for (int i = 0; i < NCH; ++i) q[r][i] = ld16(ptr + (2 * i + kg) * 16);
   }
-  const __amdgpu_buffer_rsrc_t ksrd =
-      make_srd(p.k_cache + (int64_t)h * p.cache_stride_head, (uint32_t)p.cache_len * (uint32_t)p.row_bytes);
+  const srd_words ksrd = make_srd_words(p.k_cache + (int64_t)h * p.cache_stride_head, (uint32_t)p.cache_len * (uint32_t)p.row_bytes);
   float ref[RT], sum[RT];
   row_stats<DT, D, RT>(smem, ksrd, (uint32_t)p.row_bytes, k_lo, k_hi, k_hi, lim, q, p.scale2, ks, wk, active, ref, sum);
   // the waves that shared rows meet in LDS (free after row_stats)

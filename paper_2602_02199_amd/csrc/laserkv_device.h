@@ -91,9 +91,9 @@ __device__ __forceinline__ srd_words make_srd_words(const void* base, uint32_t b
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
-__device__ __forceinline__ uint4 lds_ld16(uint32_t at) {
+__device__ __forceinline__ uint4 lds_ld16(uint32_t at, int constant = 0) {  // `constant` goes into the instruction
   typedef uint32_t u32x4_lds __attribute__((ext_vector_type(4)));
-  const u32x4_lds v = *(__attribute__((address_space(3))) const u32x4_lds*)(uintptr_t)at;
+  const u32x4_lds v = *(__attribute__((address_space(3))) const u32x4_lds*)((__attribute__((address_space(3))) const char*)(uintptr_t)at + constant);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ void async_ld16(srd_words srd, uint32_t lane_offset, uint32_t uniform_offset, uint32_t lds) {

@@ -13,8 +13,9 @@
 //   then the select + append kernel of laserkv_kernels.hip over all groups.
 //
 // In both sweeps the window rows stay in registers for the whole key range (two 32-row tiles per wave, so a key
-// fragment read from LDS feeds two matrix instructions) and the keys stream through two LDS stages, the next chunk's
-// loads in flight in registers while the current one is worked on: one barrier per chunk.
+// fragment read from LDS feeds two matrix instructions) and the keys stream through LDS stages, one barrier per chunk: the
+// statistics through four, filled by asynchronous loads, the scores through two, the next chunk's loads in flight in
+// registers.
 #include "laserkv_device.h"
 #include "laserkv_kernels.h"
 #include "laserkv_rowstats.h"
@@ -177,7 +178,7 @@ template <int DT, int D, int RT>
 __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) {
   constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
   static_assert(LY_THREADS == RS_THREADS, "row_stats works with eight waves");
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const int lin = xcd_major(blockIdx.x, gridDim.x);
   const int sp = lin % p.stat_splits;
   const LayerGroup gr = layer_group(p, lin / p.stat_splits);
@@ -202,8 +203,8 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
     for (int i = 0; i < NCH; ++i) q[r][i] = ld16(ptr + (2 * i + kg) * 16);
   }
   const uint32_t kstride = (uint32_t)p.k.stride_row;
-  const __amdgpu_buffer_rsrc_t ksrd = make_srd(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)(gr.lo - gr.n_ctx) * p.k.stride_row,
-                                               (uint32_t)n_keys * kstride);
+  const srd_words ksrd = make_srd_words(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)(gr.lo - gr.n_ctx) * p.k.stride_row,
+                                        (uint32_t)n_keys * kstride);
   float ref[RT], sum[RT];
   row_stats<DT, D, RT>(smem, ksrd, kstride, k_lo, k_hi, lim0, lim, q, p.scale2, ks, wk, active, ref, sum);
   if (!active) return;

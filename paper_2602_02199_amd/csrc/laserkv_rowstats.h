@@ -9,129 +9,279 @@ namespace lkv {
 constexpr int RS_WAVES = 8;
 constexpr int RS_THREADS = RS_WAVES * 64;
 
-// keys per LDS chunk; two chunks fill 139 KiB
-constexpr int row_stats_chunk(int row_bytes) { return row_bytes <= 256 ? 256 : 128; }
-constexpr size_t row_stats_lds(int row_bytes) { return (size_t)2 * row_stats_chunk(row_bytes) * (row_bytes + 16); }
+// Keys stand in a ring of LDS stages as the asynchronous loads leave them: 1024 bytes at a time, which is RPG rows, PAD
+// bytes between two such groups.  Chunk c of row r lies at position c ^ (r % RPG) of its row: eight consecutive rows then
+// hold one chunk in eight different sets of banks, and a lane's operand chunks are RPG / 2 addresses plus constants (with
+// rows permuted as a whole every chunk of a row has an address of its own, an addition each per tile).
+template <int CH>  // 16-byte chunks per row
+struct KeyRing {
+  static constexpr int RPG = 64 / CH;
+  static constexpr int PAD = RPG < 8 ? RPG * 16 : 0;
+  static constexpr int GROUP = 1024 + PAD;
+  static constexpr int TILE = 32 / RPG * GROUP;      // bytes of 32 keys
+  static constexpr int KC = CH <= 16 ? 128 : 64;     // keys per stage
+  static constexpr int STAGE = KC / 32 * TILE;
+  static constexpr int STAGES = 4;
+  static constexpr int LOADS = KC * CH / RS_THREADS; // loads per thread and stage
+  static constexpr int NA = RPG > 2 ? RPG / 2 : 1;   // different addresses of a lane's operand chunks
+};
+constexpr size_t row_stats_lds(int row_bytes) {
+  return row_bytes <= 128 ? (size_t)KeyRing<8>::STAGES * KeyRing<8>::STAGE
+         : row_bytes <= 256 ? (size_t)KeyRing<16>::STAGES * KeyRing<16>::STAGE : (size_t)KeyRing<32>::STAGES * KeyRing<32>::STAGE;
+}
 
 // Keys k_lo .. k_hi - 1 of the descriptor's rows against RT 32-row tiles per wave (q: the rows' MFMA fragments).  Waves
-// that share rows take different 32-key tiles (ks, ks + wk, ...).  Keys are the A operand and rows the B operand, so a
-// lane owns a row per tile; its two halves hold the same rows over different keys and are merged before the end.
+// that share rows take different 32-key tiles (ks, ks + wk, ...; active, ks and wk are the same in all lanes of a wave).
+// Keys are the A operand and rows the B operand, so a lane owns a row per tile; its two halves hold the same rows over
+// different keys and are merged before the end.
 // A row sees the keys below its lim[r]; every row sees the keys up to lim_all.  The reference is the maximum over the
 // lane's first tile plus HEADROOM; complete tiles after it cost one fma, one exponential and one add per logit.  When a
-// sum has grown past 1e34 after a chunk (a logit 137 above the first tile's, in powers of two; a thousand such sums can
-// still be merged), the wave repeats that chunk from LDS with a reference that follows the maximum.  References are
-// whole numbers, so that moving one rescales its sum exactly.
-// What bounds it: matrix and vector work of a SIMD hardly overlap (16 matrix instructions of 32 clocks and 64 vector
-// instructions of 4, 32 exponentials of 8 per pair of tiles).  512 rows over 63 520 keys of 8 heads 76 us = 870 TFLOP/s
-// with the merge, a 128k layer 181 us = 800, 256 rows over 31 681 keys 28.6 us = 580 (start and merge are a third); a
-// plain bf16 product reaches 1380.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
+// tile lifts a sum past 1e34 (a logit 137 above the first tile's, in powers of two; a thousand such sums can still be
+// merged), it is added again, its logits being in registers still, with a reference that follows the maximum.  References
+// are whole numbers, so that moving one rescales its sum exactly.
+// The products of a tile and the exponentials of the tile before it are independent: they are issued alternately, four
+// vector instructions and two exponentials (40 clocks of the vector unit, issue of the matrix instruction included) beside
+// every matrix instruction (32 clocks of the matrix unit).  Loads run two to three chunks ahead, so that one barrier per
+// chunk publishes what has landed and frees the stage before it; the tiles of a wave run on across it.
+// What bounds it: at a full clock the vector unit; over a whole layer the clock, which power sets (the same launch takes
+// 180 us on random keys from HBM, 138 when they come from the caches, 116 when they are zeros).  512 rows over 63 520 keys
+// of 8 heads, 128k layer of 256 groups: 172-181 -> 154-160 us = 910-940 TFLOP/s; 256 rows over 31 681 keys 28.4-30 ->
+// 25.4-27 us.  Before: one tile after another, products, then exponentials; the first product of every chunk waited for the
+// next chunk's loads.  Barriers cost: chunks of 64 keys (eight stages) 174 us, of 256 (two stages, the pipeline drained at
+// each) 161.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
 template <int DT, int D, int RT>
-__device__ __forceinline__ void row_stats(uint4* smem, __amdgpu_buffer_rsrc_t ksrd, uint32_t kstride, int k_lo, int k_hi, int lim_all,
-                                          const int (&lim)[RT], const uint4 (&q)[RT][D * (DT == DT_BF16 ? 2 : 4) / 32], float scale2,
+__device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t kstride, int k_lo, int k_hi, int lim_all,
+                                          const int (&lim)[RT], uint4 (&q)[RT][D * (DT == DT_BF16 ? 2 : 4) / 32], float scale2,
                                           int ks, int wk, bool active, float (&ref)[RT], float (&sum)[RT]) {
-  constexpr int CH = D * (DT == DT_BF16 ? 2 : 4) / 16, NCH = CH / 2, CHP = CH + 1;
-  constexpr int KC = row_stats_chunk(CH * 16), TPC = KC / 32;
-  constexpr int KL = KC * CH / RS_THREADS;
-  constexpr int RPL = RS_THREADS / CH;
-  const int tid = threadIdx.x, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
-  const uint32_t k_row = tid / CH, k_col = tid % CH;
-  uint4 kpre[KL];
-  auto prefetch = [&](int kc0) {
+  constexpr int CH = D * (DT == DT_BF16 ? 2 : 4) / 16, NCH = CH / 2;
+  using L = KeyRing<CH>;
+  constexpr int KC = L::KC, TPC = KC / 32, S = L::STAGES;
+  constexpr bool PIPED = RT * NCH <= 16;  // registers for a second tile's logits
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int n_keys = k_hi - k_lo;
+  const int n_tiles = (n_keys + 31) >> 5, n_chunks = (n_keys + KC - 1) / KC;
+  const int n_whole = max(min(k_hi, lim_all + 1) - k_lo, 0) >> 5;  // tiles of which every row sees every key
+
+  const uint32_t lds0 = lds_offset(smem);
+  // loads: wave w brings the w-th of every RS_WAVES groups of a stage
+  const uint32_t ld_row = lane / CH, ld_col = ((lane % CH) ^ (ld_row % L::RPG)) * 16;
+  const uint32_t ld_off = ld_row * kstride + ld_col;
+  auto prefetch = [&](int c) {
+    const int row = c * KC + wave * L::RPG;  // of the range: the first group's first
+    uint32_t dst = lds0 + (c % S) * L::STAGE + wave * L::GROUP;
+    if ((c + 1) * KC <= n_keys) {
+      uint32_t src = (uint32_t)(k_lo + row) * kstride;
 #pragma unroll
-    for (int u = 0; u < KL; ++u) kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * RPL) * kstride + k_col * 16);
+      for (int u = 0; u < L::LOADS; ++u, src += RS_WAVES * L::RPG * kstride, dst += RS_WAVES * L::GROUP) async_ld16(ksrd, ld_off, src, dst);
+    } else if (c < n_chunks) {  // rows past the end repeat the last one
+#pragma unroll 1
+      for (int u = 0; u < L::LOADS; ++u, dst += RS_WAVES * L::GROUP)
+        async_ld16(ksrd, (uint32_t)(k_lo + min(row + u * RS_WAVES * L::RPG + (int)ld_row, n_keys - 1)) * kstride + ld_col, 0u, dst);
+    }
   };
-  auto store = [&](uint4* buf) {
-#pragma unroll
-    for (int u = 0; u < KL; ++u) buf[(k_row + u * RPL) * CHP + k_col] = kpre[u];
+  // chunks that have to be there beyond the open one for a wave to read its next tile ahead of time
+  const int ahead = min(max(wk / TPC, 1), S - 2);
+  int open = 0, issued = min(ahead + 1, n_chunks);
+  auto await = [&](int c) {  // chunks up to c
+    const int flying = min(issued - 1 - c, S - 2 - 1);
+    if (flying <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (flying == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::LOADS) : "memory");
+    else if (flying == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L::LOADS) : "memory");
+    else if (flying == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * L::LOADS) : "memory");
+    else if (flying == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * L::LOADS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(5 * L::LOADS) : "memory");
+  };
+  // Opens chunk c: it and the `ahead` ones behind it have landed for every wave, and every wave has left chunk c - 1, whose
+  // stage takes the next loads.
+  auto open_to = [&](int c) {
+    while (open < c) {
+      ++open;
+      await(min(open + ahead, n_chunks - 1));
+      lds_barrier();
+      prefetch(open + S - 1);
+      issued = min(open + S, n_chunks);
+    }
   };
 
+  // LDS addresses of the lane's row in tile 0: chunk 2i + kg is at at[i % NA] + i / NA * (NA * 32)
+  uint32_t at[L::NA];
+#pragma unroll
+  for (int i = 0; i < L::NA; ++i) at[i] = lds0 + rl / L::RPG * L::GROUP + rl % L::RPG * (CH * 16) + (((2 * i + kg) ^ (rl % L::RPG)) * 16);
+  uint4 kf[NCH];
+  auto tile_off = [&](int t) -> uint32_t { return (uint32_t)(t / TPC % S) * L::STAGE + (uint32_t)(t % TPC) * L::TILE; };
+  uint32_t from[L::NA];  // the lane's addresses in the tile that is read
+  auto read_from = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < L::NA; ++i) from[i] = opaque(at[i] + tile_off(t));
+  };
+  auto load = [&](int i) { kf[i] = lds_ld16(from[i % L::NA], i / L::NA * (L::NA * 32)); };
+
+  // the first chunks' loads, then the rows that the caller has on their way, then the other chunks': the wait for the rows
+  // covers all loads issued before it
+#pragma unroll 1
+  for (int c = 0; c <= ahead; ++c) prefetch(c);
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
     ref[r] = NEG_BIG;
     sum[r] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) landed(q[r][i]);
   }
-  bool first = true;  // no tile yet: the lane has no reference
-  prefetch(k_lo);
-  store(smem);
+  async_wait();
   lds_barrier();
-  int cur = 0;
-  for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
-    const bool more = kc0 + KC < k_hi;
-    if (more) prefetch(kc0 + KC);
-    const uint4* sK = smem + (size_t)cur * KC * CHP;
-    float kept[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) kept[r] = sum[r];
-    bool fixed_ref = !first;  // wave-uniform
 #pragma unroll 1
-    for (int attempt = active ? 0 : 2; attempt < 2; ++attempt) {
-#pragma unroll 1
-      for (int nt = ks; nt < TPC; nt += wk) {
-        const int kbase = kc0 + nt * 32;
-        if (kbase >= k_hi) break;  // wave-uniform
-        f32x16 acc[RT];
+  for (int c = ahead + 1; c < S; ++c) prefetch(c);
+  issued = min(S, n_chunks);
+
+  bool first = true;      // no tile yet: the lane has no reference
+  // one tile's logits, the reference following the maximum
+  auto careful = [&](const f32x16 (&acc)[RT], int t) {
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
+    for (int r = 0; r < RT; ++r) {
+      const int n_vis = t < n_whole ? 32 : min(k_hi, lim[r]) - (k_lo + t * 32);
+      if (acc_row(0, kg) < n_vis) {  // a lane that sees none of its keys keeps its state
+        float mx = acc[r][0];
 #pragma unroll
-          for (int e = 0; e < 16; ++e) acc[r][e] = 0.0f;
-        const uint4* krow = sK + (size_t)(nt * 32 + rl) * CHP + kg;
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-          const uint4 kf = krow[2 * i];
-#pragma unroll
-          for (int r = 0; r < RT; ++r) Mma<DT>::run(acc[r], kf, q[r][i]);
-        }
-        const bool whole = kbase + 32 <= k_hi && kbase + 31 <= lim_all;  // every row sees every key
-        if (whole && fixed_ref) {
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) sum[r] += fast_exp2(fmaf(acc[r][e], scale2, -ref[r]));
-        } else {
-#pragma unroll
-          for (int r = 0; r < RT; ++r) {
-            const int n_vis = whole ? 32 : min(k_hi, lim[r]) - kbase;
-            if (acc_row(0, kg) < n_vis) {  // a lane that sees none of its keys keeps its state
-              float mx = acc[r][0];
-#pragma unroll
-              for (int e = 1; e < 16; ++e) mx = acc_row(e, kg) < n_vis ? fmaxf(mx, acc[r][e]) : mx;
-              const float nref = fmaxf(ref[r], ceilf(mx * scale2));  // scale2 > 0
-              sum[r] *= fast_exp2(ref[r] - nref);
-              ref[r] = nref;
-#pragma unroll
-              for (int e = 0; e < 16; ++e)
-                sum[r] += acc_row(e, kg) < n_vis ? fast_exp2(fmaf(acc[r][e], scale2, -nref)) : 0.0f;
-            }
-          }
-          if (first) {
-            fixed_ref = true;
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-              ref[r] += HEADROOM;
-              sum[r] = __builtin_amdgcn_ldexpf(sum[r], -(int)HEADROOM);
-            }
-          }
-          first = false;
-        }
-      }
-      // sums that have grown too large against the fixed reference: the chunk (still in LDS) once more, the reference
-      // following the maximum
-      bool over = false;
-#pragma unroll
-      for (int r = 0; r < RT; ++r) over |= !(sum[r] < 1.0e34f);
-      if (attempt || !__any(over)) break;
-      fixed_ref = false;
-#pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const float nref = kept[r] > 1.0e10f ? ref[r] + ceilf(fast_log2(kept[r])) : ref[r];
-        sum[r] = kept[r] * fast_exp2(ref[r] - nref);
+        for (int e = 1; e < 16; ++e) mx = acc_row(e, kg) < n_vis ? fmaxf(mx, acc[r][e]) : mx;
+        const float nref = fmaxf(ref[r], ceilf(mx * scale2));  // scale2 > 0
+        sum[r] *= fast_exp2(ref[r] - nref);
         ref[r] = nref;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          sum[r] += acc_row(e, kg) < n_vis ? fast_exp2(fmaf(acc[r][e], scale2, -nref)) : 0.0f;
       }
     }
-    if (more) store(smem + (size_t)(cur ^ 1) * KC * CHP);
-    cur ^= 1;
-    lds_barrier();
+    if (first) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        ref[r] += HEADROOM;
+        sum[r] = __builtin_amdgcn_ldexpf(sum[r], -(int)HEADROOM);
+      }
+    }
+    first = false;
+  };
+  float kept[RT];
+  // sums that have grown too large: the tile once more, from the sums before it
+  auto check = [&](const f32x16 (&acc)[RT], int t) {
+    bool over = false;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) over |= !(sum[r] < 1.0e34f);
+    if (!__any(over)) return;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const float nref = kept[r] > 1.0e10f ? ref[r] + ceilf(fast_log2(kept[r])) : ref[r];
+      sum[r] = kept[r] * fast_exp2(ref[r] - nref);
+      ref[r] = nref;
+    }
+    careful(acc, t);
+  };
+  auto add = [&](const f32x16 (&acc)[RT]) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) kept[r] = sum[r];
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+#pragma unroll
+      for (int r = 0; r < RT; ++r) sum[r] += fast_exp2(fmaf(acc[r][e], scale2, -ref[r]));
+  };
+  const bool roll = wk <= ahead * TPC;  // the next tile's keys are read while the current ones are multiplied
+  int t = active ? ks : n_tiles, pending = -1;
+  bool here = false;                    // kf holds tile t
+  // the products of tile t, and what the tile before it still has to add
+  auto fire = [&](f32x16 (&next)[RT], const f32x16 (&done)[RT]) {
+    open_to(t / TPC);
+    if (!here) {
+      read_from(t);
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) load(i);
+    }
+    here = roll;
+    read_from(roll && t + wk < n_tiles ? t + wk : t);
+    const bool fast = pending >= 0 && pending < n_whole && !first;  // wave-uniform
+    auto products = [&]() {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) next[r][e] = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) Mma<DT>::run(next[r], kf[i], q[r][i]);
+        load(i);
+      }
+    };
+    if (fast) {
+      products();
+      add(done);
+      if (DT == DT_BF16) {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // a matrix instruction
+            __builtin_amdgcn_sched_group_barrier(0x002, 32 / NCH, 0);  // vector instructions beside it
+            __builtin_amdgcn_sched_group_barrier(0x400, 16 / NCH, 0);  // exponentials
+          }
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);           // a read from LDS
+        }
+      }
+      check(done, pending);
+    } else {
+      products();
+      if (pending >= 0) careful(done, pending);
+    }
+    pending = t;
+    t += wk;
+  };
+  auto drain = [&](const f32x16 (&done)[RT]) {
+    if (pending < 0) return;
+    if (pending < n_whole && !first) {
+      add(done);
+      check(done, pending);
+    } else {
+      careful(done, pending);
+    }
+  };
+  f32x16 acc0[RT], acc1[RT];
+  if (PIPED) {
+    const bool even = wave < RS_WAVES / 2;  // the two waves of a SIMD take turns at being served first
+#pragma unroll 1
+    for (;;) {
+      if (t >= n_tiles) {
+        drain(acc1);
+        break;
+      }
+      even ? __builtin_amdgcn_s_setprio(1) : __builtin_amdgcn_s_setprio(0);
+      fire(acc0, acc1);
+      if (t >= n_tiles) {
+        drain(acc0);
+        break;
+      }
+      even ? __builtin_amdgcn_s_setprio(0) : __builtin_amdgcn_s_setprio(1);
+      fire(acc1, acc0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+  } else {
+#pragma unroll 1
+    for (; t < n_tiles; t += wk) {
+      open_to(t / TPC);
+      read_from(t);
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc0[r][e] = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        load(i);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) Mma<DT>::run(acc0[r], kf[i], q[r][i]);
+      }
+      pending = t;
+      drain(acc0);
+    }
   }
+  open_to(n_chunks - 1);
+  async_wait();
+  lds_barrier();  // every wave has left the stages
 #pragma unroll
   for (int r = 0; r < RT; ++r) lse_merge(ref[r], sum[r], half_other(ref[r], kg), half_other(sum[r], kg));
 }
