@@ -65,7 +65,7 @@ __global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParam
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
   constexpr int NPL = LY_CODE_PLANES * CH / LY_CODE_THREADS;  // 16-byte pieces of hyperplanes per thread at most
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const LayerGroup gr = layer_group(p, blockIdx.x);
   const bool wide = p.cells == nullptr;
   const int words = (1 << p.n_bits) >= 32 ? (1 << p.n_bits) >> 5 : 1;  // groups of 32 bins per table
@@ -223,6 +223,11 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
 // run beside the matrix work of the next.  Waves 4-7 hold the hyperplanes (PT tiles each): they take the sign bits,
 // bring the keys into LDS, and finish the previous chunk (sums and sign bits meet in LDS, two buffers): the sum over
 // the score waves, and per key and table one probe of the table's cells.  Every SIMD runs one wave of either kind.
+// The two kinds of wave of a SIMD compete: score waves whose instructions are in a fixed order (four vector instructions
+// and two exponentials beside each matrix instruction) leave the hashing wave little while they run, and it is the one that
+// the barrier waits for (128k layer 241 -> 258 us), so hashing waves are served first.  Both changes, and the partials and
+// cells fetched without a round trip each: score kernel of a 16k layer 26.5 -> 24.3 us, of 64k 86 -> 76, of groups of eight
+// (512 hyperplanes) 317 -> 275, of the 128k layer 240 -> 239, where the clock is set by power.
 // ---------------------------------------------------------------------------------------------
 constexpr int LY_HALF = LY_WAVES / 2;  // waves of either kind
 
@@ -234,10 +239,9 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
   constexpr int NLD = LY_THREADS / 2;        // threads that load keys
   constexpr int KL = KC * CH / NLD;
   constexpr int RPL = NLD / CH;
-  constexpr int AT = RT > PT ? RT : PT;
   constexpr int TP = RT > 1 ? 2 : 1;         // row tiles per step
   constexpr int NP = RT / TP;                // steps per key tile
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const int lin = xcd_major(blockIdx.x, gridDim.x);
   const LayerGroup gr = layer_group(p, lin / p.score_splits);
   const int k_lo = (lin % p.score_splits) * p.score_keys, k_hi = min(k_lo + p.score_keys, gr.s_t);
@@ -276,11 +280,9 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
 #pragma unroll
     for (int u = 0; u < KL; ++u) buf[(k_row + u * RPL) * CHP + k_col] = kpre[u];
   };
-  if (hash) prefetch(k_lo);
-
   // the row's log-sum-exp (exp2 domain): merged from the partials of layer_stats_kernel and the caller's outside
-  // keys, or the caller's complete one
-  {
+  // keys, or the caller's complete one; and the cells
+  auto rows_and_cells = [&]() {
     const int m = tid;
     float lse = 1.0e30f;  // padding rows: probability 0
     if (m < p.m_rows) {
@@ -291,9 +293,13 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       } else {
         float mm = NEG_BIG, ss = 0.0f;
         const float2* part = p.part + ((size_t)gr.g * p.m_rows + m) * p.n_parts;
-        for (int i = 0; i < p.n_parts; ++i) {
-          const float2 v = part[i];
-          lse_merge(mm, ss, v.x, v.y);
+        for (int i0 = 0; i0 < p.n_parts; i0 += 8) {  // eight loads in flight (one after another: a round trip each)
+          float2 v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = part[min(i0 + u, p.n_parts - 1)];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (i0 + u < p.n_parts) lse_merge(mm, ss, v[u].x, v[u].y);
         }
         if (outside) lse_merge(mm, ss, ext, 1.0f);
         lse = lse_log2(mm, ss);
@@ -302,29 +308,32 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     sLse[m] = lse;
     const int mc = min(m, p.m_rows - 1);
     sLim[m] = lim0 + mc - div_w(mc, p.w_magic) * p.w;
-  }
-  if (p.cells) {
-    const int n_cw = p.n_tables * p.cell_words;
-    const uint32_t* src = p.cells + (size_t)gr.g * n_cw;
-    if ((n_cw & 3) == 0) {
-      for (int i = tid; i < n_cw / 4; i += LY_THREADS) *reinterpret_cast<uint4*>(sCells + 4 * i) = ld16(src + 4 * i);
-    } else {
-      for (int i = tid; i < n_cw; i += LY_THREADS) sCells[i] = src[i];
+    if (p.cells) {
+      const int n_cw = p.n_tables * p.cell_words;
+      const uint32_t* src = p.cells + (size_t)gr.g * n_cw;
+      const int whole = (n_cw & 3) == 0 ? n_cw >> 8 : 0;  // KiB that go straight to LDS
+      const srd_words csrd = make_srd_words(src, (uint32_t)n_cw * 4u);
+      for (int kb = wave; kb < whole; kb += LY_WAVES) async_ld16(csrd, lane * 16, kb << 10, lds_offset(sCells) + (kb << 10));
+      for (int i = (whole << 8) + tid; i < n_cw; i += LY_THREADS) sCells[i] = src[i];
+      async_wait();
     }
-  }
-  uint4 a[AT][NCH];
-#pragma unroll
-  for (int t = 0; t < AT; ++t) {
-    const int tile = first + LY_HALF * t;
-    const char* ptr = hash ? p.planes + (size_t)min(tile * 32 + plane_row(rl), p.n_planes - 1) * (D * ES)
-                           : layer_row(p, gr, min(tile * 32 + rl, p.m_rows - 1));
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) a[t][i] = ld16(ptr + (2 * i + kg) * 16);
-  }
-  if (hash) store(sK);
-  __syncthreads();
-
+  };
+  // Operands of a wave's tiles.  Each kind of wave has its own, complete before its loop: what the compiler waits for at
+  // their first use there would be waited for in every round.
   if (!hash) {
+    uint4 a[RT][NCH];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const char* ptr = layer_row(p, gr, min((first + LY_HALF * t) * 32 + rl, p.m_rows - 1));
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) a[t][i] = ld16(ptr + (2 * i + kg) * 16);
+    }
+    rows_and_cells();
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) landed(a[t][i]);
+    __syncthreads();
     // logits of one step: row tiles t0, t0 + 1 against the 32 keys at LDS rows kt * 32 ..
     auto logits = [&](const uint4* stage, int kt, int t0, f32x16* acc) {
 #pragma unroll
@@ -369,6 +378,12 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       }
       return c;
     };
+    constexpr int PER = 16 / NCH;  // logits of a step per matrix instruction
+    auto lse_of = [&](int t0, int g) {  // of four consecutive rows of the lane
+      return *reinterpret_cast<const float4*>(&sLse[(first + LY_HALF * (t0 + g % TP)) * 32 + acc_row(4 * (g / TP), kg)]);
+    };
+    uint4 kf[NCH];
+    float4 l[2] = {lse_of(0, 0), lse_of(0, 1)};  // those of the next logits
     int cur = 0;
     for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
       const uint4* stage = sK + (size_t)cur * KC * CHP;
@@ -378,27 +393,55 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
         if (kg == 0) col_dst[kt * 32 + rl] = col;
       };
       if (kstep == 1 && kc0 + KC <= k_hi && kc0 + KC - 1 <= lim0) {  // workgroup-uniform: a complete chunk that every row sees
+        const uint4* brow = stage + rl * CHP + kg;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) kf[i] = brow[2 * i];
         f32x16 acc[2][TP];
-        float col = 0.0f;
-        logits(stage, 0, 0, acc[0]);
+        float c[TP];
 #pragma unroll
-        for (int s = 0; s < TPC * NP; ++s) {
-          if (s + 1 < TPC * NP) logits(stage, (s + 1) / NP, (s + 1) % NP * TP, acc[(s + 1) & 1]);
-          col += pooled(acc[s & 1], s % NP * TP);
-          if (DT == DT_BF16 && RT <= 2) {
-            // a matrix instruction, then what the vector unit can do beside it (two row tiles: 3.5 % of a layer; with four
-            // the compiler's own order is the faster one)
+        for (int t = 0; t < TP; ++t) c[t] = 0.0f;
 #pragma unroll
-            for (int q = 0; q < NCH * TP; ++q) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // MFMA
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // LDS read
-              __builtin_amdgcn_sched_group_barrier(0x002, 32 / NCH, 0);      // VALU
-              __builtin_amdgcn_sched_group_barrier(0x400, 16 / NCH, 0);      // exponentials
+        for (int s = 0; s <= TPC * NP; ++s) {
+          // the products of step s beside the probabilities of step s - 1; what stands between two fences is issued
+          // beside one matrix instruction
+          const bool mul = s < TPC * NP, sum = s > 0, newk = mul && (s + 1) % NP == 0 && s + 1 < TPC * NP;
+          f32x16* next = acc[s & 1];
+          f32x16* done = acc[(s + 1) & 1];
+          const int t0 = s % NP * TP, d0 = (s + NP - 1) % NP * TP;
+          float v[2][PER];
+          if (mul)
+#pragma unroll
+            for (int t = 0; t < TP; ++t)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) next[t][e] = 0.0f;
+#pragma unroll
+          for (int j = 0; j < NCH * TP; ++j) {
+            const int i = j / TP, t = j % TP;
+            if (mul) Mma<DT>::run(next[t], a[t0 + t][i], kf[i]);
+            if (newk && t == TP - 1) kf[i] = brow[(s + 1) / NP * 32 * CHP + 2 * i];
+            if (sum) {
+#pragma unroll
+              for (int k = 0; k < PER; ++k) {
+                const int q = j * PER + k, g = q / 4;  // logits of four consecutive rows, tile by tile, and their log-sum-exps
+                const float4 l4 = l[g & 1];
+                const float ls = (q & 3) == 0 ? l4.x : (q & 3) == 1 ? l4.y : (q & 3) == 2 ? l4.z : l4.w;
+                v[j & 1][k] = fast_exp2(fmaf(done[g % TP][4 * (g / TP) + (q & 3)], p.scale2, -ls));
+                if ((q & 3) == 3) l[g & 1] = g + 2 < 4 * TP ? lse_of(d0, g + 2) : lse_of(t0, g + 2 - 4 * TP);
+              }
+              if (j > 0)
+#pragma unroll
+                for (int k = 0; k < PER; ++k) c[((j - 1) * PER + k) / 4 % TP] += v[(j - 1) & 1][k];
             }
+            __builtin_amdgcn_sched_barrier(0);
           }
-          if (s % NP == NP - 1) {
-            put(s / NP, col);
-            col = 0.0f;
+          if (sum) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) c[((NCH * TP - 1) * PER + k) / 4 % TP] += v[(NCH * TP - 1) & 1][k];
+            if (s % NP == 0) {
+              put(s / NP - 1, TP > 1 ? c[0] + c[TP - 1] : c[0]);
+#pragma unroll
+              for (int t = 0; t < TP; ++t) c[t] = 0.0f;
+            }
           }
         }
       } else if (active) {
@@ -423,6 +466,22 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
   }
 
   // the hashing waves
+  __builtin_amdgcn_s_setprio(1);
+  prefetch(k_lo);
+  uint4 a[PT][NCH];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) {
+    const char* ptr = p.planes + (size_t)min((first + LY_HALF * t) * 32 + plane_row(rl), p.n_planes - 1) * (D * ES);
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) a[t][i] = ld16(ptr + (2 * i + kg) * 16);
+  }
+  rows_and_cells();
+  store(sK);
+#pragma unroll
+  for (int t = 0; t < PT; ++t)
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) landed(a[t][i]);
+  __syncthreads();
   const uint32_t code_mask = (1u << p.n_bits) - 1u;
   const uint32_t cell_max = p.cell_log == 2 ? 255u : 15u;  // full cells of 8 and 4 bits (cell_log 2, 3; those of 16 bits hold every count)
   // sums over the score waves and collision counts of the chunk whose first key is kc0: two lanes per key
