@@ -89,12 +89,6 @@ int env_int(const char* name, int dflt) {
   return atoi(v);
 }
 
-int bits_for(int64_t v) {
-  int b = 1;
-  while ((int64_t(1) << b) <= v) ++b;
-  return b;
-}
-
 // Runs `launch` bracketed by an event pair when the context is profiling.
 template <typename F>
 hipError_t timed(laserkv_ctx* ctx, int kind, hipStream_t st, F launch) {
@@ -489,7 +483,6 @@ int select_impl(laserkv_ctx* ctx,
   lp.n_local = n_local;
   lp.k_exact = k_exact;
   lp.k_lsh = k_lsh;
-  lp.cnt_bits = bits_for((int64_t)m_rows * c.lsh_tables);
   lp.s_exact = dbg_s_exact ? ctx->s_exact : nullptr;
   lp.keep = keep_idx;
 
@@ -842,7 +835,6 @@ int laserkv_compress_layer(laserkv_ctx* ctx,
   lp.n_local = nl;
   lp.k_exact = ke;
   lp.k_lsh = kl;
-  lp.cnt_bits = bits_for((int64_t)G * w * c.lsh_tables);
   lp.s_exact = nullptr;
   lp.keep = nullptr;
   const lkv::SelectLayer ly = {p.s_stride, n_blocks - 1, s_last, na1, nl1, ke1, kl1, keep_last};
@@ -1053,7 +1045,6 @@ int laserkv_select_consensus(laserkv_ctx* ctx, const float* score_acc, const int
   lp.n_local = n_local;
   lp.k_exact = k_exact;
   lp.k_lsh = k_lsh;
-  lp.cnt_bits = 31;  // the kernel reads the largest count and uses only the digits it needs
   lp.s_exact = nullptr;
   lp.keep = keep_idx;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);

@@ -803,16 +803,19 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Selection.  One 1024-thread workgroup per KV head; thread t owns the EPT consecutive positions
-// starting at t*EPT, so thread order is index order.  The k-th largest key is found by a radix
-// descent over 8-bit digits from the top (LDS histogram, four interleaved copies against same-
-// address atomics), which also yields how many keys equal to the threshold are still needed; those
-// are taken in index order via a prefix count.
+// Selection.  One workgroup of 256 to 1024 threads per KV head; thread t owns the EPT consecutive positions
+// starting at t*EPT, so thread order is index order.  The k-th largest key is found by narrowing an
+// interval of values that is known to hold it: a histogram of 1024 equal parts of the interval in LDS, then the
+// part with the wanted rank; where at most 64 keys are left they are ranked against each other.  The first interval
+// ends at the largest key, so that its parts are fine where the keys are (scores: 64 parts per octave over the 16
+// octaves below the largest, lower keys together in the first part; counts below 1024: one value each).  How many keys
+// equal to the threshold are still needed falls out; those are taken in index order via a prefix count.
 //
-// The kernel is a chain of short workgroup-wide phases, so each round of the descent is kept to ONE
-// barrier: after the histogram is complete every wave scans it redundantly (lane l owns digits
-// 4l..4l+3) and learns the chosen digit through a wave broadcast; nothing goes back through LDS.  Three
-// histogram buffers rotate, the one read in round r being cleared during round r + 1 and reused in
+// The kernel is a chain of short workgroup-wide phases (2048 positions: 13 400 clocks before the copy, 14 300 by 8-bit
+// digits from the top, whose first says little about a float, with every wave ranking all that is left), so each round is kept to
+// ONE barrier: after the histogram is complete every wave scans it redundantly (lane l owns parts
+// 16l..16l+15, then lanes 0-15 those of the lane that was hit) and learns the part through wave broadcasts; nothing goes
+// back through LDS.  Three histogram buffers rotate, the one read in round r being cleared during round r + 1 and reused in
 // round r + 3.
 // ---------------------------------------------------------------------------------------------
 //
@@ -820,17 +823,20 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
 // (the inputs are L2-resident and the compute units would idle otherwise), and each of them copies
 // its share of the kept K/V rows to the cache tail.  That saves a kernel boundary, which on this
 // chip costs about as much as the whole copy.
-constexpr int SEL_COPIES = 4;
+constexpr int SEL_PARTS = 1024;  // 16 per lane
 constexpr int SEL_BUFFERS = 3;
+constexpr uint32_t SEL_SCORES = (16u << 23) - 1u;  // bit patterns of 16 octaves
 
 // LAYER = true (with FUSED): the groups are all (block, KV head) pairs of a layer.
-template <int EPT, bool FUSED, bool LAYER>
-__global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendParams ap, SelectLayer ly, int split) {
-  __shared__ __align__(16) uint32_t sHist[SEL_BUFFERS][SEL_COPIES][256];
-  __shared__ int sWave[16];
-  __shared__ uint32_t sList[64];  // keys that share the threshold's leading digits
+template <int NT, int EPT, bool FUSED, bool LAYER>
+__global__ __launch_bounds__(NT) void select_kernel(SelectParams p, AppendParams ap, SelectLayer ly, int split) {
+  __shared__ __align__(16) uint32_t sHist[SEL_BUFFERS][SEL_PARTS];
+  constexpr int NW = NT / 64;
+  __shared__ int sWave[2][NW];
+  __shared__ uint2 sMax[NW];      // the waves' largest score and collision count among the candidates
+  __shared__ uint32_t sList[64];  // keys of the last interval
   __shared__ int sListN;
-  __shared__ uint32_t sMaxCnt;  // largest collision count among the candidates
+  __shared__ uint32_t sPick[3];   // the threshold among them, how many of those equal to it are needed, how many there are
   __shared__ int sKeep[FUSED ? 1024 : 1];  // FUSED: the kept indices this workgroup copies
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   // the workgroups that share a head (and read the same scores and counts) sit on one XCD
@@ -950,14 +956,14 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
     }
   }
 
-  // exclusive prefix of per-thread counts over the block, in thread (= index) order
-  auto block_excl_scan = [&](int v) -> int {
+  // exclusive prefix of per-thread counts over the block, in thread (= index) order (a buffer of its own for each of the
+  // two calls)
+  auto block_excl_scan = [&](int v, int* totals) -> int {
     const int inc = wave_incl_scan(v);
-    __syncthreads();  // sWave free again
-    if (lane == 63) sWave[wave] = inc;
+    if (lane == 63) totals[wave] = inc;
     __syncthreads();
-    // the 16 wave totals, one per lane of every 16-lane row, prefix-summed inside the row
-    int wt = sWave[lane & 15];
+    // the wave totals, one per lane of every 16-lane row, prefix-summed inside the row
+    int wt = totals[lane & (NW - 1)];
     wt += __builtin_amdgcn_update_dpp(0, wt, 0x111, 0xf, 0xf, true);  // row_shr:1
     wt += __builtin_amdgcn_update_dpp(0, wt, 0x112, 0xf, 0xf, true);  // row_shr:2
     wt += __builtin_amdgcn_update_dpp(0, wt, 0x114, 0xf, 0xf, true);  // row_shr:4
@@ -965,105 +971,125 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
     const int base = wave ? __builtin_amdgcn_readlane(wt, wave - 1) : 0;
     return base + inc - v;
   };
-  int round_no = 0;  // rounds of both descents so far: selects the histogram buffer
-  // The k-th largest value among the active elements (val < 2^(8*n_digits)): returns it in thr, with `need`
-  // = how many of the `in_bin` active elements equal to it belong to the top k.  All three block-uniform.
-  auto kth_largest = [&](const uint32_t* val, const bool* active, int k, int n_digits, uint32_t& thr, int& need, int& in_bin) {
-    uint32_t prefix = 0u, pmask = 0u;
+  int round_no = 0;  // rounds of both stages so far: selects the histogram buffer
+  // The k-th largest value among the active elements, all of them <= hi: returns it in thr, with `need` = how many of the
+  // `in_part` active elements equal to it belong to the top k.  All three block-uniform.  Values below lo are counted with
+  // the first part of the first round.
+  auto kth_largest = [&](const uint32_t* val, const bool* active, int k, uint32_t lo, uint32_t hi, uint32_t& thr, int& need, int& in_part) {
     need = k;
-    in_bin = 0;
-    for (int dg = n_digits - 1; dg >= 0; --dg) {
-      const int shift = 8 * dg;
+    bool below = true;  // the first part takes all smaller values too
+    for (;;) {
+      const uint32_t span = hi - lo;
+      const int shift = span < (uint32_t)SEL_PARTS ? 0 : 22 - __builtin_clz(span);
       const int buf = round_no % SEL_BUFFERS;
       // buffer `buf` is zero here: cleared at kernel start or two rounds ago
 #pragma unroll
       for (int e = 0; e < EPT; ++e)
-        if (active[e] && (val[e] & pmask) == prefix) atomicAdd(&sHist[buf][lane & 3][(val[e] >> shift) & 255u], 1u);
+        if (active[e] && (below || val[e] >= lo) && val[e] <= hi) atomicAdd(&sHist[buf][val[e] > lo ? (val[e] - lo) >> shift : 0u], 1u);
       __syncthreads();
       // the buffer of the round before has been read by every wave: clear it for the round after next
-      if (round_no > 0) sHist[(round_no - 1) % SEL_BUFFERS][tid >> 8][tid & 255] = 0u;
+      if (round_no > 0)
+#pragma unroll
+        for (int i = 0; i < SEL_PARTS / NT; ++i) sHist[(round_no - 1) % SEL_BUFFERS][tid + i * NT] = 0u;
       ++round_no;
-      // every wave: lane l owns digits 4l..4l+3; walk from the top digit down
-      uint4 q[SEL_COPIES];
+      // the lane whose parts hold the need-th largest key: above < need <= above + mine (quads in rotated order: neighbouring
+      // lanes read different banks)
+      int mine = 0;
 #pragma unroll
-      for (int b = 0; b < SEL_COPIES; ++b) q[b] = *reinterpret_cast<const uint4*>(&sHist[buf][b][4 * lane]);
-      const uint32_t c[4] = {q[0].x + q[1].x + q[2].x + q[3].x, q[0].y + q[1].y + q[2].y + q[3].y,
-                             q[0].z + q[1].z + q[2].z + q[3].z, q[0].w + q[1].w + q[2].w + q[3].w};
-      const int mine = (int)(c[0] + c[1] + c[2] + c[3]);
-      const int incl = wave_incl_scan(mine);
-      const int total = __builtin_amdgcn_readlane(incl, 63);
-      int above = total - incl;  // keys in digits owned by higher lanes
-      // the digit holding the need-th largest key: above < need <= above + count (one lane, one digit)
-      int p_dig = -1, p_need = 0, p_cnt = 0;
-#pragma unroll
-      for (int b = 3; b >= 0; --b) {
-        const bool hit = above < need && need <= above + (int)c[b];
-        p_dig = hit ? 4 * lane + b : p_dig;
-        p_need = hit ? need - above : p_need;
-        p_cnt = hit ? (int)c[b] : p_cnt;
-        above += (int)c[b];
+      for (int j = 0; j < 4; ++j) {
+        const uint4 q = *reinterpret_cast<const uint4*>(&sHist[buf][16 * lane + 4 * ((j + lane) & 3)]);
+        mine += (int)(q.x + q.y + q.z + q.w);
       }
-      const uint64_t hit_mask = __ballot(p_dig >= 0);
-      const int src = hit_mask ? __builtin_ctzll(hit_mask) : 0;
-      prefix |= (uint32_t)__builtin_amdgcn_readlane(p_dig, src) << shift;
-      pmask |= 255u << shift;
-      need = __builtin_amdgcn_readlane(p_need, src);
-      in_bin = __builtin_amdgcn_readlane(p_cnt, src);
-      if (dg > 0 && in_bin <= 64) {  // block-uniform
-        // few keys share the chosen digits: every wave ranks them against each other (one key per
-        // lane) instead of descending through the remaining digits
+      const int incl = wave_incl_scan(mine);
+      const int above = __builtin_amdgcn_readlane(incl, 63) - incl;  // keys in parts of higher lanes
+      const uint64_t hit = __ballot(above < need && need <= above + mine);
+      const int src = hit ? __builtin_ctzll(hit) : 0;
+      need -= __builtin_amdgcn_readlane(above, src);
+      // its parts from the top down, one per lane of every 16
+      const int c = (int)sHist[buf][16 * src + 15 - (lane & 15)];
+      int inc = c;
+      inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);
+      inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);
+      inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);
+      inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);
+      const uint64_t hit2 = __ballot(inc - c < need && need <= inc);
+      const int d = hit2 ? __builtin_ctzll(hit2) : 0;  // below 16: every 16 lanes hold the same
+      in_part = __builtin_amdgcn_readlane(c, d);
+      need -= __builtin_amdgcn_readlane(inc, d) - in_part;
+      const uint32_t part = (uint32_t)(16 * src + 15 - d), first = lo + (part << shift), last = first + ((1u << shift) - 1u);
+      below = below && part == 0u && lo > 0u;
+      hi = last - first < hi - first ? last : hi;  // without overflow where the interval ends at the type's largest value
+      lo = below ? 0u : first;
+      if (lo == hi) break;
+      if (in_part <= 64) {  // block-uniform
+        // few keys are left: each is ranked by one of the waves
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
-          if (active[e] && (val[e] & pmask) == prefix) sList[atomicAdd(&sListN, 1)] = val[e];
+          if (active[e] && val[e] >= lo && val[e] <= hi) sList[atomicAdd(&sListN, 1)] = val[e];
+        __syncthreads();
+        const uint32_t v = sList[lane];
+        const bool in = lane < in_part;
+        for (int j = wave; j < in_part; j += NW) {
+          const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)v, j);
+          const int gt = __builtin_popcountll(__ballot(in && v > u)), ge = __builtin_popcountll(__ballot(in && v >= u));
+          if (gt < need && need <= ge && lane == 0) {  // equal keys write the same
+            sPick[0] = u;
+            sPick[1] = (uint32_t)(need - gt);
+            sPick[2] = (uint32_t)(ge - gt);
+          }
+        }
         __syncthreads();
         if (tid == 0) sListN = 0;  // next used after at least one more barrier
-        const uint32_t v = lane < in_bin ? sList[lane] : 0u;
-        int gt = 0, ge = 0;
-        for (int j = 0; j < in_bin; ++j) {
-          const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)v, j);
-          gt += u > v ? 1 : 0;
-          ge += u >= v ? 1 : 0;
-        }
-        const uint64_t m2 = __ballot(lane < in_bin && gt < need && need <= ge);  // equal keys agree on the values
-        const int s2 = m2 ? __builtin_ctzll(m2) : 0;
-        prefix = (uint32_t)__builtin_amdgcn_readlane((int)v, s2);
-        const int gt_s = __builtin_amdgcn_readlane(gt, s2), ge_s = __builtin_amdgcn_readlane(ge, s2);
-        need -= gt_s;
-        in_bin = ge_s - gt_s;
+        lo = __builtin_amdgcn_readfirstlane(sPick[0]);
+        need = __builtin_amdgcn_readfirstlane((int)sPick[1]);
+        in_part = __builtin_amdgcn_readfirstlane((int)sPick[2]);
         break;
       }
+      below = false;
     }
-    thr = prefix;
+    thr = lo;
   };
 
-  for (int i = tid; i < SEL_BUFFERS * SEL_COPIES * 256; i += 1024) (&sHist[0][0][0])[i] = 0u;
-  if (tid == 0) {
-    sMaxCnt = 0u;
-    sListN = 0;
-  }
-  __syncthreads();
+  for (int i = tid; i < SEL_BUFFERS * SEL_PARTS; i += NT) (&sHist[0][0])[i] = 0u;
+  if (tid == 0) sListN = 0;
+  // the largest score and count among the candidates: what the first intervals end at
+  uint2 top = make_uint2(0u, 0u);
   {
-    // Collision counts are mostly tiny, so their top byte is usually zero for every candidate: the
-    // block-wide maximum (one LDS atomic per wave, ordered by the barriers of the first stage) tells
-    // how many digits the second stage really needs.
-    uint32_t mx = 0u;
+    auto wave_max = [&](uint32_t v) -> uint32_t {
+      v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));
+      v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+      v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+      v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+      return v;  // lane 16 i + 15: of its 16 lanes
+    };
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) mx = max(mx, cand[e] ? c2[e] : 0u);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-    if (lane == 0 && mx) atomicMax(&sMaxCnt, mx);
+    for (int e = 0; e < EPT; ++e) {
+      top.x = max(top.x, cand[e] ? key[e] : 0u);
+      top.y = max(top.y, cand[e] ? c2[e] : 0u);
+    }
+    auto all = [&](uint32_t v) -> uint32_t {
+      v = wave_max(v);
+      return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 15), (uint32_t)__builtin_amdgcn_readlane((int)v, 31)),
+                 max((uint32_t)__builtin_amdgcn_readlane((int)v, 47), (uint32_t)__builtin_amdgcn_readlane((int)v, 63)));
+    };
+    const uint32_t ts = all(top.x), tc = all(top.y);
+    if (lane == 0) sMax[wave] = make_uint2(ts, tc);
+    __syncthreads();
+    const uint2 w = sMax[lane & (NW - 1)];
+    top.x = (uint32_t)__builtin_amdgcn_readlane((int)wave_max(w.x), 15);
+    top.y = (uint32_t)__builtin_amdgcn_readlane((int)wave_max(w.y), 15);
   }
   // stage 1 (Alg. 1 step 4): the k_exact candidates ranked first by (score descending, index ascending)
   if (p.k_exact > 0) {  // block-uniform
     uint32_t thr;
     int need, in_bin;
-    kth_largest(key, cand, p.k_exact, 4, thr, need, in_bin);
+    kth_largest(key, cand, p.k_exact, top.x > SEL_SCORES ? top.x - SEL_SCORES : 0u, top.x, thr, need, in_bin);
     int rank = 0;
     if (need < in_bin) {  // ties at the threshold (rare for scores): the lowest indices win
       int n_eq = 0;
 #pragma unroll
       for (int e = 0; e < EPT; ++e) n_eq += (cand[e] && key[e] == thr) ? 1 : 0;
-      rank = block_excl_scan(n_eq);
+      rank = block_excl_scan(n_eq, sWave[0]);
     }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
@@ -1076,8 +1102,6 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
         }
       }
     }
-  } else {
-    __syncthreads();  // orders the atomicMax above before its read below
   }
   // stage 2 (Alg. 1 steps 5-7): the k_lsh remaining candidates ranked first by (count descending, index
   // ascending).  Only the threshold is found here; its ties are resolved inside the compaction below.
@@ -1087,8 +1111,8 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
   uint32_t thr2 = 0xffffffffu;  // k_lsh == 0: nothing of the residual is kept
   int need2 = 0, in2 = 0;
   if (p.k_lsh > 0) {
-    const int cnt_digits = sMaxCnt < 256u ? 1 : (sMaxCnt < 65536u ? 2 : (sMaxCnt < (1u << 24) ? 3 : 4));
-    kth_largest(c2, act2, p.k_lsh, min(cnt_digits, (p.cnt_bits + 7) >> 3), thr2, need2, in2);
+    // the largest count of the residual may be smaller; counts up to it are one part each below 1024
+    kth_largest(c2, act2, p.k_lsh, 0u, top.y, thr2, need2, in2);
   }
 
   // Compaction (Alg. 1 step 8 and the Sec. 3.1 partition).  Kept for certain: protected positions, stage-1
@@ -1103,7 +1127,7 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
     act2[e] = tie;
     packed += (sel[e] ? 1 << 16 : 0) + (tie ? 1 : 0);
   }
-  const int pre = block_excl_scan(packed);
+  const int pre = block_excl_scan(packed, sWave[1]);
   int n_sure = pre >> 16, n_tie = pre & 0xffff;
   const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
   // FUSED: this workgroup copies output ranks [r0, r1)
@@ -1124,14 +1148,14 @@ __global__ __launch_bounds__(1024) void select_kernel(SelectParams p, AppendPara
   }
   if (FUSED) {
     __syncthreads();
-    const int cpr = ap.row_bytes / 16;
+    const int cpr = ap.row_bytes / 16, cpr_log = __builtin_ctz(cpr);  // a power of two
     const int n_copy = (r1 - r0) * cpr;
     // two chunk pairs per thread and step, all four loads in flight before the first store
-    for (int t0 = tid; t0 < n_copy; t0 += 2048) {
-      const int t1 = t0 + 1024;
+    for (int t0 = tid; t0 < n_copy; t0 += 2 * NT) {
+      const int t1 = t0 + NT;
       const bool two = t1 < n_copy;
-      const int row0 = t0 / cpr, c0 = t0 - row0 * cpr;
-      const int row1 = two ? t1 / cpr : row0, c1 = two ? t1 - row1 * cpr : c0;
+      const int row0 = t0 >> cpr_log, c0 = t0 & (cpr - 1);
+      const int row1 = two ? t1 >> cpr_log : row0, c1 = two ? t1 & (cpr - 1) : c0;
       // an index from LDS never addresses past the block, whatever the counts held
       const int src0 = min((uint32_t)sKeep[row0], (uint32_t)p.s_t - 1u), src1 = min((uint32_t)sKeep[row1], (uint32_t)p.s_t - 1u);
       const char* kh = ap.kb.base + (int64_t)h * ap.kb.stride_head;
@@ -1299,16 +1323,34 @@ hipError_t launch_accumulate(const AccumParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Threads of a selection.  Every phase costs issue slots per wave and the waves scan redundantly, so small blocks take few
+// waves (one block of 512 positions 6.5 -> 5.7 us with 256 threads), but more than four positions per thread are the
+// slower again (2048 positions: 512 threads 17.6 us in a 16k layer, 256 21.1, 1024 18.8).  A layer's launch, whose copies
+// hide one workgroup's phases behind another's, takes 512 threads up to 4096 positions (128k layer 104.3 -> 99.8 us).
+static int select_threads(int s_t, bool layer) { return s_t <= 1024 ? 256 : (s_t <= (layer ? 4096 : 2048) ? 512 : 1024); }
+
 template <bool FUSED, bool LAYER>
 static hipError_t launch_select_t(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_groups, int split, hipStream_t st) {
-  const int ept = (p.s_t + 1023) / 1024;
+  const int nt = select_threads(p.s_t, LAYER), ept = (p.s_t + nt - 1) / nt;
   // `split` workgroups per group select (and, fused, copy)
-  dim3 grid(n_groups * split);
-  if (ept <= 1) hipLaunchKernelGGL((select_kernel<1, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
-  else if (ept <= 2) hipLaunchKernelGGL((select_kernel<2, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
-  else if (ept <= 4) hipLaunchKernelGGL((select_kernel<4, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
-  else if (ept <= 8) hipLaunchKernelGGL((select_kernel<8, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
-  else if (ept <= 16) hipLaunchKernelGGL((select_kernel<16, FUSED, LAYER>), grid, dim3(1024), 0, st, p, ap, ly, split);
+  const dim3 grid(n_groups * split), blk(nt);
+  if constexpr (LAYER) {
+    if (nt == 512 && ept > 4) {
+      hipLaunchKernelGGL((select_kernel<512, 8, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+      return hipGetLastError();
+    }
+  } else {
+    if (nt == 1024 && ept <= 4) {
+      hipLaunchKernelGGL((select_kernel<1024, 4, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+      return hipGetLastError();
+    }
+  }
+  if (nt == 256 && ept <= 1) hipLaunchKernelGGL((select_kernel<256, 1, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+  else if (nt == 256 && ept <= 2) hipLaunchKernelGGL((select_kernel<256, 2, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+  else if (nt == 256) hipLaunchKernelGGL((select_kernel<256, 4, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+  else if (nt == 512) hipLaunchKernelGGL((select_kernel<512, 4, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+  else if (ept <= 8) hipLaunchKernelGGL((select_kernel<1024, 8, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
+  else if (ept <= 16) hipLaunchKernelGGL((select_kernel<1024, 16, FUSED, LAYER>), grid, blk, 0, st, p, ap, ly, split);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -1317,9 +1359,11 @@ hipError_t launch_select(const SelectParams& p, hipStream_t st) {
   return launch_select_t<false, false>(p, AppendParams{}, SelectLayer{}, p.n_kv_heads, 1, st);
 }
 
-// enough workgroups per group to fill the chip, each copying at most 1024 rows
-static int select_split(int n_groups, int b_t, int n_cu, int split_override) {
-  int split = split_override > 0 ? split_override : n_cu / n_groups;
+// enough workgroups per group to fill the chip with `per_cu` on a compute unit, each copying at most 1024 rows and, unless
+// the caller says how many, a 16-byte chunk per thread
+static int select_split(int n_groups, int threads, int b_t, int row_bytes, int n_cu, int per_cu, int split_override) {
+  const int least = threads * 16 / row_bytes;  // rows
+  int split = split_override > 0 ? split_override : min(per_cu * n_cu / n_groups, b_t / least);
   if (split < 1) split = 1;
   while ((b_t + split - 1) / split > 1024) ++split;
   return split;
@@ -1327,14 +1371,14 @@ static int select_split(int n_groups, int b_t, int n_cu, int split_override) {
 
 hipError_t launch_select_append(const SelectParams& p, const AppendParams& ap, int n_cu, int split_override, hipStream_t st) {
   const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
-  return launch_select_t<true, false>(p, ap, SelectLayer{}, p.n_kv_heads, select_split(p.n_kv_heads, b_t, n_cu, split_override), st);
+  return launch_select_t<true, false>(p, ap, SelectLayer{}, p.n_kv_heads, select_split(p.n_kv_heads, select_threads(p.s_t, false), b_t, ap.row_bytes, n_cu, 1, split_override), st);
 }
 
 hipError_t launch_select_layer(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_cu, hipStream_t st) {
   const int n_groups = (ly.last + 1) * p.n_kv_heads;
   const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
-  // two workgroups fit a compute unit
-  return launch_select_t<true, true>(p, ap, ly, n_groups, select_split(n_groups, b_t, 2 * n_cu, 0), st);
+  const int threads = select_threads(p.s_t, true);  // 2048 fit a compute unit
+  return launch_select_t<true, true>(p, ap, ly, n_groups, select_split(n_groups, threads, b_t, ap.row_bytes, n_cu, 2048 / threads, 0), st);
 }
 
 hipError_t launch_append(const AppendParams& p, int n_kv_heads, hipStream_t st) {
