@@ -68,7 +68,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
   constexpr int NTHR = PASS_WAVES * 64;
   constexpr int MQ = PASS_ROWS;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   // work item: heads are the slow index of the XCD-major order, so one head's keys, queries and
   // query histograms are fetched into one L2 (or as few as the head count allows)
   const int n_qg = p.n_qgroups;
@@ -110,6 +110,12 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
   // roles
   const bool hash_wave = !PASS2 && wave >= 8;
   const int rt = wave & 7;  // row tile of a score wave; index of a hashing wave
+  const int n_rtg = min((p.m_rows - qg * MQ + 31) >> 5, 8);  // row tiles of this group
+  // Score waves without a row tile of their own do nothing (in fp32 a tile keeps a SIMD's matrix unit for 0.9 us); in sweep 1,
+  // where at most half of them have one, the others hash the window rows meanwhile.  A block of 512 fp32 keys with 64 rows per
+  // head: sweep 1 11.3 -> 7.9 us, sweep 2 8.1 -> 7.0; 100 rows per head, 2859 bf16 keys: 25.3 -> 23.5 us a block.
+  const bool rows_twice = !PASS2 && 2 * n_rtg <= 8;
+  const int art = rows_twice && rt >= n_rtg ? rt - n_rtg : rt;  // the row tile in the wave's registers
 
   extern __shared__ uint4 smem[];
   uint4* sK = smem;                                                    // [nkr][CHP]
@@ -167,16 +173,17 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
     for (int u = 0; u < 4; ++u) pv[u] = ld16(pr_ptr + min(2 * u, pr_per - 2));
   }
   // Sweep 2, collision counts (Alg. 1 step 6) of this range's keys over this workgroup's share of the
-  // tables: 1, 2 or 4 lanes per key, eight tables per lane and step.  In the common shape (two row
-  // groups, one step per lane, aligned codes) the job rides along with the main loop: the key's eight
-  // codes are fetched here with the other loads, each loop iteration issues the histogram lookups of
-  // two tables and adds up those of the iteration before, so their latency costs nothing.
+  // tables: 1, 2 or 4 lanes per key, eight tables per lane and step.  In the common shapes (one or two row
+  // groups, one step per lane, aligned codes) the key's eight codes are fetched here with the other loads.  With one row
+  // group all eight histogram lookups are on their way before the main loop and added up behind it (a block of 512 fp32
+  // keys: 0.9 us; two of them per iteration of a short loop left the other six for its end); with two, each loop iteration
+  // issues the lookups of two tables and adds up those of the iteration before, so their latency costs nothing.
   const int tab0c = qg * p.tables_per_split;
   const int n_tabc = PASS2 && p.qhist ? max(0, min(p.tables_per_split, p.n_tables - tab0c)) : 0;
   int lpk_log = n_tabc > 16 ? 2 : (n_tabc > 8 ? 1 : 0);
   while (lpk_log > 0 && (nb << lpk_log) > NTHR) --lpk_log;
   const bool cnt_piped = NCH <= 8 && n_tabc > 0 && n_tabc == (8 << lpk_log) && (p.n_tables & 7) == 0 && (tab0c & 7) == 0 &&
-                         (nb << lpk_log) <= NTHR && n_qg == 2;
+                         (nb << lpk_log) <= NTHR && n_qg <= 2;
   const bool cnt_lane = cnt_piped && tid < (nb << lpk_log);
   const int cnt_key = tid >> lpk_log, cnt_tb = (tid & ((1 << lpk_log) - 1)) * 8;
   uint4 cnt_codes = make_uint4(0u, 0u, 0u, 0u);  // two 16-bit codes per word, consumed from .x upwards
@@ -252,7 +259,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
       }
       __syncthreads();
       {
-        const uint4* arow = smem + (size_t)(hash_wave ? MQ + rt * 32 + plane_row(rl) : rt * 32 + rl) * CHP + kg;
+        const uint4* arow = smem + (size_t)(hash_wave ? MQ + rt * 32 + plane_row(rl) : art * 32 + rl) * CHP + kg;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) a[i] = arow[2 * i];
       }
@@ -271,7 +278,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
 #pragma unroll
       for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + (2 * i + kg) * 16);
     } else {
-      const int mc = min(qg * MQ + rt * 32 + rl, p.m_rows - 1);
+      const int mc = min(qg * MQ + art * 32 + rl, p.m_rows - 1);
       const int g = div_w(mc, p.w_magic), j = mc - g * p.w;
       const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row;
 #pragma unroll
@@ -405,12 +412,20 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
     for (int r = 0; r < 16; ++r) lse[r] = sLse[rt * 32 + acc_row(r, kg)];
     const int t_half = (n_tiles + 1) >> 1;  // this wave's half of the tiles
     const int nt_beg = (wave >> 3) * t_half;
-    const int nt_end = min(n_tiles, nt_beg + t_half);
+    const int nt_end = rt < n_rtg ? min(n_tiles, nt_beg + t_half) : nt_beg;
     // pipelined count job: step s looks up tables cnt_tb + 2s and + 2s + 1 (both row groups' bins in one
     // 8-byte word pair) and adds up the pair fetched by step s - 1
     const uint32_t* cnt_hist =
-        cnt_piped ? p.qhist + ((size_t)h * p.n_tables + tab0c + cnt_tb) * ((size_t)(1 << p.n_bits) >> 1) * 2 : nullptr;
+        cnt_piped ? p.qhist + ((size_t)h * p.n_tables + tab0c + cnt_tb) * ((size_t)(1 << p.n_bits) >> 1) * n_qg : nullptr;
     const uint32_t cnt_hw2 = (uint32_t)(1 << p.n_bits);  // words per table: 2^K / 2 bins x 2 row groups
+    // one row group: all eight tables' words on their way before the loop
+    uint32_t cnt_w[8];
+    if (cnt_lane && n_qg == 1) {
+      const uint32_t cw[4] = {cnt_codes.x, cnt_codes.y, cnt_codes.z, cnt_codes.w};
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        cnt_w[u] = cnt_hist[(size_t)u * (cnt_hw2 >> 1) + (((cw[u >> 1] >> ((u & 1) * 16)) & 0xffffu) >> 1)];
+    }
     uint2 cnt_pa = make_uint2(0u, 0u), cnt_pb = make_uint2(0u, 0u);
     uint32_t cnt_psh = 0u;  // shifts (0 / 16) of the pending pair, packed
     int cnt_sum = 0, cnt_step = 0;
@@ -434,7 +449,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
 #pragma unroll 1
     for (int nt = nt_beg; nt < nt_end; ++nt) {
       const int kbase = k0 + nt * 32;
-      if (cnt_piped) cnt_advance();
+      if (cnt_piped && n_qg == 2) cnt_advance();
       f32x16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
@@ -464,7 +479,12 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
       col = half_pair_sum(col);
       if (kg == 0) sCol[rt * nkr + nt * 32 + rl] = col;
     }
-    if (cnt_piped) {
+    if (cnt_piped && n_qg == 1) {
+      const uint32_t cw[4] = {cnt_codes.x, cnt_codes.y, cnt_codes.z, cnt_codes.w};
+      if (cnt_lane)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cnt_sum += (int)((cnt_w[u] >> (((cw[u >> 1] >> ((u & 1) * 16)) & 1u) * 16)) & 0xffffu);
+    } else if (cnt_piped) {
       // the last pending pair, and the steps a short loop did not reach, all issued before any is added
       cnt_advance();
       uint2 ra[4], rb[4];
@@ -491,19 +511,22 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
       for (int u = 0; u < 4; ++u)
         cnt_sum += (int)(((ra[u].x >> (rsh[u] & 31u)) & 0xffffu) + ((ra[u].y >> (rsh[u] & 31u)) & 0xffffu) +
                          ((rb[u].x >> (rsh[u] >> 8)) & 0xffffu) + ((rb[u].y >> (rsh[u] >> 8)) & 0xffffu));
+    }
+    if (cnt_piped) {
       if (lpk_log > 0) cnt_sum += lane_xor1(cnt_sum);
       if (lpk_log > 1) cnt_sum += lane_xor2(cnt_sum);
       if (cnt_lane && (tid & ((1 << lpk_log) - 1)) == 0)
         p.cnt[((size_t)qg * p.n_kv_heads + h) * p.s_t + b0 + cnt_key] = cnt_sum;
     }
   } else if (!hash_wave) {
+    if (art < n_rtg) {
     // Sweep 1 multiplies the other way round (keys as the A operand, window rows as B): lane = window
     // row rt*32 + rl, registers = 16 keys of the tile, so a row's statistics never leave the lane.
     // Each lane keeps (ref, sum) with sum = sum_i 2^(x_i - ref) over its keys; ref is the lane's
     // maximum over the first tile and is not raised afterwards (see the overflow check below).
-    const int lim = sLim[rt * 32 + rl];
-    const int row = qg * MQ + rt * 32 + rl;
-    if (!p.lse_complete) {  // workgroup-uniform: with complete row statistics from the caller only the hashing remains
+    const int lim = sLim[art * 32 + rl];
+    const int row = qg * MQ + art * 32 + rl;
+    if (!p.lse_complete && rt < n_rtg) {  // with complete row statistics from the caller only the hashing remains
     auto tile = [&](int nt, f32x16& acc) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
@@ -585,7 +608,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
     const uint32_t code_mask = (1u << p.n_bits) - 1u;
     const int hist_w = p.hist_lds_words ? (1 << p.n_bits) >> 1 : 0;  // words per table, 0: no histograms
 #pragma unroll 1
-    for (int t = 0; t < n_qpt; ++t) {
+    for (int t = rows_twice && rt < n_rtg ? n_qpt : 0; t < n_qpt; ++t) {
       f32x16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
@@ -607,6 +630,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
           p.sig_q[((size_t)h * p.m_rows + row) * p.n_tables + t_tab0 + tt] = (uint16_t)code;
           if (hist_w) atomicAdd(sHist + (t_tab0 + tt - qt0) * hist_w + (code >> 1), 1u << ((code & 1u) * 16));
         }
+    }
     }
   } else {
     // hashing waves: SimHash sign bits of the range's block keys
@@ -645,7 +669,8 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
     for (int t = tid; t < nb; t += NTHR) {
       float v = 0.0f;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) v += sCol[w * nkr + t];
+      for (int w = 0; w < 8; ++w)
+        v += w < n_rtg ? sCol[w * nkr + t] : 0.0f;  // no branches: all reads at once
       p.s_part[((size_t)qg * p.n_kv_heads + h) * p.s_t + b0 + t] = v;
     }
   } else {
