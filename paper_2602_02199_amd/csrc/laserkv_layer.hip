@@ -14,13 +14,14 @@
 //
 // In both sweeps the window rows stay in registers for the whole key range (two 32-row tiles per wave, so a key
 // fragment read from LDS feeds two matrix instructions) and the keys stream through LDS stages, one barrier per chunk: the
-// statistics through four, filled by asynchronous loads, the scores through two, the next chunk's loads in flight in
-// registers.
+// statistics through four stages, the scores through two, both filled by asynchronous loads.
 #include "laserkv_device.h"
 #include "laserkv_kernels.h"
 #include "laserkv_rowstats.h"
 
 #include <limits.h>
+
+#include <type_traits>
 
 namespace lkv {
 
@@ -223,22 +224,23 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
 // run beside the matrix work of the next.  Waves 4-7 hold the hyperplanes (PT tiles each): they take the sign bits,
 // bring the keys into LDS, and finish the previous chunk (sums and sign bits meet in LDS, two buffers): the sum over
 // the score waves, and per key and table one probe of the table's cells.  Every SIMD runs one wave of either kind.
-// The two kinds of wave of a SIMD compete: score waves whose instructions are in a fixed order (four vector instructions
-// and two exponentials beside each matrix instruction) leave the hashing wave little while they run, and it is the one that
-// the barrier waits for (128k layer 241 -> 258 us), so hashing waves are served first.  Both changes, and the partials and
-// cells fetched without a round trip each: score kernel of a 16k layer 26.5 -> 24.3 us, of 64k 86 -> 76, of groups of eight
-// (512 hyperplanes) 317 -> 275, of the 128k layer 240 -> 239, where the clock is set by power.
+// Both kinds have their instructions in a fixed order where a chunk is complete: a score wave four vector instructions and
+// two exponentials beside each matrix instruction, a hashing wave two of the previous plane tile's signs.  The two of a SIMD
+// compete, and the hashing wave, which also counts, is the one that the barrier waits for, so it is served first (128k layer
+// 262 us instead of 233 otherwise).  Keys arrive by asynchronous loads (KeyRing); partials of the statistics are fetched
+// eight at a time.  Score kernel of a 16k layer 26.5 -> 23.6 us, of 64k 86 -> 70, of groups of eight (512 hyperplanes) 317
+// -> 257, of the 128k layer 240 -> 215-230, where the clock is set by power (before: order left to the compiler, keys
+// through registers, serial loads at the start, plane tiles past the last one multiplied too).
 // ---------------------------------------------------------------------------------------------
 constexpr int LY_HALF = LY_WAVES / 2;  // waves of either kind
 
 template <int DT, int D, int RT, int PT>
 __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) {
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
-  constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
+  constexpr int CH = D * ES / 16, NCH = CH / 2;
+  using L = KeyRing<CH>;
+  static_assert(L::KC == LY_KC, "a chunk of keys is a stage");
   constexpr int KC = LY_KC, TPC = KC / 32;
-  constexpr int NLD = LY_THREADS / 2;        // threads that load keys
-  constexpr int KL = KC * CH / NLD;
-  constexpr int RPL = NLD / CH;
   constexpr int TP = RT > 1 ? 2 : 1;         // row tiles per step
   constexpr int NP = RT / TP;                // steps per key tile
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
@@ -260,26 +262,25 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
 
   const int bits_pitch = (n_pt + 1) | 1;  // words per key in the sign-bit scratch: odd, and one past the last tile
   extern __shared__ uint4 smem[];
-  uint4* sK = smem;                                                                         // [2][KC][CHP]
-  uint32_t* sBits = reinterpret_cast<uint32_t*>(smem + (size_t)2 * KC * CHP);               // [2][KC][bits_pitch]
+  uint32_t* sBits = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(smem) + 2 * L::STAGE);  // [2][KC][bits_pitch], behind two stages of keys
   float* sCol = reinterpret_cast<float*>(sBits + 2 * KC * bits_pitch);                      // [2][LY_HALF][KC]
   int* sLim = reinterpret_cast<int*>(sCol + 2 * LY_HALF * KC);                              // [LY_ROWS]
   float* sLse = reinterpret_cast<float*>(sLim + LY_ROWS);                                   // [LY_ROWS]
   uint32_t* sCells = reinterpret_cast<uint32_t*>(sLse + LY_ROWS);                             // [n_tables][cell_words]
 
   const uint32_t kstride = (uint32_t)p.k.stride_row;
-  const __amdgpu_buffer_rsrc_t ksrd =
-      make_srd(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)gr.lo * p.k.stride_row, (uint32_t)gr.s_t * kstride);
-  const uint32_t k_row = (tid & (NLD - 1)) / CH, k_col = tid % CH;
-  uint4 kpre[KL];
-  auto prefetch = [&](int kc0) {
+  const srd_words ksrd =
+      make_srd_words(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)gr.lo * p.k.stride_row, (uint32_t)gr.s_t * kstride);
+  // LDS addresses of the lane's row in the first tile of a chunk: operand chunk pair i is at from[i % NA] + i / NA * (NA * 32)
+  const uint32_t lds0 = lds_offset(smem);
+  uint32_t from[L::NA];
+  auto read_from = [&](int stage) {
 #pragma unroll
-    for (int u = 0; u < KL; ++u) kpre[u] = buf_ld16(ksrd, (uint32_t)(kc0 + k_row + u * RPL) * kstride + k_col * 16);
+    for (int i = 0; i < L::NA; ++i)
+      from[i] = opaque(lds0 + stage * L::STAGE + rl / L::RPG * L::GROUP + rl % L::RPG * (CH * 16) + (((2 * i + kg) ^ (rl % L::RPG)) * 16));
   };
-  auto store = [&](uint4* buf) {
-#pragma unroll
-    for (int u = 0; u < KL; ++u) buf[(k_row + u * RPL) * CHP + k_col] = kpre[u];
-  };
+  auto key = [&](int tile, int i) { return lds_ld16(from[i % L::NA], tile * L::TILE + i / L::NA * (L::NA * 32)); };
+
   // the row's log-sum-exp (exp2 domain): merged from the partials of layer_stats_kernel and the caller's outside
   // keys, or the caller's complete one; and the cells
   auto rows_and_cells = [&]() {
@@ -335,15 +336,17 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       for (int i = 0; i < NCH; ++i) landed(a[t][i]);
     __syncthreads();
     // logits of one step: row tiles t0, t0 + 1 against the 32 keys at LDS rows kt * 32 ..
-    auto logits = [&](const uint4* stage, int kt, int t0, f32x16* acc) {
+    auto logits = [&](int kt, int t0, f32x16* acc) {
 #pragma unroll
       for (int t = 0; t < TP; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
-      const uint4* brow = stage + (kt * 32 + rl) * CHP + kg;
+      uint32_t base[L::NA];  // kt is not a constant here
+#pragma unroll
+      for (int i = 0; i < L::NA; ++i) base[i] = from[i] + kt * L::TILE;
 #pragma unroll
       for (int i = 0; i < NCH; ++i) {
-        const uint4 kf = brow[2 * i];
+        const uint4 kf = lds_ld16(base[i % L::NA], i / L::NA * (L::NA * 32));
 #pragma unroll
         for (int t = 0; t < TP; ++t) Mma<DT>::run(acc[t], a[t0 + t][i], kf);
       }
@@ -386,16 +389,15 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     float4 l[2] = {lse_of(0, 0), lse_of(0, 1)};  // those of the next logits
     int cur = 0;
     for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
-      const uint4* stage = sK + (size_t)cur * KC * CHP;
+      read_from(cur);
       float* col_dst = sCol + (size_t)(cur * LY_HALF + first) * KC;
       auto put = [&](int kt, float col) {
         col = half_pair_sum(col);
         if (kg == 0) col_dst[kt * 32 + rl] = col;
       };
       if (kstep == 1 && kc0 + KC <= k_hi && kc0 + KC - 1 <= lim0) {  // workgroup-uniform: a complete chunk that every row sees
-        const uint4* brow = stage + rl * CHP + kg;
 #pragma unroll
-        for (int i = 0; i < NCH; ++i) kf[i] = brow[2 * i];
+        for (int i = 0; i < NCH; ++i) kf[i] = key(0, i);
         f32x16 acc[2][TP];
         float c[TP];
 #pragma unroll
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
           for (int j = 0; j < NCH * TP; ++j) {
             const int i = j / TP, t = j % TP;
             if (mul) Mma<DT>::run(next[t], a[t0 + t][i], kf[i]);
-            if (newk && t == TP - 1) kf[i] = brow[(s + 1) / NP * 32 * CHP + 2 * i];
+            if (newk && t == TP - 1) kf[i] = key((s + 1) / NP, i);
             if (sum) {
 #pragma unroll
               for (int k = 0; k < PER; ++k) {
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
 #pragma unroll
           for (int t0 = 0; t0 < RT; t0 += TP) {
             f32x16 acc[TP];
-            logits(stage, kt, t0, acc);
+            logits(kt, t0, acc);
             col += kbase + 31 <= lim0 ? pooled(acc, t0) : pooled_masked(acc, t0, kbase + rl);
           }
           put(kt, col);
@@ -467,7 +469,24 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
 
   // the hashing waves
   __builtin_amdgcn_s_setprio(1);
-  prefetch(k_lo);
+  // They bring the keys in: wave w of the four the w-th of every four groups of a stage; rows past the range's end repeat its
+  // last one.
+  const uint32_t ld_row = lane / CH, ld_col = ((lane % CH) ^ (ld_row % L::RPG)) * 16, ld_off = ld_row * kstride + ld_col;
+  auto prefetch = [&](int kc0, int stage) {
+    const int row = kc0 + idx * L::RPG;
+    uint32_t dst = lds0 + stage * L::STAGE + idx * L::GROUP;
+    constexpr int LOADS = KC / L::RPG / LY_HALF;
+    if (kc0 + KC <= k_hi) {
+      uint32_t src = (uint32_t)row * kstride;
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u, src += LY_HALF * L::RPG * kstride, dst += LY_HALF * L::GROUP) async_ld16(ksrd, ld_off, src, dst);
+    } else {
+#pragma unroll 1
+      for (int u = 0; u < LOADS; ++u, dst += LY_HALF * L::GROUP)
+        async_ld16(ksrd, (uint32_t)min(row + u * LY_HALF * L::RPG + (int)ld_row, k_hi - 1) * kstride + ld_col, 0u, dst);
+    }
+  };
+  prefetch(k_lo, 0);
   uint4 a[PT][NCH];
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
@@ -476,17 +495,17 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     for (int i = 0; i < NCH; ++i) a[t][i] = ld16(ptr + (2 * i + kg) * 16);
   }
   rows_and_cells();
-  store(sK);
 #pragma unroll
   for (int t = 0; t < PT; ++t)
 #pragma unroll
     for (int i = 0; i < NCH; ++i) landed(a[t][i]);
+  async_wait();
   __syncthreads();
   const uint32_t code_mask = (1u << p.n_bits) - 1u;
   const uint32_t cell_max = p.cell_log == 2 ? 255u : 15u;  // full cells of 8 and 4 bits (cell_log 2, 3; those of 16 bits hold every count)
   // sums over the score waves and collision counts of the chunk whose first key is kc0: two lanes per key
   auto finish = [&](int buf, int kc0) {
-    const int key = (tid - NLD) >> 1, sub = tid & 1;
+    const int key = (tid - LY_HALF * 64) >> 1, sub = tid & 1;
     const int kidx = kc0 + key;
     const uint32_t* bits = sBits + (buf * KC + key) * bits_pitch;
     const size_t at = (size_t)gr.g * p.s_stride + kidx;
@@ -550,13 +569,48 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
   int cur = 0;
   for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
     const bool more = kc0 + KC < k_hi;
-    if (more) prefetch(kc0 + KC);
-    const uint4* stage = sK + (size_t)cur * KC * CHP;
-    if (active) {
+    if (more) prefetch(kc0 + KC, cur ^ 1);
+    read_from(cur);
+    if (active && kstep == 1 && kc0 + KC <= k_hi) {  // a complete chunk
+      // The products of a (key tile, plane tile) beside the sign bits of the one before.
+      auto steps = [&](auto tiles) {
+        constexpr int N = decltype(tiles)::value;  // plane tiles of this wave
+        constexpr int PER = 16 / NCH;
+        uint32_t* bits = sBits + (cur * KC + rl) * bits_pitch + first;
+        uint4 kf[NCH];
+        f32x16 acc[2];
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) kf[i] = key(0, i);
+#pragma unroll
+        for (int s = 0; s <= TPC * N; ++s) {
+          const bool mul = s < TPC * N, newk = mul && s % N == N - 1 && s / N + 1 < TPC;
+          uint32_t neg = 0u;
+          if (mul)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[s & 1][e] = 0.0f;
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) {
+            if (mul) Mma<DT>::run(acc[s & 1], a[s % N][i], kf[i]);
+            if (newk) kf[i] = key(s / N + 1, i);
+            if (s > 0)
+#pragma unroll
+              for (int e = i * PER; e < (i + 1) * PER; ++e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[(s + 1) & 1][15 - e]), 31);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (s > 0) {
+            // 16 consecutive planes per lane (see plane_row): their sign bits have been shifted into one word
+            const uint32_t pos = ~neg & 0xffffu;
+            const uint32_t mask = pos | (half_other(pos, kg) << 16);
+            if (kg == 0) bits[(s - 1) / N * 32 * bits_pitch + LY_HALF * ((s - 1) % N)] = mask;
+          }
+        }
+      };
+      if (first + LY_HALF * (PT - 1) < n_pt) steps(std::integral_constant<int, PT>{});
+      else steps(std::integral_constant<int, PT == 1 ? 1 : PT - 1>{});
+    } else if (active) {
 #pragma unroll 1
       for (int vt = k0; vt < TPC; vt += kstep) {
         if (kc0 + vt * 32 >= k_hi) break;
-        const uint4* brow = stage + (vt * 32 + rl) * CHP + kg;
         auto signs = [&](const f32x16& acc, int t) {
           // 16 consecutive planes per lane (see plane_row): their sign bits shift into one word
           uint32_t neg = 0u;
@@ -577,7 +631,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
             for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
 #pragma unroll
           for (int i = 0; i < NCH; ++i) {
-            const uint4 kf = brow[2 * i];
+            const uint4 kf = lds_ld16(from[i % L::NA] + vt * L::TILE, i / L::NA * (L::NA * 32));
 #pragma unroll
             for (int t = 0; t < HT; ++t) Mma<DT>::run(acc[t], a[t0 + t][i], kf);
           }
@@ -588,8 +642,8 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       }
     }
     if (kc0 > k_lo) finish(cur ^ 1, kc0 - KC);
-    if (more) store(sK + (size_t)(cur ^ 1) * KC * CHP);
     cur ^= 1;
+    if (more) async_wait();
     lds_barrier();
   }
   finish(cur ^ 1, k_lo + (k_hi - k_lo - 1) / KC * KC);
@@ -602,7 +656,8 @@ bool layer_supports(int dtype, int head_dim, int m_rows) {
 
 static size_t score_lds(int head_dim, int es, int n_planes, int cell_total_words) {
   const int bits_pitch = ((n_planes + 31) / 32 + 1) | 1;
-  return (size_t)2 * LY_KC * (head_dim * es / 16 + 1) * 16 + (size_t)2 * LY_KC * bits_pitch * 4 +
+  const size_t stage = head_dim * es <= 128 ? KeyRing<8>::STAGE : KeyRing<16>::STAGE;
+  return 2 * stage + (size_t)2 * LY_KC * bits_pitch * 4 +
          (size_t)2 * LY_HALF * LY_KC * 4 + (size_t)LY_ROWS * 8 + (size_t)cell_total_words * 4 + 16;
 }
 
