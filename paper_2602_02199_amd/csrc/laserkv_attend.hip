@@ -341,13 +341,14 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
 //   then on the two waves take alternate 32-key tiles, and their states meet in LDS at the end.  (With
 //   consecutive tiles in a workgroup a launch takes as long as the block's last rows: a 16k prefill of 32 heads in blocks
 //   of 2048 rows took 169 us a block on average, with pairs 151.)
-//   Tile loop.  Two key tiles at a time: one's exponentials run while the matrix unit works on the other.  Over long key
-//   ranges references are fixed, so that the output accumulators see nothing but matrix instructions, and LDS addresses are kept per operand chunk (computed at each read they cost 4 % of the time: vector
-//   instructions hardly overlap with matrix instructions here).
-//   Chunks alternate between two LDS stages and arrive through async_ld16, the next one while the current one is worked
-//   on, so one barrier per chunk suffices.
-// Bound by the matrix unit, at the clock that power allows: 128k prefill, last block, 1136 TFLOP/s, and 1404 when all
-// operands are zero (a plain bf16 product of 8192: 1380 and 1800).
+//   Tile loop.  Over long key ranges references are fixed, so that the output accumulators see nothing but matrix
+//   instructions: there the tiles of a wave run on through a ring of four LDS stages in a fixed order of instructions
+//   (`ring`).  Elsewhere two key tiles at a time, chunks alternating between two LDS stages; one barrier per chunk either
+//   way, the next chunks arriving through async_ld16.  LDS addresses are kept per operand chunk (computed at each read they
+//   cost 4 % of the time).
+// Bound by the matrix unit, at the clock that power allows: 128k prefill, last block, 1157 -> 1220 TFLOP/s with the ring (3690
+// -> 3500 us; the loop alone on operands in LDS reaches 1326, and 1850 when they are zeros), window rows over 63 520 keys
+// 149 -> 140 us.  By LDS reads it is bound to about the same: 16 KiB per wave and tile, a clock for 128 bytes.
 template <int DT>
 __host__ __device__ constexpr int rows_chunk_keys() { return DT == DT_BF16 ? 128 : 64; }
 
@@ -664,9 +665,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // position in the split's chunks
   int seg, kc0, nseg, nkc, cur;
   bool have, nhave;
-  auto start = [&]() {  // the first chunk's loads
-    seg = lo0 < hi0 ? 0 : 1;
-    kc0 = seg ? lo1 : lo0;
+  auto start = [&](int from) {  // the first chunk's loads, cache rows from `from` on
+    seg = from < hi0 ? 0 : 1;
+    kc0 = seg ? lo1 : from;
     have = seg ? lo1 < hi1 : true;
     nseg = seg;
     nkc = kc0;
@@ -719,15 +720,143 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) vx[dt] = opaque((v_at + cur * (STAGE * 16) + nt0 * V_TILE) ^ (64 * dt));
   };
+  // Long ranges of cache rows against fixed references (bf16): a ring of four stages of 64 keys, each with its K and V.  The
+  // tiles of a wave run on across the chunks: the products of a tile with the keys stand beside the exponentials of the
+  // tile before, those with the values beside the next exponents.  One barrier per chunk tells that the next chunk has landed
+  // and that the one before has been left.
+  constexpr int RC = 64;                                     // keys per ring stage
+  constexpr uint32_t R_V = RC * CH * 16, R_STAGE = 2 * R_V;  // bytes of K in a stage, and of K and V
+  constexpr int R_LOADS = RC * CH / ATT_THREADS;             // per thread, tensor and chunk
+  // (not in the workgroup whose waves share the middle tile of an odd number from the start)
+  const bool middle = (n_tiles & 1) && pg == (n_pairs - 1) / 4;
+  const int ring_keys = BF16 && fixed && !middle ? (hi0 - lo0) & ~(2 * RC - 1) : 0;
+  const int n_ring = ring_keys / RC;
+  auto ring_prefetch = [&](int c) {
+    const srd_words ksrd = make_srd_words(k_base0, c_bytes), vsrd = make_srd_words(v_base0, c_bytes);
+    const uint32_t r0 = fresh(ld_row) * (uint32_t)p.row_bytes, src = (uint32_t)(lo0 + c * RC) * (uint32_t)p.row_bytes;
+    const uint32_t dst = lds0 + (c & 3) * R_STAGE + __builtin_amdgcn_readfirstlane(wave) * 1024;
+#pragma unroll
+    for (int u = 0; u < R_LOADS; ++u) {
+      async_ld16(ksrd, r0 + k_col, src + u * ROWS_PER_LOAD * (uint32_t)p.row_bytes, dst + u * (ATT_THREADS * 16));
+      async_ld16(vsrd, r0 + v_col, src + u * ROWS_PER_LOAD * (uint32_t)p.row_bytes, dst + R_V + u * (ATT_THREADS * 16));
+    }
+  };
+  auto ring = [&](bool has_ref) {
+    constexpr int AHEAD = NCH / 2;  // operands read ahead of the matrix instructions
+    constexpr int PER = 16 / NCH;   // logits per step
+    uint32_t kr[NCH], vr[NDT];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) kr[i] = opaque(k_at ^ (32 * i));
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) vr[dt] = opaque((v_at ^ (64 * dt)) - KC * CH * 16 + R_V);
+    f32x16 x, nxt;  // a tile's exponents, the next one's logits
+    uint4 kf[AHEAD], vf[AHEAD];
+    // tile t of the four that two stages hold
+    auto read_k = [&](int t, int i) { kf[i % AHEAD] = lds_ld16(kr[i], (t >> 1) * R_STAGE + (t & 1) * K_TILE); };
+    auto read_v = [&](int t, int i) {
+      // registers 8s .. 8s+3 of the logits are keys 16s + 4kg + (0..3), registers 8s+4 .. 8s+7 the same + 8
+      const uint32_t at = vr[i % NDT] + (t >> 1) * R_STAGE + (t & 1) * V_TILE + 16 * (i / NDT) * CH * 16;
+      const uint2 lo = ds_read_tr16(at), hi = ds_read_tr16(at + 8 * CH * 16);
+      vf[i % AHEAD] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    };
+    uint32_t move = 2 * R_STAGE;  // to the other two stages
+    float m_sub;
+    auto unit = [&](int t) {
+      uint4 pb[2];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nxt[r] = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        Mma<DT>::run(nxt, kf[i % AHEAD], a[i]);
+#pragma unroll
+        for (int r = i * PER; r < (i + 1) * PER; ++r) {
+          x[r] = fast_exp2(x[r]);
+          l_sum += x[r];
+        }
+        if (i + AHEAD < NCH) read_k((t + 1) & 3, i + AHEAD);
+        else read_v(t, i + AHEAD - NCH);
+        if (i == NCH / 2 - 1 || i == NCH - 1) {
+          const int s = i / (NCH / 2);
+          pb[s] = make_uint4(pack_bf16(x[8 * s], x[8 * s + 1]), pack_bf16(x[8 * s + 2], x[8 * s + 3]),
+                             pack_bf16(x[8 * s + 4], x[8 * s + 5]), pack_bf16(x[8 * s + 6], x[8 * s + 7]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (t == 2)  // the keys of the next tile but one lie in the other stages
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) kr[i] = opaque(kr[i] + move);
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        Mma<DT>::run(o[i % NDT], vf[i % AHEAD], pb[i / NDT]);  // O^T += V^T P^T
+        if (i + AHEAD < NCH) read_v(t, i + AHEAD);
+        else read_k((t + 2) & 3, i + AHEAD - NCH);
+        if (i > 0)  // the last product with the keys takes a step to arrive
+#pragma unroll
+          for (int r = (i - 1) * 16 / (NCH - 1); r < i * 16 / (NCH - 1); ++r) x[r] = fmaf(nxt[r], p.scale2, -m_sub);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * R_LOADS) : "memory");
+    lds_barrier();
+    if (present) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nxt[r] = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) {
+        kf[0] = lds_ld16(kr[i]);
+        Mma<DT>::run(nxt, kf[0], a[i]);
+      }
+      if (!has_ref) {
+        float mx = nxt[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, nxt[r]);
+        mx = half_pair_max(mx);
+        m_ref = mx > NEG_BIG ? fmaf(mx, p.scale2, HEADROOM) : NEG_BIG;
+      }
+      m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[r] = fmaf(nxt[r], p.scale2, -m_sub);
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) read_k(1, i);
+    }
+#pragma unroll 1
+    for (int c = 0; c < n_ring; c += 2) {
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        if (c + half + 2 < n_ring) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * R_LOADS) : "memory");
+        else async_wait();
+        lds_barrier();
+        if (present) unit(2 * half);
+        if (c + half + 3 < n_ring) ring_prefetch(c + half + 3);  // between two tiles: behind the barrier both waves of a SIMD stand still for it (2 - 3 %)
+        if (present) unit(2 * half + 1);
+      }
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) vr[dt] = opaque(vr[dt] + move);
+      move = -move;
+    }
+    lds_barrier();  // every wave has left the stages
+  };
 #pragma unroll 1
   for (int pass = 0;; ++pass) {
-    start();
-    joined = single && have;
-    place();
-    load_rows(upper || single ? t_hi : t_lo);
-    clear();
     bool has_ref = pass != 0, bad = false;
-    if (pass) m_ref = ref_own;
+    if (ring_keys) {
+      for (int c = 0; c < 3; ++c) ring_prefetch(c);
+      load_rows(upper ? t_hi : t_lo);
+      clear();
+      if (pass) m_ref = ref_own;
+      ring(has_ref);
+      has_ref = true;
+      start(lo0 + ring_keys);
+      joined = false;
+      place();
+    } else {
+      start(lo0);
+      joined = single && have;
+      place();
+      load_rows(upper || single ? t_hi : t_lo);
+      clear();
+      if (pass) m_ref = ref_own;
+    }
     if (have) {
       land(0);
       lds_barrier();
@@ -874,7 +1003,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     if (bad || !finite()) *redo = 1;
     __syncthreads();
     if (!*redo) break;
-    start();
+    start(lo0);
     joined = single && have;
     nt0 = joined && !upper ? TPC / 2 : 0;
     load_rows(upper || single ? t_hi : t_lo);
