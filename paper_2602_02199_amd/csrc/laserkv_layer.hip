@@ -229,8 +229,10 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
 // compete, and the hashing wave, which also counts, is the one that the barrier waits for, so it is served first (128k layer
 // 262 us instead of 233 otherwise).  Keys arrive by asynchronous loads (KeyRing); partials of the statistics are fetched
 // eight at a time.  Score kernel of a 16k layer 26.5 -> 23.6 us, of 64k 86 -> 70, of groups of eight (512 hyperplanes) 317
-// -> 257, of the 128k layer 240 -> 215-230, where the clock is set by power (before: order left to the compiler, keys
-// through registers, serial loads at the start, plane tiles past the last one multiplied too).
+// -> 246, of the 128k layer 240 -> 215-230, where the clock is set by power (before: order left to the compiler, keys
+// through registers, serial loads at the start, plane tiles past the last one multiplied too).  What the counting needs is
+// computed from the thread's number chunk by chunk: kept in registers across the loop it went to scratch memory, whose loads
+// wait for the keys on their way (groups of eight 267 us instead of 246, one chunk per workgroup 21.1 instead of 18.9).
 // ---------------------------------------------------------------------------------------------
 constexpr int LY_HALF = LY_WAVES / 2;  // waves of either kind
 
@@ -393,7 +395,8 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       float* col_dst = sCol + (size_t)(cur * LY_HALF + first) * KC;
       auto put = [&](int kt, float col) {
         col = half_pair_sum(col);
-        if (kg == 0) col_dst[kt * 32 + rl] = col;
+        const int l = fresh(lane);
+        if (l < 32) col_dst[kt * 32 + l] = col;
       };
       if (kstep == 1 && kc0 + KC <= k_hi && kc0 + KC - 1 <= lim0) {  // workgroup-uniform: a complete chunk that every row sees
 #pragma unroll
@@ -505,7 +508,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
   const uint32_t cell_max = p.cell_log == 2 ? 255u : 15u;  // full cells of 8 and 4 bits (cell_log 2, 3; those of 16 bits hold every count)
   // sums over the score waves and collision counts of the chunk whose first key is kc0: two lanes per key
   auto finish = [&](int buf, int kc0) {
-    const int key = (tid - LY_HALF * 64) >> 1, sub = tid & 1;
+    const int at_tid = fresh(tid), key = (at_tid - LY_HALF * 64) >> 1, sub = at_tid & 1;
     const int kidx = kc0 + key;
     const uint32_t* bits = sBits + (buf * KC + key) * bits_pitch;
     const size_t at = (size_t)gr.g * p.s_stride + kidx;
