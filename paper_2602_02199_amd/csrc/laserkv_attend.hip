@@ -348,7 +348,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
 //   cost 4 % of the time).
 // Bound by the matrix unit, at the clock that power allows: 128k prefill, last block, 1157 -> 1220 TFLOP/s with the ring (3690
 // -> 3500 us; the loop alone on operands in LDS reaches 1326, and 1850 when they are zeros), window rows over 63 520 keys
-// 149 -> 140 us.  By LDS reads it is bound to about the same: 16 KiB per wave and tile, a clock for 128 bytes.
+// 149 -> 140 us.  What is needed only before and after the loops is computed from the thread's number there: registers are
+// short, and with two of them in scratch memory a block of 1298 rows without a cache took 73.5 us instead of 71.1.  By LDS reads it is bound to about the same: 16 KiB per wave and tile, a clock for 128 bytes.
 template <int DT>
 __host__ __device__ constexpr int rows_chunk_keys() { return DT == DT_BF16 ? 128 : 64; }
 
@@ -437,12 +438,12 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   uint4 a[NCH];
   int blk_end_lane;  // block keys [0, blk_end_lane) are visible to this lane's row
   auto load_rows = [&](int t) {
-    const int m = min(fresh(t * 32 + rl), p.m_rows - 1);
+    const int tid_r = fresh(tid), m = min(t * 32 + (tid_r & 31), p.m_rows - 1);
     int j;
     const int g = div_rem(m, p.n_q, p.nq_magic, &j);
-    const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row;
+    const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row + (tid_r >> 5 & 1) * 16;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + (2 * i + kg) * 16);
+    for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + 2 * i * 16);
     blk_end_lane = max(0, min(p.s_t, p.diag + j + 1));
 #pragma unroll
     for (int i = 0; i < NCH; ++i) landed(a[i]);
@@ -609,7 +610,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // lines of eight rows (with 32-byte pieces of
   // 32 rows the 33 MB of 65536 rows took 3.6 us longer).
   auto write_tile = [&](int t) {
-    const int row = fresh(t * 32 + rl);
+    const int tid_w = fresh(tid), wave = tid_w >> 6, lane = tid_w & 63, rl = lane & 31, kg = lane >> 5;  // not kept through the loops
+    const int row = t * 32 + rl;
     const float l = half_pair_sum(l_sum);
     float scale = 1.0f, *dst;
     if (direct) {
@@ -1035,14 +1037,15 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // against bank conflicts)
   constexpr int OP = D + 4;
   static_assert((size_t)4 * 32 * (OP + 2) * 4 <= (size_t)2 * STAGE * 16, "the states do not fit the stages");
-  float* so = reinterpret_cast<float*>(smem) + (size_t)((wave & 3) * 32 + rl) * OP;
-  float2* sml = reinterpret_cast<float2*>(reinterpret_cast<float*>(smem) + (size_t)4 * 32 * OP) + (wave & 3) * 64 + lane;
+  const int tid_s = fresh(tid), kg_s = tid_s >> 5 & 1;
+  float* so = reinterpret_cast<float*>(smem) + (size_t)((tid_s >> 6 & 3) * 32 + (tid_s & 31)) * OP;
+  float2* sml = reinterpret_cast<float2*>(reinterpret_cast<float*>(smem) + (size_t)4 * 32 * OP) + (tid_s & 255);
   if (joined && !upper) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
-        *reinterpret_cast<float4*>(so + dt * 32 + 8 * q4 + 4 * kg) =
+        *reinterpret_cast<float4*>(so + dt * 32 + 8 * q4 + 4 * kg_s) =
             make_float4(o[dt][4 * q4], o[dt][4 * q4 + 1], o[dt][4 * q4 + 2], o[dt][4 * q4 + 3]);
     *sml = make_float2(m_ref, l_sum);
   }
@@ -1057,7 +1060,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 ov = *reinterpret_cast<const float4*>(so + dt * 32 + 8 * q4 + 4 * kg);
+        const float4 ov = *reinterpret_cast<const float4*>(so + dt * 32 + 8 * q4 + 4 * kg_s);
         const float of[4] = {ov.x, ov.y, ov.z, ov.w};
 #pragma unroll
         for (int u = 0; u < 4; ++u) o[dt][4 * q4 + u] = o[dt][4 * q4 + u] * wa + of[u] * wb;
