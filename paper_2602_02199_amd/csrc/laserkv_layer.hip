@@ -527,7 +527,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       auto nibble_of = [&](int t, uint32_t code) {
         return __builtin_amdgcn_ubfe(sCells[t * p.cell_words + (code >> 3)], (code & 7u) << 2, 4u);
       };
-      // cells are read at their own width: vector instructions hardly overlap with the score waves' matrix instructions
+      // cells are read at their own width: the barrier waits for the counting
       if (p.cell_log == 1) {
 #pragma unroll 8
         for (int t = sub; t < p.n_tables; t += 2)
