@@ -358,7 +358,11 @@ __host__ __device__ constexpr int rows_chunk_keys() { return DT == DT_BF16 ? 128
 template <int CH>
 __device__ __forceinline__ uint32_t v_swz(uint32_t key) { return CH == 8 ? key : 2 * key + (key >> 1); }
 
-template <int DT, int D>
+// Cache rows of a key range from which on its references are fixed (bf16).
+constexpr int FIXED_KEYS = 320;
+
+// RING: with the ring (key ranges of at most FIXED_KEYS cache rows never enter it)
+template <int DT, int D, bool RING>
 __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p) {
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int CH = D * ES / 16;             // 16-byte chunks per row
@@ -659,7 +663,6 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // Sums or outputs that overflow against a fixed reference (from about a logit 145 above the first tile's on, in powers
   // of two) make the workgroup repeat the pass with the exact maxima, which a sweep over the keys finds first.  (One
   // workgroup in a round that repeats it costs three times the round; keys whose lengths spread by e^0.5 reach 140.)
-  constexpr int FIXED_KEYS = 320;
   constexpr bool BF16 = DT == DT_BF16;
   const bool fixed = !BF16 || hi0 - lo0 > FIXED_KEYS;
   int* redo = reinterpret_cast<int*>(smem + (size_t)2 * STAGE);  // one word behind the two stages
@@ -731,7 +734,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   constexpr int R_LOADS = RC * CH / ATT_THREADS;             // per thread, tensor and chunk
   // (not in the workgroup whose waves share the middle tile of an odd number from the start)
   const bool middle = (n_tiles & 1) && pg == (n_pairs - 1) / 4;
-  const int ring_keys = BF16 && fixed && !middle ? (hi0 - lo0) & ~(2 * RC - 1) : 0;
+  const int ring_keys = BF16 && RING && fixed && !middle ? (hi0 - lo0) & ~(2 * RC - 1) : 0;
   const int n_ring = ring_keys / RC;
   auto ring_prefetch = [&](int c) {
     const srd_words ksrd = make_srd_words(k_base0, c_bytes), vsrd = make_srd_words(v_base0, c_bytes);
@@ -1328,7 +1331,13 @@ static hipError_t launch_attend_t(const AttendParams& p, hipStream_t st) {
     constexpr size_t v_stage = DT == DT_BF16 ? (size_t)KC * (D * ES / 16) : (size_t)D * (KC / (16 / ES) + 1);
     constexpr size_t lds = (size_t)2 * ((size_t)KC * (D * ES / 16) + v_stage) * 16 + 16;  // two stages and the redo flag
     static_assert(lds <= 160 * 1024, "two attention chunks do not fit the LDS");
-    hipLaunchKernelGGL((attend_rows_kernel<DT, D>), dim3(p.n_full + p.n_cut * p.n_splits), dim3(ATT_THREADS), lds, st, p);
+    // The ring takes scalar registers and a longer start.  Where no range is long enough for it, the instance without it: 50
+    // rows over 74 and 2691 keys 11.9 -> 11.7 and 21.5 -> 21.3 us, a block of 1298 rows without a cache 71.1 -> 70.3.  (The
+    // ranges that the kernel cuts may be some keys longer than this mean; either instance takes any range.)
+    const dim3 grid(p.n_full + p.n_cut * p.n_splits);
+    const bool ring = DT == DT_BF16 && (p.n_full ? (int64_t)p.cache_len : (int64_t)p.cache_len / p.n_splits) > FIXED_KEYS;
+    if (ring) hipLaunchKernelGGL((attend_rows_kernel<DT, D, DT == DT_BF16>), grid, dim3(ATT_THREADS), lds, st, p);
+    else hipLaunchKernelGGL((attend_rows_kernel<DT, D, false>), grid, dim3(ATT_THREADS), lds, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.n_cut) return e;
   } else if (p.n_splits > 0) {
@@ -1378,7 +1387,9 @@ template <int DT, int D>
 static hipError_t attend_attr() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_kernel<DT, D, att_chunk_keys<DT>()>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_rows_kernel<DT, D>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_rows_kernel<DT, D, false>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_rows_kernel<DT, D, DT == DT_BF16>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess)
