@@ -361,6 +361,8 @@ __device__ __forceinline__ uint32_t v_swz(uint32_t key) { return CH == 8 ? key :
 // Cache rows of a key range from which on its references are fixed (bf16).
 constexpr int FIXED_KEYS = 320;
 
+LKV_HD RowsShape rows_shape(const AttendParams& p) { return {p.m_rows, p.n_q, p.nq_magic, p.cache_len, p.s_t, p.diag}; }
+
 // RING: with the ring (key ranges of at most FIXED_KEYS cache rows never enter it)
 template <int DT, int D, bool RING>
 __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p) {
@@ -395,41 +397,26 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   const int wg = full ? idx : p.n_full + cut_wg, pg = wg % p.n_qgroups, h = wg / p.n_qgroups;
   const bool direct = n_splits == 1;
 
-  // end of the block keys that some row of a tile sees
   const int n_tiles = (p.m_rows + 31) >> 5, n_pairs = (n_tiles + 1) >> 1;
-  auto tile_end = [&](int t) {
-    if (p.s_t == 0) return 0;
-    const int m0 = t * 32, m1 = min(m0 + 32, p.m_rows) - 1;
-    int j0, j1;
-    const int g0 = div_rem(m0, p.n_q, p.nq_magic, &j0), g1 = div_rem(m1, p.n_q, p.nq_magic, &j1);
-    const int j_max = g0 == g1 ? j1 : p.n_q - 1;
-    return max(0, min(p.s_t, p.diag + j_max + 1));
-  };
+  const RowsShape shape = rows_shape(p);
   const int upper = __builtin_amdgcn_readfirstlane(wave >> 2);  // the pair's wave whose tile sees more keys
   const int pr = pg * 4 + (__builtin_amdgcn_readfirstlane(wave) & 3);
   const bool present = pr < n_pairs;
   int t_lo = min(pr, n_pairs - 1), t_hi = n_tiles - 1 - t_lo;
   const bool single = t_lo == t_hi;           // the middle tile of an odd number: both waves work on it
-  int end_lo = tile_end(t_lo), end_hi = tile_end(t_hi);
+  int end_lo = rows_tile_end(shape, t_lo), end_hi = rows_tile_end(shape, t_hi);
   if (end_lo > end_hi) {
     int t = t_lo; t_lo = t_hi; t_hi = t;
     t = end_lo; end_lo = end_hi; end_hi = t;
   }
-  // This split's keys: an equal share of the time the workgroup takes, which passes one key per unit where both waves of
-  // a pair work on their own tiles and two where they share one (the workgroup's first pair stands for all).
+  // this split's keys
   int lo0, hi0, lo1, hi1;
   {
-    const int pr0 = pg * 4, ea = tile_end(pr0), eb = tile_end(n_tiles - 1 - pr0);
-    const int both = p.cache_len + min(ea, eb);
-    int wg_end = max(ea, eb);
-    for (int q = 1; q < 4; ++q)
-      if (pr0 + q < n_pairs) wg_end = max(wg_end, max(tile_end(pr0 + q), tile_end(n_tiles - 1 - pr0 - q)));
-    const int total = both + (max(ea, eb) - min(ea, eb) + 1) / 2;
-    const int share = ((total + n_splits - 1) / n_splits + 31) & ~31;
+    const RowsCut rc = rows_cut(shape, pg, n_splits);
     auto cut = [&](int s, int& c, int& b) {  // the start of split s in the two segments, multiples of 32 (or their ends)
-      const int t = s * share, x = t <= both ? t : both + 2 * (t - both);
+      const int t = s * rc.share, x = t <= rc.both ? t : rc.both + 2 * (t - rc.both);
       c = min(x, p.cache_len);
-      b = s >= n_splits ? wg_end : min(max(x - p.cache_len, 0) & ~31, wg_end);
+      b = s >= n_splits ? rc.end : min(max(x - p.cache_len, 0) & ~31, rc.end);
     };
     cut(split, lo0, lo1);
     cut(split + 1, hi0, hi1);
@@ -1332,11 +1319,16 @@ static hipError_t launch_attend_t(const AttendParams& p, hipStream_t st) {
     constexpr size_t lds = (size_t)2 * ((size_t)KC * (D * ES / 16) + v_stage) * 16 + 16;  // two stages and the redo flag
     static_assert(lds <= 160 * 1024, "two attention chunks do not fit the LDS");
     // The ring takes scalar registers and a longer start.  Where no range is long enough for it, the instance without it: 50
-    // rows over 74 and 2691 keys 11.9 -> 11.7 and 21.5 -> 21.3 us, a block of 1298 rows without a cache 71.1 -> 70.3.  (The
-    // ranges that the kernel cuts may be some keys longer than this mean; either instance takes any range.)
+    // rows over 74 and 2691 keys 11.9 -> 11.7 and 21.5 -> 21.3 us, a block of 1298 rows without a cache 71.1 -> 70.3.  Ranges
+    // run over cache and block keys together: before a long block they hold more cache rows than the mean of the splits (128
+    // rows, 64 heads, 2400 cache rows, block of 4096: mean 300, up to 832; 50.3 us without the ring, 50.1 with).
     const dim3 grid(p.n_full + p.n_cut * p.n_splits);
-    const bool ring = DT == DT_BF16 && (p.n_full ? (int64_t)p.cache_len : (int64_t)p.cache_len / p.n_splits) > FIXED_KEYS;
-    if (ring) hipLaunchKernelGGL((attend_rows_kernel<DT, D, DT == DT_BF16>), grid, dim3(ATT_THREADS), lds, st, p);
+    bool ring = p.n_full && p.cache_len > FIXED_KEYS;
+    if (DT == DT_BF16 && !p.n_full && p.cache_len > FIXED_KEYS) {
+      const RowsShape shape = rows_shape(p);
+      for (int pg = 0; pg < (p.s_t ? p.n_qgroups : 1) && !ring; ++pg) ring = rows_longest_cache_range(shape, pg, p.n_splits) > FIXED_KEYS;
+    }
+    if (DT == DT_BF16 && ring) hipLaunchKernelGGL((attend_rows_kernel<DT, D, DT == DT_BF16>), grid, dim3(ATT_THREADS), lds, st, p);
     else hipLaunchKernelGGL((attend_rows_kernel<DT, D, false>), grid, dim3(ATT_THREADS), lds, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.n_cut) return e;

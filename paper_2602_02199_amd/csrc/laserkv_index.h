@@ -33,4 +33,50 @@ LKV_HD int div_rem(int m, int n, uint32_t magic, int* rem) {
   return q;
 }
 
+// Row tiles and key ranges of attend_rows_kernel: m_rows = G * n_q rows per KV head in tiles of 32, cache_len cache rows,
+// then s_t block keys of which query j sees those up to diag + j.
+struct RowsShape {
+  int m_rows, n_q;
+  uint32_t nq_magic;
+  int cache_len, s_t, diag;
+};
+// the end of the block keys that some row of tile t sees
+LKV_HD int rows_tile_end(const RowsShape& s, int t) {
+  if (s.s_t == 0) return 0;
+  const int m0 = t * 32, m1 = (m0 + 32 < s.m_rows ? m0 + 32 : s.m_rows) - 1;
+  int j0, j1;
+  const int g0 = div_rem(m0, s.n_q, s.nq_magic, &j0), g1 = div_rem(m1, s.n_q, s.nq_magic, &j1);
+  const int end = s.diag + (g0 == g1 ? j1 : s.n_q - 1) + 1, last = end < s.s_t ? end : s.s_t;
+  return last > 0 ? last : 0;
+}
+// Row group pg (four pairs of tiles, the first and the last tile that remain each) cut into n_splits key ranges of equal
+// time, which passes one key per unit where both waves of a pair work on their own tiles and two where they share one (the
+// group's first pair stands for all): range r covers the units [r * share, (r + 1) * share), the first `both` of which are
+// single keys, cache rows first.
+struct RowsCut {
+  int both, share, end;  // end: of the block keys that some row of the group sees
+};
+LKV_HD RowsCut rows_cut(const RowsShape& s, int pg, int n_splits) {
+  const int n_tiles = (s.m_rows + 31) >> 5, n_pairs = (n_tiles + 1) >> 1, pr0 = pg * 4;
+  const int ea = rows_tile_end(s, pr0), eb = rows_tile_end(s, n_tiles - 1 - pr0);
+  const int lo = ea < eb ? ea : eb, hi = ea < eb ? eb : ea;
+  RowsCut c;
+  c.both = s.cache_len + lo;
+  c.end = hi;
+  for (int q = 1; q < 4; ++q)
+    if (pr0 + q < n_pairs) {
+      const int a = rows_tile_end(s, pr0 + q), b = rows_tile_end(s, n_tiles - 1 - pr0 - q);
+      c.end = a > c.end ? a : c.end;
+      c.end = b > c.end ? b : c.end;
+    }
+  const int total = c.both + (hi - lo + 1) / 2;
+  c.share = ((total + n_splits - 1) / n_splits + 31) & ~31;
+  return c;
+}
+// the cache rows of the longest of a group's ranges
+LKV_HD int rows_longest_cache_range(const RowsShape& s, int pg, int n_splits) {
+  const int share = rows_cut(s, pg, n_splits).share;
+  return share < s.cache_len ? share : s.cache_len;
+}
+
 }  // namespace lkv

@@ -74,3 +74,17 @@ def test_causal_block_behind_the_cache(n_q, n, s_t):
 @pytest.mark.parametrize("n_q", [192, 160])
 def test_logits_that_outgrow_the_reference(n_q, late):
     run(128, n_q, 650, 0, late)
+
+
+# the same in ranges that are cut (eight heads, 32 ranges a head), each against a reference of its own, and at d = 64
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("n_q", [160, 256])
+@pytest.mark.parametrize("late", [(15000,), (10, 9000, 15999)])
+def test_logits_that_outgrow_the_reference_of_a_cut_range(d, n_q, late):
+    run(d, n_q, 16000, 0, late, H=8)
+
+
+# window rows before a long block: 300 cache rows a split on average, ranges of up to 832
+def test_cache_rows_of_ranges_that_a_long_block_makes_longer():
+    run(128, 1024, 2400, 4096, H=8)
+    run(128, 1024, 2400, 4096, (1500,), H=8)
