@@ -64,3 +64,24 @@ def test_against_sorting(n):
 def test_layer_thread_counts(s_block):
     check_layer(synth.shrink(synth.WORKLOADS["llama8b-16k"], index=61, name=f"threads-{s_block}", l_ctx=2 * s_block + s_block // 2,
                              s_block=s_block, n_q_heads=8, n_kv_heads=2, needles_per_block=2), with_oracle=s_block <= 1025)
+
+
+# where the interval of counts gets four, two and one counters per value and then parts of several values; few values share
+# all positions, the threshold lies in the part that is not counted, above it, or at the largest
+@pytest.mark.parametrize("top", [0, 1, 3, 254, 255, 256, 257, 510, 511, 512, 513, 1022, 1023, 1024, 1025, 2047, 2048])
+@pytest.mark.parametrize("n", [300, 2000, 4096, 9000])
+def test_counters_of_small_intervals(n, top):
+    lib = binding.LaserKV(2, 1, 64, "bf16", 8, 8, max_block=16384, max_window=8, max_ctx_keys=0)
+    rng = np.random.default_rng(n + top)
+    b = n // 4
+    na = nl = b // 8
+    ke, kl = 3, b - 2 * na - 3
+    for p_zero in (0.0, 0.5, 0.99):
+        values = np.unique([1, top // 2, max(top - 1, 0), top])
+        score = np.where(rng.random(n) < p_zero, 0.0, rng.integers(1, 4, n) * np.float32(0.1234567)).astype(np.float32)
+        count = np.where(rng.random(n) < p_zero, 0, np.minimum(rng.choice(values, n), top)).astype(np.int32)
+        count[n // 2] = top
+        keep = torch.full((b,), -1, dtype=torch.int32, device=DEV)
+        lib.laserkv_select_consensus(torch.from_numpy(score).to(DEV), torch.from_numpy(count).to(DEV), s_t=n, n_anchor=na,
+                                     n_local=nl, k_exact=ke, k_lsh=kl, keep_idx=keep)
+        assert np.array_equal(keep.cpu().numpy(), wanted(score, count, na, nl, ke, kl)), f"{n} {top} {p_zero}"
