@@ -360,6 +360,9 @@ __device__ __forceinline__ uint32_t v_swz(uint32_t key) { return CH == 8 ? key :
 
 // Cache rows of a key range from which on its references are fixed (bf16).
 constexpr int FIXED_KEYS = 320;
+// ... from which on they pass through the ring before a block's own keys: 1024 rows over 455 and their block 47.7 us, with the
+// ring 48.5, but block of 2048 over 1000 88.4 and 86.4.
+constexpr int RING_KEYS = 512;
 
 LKV_HD RowsShape rows_shape(const AttendParams& p) { return {p.m_rows, p.n_q, p.nq_magic, p.cache_len, p.s_t, p.diag}; }
 
@@ -429,7 +432,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   uint4 a[NCH];
   int blk_end_lane;  // block keys [0, blk_end_lane) are visible to this lane's row
   auto load_rows = [&](int t) {
-    const int tid_r = fresh(tid), m = min(t * 32 + (tid_r & 31), p.m_rows - 1);
+    const int tid_r = fresh(tid), row = t * 32 + (tid_r & 31), m = min(RING ? row : fresh(row), p.m_rows - 1);
     int j;
     const int g = div_rem(m, p.n_q, p.nq_magic, &j);
     const char* ptr = p.q.base + (int64_t)(h * p.group + g) * p.q.stride_head + (int64_t)j * p.q.stride_row + (tid_r >> 5 & 1) * 16;
@@ -600,9 +603,12 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // bytes of every 32 of its row; groups of four lanes exchange them so that a store instruction writes whole 128-byte
   // lines of eight rows (with 32-byte pieces of
   // 32 rows the 33 MB of 65536 rows took 3.6 us longer).
+  // the ring's instance keeps nothing of it through the loops (the other one has the registers: 11.85 -> 11.7 us for 64 rows a
+  // head over 74 keys)
+  auto late = [&]() { return RING ? fresh(tid) : tid; };
   auto write_tile = [&](int t) {
-    const int tid_w = fresh(tid), wave = tid_w >> 6, lane = tid_w & 63, rl = lane & 31, kg = lane >> 5;  // not kept through the loops
-    const int row = t * 32 + rl;
+    const int tid_w = late(), wave = tid_w >> 6, lane = tid_w & 63, rl = lane & 31, kg = lane >> 5;
+    const int row = RING ? t * 32 + rl : fresh(t * 32 + rl);
     const float l = half_pair_sum(l_sum);
     float scale = 1.0f, *dst;
     if (direct) {
@@ -1027,7 +1033,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // against bank conflicts)
   constexpr int OP = D + 4;
   static_assert((size_t)4 * 32 * (OP + 2) * 4 <= (size_t)2 * STAGE * 16, "the states do not fit the stages");
-  const int tid_s = fresh(tid), kg_s = tid_s >> 5 & 1;
+  const int tid_s = late(), kg_s = tid_s >> 5 & 1;
   float* so = reinterpret_cast<float*>(smem) + (size_t)((tid_s >> 6 & 3) * 32 + (tid_s & 31)) * OP;
   float2* sml = reinterpret_cast<float2*>(reinterpret_cast<float*>(smem) + (size_t)4 * 32 * OP) + (tid_s & 255);
   if (joined && !upper) {
@@ -1318,15 +1324,21 @@ static hipError_t launch_attend_t(const AttendParams& p, hipStream_t st) {
     constexpr size_t v_stage = DT == DT_BF16 ? (size_t)KC * (D * ES / 16) : (size_t)D * (KC / (16 / ES) + 1);
     constexpr size_t lds = (size_t)2 * ((size_t)KC * (D * ES / 16) + v_stage) * 16 + 16;  // two stages and the redo flag
     static_assert(lds <= 160 * 1024, "two attention chunks do not fit the LDS");
-    // The ring takes scalar registers and a longer start.  Where no range is long enough for it, the instance without it: 50
-    // rows over 74 and 2691 keys 11.9 -> 11.7 and 21.5 -> 21.3 us, a block of 1298 rows without a cache 71.1 -> 70.3.  Ranges
-    // run over cache and block keys together: before a long block they hold more cache rows than the mean of the splits (128
-    // rows, 64 heads, 2400 cache rows, block of 4096: mean 300, up to 832; 50.3 us without the ring, 50.1 with).
+    // The ring takes registers and a longer start.  Where no range is long enough for it, the instance without it: 50 rows
+    // over 74 and 2691 keys 11.9 -> 11.7 and 21.5 -> 21.3 us, a block of 1298 rows without a cache 71.1 -> 70.3.  Without block
+    // keys it pays from the shortest ranges on (256 rows, 384 a range: 35.3 -> 33.5 us).  Before a block, cut ranges run
+    // over cache and block keys together, and the last ones, with the block's keys, decide: unless these hold many cache rows
+    // too, the others only wait for them (eight heads, block of 2048 behind 6000 rows, 1760 a range and 720 in the last: 87.5
+    // us without the ring, 89.4 with; 1024 rows of 32 heads behind 1500: 61.2, 62.7).
     const dim3 grid(p.n_full + p.n_cut * p.n_splits);
-    bool ring = p.n_full && p.cache_len > FIXED_KEYS;
-    if (DT == DT_BF16 && !p.n_full && p.cache_len > FIXED_KEYS) {
+    const int n_tiles = (p.m_rows + 31) >> 5;
+    bool ring = DT == DT_BF16 && p.cache_len > (p.s_t ? RING_KEYS : FIXED_KEYS);
+    if (n_tiles <= 7 && (n_tiles & 1)) ring = false;  // the only workgroup of a range holds the tile that two waves share
+    if (ring && !p.n_full) {
       const RowsShape shape = rows_shape(p);
-      for (int pg = 0; pg < (p.s_t ? p.n_qgroups : 1) && !ring; ++pg) ring = rows_longest_cache_range(shape, pg, p.n_splits) > FIXED_KEYS;
+      if (!p.s_t) ring = rows_cut(shape, 0, p.n_splits).share > FIXED_KEYS;
+      else
+        for (int pg = 0; pg < p.n_qgroups && ring; ++pg) ring = rows_last_cache_range(shape, pg, p.n_splits) > 2 * RING_KEYS;
     }
     if (DT == DT_BF16 && ring) hipLaunchKernelGGL((attend_rows_kernel<DT, D, DT == DT_BF16>), grid, dim3(ATT_THREADS), lds, st, p);
     else hipLaunchKernelGGL((attend_rows_kernel<DT, D, false>), grid, dim3(ATT_THREADS), lds, st, p);

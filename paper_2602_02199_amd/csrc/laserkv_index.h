@@ -73,10 +73,10 @@ LKV_HD RowsCut rows_cut(const RowsShape& s, int pg, int n_splits) {
   c.share = ((total + n_splits - 1) / n_splits + 31) & ~31;
   return c;
 }
-// the cache rows of the longest of a group's ranges
-LKV_HD int rows_longest_cache_range(const RowsShape& s, int pg, int n_splits) {
-  const int share = rows_cut(s, pg, n_splits).share;
-  return share < s.cache_len ? share : s.cache_len;
+// the cache rows of a group's last range, the fewest of all ranges
+LKV_HD int rows_last_cache_range(const RowsShape& s, int pg, int n_splits) {
+  const int64_t before = (int64_t)(n_splits - 1) * rows_cut(s, pg, n_splits).share;
+  return before < s.cache_len ? (int)(s.cache_len - before) : 0;
 }
 
 }  // namespace lkv

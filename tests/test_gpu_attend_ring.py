@@ -1,5 +1,5 @@
-"""Attention of many rows over long ranges of cache rows (more than 320: the ring of four stages of 64 keys, entered with a
-whole number of 128 keys) against float64: ranges around those numbers, rows that leave waves of a workgroup without a tile or
+"""Attention of many rows over long ranges of cache rows (fixed references from 320 rows on, from 512 on the ring of four
+stages of 64 keys, entered with a whole number of 128 keys) against float64: ranges around those numbers, rows that leave waves of a workgroup without a tile or
 share a middle tile, causal blocks behind the ring, and logits that outgrow the fixed reference inside and behind it.
 
 256 KV heads of one row group each, so that a workgroup takes all keys.  Bounds: probabilities rounded to bf16 (2^-8 each)
@@ -52,15 +52,15 @@ def run(d, n_q, n, s_t=0, late=(), H=H):
 
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("n_q", [129, 160, 192, 256])  # five to eight row tiles: a middle tile, absent pairs
-@pytest.mark.parametrize("n", [321, 383, 384, 385, 511, 512, 640, 1000, 1151])
+@pytest.mark.parametrize("n", [321, 383, 384, 385, 511, 512, 513, 575, 639, 640, 641, 767, 768, 1000, 1151])
 def test_cache_lengths(d, n_q, n):
     run(d, n_q, n)
 
 
-# few heads: key ranges are cut, 32 a head on 256 compute units; about 320 keys each, where the launch changes to the instance
-# with the ring and a range's references become fixed, not at the same length
+# few heads: key ranges are cut, 32 a head on 256 compute units; about 320 keys each, where a range's references become fixed,
+# and about 512, where the launch changes to the instance with the ring and a range enters it
 @pytest.mark.parametrize("n_q", [160, 256])
-@pytest.mark.parametrize("n", [10239, 10240, 10250, 10271, 10272, 10300, 11300])
+@pytest.mark.parametrize("n", [10239, 10240, 10250, 10271, 10272, 10300, 11300, 15900, 16383, 16384, 16385, 16500, 17000, 17408])
 def test_cut_ranges(n_q, n):
     run(128, n_q, n, H=8)
 
@@ -84,7 +84,13 @@ def test_logits_that_outgrow_the_reference_of_a_cut_range(d, n_q, late):
     run(d, n_q, 16000, 0, late, H=8)
 
 
-# window rows before a long block: 300 cache rows a split on average, ranges of up to 832
+# cut ranges of cache rows and the block's keys: all of them long, references overflowing in the last too
+@pytest.mark.parametrize("late", [(), (7, 15900)])
+def test_cut_ranges_before_a_block(late):
+    run(128, 1024, 16000, 1024, late, H=8)
+
+
+# window rows before a long block: 300 cache rows a split on average, ranges of up to 832 and none
 def test_cache_rows_of_ranges_that_a_long_block_makes_longer():
     run(128, 1024, 2400, 4096, H=8)
     run(128, 1024, 2400, 4096, (1500,), H=8)

@@ -29,11 +29,11 @@ extern "C" long all_rows(int n_max, int limit, int block) {
 }
 // the first and last rows of heads 0 .. group - 1 for n == 1 .. n_max: the products are monotonic in m, so a quotient
 // that is right at both ends of a head is right in between
-extern "C" void rows_ranges(int m_rows, int n_q, int cache_len, int s_t, int diag, int pg, int n_splits, int* both, int* share, int* longest) {
+extern "C" void rows_ranges(int m_rows, int n_q, int cache_len, int s_t, int diag, int pg, int n_splits, int* both, int* share, int* last) {
   const lkv::RowsShape s{m_rows, n_q, lkv::div_magic(n_q), cache_len, s_t, diag};
   *both = lkv::rows_cut(s, pg, n_splits).both;
   *share = lkv::rows_cut(s, pg, n_splits).share;
-  *longest = lkv::rows_longest_cache_range(s, pg, n_splits);
+  *last = lkv::rows_last_cache_range(s, pg, n_splits);
 }
 extern "C" long head_ends(int n_max, int group, int block) {
   long wrong = 0;
@@ -79,9 +79,9 @@ def test_the_kernel_of_many_rows_takes_the_long_division():
 
 
 @pytest.mark.parametrize("group,n_q,cache_len,s_t,n_splits", [
-    (8, 128, 2400, 4096, 8),   # window rows before a long block: 300 cache rows a split on average, ranges of up to 832
-    (4, 128, 63520, 0, 8), (4, 2048, 910, 2048, 3), (1, 160, 400, 160, 2), (7, 33, 5000, 300, 16), (4, 64, 0, 2048, 4), (2, 250, 333, 1000, 5)])
-def test_the_longest_cache_range_of_a_cut_row_group(host, group, n_q, cache_len, s_t, n_splits):
+    (8, 128, 2400, 4096, 8),   # window rows before a long block: 300 cache rows a split on average, ranges of up to 832 and none
+    (4, 128, 63520, 0, 8), (4, 128, 63520, 0, 8), (4, 2048, 910, 2048, 3), (1, 160, 400, 160, 2), (7, 33, 5000, 300, 16), (4, 64, 0, 2048, 4), (2, 250, 333, 1000, 5)])
+def test_the_last_cache_range_of_a_cut_row_group(host, group, n_q, cache_len, s_t, n_splits):
     m_rows, diag = group * n_q, s_t - n_q
     n_tiles = (m_rows + 31) // 32
     ends = [max([0] + [min(s_t, diag + m % n_q + 1) for m in range(32 * t, min(32 * t + 32, m_rows))]) for t in range(n_tiles)]
@@ -90,15 +90,16 @@ def test_the_longest_cache_range_of_a_cut_row_group(host, group, n_q, cache_len,
         ea, eb = ends[4 * pg], ends[n_tiles - 1 - 4 * pg]
         units = cache_len + min(ea, eb) + (abs(ea - eb) + 1) // 2
         share = (-(-units // n_splits) + 31) // 32 * 32
-        longest = max(min(cache_len, (r + 1) * share) - min(cache_len, r * share) for r in range(n_splits))
+        rows = [min(cache_len, (r + 1) * share) - min(cache_len, r * share) for r in range(n_splits)]
+        assert rows[-1] == min(rows)
         got = [ctypes.c_int() for _ in range(3)]
         host.rows_ranges(m_rows, n_q, cache_len, s_t, diag, pg, n_splits, *[ctypes.byref(x) for x in got])
-        assert [x.value for x in got] == [cache_len + min(ea, eb), share, longest]
+        assert [x.value for x in got] == [cache_len + min(ea, eb), share, rows[-1]]
 
 
-def test_the_instance_with_the_ring_is_chosen_by_the_longest_range():
+def test_the_instance_with_the_ring_is_chosen_by_the_ranges_that_the_kernel_cuts():
     src = open(os.path.join(CSRC, "laserkv_attend.hip")).read()
     launch = src[src.index("hipError_t launch_attend_t("):]
-    assert "rows_longest_cache_range(shape, pg, p.n_splits) > FIXED_KEYS" in launch[:launch.index("\n}")]
+    assert "rows_last_cache_range(shape, pg, p.n_splits) > 2 * RING_KEYS" in launch[:launch.index("\n}")]
     kernel = src[src.index("void attend_rows_kernel"):]
     assert "rows_cut(shape, pg, n_splits)" in kernel[:kernel.index("\n__global__")]
