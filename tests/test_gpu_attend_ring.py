@@ -1,6 +1,7 @@
-"""Attention of many rows over long ranges of cache rows (fixed references from 320 rows on, from 512 on the ring of four
-stages of 64 keys, entered with a whole number of 128 keys) against float64: ranges around those numbers, rows that leave waves of a workgroup without a tile or
-share a middle tile, causal blocks behind the ring, and logits that outgrow the fixed reference inside and behind it.
+"""Attention of many rows over long ranges of cache rows (more than 320, before a block 512: the ring of four stages of 64
+keys, entered with a whole number of 128 keys) against float64: ranges around those numbers, rows that leave waves of a
+workgroup without a tile or share a middle tile, causal blocks behind the ring, and logits that outgrow the fixed reference
+inside and behind it.
 
 256 KV heads of one row group each, so that a workgroup takes all keys.  Bounds: probabilities rounded to bf16 (2^-8 each)
 against weights in float64, plus 4e-6 for 32-bit sums; a row's log-sum-exp 1e-4."""
@@ -43,11 +44,13 @@ def run(d, n_q, n, s_t=0, late=(), H=H):
         w = torch.softmax(x, dim=-1)
         vd = v[h].double()
         bound = (2.0 ** -8 + 4e-6) * (w @ vd.abs())
-        worst = max(worst, float(((out[h].double() - w @ vd).abs() / bound).max()))
+        err = (out[h].double() - w @ vd).abs()
+        worst = max(worst, float((err / bound).max()))
+        # element by element: a maximum over values that are not numbers compares with nothing
+        assert bool((err <= bound).all()), f"output of head {h}: {int((~(err <= bound)).sum())} values beyond the bound, the largest {worst:.3f} times it"
         off = (lse[h].double() - torch.logsumexp(x, dim=-1)).abs()
         assert bool((off <= 1e-4 + 1e-6 * torch.logsumexp(x, dim=-1).abs()).all()), f"log-sum-exp of head {h}: {float(off.max())}"
     print(f"[ring d{d} rows {n_q} cache {n} block {s_t} late {late}] error / bound {worst:.3f}", flush=True)
-    assert worst <= 1.0
 
 
 @pytest.mark.parametrize("d", [128, 64])
@@ -57,8 +60,15 @@ def test_cache_lengths(d, n_q, n):
     run(d, n_q, n)
 
 
-# few heads: key ranges are cut, 32 a head on 256 compute units; about 320 keys each, where a range's references become fixed,
-# and about 512, where the launch changes to the instance with the ring and a range enters it
+# a head's second workgroup holds the middle tile and stays out of the ring that the first one takes
+@pytest.mark.parametrize("n_q", [288, 352])
+@pytest.mark.parametrize("n", [321, 640, 1000])
+def test_a_middle_tile_beside_the_ring(n_q, n):
+    run(128, n_q, n)
+
+
+# few heads: key ranges are cut, 32 a head on 256 compute units; about 320 keys each, where a range's references become fixed
+# and the launch changes to the instance with the ring, not at the same length, and longer ones
 @pytest.mark.parametrize("n_q", [160, 256])
 @pytest.mark.parametrize("n", [10239, 10240, 10250, 10271, 10272, 10300, 11300, 15900, 16383, 16384, 16385, 16500, 17000, 17408])
 def test_cut_ranges(n_q, n):
