@@ -346,10 +346,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_kernel(AttendParams p) {
 //   (`ring`).  Elsewhere two key tiles at a time, chunks alternating between two LDS stages; one barrier per chunk either
 //   way, the next chunks arriving through async_ld16.  LDS addresses are kept per operand chunk (computed at each read they
 //   cost 4 % of the time).
-// Bound by the matrix unit, at the clock that power allows: 128k prefill, last block, 1157 -> 1220 TFLOP/s with the ring (3690
-// -> 3500 us; the loop alone on operands in LDS reaches 1326, and 1850 when they are zeros), window rows over 63 520 keys
-// 149 -> 140 us.  What is needed only before and after the loops is computed from the thread's number there: registers are
-// short, and with two of them in scratch memory a block of 1298 rows without a cache took 73.5 us instead of 71.1.  By LDS reads it is bound to about the same: 16 KiB per wave and tile, a clock for 128 bytes.
+// Bound by the matrix unit, at the clock that power allows: 128k prefill, last block, 1136 -> 1249 TFLOP/s sustained with the
+// ring (calls of 3690-3830 us -> 3500-3530; the loop alone on operands in LDS reaches 1326, and 1850 when they are zeros),
+// window rows over 63 520 keys 149 -> 140 us.  By LDS reads it is bound to about the same: 16 KiB per wave and tile, a clock for
+// 128 bytes.  In the ring's instance registers are short: what is needed only before and after the loops is computed from the
+// thread's number there (with two registers in scratch memory a block of 1298 rows without a cache took 73.5 us instead of 71.1).
 template <int DT>
 __host__ __device__ constexpr int rows_chunk_keys() { return DT == DT_BF16 ? 128 : 64; }
 
