@@ -225,11 +225,12 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
 // bring the keys into LDS, and finish the previous chunk (sums and sign bits meet in LDS, two buffers): the sum over
 // the score waves, and per key and table one probe of the table's cells.  Every SIMD runs one wave of either kind.
 // Both kinds have their instructions in a fixed order where a chunk is complete: a score wave four vector instructions and
-// two exponentials beside each matrix instruction, a hashing wave two of the previous plane tile's signs.  The two of a SIMD
-// compete, and the hashing wave, which also counts, is the one that the barrier waits for, so it is served first (128k layer
-// 262 us instead of 233 otherwise).  Keys arrive by asynchronous loads (KeyRing); partials of the statistics are fetched
-// eight at a time.  Score kernel of a 16k layer 26.5 -> 23.6 us, of 64k 86 -> 70, of groups of eight (512 hyperplanes) 317
-// -> 246, of the 128k layer 240 -> 215-230, where the clock is set by power (before: order left to the compiler, keys
+// two exponentials beside each matrix instruction (exponents a step ahead of their exponentials, sums a step behind), a
+// hashing wave two of the previous plane tile's signs.  A hashing wave first finishes the chunk before, served before the
+// score wave of its SIMD, and then takes its products on equal terms: what is left at the barrier is then the score waves'
+// (128k layer 227 -> 214-218 us, 64k 74.7 -> 68.5, 16k 23.6 -> 22.7, groups of eight 249 -> 240-245; with the hashing waves
+// served first throughout and finishing last 227, never served first 251).  Keys arrive by asynchronous loads (KeyRing);
+// partials of the statistics are fetched eight at a time.  Earlier, with the order left to the compiler, keys
 // through registers, serial loads at the start, plane tiles past the last one multiplied too).  What the counting needs is
 // computed from the thread's number chunk by chunk: kept in registers across the loop it went to scratch memory, whose loads
 // wait for the keys on their way (groups of eight 267 us instead of 246, one chunk per workgroup 21.1 instead of 18.9).
@@ -413,35 +414,43 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
           f32x16* next = acc[s & 1];
           f32x16* done = acc[(s + 1) & 1];
           const int t0 = s % NP * TP, d0 = (s + NP - 1) % NP * TP;
-          float v[2][PER];
           if (mul)
 #pragma unroll
             for (int t = 0; t < TP; ++t)
 #pragma unroll
               for (int e = 0; e < 16; ++e) next[t][e] = 0.0f;
+          float x[PER], y[PER];
+          auto exponents = [&](int j) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+              const int q = j * PER + k, g = q / 4;  // logits of four consecutive rows, tile by tile, and their log-sum-exps
+              const float4 l4 = l[g & 1];
+              const float ls = (q & 3) == 0 ? l4.x : (q & 3) == 1 ? l4.y : (q & 3) == 2 ? l4.z : l4.w;
+              x[k] = fmaf(done[g % TP][4 * (g / TP) + (q & 3)], p.scale2, -ls);
+              if ((q & 3) == 3) l[g & 1] = g + 2 < 4 * TP ? lse_of(d0, g + 2) : lse_of(t0, g + 2 - 4 * TP);
+            }
+          };
+          auto sums = [&](int j) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) c[(j * PER + k) / 4 % TP] += y[k];
+          };
+          if (sum) exponents(0);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int j = 0; j < NCH * TP; ++j) {
             const int i = j / TP, t = j % TP;
             if (mul) Mma<DT>::run(next[t], a[t0 + t][i], kf[i]);
             if (newk && t == TP - 1) kf[i] = key((s + 1) / NP, i);
             if (sum) {
+              if (j > 0) sums(j - 1);
 #pragma unroll
-              for (int k = 0; k < PER; ++k) {
-                const int q = j * PER + k, g = q / 4;  // logits of four consecutive rows, tile by tile, and their log-sum-exps
-                const float4 l4 = l[g & 1];
-                const float ls = (q & 3) == 0 ? l4.x : (q & 3) == 1 ? l4.y : (q & 3) == 2 ? l4.z : l4.w;
-                v[j & 1][k] = fast_exp2(fmaf(done[g % TP][4 * (g / TP) + (q & 3)], p.scale2, -ls));
-                if ((q & 3) == 3) l[g & 1] = g + 2 < 4 * TP ? lse_of(d0, g + 2) : lse_of(t0, g + 2 - 4 * TP);
-              }
-              if (j > 0)
-#pragma unroll
-                for (int k = 0; k < PER; ++k) c[((j - 1) * PER + k) / 4 % TP] += v[(j - 1) & 1][k];
+              for (int k = 0; k < PER; ++k) y[k] = fast_exp2(x[k]);
+              if (j + 1 < NCH * TP) exponents(j + 1);
             }
             __builtin_amdgcn_sched_barrier(0);
           }
           if (sum) {
-#pragma unroll
-            for (int k = 0; k < PER; ++k) c[((NCH * TP - 1) * PER + k) / 4 % TP] += v[(NCH * TP - 1) & 1][k];
+            sums(NCH * TP - 1);
             if (s % NP == 0) {
               put(s / NP - 1, TP > 1 ? c[0] + c[TP - 1] : c[0]);
 #pragma unroll
@@ -574,6 +583,9 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     const bool more = kc0 + KC < k_hi;
     if (more) prefetch(kc0 + KC, cur ^ 1);
     read_from(cur);
+    __builtin_amdgcn_s_setprio(1);
+    if (kc0 > k_lo) finish(cur ^ 1, kc0 - KC);
+    __builtin_amdgcn_s_setprio(0);
     if (active && kstep == 1 && kc0 + KC <= k_hi) {  // a complete chunk
       // The products of a (key tile, plane tile) beside the sign bits of the one before.
       auto steps = [&](auto tiles) {
@@ -644,9 +656,8 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
         }
       }
     }
-    if (kc0 > k_lo) finish(cur ^ 1, kc0 - KC);
-    cur ^= 1;
     if (more) async_wait();
+    cur ^= 1;
     lds_barrier();
   }
   finish(cur ^ 1, k_lo + (k_hi - k_lo - 1) / KC * KC);
