@@ -792,6 +792,18 @@ int laserkv_compress_layer(laserkv_ctx* ctx,
   p.sig_k = plan.use_cells ? nullptr : reinterpret_cast<uint16_t*>(ws + plan.off_sig_k);
   p.sig_q = plan.use_cells ? nullptr : reinterpret_cast<uint16_t*>(ws + plan.off_sig_q);
 
+  p.v = ap.vb;
+  p.k_cache = ap.k_cache;
+  p.v_cache = ap.v_cache;
+  p.cache_stride_head = ap.cache_stride_head;
+  p.n_anchor = na;
+  p.n_local = nl;
+  p.n_kept = b_full;
+  p.last_anchor = na1;
+  p.last_local = nl1;
+  p.last_kept = b_last;
+  lkv::layer_plan_copies(&p);
+
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   const int dt = c.dtype, n_groups = n_blocks * c.n_kv_heads;
   hipError_t e;
@@ -837,7 +849,8 @@ int laserkv_compress_layer(laserkv_ctx* ctx,
   lp.k_lsh = kl;
   lp.s_exact = nullptr;
   lp.keep = nullptr;
-  const lkv::SelectLayer ly = {p.s_stride, n_blocks - 1, s_last, na1, nl1, ke1, kl1, keep_last};
+  const int copied = p.copies || p.last_copies;
+  const lkv::SelectLayer ly = {p.s_stride, n_blocks - 1, s_last, na1, nl1, ke1, kl1, keep_last, copied};
   const int n_cu = ctx->n_cu;
   if ((e = timed(ctx, LKV_KERN_SELECT, st, [&] { return lkv::launch_select_layer(lp, ap, ly, n_cu, st); })) != hipSuccess)
     return fail_hip(ctx, e, "compress_layer: select + append kernel");

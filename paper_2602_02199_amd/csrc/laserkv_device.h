@@ -115,6 +115,10 @@ __device__ __forceinline__ T fresh(T x) {
   asm volatile("" : "+v"(x));
   return x;
 }
+__device__ __forceinline__ int fresh_scalar(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
 // The same for values that change with the loop: only derived addresses (an xor per operand chunk) are kept from
 // becoming induction variables, the scheduler stays free to move the instructions.
 __device__ __forceinline__ uint32_t opaque(uint32_t x) {
@@ -129,6 +133,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void st16_stream(void* p, const uint4& v) {
   u32x4 t = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
+}
+__device__ __forceinline__ void buf_st16_stream(__amdgpu_buffer_rsrc_t r, uint32_t byte_offset, const uint4& v) {
+  const u32x4_ld t = {v.x, v.y, v.z, v.w};
+  __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)byte_offset, 0, 2);  // 2: nt
 }
 template <typename T>
 __device__ __forceinline__ void st_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }

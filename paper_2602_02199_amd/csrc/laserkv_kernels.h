@@ -100,6 +100,7 @@ struct SelectLayer {
   int last;             // index of the last block
   int last_s_t, last_anchor, last_local, last_exact, last_lsh;
   int32_t* keep_last;   // [H_kv, B_last] kept indices of the last block, or null (the positions say it all)
+  int copied;           // the protected rows are in the cache already (their positions are not)
 };
 
 // Adds one layer's scores and counts, summed over its KV heads, into [S] accumulators.
@@ -194,6 +195,15 @@ struct LayerParams {
   int32_t* cnt;          // [groups, s_stride]
   uint16_t* sig_k;       // [groups, s_stride, L] when cells is null
   uint16_t* sig_q;       // [groups, M, L] when cells is null
+  // the blocks' protected rows, which the score kernel copies to the cache: this many per key range of a block, and of the
+  // last one (0: the selection copies them)
+  int copies, last_copies;
+  RowSrc v;              // [H_kv, n_tok, d]
+  char* k_cache;
+  char* v_cache;
+  int64_t cache_stride_head;  // bytes
+  int n_anchor, n_local, n_kept;           // per block
+  int last_anchor, last_local, last_kept;  // of the last one
 };
 struct LayerPlan {
   int rt, use_cells, code_split;  // code_split: workgroups a group's tables are shared out to in the code kernel
@@ -202,6 +212,7 @@ struct LayerPlan {
 };
 bool layer_supports(int dtype, int head_dim, int m_rows);
 void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* plan);  // fills the launch geometry of both
+void layer_plan_copies(LayerParams* p);  // copies and last_copies, of the geometry, v and the parts of the kept rows
 hipError_t launch_layer_codes(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
 hipError_t launch_layer_stats(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
 hipError_t launch_layer_score(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);

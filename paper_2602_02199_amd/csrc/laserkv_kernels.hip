@@ -853,7 +853,8 @@ constexpr int SEL_PARTS = 1024;  // 16 per lane
 constexpr int SEL_BUFFERS = 3;
 constexpr uint32_t SEL_SCORES = (16u << 23) - 1u;  // bit patterns of 16 octaves
 
-// LAYER = true (with FUSED): the groups are all (block, KV head) pairs of a layer.
+// LAYER = true (with FUSED): the groups are all (block, KV head) pairs of a layer, whose protected rows layer_score_kernel
+// copies (but for those of huge strides).
 template <int NT, int EPT, bool FUSED, bool LAYER>
 __global__ __launch_bounds__(NT) void select_kernel(SelectParams p, AppendParams ap, SelectLayer ly, int split) {
   __shared__ __align__(16) uint32_t sHist[SEL_BUFFERS][SEL_PARTS];
@@ -1170,9 +1171,10 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectParams p, AppendParams
   const int pre = block_excl_scan(packed, sWave[1]);
   int n_sure = pre >> 16, n_tie = pre & 0xffff;
   const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
-  // FUSED: this workgroup copies output ranks [r0, r1)
-  const int per = (b_t + split - 1) / split;
-  const int r0 = FUSED ? min(part * per, b_t) : 0, r1 = FUSED ? min(r0 + per, b_t) : b_t;
+  // FUSED: this workgroup copies output ranks [r0, r1); of a layer's, those of the protected rows may have been copied
+  const int c_lo = LAYER && ly.copied ? p.n_anchor : 0, c_hi = LAYER && ly.copied ? b_t - p.n_local : b_t;
+  const int per = (c_hi - c_lo + split - 1) / split;
+  const int r0 = FUSED ? min(c_lo + part * per, c_hi) : 0, r1 = FUSED ? min(r0 + per, c_hi) : b_t;
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
     const bool kept = sel[e] || (act2[e] && n_tie < need2);
@@ -1181,11 +1183,17 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectParams p, AppendParams
       if (pos >= r0 && pos < r1) {
         if (!LAYER || p.keep) p.keep[(size_t)h * b_t + pos] = tid * EPT + e;
         if (FUSED) sKeep[pos - r0] = tid * EPT + e;
+      } else if (LAYER && p.keep && part == 0 && (pos < c_lo || pos >= c_hi)) {
+        p.keep[(size_t)h * b_t + pos] = tid * EPT + e;
       }
     }
     n_sure += sel[e] ? 1 : 0;
     n_tie += act2[e] ? 1 : 0;
   }
+  if (LAYER && part == 0)
+    for (int i = tid; i < c_lo + b_t - c_hi; i += NT)  // the positions of rows that have been copied
+      ap.cache_pos[(int64_t)h * ap.pos_stride_head + ap.cache_len + (i < c_lo ? i : c_hi + i - c_lo)] =
+          ap.block_pos0 + (i < c_lo ? i : p.s_t - p.n_local + i - c_lo);
   if (FUSED) {
     __syncthreads();
     const int cpr = ap.row_bytes / 16, cpr_log = __builtin_ctz(cpr);  // a power of two
@@ -1416,12 +1424,13 @@ hipError_t launch_select_append(const SelectParams& p, const AppendParams& ap, i
 
 hipError_t launch_select_layer(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_cu, hipStream_t st) {
   const int n_groups = (ly.last + 1) * p.n_kv_heads;
-  const int b_t = p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
+  // the others are layer_score_kernel's
+  const int rows = ly.copied ? max(p.k_exact + p.k_lsh, ly.last_exact + ly.last_lsh) : p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
   const int threads = select_threads(p.s_t, true);  // 2048 fit a compute unit
   // Every workgroup of a group selects, and an XCD starts eight workgroups in a microsecond: one chunk per thread made up to
   // 2048 workgroups of few rows (layer of 16k, 64 groups: 65.3 us; four: 62.8; 12 blocks of 1238 keys, 4 heads: 34.3, 28.7;
   // where all workgroups have more rows anyway the same).
-  return launch_select_t<true, true>(p, ap, ly, n_groups, select_split(n_groups, threads, b_t, ap.row_bytes, n_cu, 2048 / threads, 4, 0), st);
+  return launch_select_t<true, true>(p, ap, ly, n_groups, select_split(n_groups, threads, rows, ap.row_bytes, n_cu, 2048 / threads, 4, 0), st);
 }
 
 hipError_t launch_append(const AppendParams& p, int n_kv_heads, hipStream_t st) {

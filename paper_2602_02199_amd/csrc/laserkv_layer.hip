@@ -237,7 +237,8 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
 // ---------------------------------------------------------------------------------------------
 constexpr int LY_HALF = LY_WAVES / 2;  // waves of either kind
 
-template <int DT, int D, int RT, int PT>
+// COPIES: the hashing waves copy protected rows too
+template <int DT, int D, int RT, int PT, bool COPIES>
 __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) {
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int CH = D * ES / 16, NCH = CH / 2;
@@ -578,13 +579,54 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       if (sub == 1) p.cnt[at] = 0;  // count_kernel accumulates with atomics
     }
   };
+  // Rows that are kept whatever the scores (the block's first n_anchor and last n_local) go to the cache from here: this
+  // kernel leaves the memory idle, and the selection behind it, which is bound by it, has so much less to copy (a quarter to
+  // a half of the kept rows at divisors of 8 and 4).  A piece is 16 bytes of a key and of its value; each range takes a share
+  // of them, its threads two a chunk, loaded in one chunk and stored in the next.  Offsets are 32-bit ones into descriptors (64-bit addresses took 0.5 us a
+  // chunk), past whose end nothing is loaded or stored.
+  constexpr int PIECES = 2, STEP = LY_HALF * 64 / CH;  // rows from one of a thread's pieces to its next
+  const bool last_blk = gr.b == p.n_blocks - 1;
+  const int n_front = last_blk ? p.last_anchor : p.n_anchor, n_prot = n_front + (last_blk ? p.last_local : p.n_local);
+  const int n_kept = last_blk ? p.last_kept : p.n_kept, rows_of = last_blk ? p.last_copies : p.copies;
+  int row0 = lin % p.score_splits * rows_of;  // protected rows from here on are still to be stored
+  const int row_end = COPIES ? min(row0 + rows_of, n_prot) : 0;
+  uint4 k_piece[PIECES], v_piece[PIECES];
+  auto each_piece = [&](auto f) {  // (which, row among the protected ones, byte in the row)
+    const int t = fresh(tid) - LY_HALF * 64;
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) f(u, row0 + t / CH + u * STEP, (uint32_t)(t % CH * 16));
+  };
+  auto fetch_pieces = [&]() {
+    const int h = fresh_scalar(gr.h);
+    const __amdgpu_buffer_rsrc_t ks = make_srd(p.k.base + (int64_t)h * p.k.stride_head + (int64_t)gr.lo * p.k.stride_row, (uint32_t)gr.s_t * kstride);
+    const uint32_t vstride = (uint32_t)p.v.stride_row;
+    const __amdgpu_buffer_rsrc_t vs = make_srd(p.v.base + (int64_t)h * p.v.stride_head + (int64_t)gr.lo * p.v.stride_row, (uint32_t)gr.s_t * vstride);
+    each_piece([&](int u, int j, uint32_t c) {
+      const uint32_t token = j < n_front ? j : gr.s_t - n_prot + j;  // past the last one: past the block
+      k_piece[u] = buf_ld16(ks, token * kstride + c);
+      v_piece[u] = buf_ld16(vs, token * vstride + c);
+    });
+  };
+  auto store_pieces = [&]() {
+    const int64_t at = (int64_t)fresh_scalar(gr.h) * p.cache_stride_head + (int64_t)gr.b * p.n_kept * (CH * 16);
+    const uint32_t bytes = (uint32_t)n_kept * (CH * 16);
+    const __amdgpu_buffer_rsrc_t ks = make_srd(p.k_cache + at, bytes), vs = make_srd(p.v_cache + at, bytes);
+    each_piece([&](int u, int j, uint32_t c) {
+      const uint32_t row = j >= row_end ? 0x00ffffffu : j < n_front ? j : n_kept - n_prot + j;
+      buf_st16_stream(ks, row * (CH * 16) + c, k_piece[u]);
+      buf_st16_stream(vs, row * (CH * 16) + c, v_piece[u]);
+    });
+    row0 += PIECES * STEP;
+  };
   int cur = 0;
   for (int kc0 = k_lo; kc0 < k_hi; kc0 += KC) {
     const bool more = kc0 + KC < k_hi;
+    __builtin_amdgcn_s_setprio(1);
+    if (COPIES && kc0 > k_lo && row0 < row_end) store_pieces();  // before the keys' loads: what they wait for has landed
     if (more) prefetch(kc0 + KC, cur ^ 1);
     read_from(cur);
-    __builtin_amdgcn_s_setprio(1);
     if (kc0 > k_lo) finish(cur ^ 1, kc0 - KC);
+    if (COPIES && row0 < row_end) fetch_pieces();
     __builtin_amdgcn_s_setprio(0);
     if (active && kstep == 1 && kc0 + KC <= k_hi) {  // a complete chunk
       // The products of a (key tile, plane tile) beside the sign bits of the one before.
@@ -661,6 +703,10 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     lds_barrier();
   }
   finish(cur ^ 1, k_lo + (k_hi - k_lo - 1) / KC * KC);
+  while (COPIES && row0 < row_end) {
+    store_pieces();
+    if (row0 < row_end) fetch_pieces();
+  }
 }
 
 // ---- host side ----
@@ -673,6 +719,24 @@ static size_t score_lds(int head_dim, int es, int n_planes, int cell_total_words
   const size_t stage = head_dim * es <= 128 ? KeyRing<8>::STAGE : KeyRing<16>::STAGE;
   return 2 * stage + (size_t)2 * LY_KC * bits_pitch * 4 +
          (size_t)2 * LY_HALF * LY_KC * 4 + (size_t)LY_ROWS * 8 + (size_t)cell_total_words * 4 + 16;
+}
+
+// Whether the score kernel copies the blocks' protected rows.  Where it has at least three chunks per workgroup to load and
+// store in (64 groups of four ranges of one chunk 34.3 us a layer, 35.3 with; of two chunks 46.0, 46.2; of three 51.1,
+// 48.9); at least a fifth of the kept rows are protected (16 blocks of 4096 at a divisor of 8 250.7, 244.8; of 16 263, 265);
+// and the plane tiles leave registers (four a wave: 60 bytes in scratch memory, groups of eight 577, 600).
+static bool copies_protected(const LayerParams& p) {
+  return p.score_keys >= 3 * LY_KC && 5 * (p.n_anchor + p.n_local) >= p.n_kept && p.n_planes <= 3 * 32 * LY_HALF;
+}
+
+void layer_plan_copies(LayerParams* p) {
+  auto rows = [&](int s_t, int n_prot) {  // per range with keys
+    const int n_rng = (s_t + p->score_keys - 1) / p->score_keys;
+    return (n_prot + n_rng - 1) / n_rng;
+  };
+  const bool copies = copies_protected(*p) && (int64_t)p->s_block * p->v.stride_row < (int64_t(1) << 31);  // 32-bit offsets
+  p->copies = copies ? rows(p->s_block, p->n_anchor + p->n_local) : 0;
+  p->last_copies = copies ? rows(p->n_tok - (p->n_blocks - 1) * p->s_block, p->last_anchor + p->last_local) : 0;
 }
 
 // Key ranges per group: workgroups come in rounds of n_cu (one per compute unit); a workgroup costs its keys plus
@@ -756,10 +820,14 @@ template <int DT, int D, int RT>
 static hipError_t launch_score_rt(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
   const dim3 grid(p.n_blocks * p.n_kv_heads * p.score_splits), blk(LY_THREADS);
   const int pt = (p.n_planes + 32 * LY_HALF - 1) / (32 * LY_HALF);
-  if (pt == 1) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 1>), grid, blk, plan.score_lds, st, p);
-  else if (pt == 2) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 2>), grid, blk, plan.score_lds, st, p);
-  else if (pt == 3) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 3>), grid, blk, plan.score_lds, st, p);
-  else hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 4>), grid, blk, plan.score_lds, st, p);
+  const bool copies = p.copies || p.last_copies;
+  if (pt == 1 && copies) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 1, true>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 1) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 1, false>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 2 && copies) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 2, true>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 2) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 2, false>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 3 && copies) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 3, true>), grid, blk, plan.score_lds, st, p);
+  else if (pt == 3) hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 3, false>), grid, blk, plan.score_lds, st, p);
+  else hipLaunchKernelGGL((layer_score_kernel<DT, D, RT, 4, false>), grid, blk, plan.score_lds, st, p);
   return hipGetLastError();
 }
 template <int DT, int D>
@@ -783,11 +851,15 @@ hipError_t launch_layer_score(int dtype, int head_dim, const LayerParams& p, con
 static hipError_t allow_lds(const void* kernel) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); }
 template <int DT, int D, int RT>
 static hipError_t score_attrs() {
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 1>));
-  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 2>));
-  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 3>));
-  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 4>));
-  return e;
+  const void* fns[] = {reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 1, false>), reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 1, true>),
+                       reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 2, false>), reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 2, true>),
+                       reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 3, false>), reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 3, true>),
+                       reinterpret_cast<const void*>(&layer_score_kernel<DT, D, RT, 4, false>)};
+  for (const void* f : fns) {
+    const hipError_t e = allow_lds(f);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 template <int DT, int D>
 static hipError_t layer_attrs() {
