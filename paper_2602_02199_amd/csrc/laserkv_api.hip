@@ -808,10 +808,7 @@ int laserkv_compress_layer(laserkv_ctx* ctx,
   const int dt = c.dtype, n_groups = n_blocks * c.n_kv_heads;
   hipError_t e;
   if (!lse_complete) {
-    e = timed(ctx, LKV_KERN_SWEEP1, st, [&] {
-      hipError_t r = lkv::launch_layer_codes(dt, d, p, plan, st);
-      return r != hipSuccess ? r : lkv::launch_layer_stats(dt, d, p, plan, st);
-    });
+    e = timed(ctx, LKV_KERN_SWEEP1, st, [&] { return lkv::launch_layer_stats(dt, d, p, plan, st); });
     if (e != hipSuccess) return fail_hip(ctx, e, "compress_layer: window-row codes and row statistics");
     e = timed(ctx, LKV_KERN_SWEEP2, st, [&] { return lkv::launch_layer_score(dt, d, p, plan, st); });
   } else {

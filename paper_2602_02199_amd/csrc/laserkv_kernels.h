@@ -186,7 +186,7 @@ struct LayerParams {
   int stat_splits, stat_keys, score_splits, score_keys;  // key ranges per group and keys per range
   int n_parts;           // statistics partials per row
   float2* part;          // [groups, M, n_parts]
-  int code_tables, code_tiles;  // tables per pass of the code kernel, 32-plane tiles they take
+  int code_tables, stat_tables;  // tables per set of the code kernel, and of the statistics kernel where it takes the codes
   int cell_log, cell_words;  // log2 of the cells per word of a table's histogram (16, 8 or 4 bits each), words per table
   uint32_t* cells;       // [groups, L, cell_words] histograms of the window-row codes, counts clamped to a cell; or null
   uint32_t* heavy;       // [groups, L, 36] bins whose narrow cell is full: their number, then (code << 16 | count)

@@ -5,9 +5,10 @@
 // worth of groups in a launch the chip is full, and what a launch per block pays once per block (launch, loads of the
 // window rows and hyperplanes, tail) is paid once per layer.
 //
-//   layer_codes_kernel   SimHash codes of the window rows (Sec. 3.3 "Recall") and their histograms, compact enough
-//                        for the score kernel's LDS                                                           [MFMA]
-//   layer_stats_kernel   per window row, partial (reference, sum) of 2^(logit) over a key range (Alg. 1 step 3) [MFMA]
+//   layer_stats_kernel   per window row, partial (reference, sum) of 2^(logit) over a key range (Alg. 1 step 3); then SimHash
+//                        codes of the window rows (Sec. 3.3 "Recall") and their histograms, compact enough for the score
+//                        kernel's LDS                                                                         [MFMA]
+//   layer_codes_kernel   the codes alone, where the caller brings the statistics                              [MFMA]
 //   layer_score_kernel   one pass over the block's keys: pooled probabilities (Alg. 1 step 3), sign bits against all
 //                        hyperplanes, collision counts (Alg. 1 step 6)                                        [MFMA]
 //   then the select + append kernel of laserkv_kernels.hip over all groups.
@@ -32,6 +33,9 @@ constexpr int LY_KC = 128;           // keys per LDS chunk of the score kernel
 constexpr int LY_HEAVY = 36;         // words per table's list of heavy bins: at most LY_ROWS / 15 = 34 of them
 constexpr int LY_CODE_PLANES = 256;  // hyperplanes per pass of layer_codes_kernel at most
 
+// Rows of LDS for the hyperplanes of a set of tables: a wave's tiles of 32 may start at any table and end past the last one
+constexpr int code_plane_rows(int tables, int n_bits) { return tables * n_bits + 31; }
+
 struct LayerGroup {
   int g, b, h, lo, s_t, n_ctx;
 };
@@ -52,7 +56,7 @@ __device__ __forceinline__ const char* layer_row(const LayerParams& p, const Lay
 }
 
 // ---------------------------------------------------------------------------------------------
-// Codes of a group's window rows.  Workgroup = (group, share of its tables); a wave holds 32 rows as MFMA operands and the tables
+// Codes of a group's window rows.  Waves hold 32 or 64 rows as MFMA operands and the tables
 // pass by in sets whose hyperplanes and histograms fit the LDS.  A set's codes are counted in LDS histograms (16-bit
 // bins, 32 bins per 17 words against bank conflicts), which leave as cells of 16, 8 or 4 bits per bin, the widest with
 // which a group's tables fit 64 KiB of the score kernel's LDS (4 bits at K = 12, L = 32).  A narrow cell that is full
@@ -61,119 +65,162 @@ __device__ __forceinline__ const char* layer_row(const LayerParams& p, const Lay
 // ---------------------------------------------------------------------------------------------
 constexpr int LY_CODE_THREADS = 1024;
 
-template <int DT, int D>
-__global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParams p) {
+// b: the wave's rows row0 .. as MFMA fragments; t_first, t_step: the workgroup's sets of `n_set` tables.  Waves that share rows
+// (wk of them) take different tables of a set.  All NT threads take part.
+template <int DT, int D, int RT, int NT>
+__device__ __forceinline__ void window_codes(const LayerParams& p, int g, uint4* smem, const uint4 (&b)[RT][D * (DT == DT_BF16 ? 2 : 4) / 32],
+                                             int row0, bool active, int ks, int wk, int n_set, int t_first, int t_step) {
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int CH = D * ES / 16, NCH = CH / 2, CHP = CH + 1;
-  constexpr int NPL = LY_CODE_PLANES * CH / LY_CODE_THREADS;  // 16-byte pieces of hyperplanes per thread at most
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
-  const LayerGroup gr = layer_group(p, blockIdx.x);
+  constexpr int NPL = LY_CODE_PLANES * CH / NT;  // 16-byte pieces of hyperplanes per thread at most
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  const int tid = threadIdx.x, lane = tid & 63, rl = lane & 31, kg = lane >> 5;
   const bool wide = p.cells == nullptr;
   const int words = (1 << p.n_bits) >= 32 ? (1 << p.n_bits) >> 5 : 1;  // groups of 32 bins per table
   const int hp = words * 17;
 
-  extern __shared__ uint4 smem[];
-  uint4* sP = smem;                                                                    // [code_tiles * 32][CHP]
-  uint32_t* sH = reinterpret_cast<uint32_t*>(smem + (size_t)p.code_tiles * 32 * CHP);  // [code_tables][hp]
-  int* sHeavy = reinterpret_cast<int*>(sH + ((p.code_tables * hp + 3) & ~3));          // [code_tables]
+  uint4* sP = smem;                                                                          // [planes of a set][CHP]
+  uint32_t* sH = reinterpret_cast<uint32_t*>(smem + (size_t)code_plane_rows(n_set, p.n_bits) * CHP);  // [n_set][hp]
+  int* sHeavy = reinterpret_cast<int*>(sH + ((n_set * hp + 3) & ~3));                        // [n_set]
 
   uint4 pre[NPL];  // the next set's hyperplanes, on their way while the current set is worked on
   auto fetch = [&](int t0) {
-    const int np = min(p.code_tables, p.n_tables - t0) * p.n_bits;
+    const int np = min(n_set, p.n_tables - t0) * p.n_bits;
 #pragma unroll
     for (int u = 0; u < NPL; ++u) {
-      const int row = (tid + u * LY_CODE_THREADS) / CH;
-      pre[u] = ld16(p.planes + (size_t)(t0 * p.n_bits + min(row, np - 1)) * (D * ES) + tid % CH * 16);
+      const int row = (tid + u * NT) / CH;
+      if (row < np) pre[u] = ld16(p.planes + (size_t)(t0 * p.n_bits + row) * (D * ES) + tid % CH * 16);
     }
   };
-  const int t_first = blockIdx.y * p.code_tables, t_step = gridDim.y * p.code_tables;  // this workgroup's sets of tables
-  fetch(t_first);
-  uint4 b[NCH];  // this wave's 32 window rows
-  const int row = wave * 32 + rl;
-  const bool active = wave * 32 < p.m_rows;
-  if (active) {
-    const char* ptr = layer_row(p, gr, min(row, p.m_rows - 1));
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) b[i] = ld16(ptr + (2 * i + kg) * 16);
-  }
+  if (t_first < p.n_tables) fetch(t_first);
   const uint32_t code_mask = (1u << p.n_bits) - 1u;
-  const int cpw = 1 << p.cell_log, cbits = 32 >> p.cell_log, cw_log = max(p.n_bits - p.cell_log, 0);  // cell_words = 1 << cw_log
+  const int cbits = 32 >> p.cell_log, cw_log = max(p.n_bits - p.cell_log, 0);  // cell_words = 1 << cw_log
   const uint32_t cmax = cbits == 16 ? 0xffffu : (1u << cbits) - 1u;
   for (int t0 = t_first; t0 < p.n_tables; t0 += t_step) {
-    const int n_tab = min(p.code_tables, p.n_tables - t0);
-    const int np = n_tab * p.n_bits, n_tile = (np + 31) >> 5;
+    const int n_tab = min(n_set, p.n_tables - t0), np = n_tab * p.n_bits;
     __syncthreads();  // the previous set's histograms have been read
 #pragma unroll
     for (int u = 0; u < NPL; ++u) {
-      const int r = (tid + u * LY_CODE_THREADS) / CH;
-      if (r < n_tile * 32) sP[r * CHP + tid % CH] = pre[u];
+      const int r = (tid + u * NT) / CH;
+      if (r < np) sP[r * CHP + tid % CH] = pre[u];
     }
     if (!wide) {
       uint4* h4 = reinterpret_cast<uint4*>(sH);
-      for (int i = tid; i < (n_tab * hp + 3) / 4; i += LY_CODE_THREADS) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+      for (int i = tid; i < (n_tab * hp + 3) / 4; i += NT) h4[i] = make_uint4(0u, 0u, 0u, 0u);
       if (tid < n_tab) sHeavy[tid] = 0;
     }
     __syncthreads();
     if (t0 + t_step < p.n_tables) fetch(t0 + t_step);
-    if (active) {
-      uint32_t prev = 0u;
-      int tt0 = 0;  // first table of the set whose bits are not complete yet
+    const int ta = n_tab * ks / wk, tb = n_tab * (ks + 1) / wk;  // this wave's tables of the set
+    // Codes of 16 bits lie in sig_q as the tiles' words follow each other: eight at a time go out (two bytes at a time every
+    // store writes to 64 lines)
+    const bool plain = wide && p.n_bits == 16 && ((p.n_tables | (t0 + ta)) & 7) == 0;
+    if (active && ta < tb) {
+      uint32_t prev[RT] = {};
+      uint4 last4[RT];  // the last four words
+      int tt0 = ta;  // first table whose bits are not complete yet
 #pragma unroll 1
-      for (int t = 0; t < n_tile; ++t) {
-        const uint4* prow = sP + (size_t)(t * 32 + plane_row(rl)) * CHP + kg;
-        f32x16 acc;
+      for (int t = 0; tt0 < tb; ++t) {
+        const uint4* prow = sP + (size_t)(ta * p.n_bits + t * 32 + plane_row(rl)) * CHP + kg;  // rows past the set's planes hold anything
+        f32x16 acc[RT];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int i = 0; i < NCH; ++i) Mma<DT>::run(acc, prow[2 * i], b[i]);
-        const int tt1 = min(32 * (t + 1), np) / p.n_bits;  // tables complete after this tile
-        uint32_t neg = 0u;
+          for (int e = 0; e < 16; ++e) acc[r][e] = 0.0f;
 #pragma unroll
-        for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[e]), 31);
-        const uint32_t pos = ~neg & 0xffffu;  // bit = projection >= 0
-        const uint32_t other = half_other(pos, kg);
-        const uint32_t word = kg ? (other | (pos << 16)) : (pos | (other << 16));
-        const uint64_t two = ((uint64_t)word << 32) | prev;
-        prev = word;
-        if (row < p.m_rows)
-          for (int tt = tt0 + ((tt0 ^ kg) & 1); tt < tt1; tt += 2) {  // tables alternate between the two lanes of a row
-            const uint32_t code = (uint32_t)(two >> (tt * p.n_bits - 32 * t + 32)) & code_mask;
-            if (wide) p.sig_q[((size_t)gr.g * p.m_rows + row) * p.n_tables + t0 + tt] = (uint16_t)code;
-            else atomicAdd(sH + tt * hp + (code >> 5) * 17 + ((code & 31u) >> 1), 1u << ((code & 1u) * 16));
-          }
+        for (int i = 0; i < NCH; ++i) {
+          const uint4 pf = prow[2 * i];
+#pragma unroll
+          for (int r = 0; r < RT; ++r) Mma<DT>::run(acc[r], pf, b[r][i]);
+        }
+        const int tt1 = min(ta + 32 * (t + 1) / p.n_bits, tb);  // tables complete after this tile
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          uint32_t neg = 0u;
+#pragma unroll
+          for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[r][e]), 31);
+          const uint32_t pos = ~neg & 0xffffu;  // bit = projection >= 0
+          const uint32_t other = half_other(pos, kg);
+          const uint32_t word = kg ? (other | (pos << 16)) : (pos | (other << 16));
+          const int row = row0 + r * 32 + rl;
+          last4[r] = make_uint4(last4[r].y, last4[r].z, last4[r].w, word);
+          if (plain && ta + 2 * (t | 3) + 1 < tb) {
+            if ((t & 3) == 3 && row < p.m_rows && kg == (r & 1)) *reinterpret_cast<uint4*>(p.sig_q + ((size_t)g * p.m_rows + row) * p.n_tables + t0 + ta + 2 * (t - 3)) = last4[r];
+          } else if (row < p.m_rows)
+            for (int tt = tt0 + ((tt0 ^ kg) & 1); tt < tt1; tt += 2) {  // tables alternate between the two lanes of a row
+              const int at = (tt - ta) * p.n_bits - 32 * t;  // its first bit in this tile's word, below 0: in the word before
+              const uint32_t code = __builtin_amdgcn_alignbit(word, at < 0 ? prev[r] : word, at & 31) & code_mask;
+              if (wide) p.sig_q[((size_t)g * p.m_rows + row) * p.n_tables + t0 + tt] = (uint16_t)code;
+              else atomicAdd(sH + tt * hp + (code >> 5) * 17 + ((code & 31u) >> 1), 1u << ((code & 1u) * 16));
+            }
+          prev[r] = word;
+        }
         tt0 = tt1;
       }
     }
     if (wide) continue;
     __syncthreads();
-    for (int i = tid; i < n_tab << cw_log; i += LY_CODE_THREADS) {
-      const int tt = i >> cw_log, cw = i & (p.cell_words - 1), c0 = cw << p.cell_log;
-      const uint32_t* hist = sH + tt * hp + (c0 >> 5) * 17 + ((c0 & 31) >> 1);
-      const size_t table = (size_t)gr.g * p.n_tables + t0 + tt;
-      uint32_t v[4], out = 0u;
-      bool full = false;
+    // cells of CPW per word, WORDS words at a time: two bins at a time, clamped and moved next to each other
+    auto pack = [&](auto cpw, auto n_words) {
+      constexpr int CPW = decltype(cpw)::value, CB = 32 / CPW, WORDS = decltype(n_words)::value;
+      const int per_log = cw_log - (WORDS == 4 ? 2 : 0);
+      for (int i = tid; i < n_tab << per_log; i += NT) {
+        const int tt = i >> per_log, cw = (i & ((1 << per_log) - 1)) * WORDS, c0 = cw * CPW;
+        const uint32_t* hist = sH + tt * hp + (c0 >> 5) * 17 + ((c0 & 31) >> 1);  // at most 32 bins, within their 17 words
+        const size_t table = (size_t)g * p.n_tables + t0 + tt;
+        uint32_t out[4] = {0u, 0u, 0u, 0u};
+        u16x2 most = {0, 0};
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        v[u] = 2 * u < cpw ? hist[u] : 0u;
-        const uint32_t lo = v[u] & 0xffffu, hi = v[u] >> 16;
-        full |= max(lo, hi) >= cmax;
-        out |= (min(lo, cmax) | (min(hi, cmax) << cbits)) << (2 * u * cbits & 31);  // words past the cells are zero
-      }
-      p.cells[table * p.cell_words + cw] = out;
-      if (full)
-        for (int u = 0; u < cpw; ++u) {
-          const uint32_t c = hist[u >> 1] >> ((u & 1) * 16) & 0xffffu;
-          if (c >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u) << 16 | c;
+        for (int u = 0; u < WORDS * CPW / 2; ++u) {
+          const u16x2 v = __builtin_bit_cast(u16x2, hist[u]), limit = {(unsigned short)cmax, (unsigned short)cmax};
+          most = __builtin_elementwise_max(most, v);
+          const uint32_t two = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(v, limit));
+          out[u / (CPW / 2)] |= (CPW == 2 ? two : (two | two >> (16 - CB)) & ((1u << (2 * CB & 31)) - 1u)) << (2 * CB * u & 31);
         }
-    }
+        uint32_t* dst = p.cells + table * p.cell_words + cw;
+        if (WORDS == 4) *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
+        else *dst = out[0];
+        if (max(most.x, most.y) >= cmax)
+          for (int u = 0; u < WORDS * CPW; ++u) {
+            const uint32_t c = hist[u >> 1] >> ((u & 1) * 16) & 0xffffu;
+            if (c >= cmax) p.heavy[table * LY_HEAVY + 1 + atomicAdd(&sHeavy[tt], 1)] = (uint32_t)(c0 + u) << 16 | c;
+          }
+      }
+    };
+    auto pack_cells = [&](auto cpw) {
+      if (cw_log >= 2) pack(cpw, std::integral_constant<int, 4>{});
+      else pack(cpw, std::integral_constant<int, 1>{});
+    };
+    if (p.cell_log == 1) pack_cells(std::integral_constant<int, 2>{});
+    else if (p.cell_log == 2) pack_cells(std::integral_constant<int, 4>{});
+    else pack_cells(std::integral_constant<int, 8>{});
     __syncthreads();
-    if (tid < n_tab) p.heavy[((size_t)gr.g * p.n_tables + t0 + tid) * LY_HEAVY] = (uint32_t)sHeavy[tid];
+    if (tid < n_tab) p.heavy[((size_t)g * p.n_tables + t0 + tid) * LY_HEAVY] = (uint32_t)sHeavy[tid];
   }
+}
+
+template <int DT, int D>
+__global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParams p) {
+  constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
+  const LayerGroup gr = layer_group(p, blockIdx.x);
+  extern __shared__ uint4 smem[];
+  uint4 b[1][NCH];  // this wave's 32 window rows
+  const bool active = wave * 32 < p.m_rows;
+  if (active) {
+    const char* ptr = layer_row(p, gr, min(wave * 32 + rl, p.m_rows - 1));
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) b[0][i] = ld16(ptr + (2 * i + kg) * 16);
+  }
+  window_codes<DT, D, 1, LY_CODE_THREADS>(p, gr.g, smem, b, wave * 32, active, 0, 1, p.code_tables, blockIdx.y * p.code_tables, gridDim.y * p.code_tables);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Row statistics (laserkv_rowstats.h).  Workgroup = (group, key range); 2^wr_log waves share the rows (RT tiles each) and,
 // where the rows need fewer than eight waves, the others take different key tiles.
+// The rows' codes follow, while the rows are in registers: a launch of their own paid its start, the rows' way into registers
+// and a round of workgroups once more (16k layer 7.0 + 21.2 -> 23.4 us, 64k 13.8 + 50.9 -> 59.7, groups of eight 15.1 + 144.7
+// -> 157.7, 128k 33.7 + 155.6 -> 186).
 // ---------------------------------------------------------------------------------------------
 template <int DT, int D, int RT>
 __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) {
@@ -208,13 +255,14 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
                                         (uint32_t)n_keys * kstride);
   float ref[RT], sum[RT];
   row_stats<DT, D, RT>(smem, ksrd, kstride, k_lo, k_hi, lim0, lim, q, p.scale2, ks, wk, active, ref, sum);
-  if (!active) return;
+  if (active)
 #pragma unroll
-  for (int r = 0; r < RT; ++r) {
-    const int row = row0 + r * 32 + rl;
-    if (kg == 0 && row < p.m_rows)
-      p.part[((size_t)gr.g * p.m_rows + row) * p.n_parts + sp * wk + ks] = make_float2(ref[r], sum[r]);
-  }
+    for (int r = 0; r < RT; ++r) {
+      const int row = row0 + r * 32 + rl;
+      if (kg == 0 && row < p.m_rows)
+        p.part[((size_t)gr.g * p.m_rows + row) * p.n_parts + sp * wk + ks] = make_float2(ref[r], sum[r]);
+    }
+  window_codes<DT, D, RT, LY_THREADS>(p, gr.g, smem, q, row0, active, ks, wk, p.stat_tables, sp * p.stat_tables, p.stat_splits * p.stat_tables);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -786,9 +834,21 @@ void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* pl
   const int share = min(max(1, n_cu / n_groups), p->n_tables);
   p->code_tables = min(p->code_tables, (p->n_tables + share - 1) / share);
   plan->code_split = min(share, (p->n_tables + p->code_tables - 1) / p->code_tables);
-  p->code_tiles = (p->code_tables * p->n_bits + 31) / 32;
-  plan->codes_lds = (size_t)p->code_tiles * 32 * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)(p->code_tables * (words * 17 + 1) + 4) * 4 : 0);
-  plan->stats_lds = row_stats_lds(head_dim * es);
+  auto codes_lds = [&](int tables) {
+    return (size_t)code_plane_rows(tables, p->n_bits) * (head_dim * es / 16 + 1) * 16 + (plan->use_cells ? (size_t)(tables * (words * 17 + 1) + 4) * 4 : 0);
+  };
+  plan->codes_lds = codes_lds(p->code_tables);
+  // The statistics kernel takes the codes along, a group's tables shared out over its key ranges.  Where they need more than
+  // one set, sets that fill whole tiles of hyperplanes (32 tables of 12 bits: eight at a time 177.5 us, eleven 179.1).
+  const int tables_of = (p->n_tables + p->stat_splits - 1) / p->stat_splits;
+  p->stat_tables = min(LY_CODE_PLANES / p->n_bits, tables_of);
+  while (p->stat_tables > 1 && codes_lds(p->stat_tables) > 160 * 1024) --p->stat_tables;
+  if (p->stat_tables < tables_of) {
+    int whole = 1;
+    while (whole * p->n_bits & 31) ++whole;
+    if (whole <= p->stat_tables) p->stat_tables -= p->stat_tables % whole;
+  }
+  plan->stats_lds = max(row_stats_lds(head_dim * es), codes_lds(p->stat_tables));
   plan->score_lds = score_lds(head_dim, es, p->n_planes, plan->use_cells ? cw * p->n_tables : 0);
   // workspace
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
