@@ -1149,7 +1149,7 @@ __global__ __launch_bounds__((D / 4) * COMB_SLICES) void attend_combine_kernel(A
 // ---------------------------------------------------------------------------------------------
 constexpr int LSE_ROWS = 512;
 
-template <int DT, int D, int RT>
+template <int DT, int D, int RT, bool LONG>
 __global__ __launch_bounds__(RS_THREADS) void attend_lse_kernel(AttendParams p) {
   constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(RS_THREADS) void attend_lse_kernel(AttendParams p) 
   }
   const srd_words ksrd = make_srd_words(p.k_cache + (int64_t)h * p.cache_stride_head, (uint32_t)p.cache_len * (uint32_t)p.row_bytes);
   float ref[RT], sum[RT];
-  row_stats<DT, D, RT>(smem, ksrd, (uint32_t)p.row_bytes, k_lo, k_hi, k_hi, lim, q, p.scale2, ks, wk, active, ref, sum);
+  row_stats<DT, D, RT, LONG>(smem, ksrd, (uint32_t)p.row_bytes, k_lo, k_hi, k_hi, lim, q, p.scale2, ks, wk, active, ref, sum);
   // the waves that shared rows meet in LDS (free after row_stats)
   float2* sP = reinterpret_cast<float2*>(smem);  // [wk][rows of the group]
   const int n_rows = RT * 32 << p.wprt_log;
@@ -1362,8 +1362,11 @@ static hipError_t launch_attend_lse_t(const AttendParams& p, hipStream_t st) {
   if (p.n_splits > 0) {
     const dim3 grid(p.n_splits * p.n_qgroups * p.n_kv_heads), blk(RS_THREADS);
     const size_t lds = row_stats_lds(D * (DT == DT_BF16 ? 2 : 4));
-    if (min(p.m_rows, LSE_ROWS) > 128) hipLaunchKernelGGL((attend_lse_kernel<DT, D, 2>), grid, blk, lds, st, p);
-    else hipLaunchKernelGGL((attend_lse_kernel<DT, D, 1>), grid, blk, lds, st, p);
+    const int rt = min(p.m_rows, LSE_ROWS) > 128 ? 2 : 1;
+    const bool lng = row_stats_long(DT, D * (DT == DT_BF16 ? 2 : 4), rt, p.keys_per_split);
+    if (rt == 2 && lng) hipLaunchKernelGGL((attend_lse_kernel<DT, D, 2, DT == DT_BF16>), grid, blk, lds, st, p);
+    else if (rt == 2) hipLaunchKernelGGL((attend_lse_kernel<DT, D, 2, false>), grid, blk, lds, st, p);
+    else hipLaunchKernelGGL((attend_lse_kernel<DT, D, 1, false>), grid, blk, lds, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1396,9 +1399,11 @@ static hipError_t attend_attr() {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_rows_kernel<DT, D, DT == DT_BF16>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 2>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 2, false>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attend_lse_kernel<DT, D, 2, DT == DT_BF16>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
 }
 

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(LY_CODE_THREADS) void layer_codes_kernel(LayerParam
 // and a round of workgroups once more (16k layer 7.0 + 21.2 -> 23.4 us, 64k 13.8 + 50.9 -> 59.7, groups of eight 15.1 + 144.7
 // -> 157.7, 128k 33.7 + 155.6 -> 186).
 // ---------------------------------------------------------------------------------------------
-template <int DT, int D, int RT>
+template <int DT, int D, int RT, bool LONG>
 __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) {
   constexpr int NCH = D * (DT == DT_BF16 ? 2 : 4) / 32;
   static_assert(LY_THREADS == RS_THREADS, "row_stats works with eight waves");
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
   const srd_words ksrd = make_srd_words(p.k.base + (int64_t)gr.h * p.k.stride_head + (int64_t)(gr.lo - gr.n_ctx) * p.k.stride_row,
                                         (uint32_t)n_keys * kstride);
   float ref[RT], sum[RT];
-  row_stats<DT, D, RT>(smem, ksrd, kstride, k_lo, k_hi, lim0, lim, q, p.scale2, ks, wk, active, ref, sum);
+  row_stats<DT, D, RT, LONG>(smem, ksrd, kstride, k_lo, k_hi, lim0, lim, q, p.scale2, ks, wk, active, ref, sum);
   if (active)
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
@@ -872,8 +872,10 @@ static hipError_t launch_codes_t(const LayerParams& p, const LayerPlan& plan, hi
 template <int DT, int D>
 static hipError_t launch_stats_t(const LayerParams& p, const LayerPlan& plan, hipStream_t st) {
   const dim3 grid(p.n_blocks * p.n_kv_heads * p.stat_splits);
-  if (plan.rt == 2) hipLaunchKernelGGL((layer_stats_kernel<DT, D, 2>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
-  else hipLaunchKernelGGL((layer_stats_kernel<DT, D, 1>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
+  const bool lng = row_stats_long(DT, D * (DT == DT_BF16 ? 2 : 4), plan.rt, p.stat_keys);
+  if (plan.rt == 2 && lng) hipLaunchKernelGGL((layer_stats_kernel<DT, D, 2, DT == DT_BF16>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
+  else if (plan.rt == 2) hipLaunchKernelGGL((layer_stats_kernel<DT, D, 2, false>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
+  else hipLaunchKernelGGL((layer_stats_kernel<DT, D, 1, false>), grid, dim3(LY_THREADS), plan.stats_lds, st, p);
   return hipGetLastError();
 }
 template <int DT, int D, int RT>
@@ -924,8 +926,9 @@ static hipError_t score_attrs() {
 template <int DT, int D>
 static hipError_t layer_attrs() {
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&layer_codes_kernel<DT, D>));
-  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 1>));
-  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 2>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 1, false>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 2, false>));
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&layer_stats_kernel<DT, D, 2, DT == DT_BF16>));
   if (e == hipSuccess) e = score_attrs<DT, D, 1>();
   if (e == hipSuccess) e = score_attrs<DT, D, 2>();
   if (e == hipSuccess) e = score_attrs<DT, D, 4>();

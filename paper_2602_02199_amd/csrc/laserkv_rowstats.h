@@ -30,6 +30,13 @@ constexpr size_t row_stats_lds(int row_bytes) {
          : row_bytes <= 256 ? (size_t)KeyRing<16>::STAGES * KeyRing<16>::STAGE : (size_t)KeyRing<32>::STAGES * KeyRing<32>::STAGE;
 }
 
+// Whether ranges of this many keys take the instance for long ones: from twelve chunks on (512 rows over 63 520 keys in ranges
+// of 15.5 chunks 77.1 -> 73.5 us, 64k layer of 18 a range 167.9 -> 166.6; 256 rows in ranges of 8 29.1 -> 29.6, 16k layer of 5
+// a range 59.3 -> 60.4).
+constexpr bool row_stats_long(int dtype, int row_bytes, int rt, int keys) {
+  return dtype == DT_BF16 && rt == 2 && keys >= 12 * (row_bytes <= 256 ? 128 : 64);
+}
+
 // Keys k_lo .. k_hi - 1 of the descriptor's rows against RT 32-row tiles per wave (q: the rows' MFMA fragments).  Waves
 // that share rows take different 32-key tiles (ks, ks + wk, ...; active, ks and wk are the same in all lanes of a wave).
 // Keys are the A operand and rows the B operand, so a lane owns a row per tile; its two halves hold the same rows over
@@ -49,7 +56,8 @@ constexpr size_t row_stats_lds(int row_bytes) {
 // 25.4-27 us.  Before: one tile after another, products, then exponentials; the first product of every chunk waited for the
 // next chunk's loads.  Barriers cost: chunks of 64 keys (eight stages) 174 us, of 256 (two stages, the pipeline drained at
 // each) 161.  64 rows per wave halve the LDS reads per instruction (32 rows: LDS-bound).
-template <int DT, int D, int RT>
+// LONG: whole chunks in the middle of a range take a loop without control per tile (see middle_chunks).
+template <int DT, int D, int RT, bool LONG>
 __device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t kstride, int k_lo, int k_hi, int lim_all,
                                           const int (&lim)[RT], uint4 (&q)[RT][D * (DT == DT_BF16 ? 2 : 4) / 32], float scale2,
                                           int ks, int wk, bool active, float (&ref)[RT], float (&sum)[RT]) {
@@ -254,10 +262,73 @@ __device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t 
     }
   };
   f32x16 acc0[RT], acc1[RT];
+  // A tile in the middle of a range: its products beside the exponentials of the tile before, in a fixed order.  What stands
+  // between two fences is issued beside one matrix instruction: exponents one step ahead of their exponentials, sums one behind.
+  auto middle = [&](f32x16 (&next)[RT], const f32x16 (&done)[RT]) {
+    constexpr int SLOTS = NCH * RT, PER = 16 * RT / SLOTS;  // matrix instructions, logits beside each
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      kept[r] = sum[r];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) next[r][e] = 0.0f;
+    }
+    float x[PER], y[PER];
+    auto exponents = [&](int j) {
+#pragma unroll
+      for (int k = 0; k < PER; ++k) x[k] = fmaf(done[(j * PER + k) % RT][(j * PER + k) / RT], scale2, -ref[(j * PER + k) % RT]);
+    };
+    auto sums = [&](int j) {
+#pragma unroll
+      for (int k = 0; k < PER; ++k) sum[(j * PER + k) % RT] += y[k];
+    };
+    exponents(0);
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+      Mma<DT>::run(next[j % RT], kf[j / RT], q[j % RT][j / RT]);
+      if (j % RT == RT - 1) load(j / RT);
+      if (j > 0) sums(j - 1);
+#pragma unroll
+      for (int k = 0; k < PER; ++k) y[k] = fast_exp2(x[k]);
+      if (j + 1 < SLOTS) exponents(j + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    sums(SLOTS - 1);
+    check(done, pending);
+    pending = t;
+    t += wk;
+  };
+  // Chunks in the middle of a range, from one that is not open yet on: every row sees every key, the loads that opening them
+  // starts are whole chunks, and each has an even number of tiles for the wave.  Between the barriers there is no control flow
+  // but the test for sums that have grown too large (128k layer 157 -> 149 us, groups of eight 149.6 -> 141.7).  An instance of
+  // its own, for long ranges: the code alone made short ones 1-4 % slower.
+  auto middle_chunks = [&]() {
+    if (wk > 2 || !roll || !here || first || pending < 0 || pending >= n_whole || t / TPC <= open) return;
+    while ((open + 1 + S) * KC <= n_keys && (open + 2) * TPC <= n_whole) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::LOADS) : "memory");
+      lds_barrier();
+      ++open;
+      prefetch(open + S - 1);
+      issued = open + S;
+      const uint32_t step = (uint32_t)wk * L::TILE;
+      uint32_t off = (uint32_t)(open % S) * L::STAGE + (uint32_t)ks * L::TILE;
+      const uint32_t off_next = (uint32_t)((open + 1) % S) * L::STAGE + (uint32_t)ks * L::TILE;
+      for (int u = TPC / wk; u > 0; u -= 2) {
+        off += step;
+#pragma unroll
+        for (int i = 0; i < L::NA; ++i) from[i] = opaque(at[i] + off);
+        middle(acc0, acc1);
+        off = u > 2 ? off + step : off_next;
+#pragma unroll
+        for (int i = 0; i < L::NA; ++i) from[i] = opaque(at[i] + off);
+        middle(acc1, acc0);
+      }
+    }
+  };
   if (PIPED) {
     const bool even = wave < RS_WAVES / 2;  // the two waves of a SIMD take turns at being served first
 #pragma unroll 1
     for (;;) {
+      if (LONG) middle_chunks();
       if (t >= n_tiles) {
         drain(acc1);
         break;

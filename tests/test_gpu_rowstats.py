@@ -55,3 +55,12 @@ def test_key_ranges(dtype, d, g, n_q, n):
 @pytest.mark.parametrize("late", [(40,), (700,), (1151,), (8999,), (300, 420, 1100)])
 def test_logits_that_outgrow_the_reference(dtype, d, g, n_q, late):
     check(dtype, d, g, n_q, 9000, late)  # ranges of 1152 keys
+
+
+# ranges of 1536 keys and more: whole chunks in the middle take a loop of their own (one wave per row, and two)
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("g,n_q", [(4, 33), (4, 64), (4, 128), (8, 70)])
+@pytest.mark.parametrize("n,late", [(12287, ()), (12288, ()), (12289, ()), (13100, ()), (17000, ()), (13000, (650,)), (13000, (200, 1000, 1600, 8000)),
+                                    (17000, (383, 384, 1500, 2120))])
+def test_long_ranges(d, g, n_q, n, late):
+    check("bf16", d, g, n_q, n, late)
