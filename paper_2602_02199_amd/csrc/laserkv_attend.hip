@@ -432,7 +432,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // the rows of the wave's current tile, as the B operand of S^T
   uint4 a[NCH];
   int blk_end_lane;  // block keys [0, blk_end_lane) are visible to this lane's row
-  auto load_rows = [&](int t) {
+  auto fetch_rows = [&](int t) {
     const int tid_r = fresh(tid), row = t * 32 + (tid_r & 31), m = min(RING ? row : fresh(row), p.m_rows - 1);
     int j;
     const int g = div_rem(m, p.n_q, p.nq_magic, &j);
@@ -440,8 +440,14 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
 #pragma unroll
     for (int i = 0; i < NCH; ++i) a[i] = ld16(ptr + 2 * i * 16);
     blk_end_lane = max(0, min(p.s_t, p.diag + j + 1));
+  };
+  auto rows_landed = [&]() {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) landed(a[i]);
+  };
+  auto load_rows = [&](int t) {
+    fetch_rows(t);
+    rows_landed();
   };
 
   // the segments: the cache (0) and the block's own rows (1)
@@ -458,7 +464,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   const uint32_t k_col = (ld_pos ^ (ld_row & KX)) * 16, v_col = (ld_pos ^ (2 * v_swz<CH>(ld_row & 3))) * 16;
   const uint32_t v_i = tid % EPC, v_c = (tid / EPC) % CH, v_grp = tid / (EPC * CH);
   uint4 vpre[TR ? 1 : KL];
-  // Starts the loads of a chunk into a stage.  Rows past the segment's last one repeat it (they weigh nothing).
+  // Starts the loads of a chunk into a stage.  Rows past the segment's last one repeat it (they weigh nothing).  The
+  // asynchronous loads come from the first wave of every SIMD: 64 KiB keep the address unit busy for a thousand clocks, and
+  // while the first waves wait for it the second ones have the SIMDs to themselves.  From all waves, behind the barrier, both
+  // stood still for it, and so they did with the loads spread over the tiles' steps.  (Here block of 4096 rows over 64 cache
+  // rows 186 -> 181 us, in the ring last block of a 128k prefill 3580 -> 3540, window rows over 63 520 keys 135.2 -> 134.5.)
   auto prefetch = [&](int seg, int kc0, int stage) {
     const srd_words ksrd = make_srd_words(seg ? k_base1 : k_base0, seg ? kb_bytes : c_bytes);
     const srd_words vsrd = make_srd_words(seg ? v_base1 : v_base0, seg ? vb_bytes : c_bytes);
@@ -467,20 +477,23 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     const uint32_t rows = (uint32_t)(seg ? p.s_t : p.cache_len);
     const uint32_t dst = lds0 + stage * (STAGE * 16) + __builtin_amdgcn_readfirstlane(wave) * 1024;
     const uint32_t r0 = fresh(ld_row);
+    if (TR && upper) return;
+    // (fp32: every thread has its loads of V besides)
+    constexpr int N = TR ? 2 * KL : KL, ROWS = ROWS_PER_LOAD * KL / N, BYTES = ATT_THREADS * 16 * KL / N;
     if (kc0 + KC <= (int)rows) {
       const uint32_t k_off = r0 * kstride + k_col, v_off = r0 * vstride + v_col;
 #pragma unroll
-      for (int u = 0; u < KL; ++u) {
-        const uint32_t row = kc0 + u * ROWS_PER_LOAD;
-        async_ld16(ksrd, k_off, row * kstride, dst + u * (ATT_THREADS * 16));
-        if (TR) async_ld16(vsrd, v_off, row * vstride, dst + KC * CH * 16 + u * (ATT_THREADS * 16));
+      for (int u = 0; u < N; ++u) {
+        const uint32_t row = kc0 + u * ROWS;
+        async_ld16(ksrd, k_off, row * kstride, dst + u * BYTES);
+        if (TR) async_ld16(vsrd, v_off, row * vstride, dst + KC * CH * 16 + u * BYTES);
       }
     } else {
 #pragma unroll 1
-      for (int u = 0; u < KL; ++u) {
-        const uint32_t row = min((uint32_t)kc0 + r0 + u * ROWS_PER_LOAD, rows - 1u);
-        async_ld16(ksrd, row * kstride + k_col, 0u, dst + u * (ATT_THREADS * 16));
-        if (TR) async_ld16(vsrd, row * vstride + v_col, 0u, dst + KC * CH * 16 + u * (ATT_THREADS * 16));
+      for (int u = 0; u < N; ++u) {
+        const uint32_t row = min((uint32_t)kc0 + r0 + u * ROWS, rows - 1u);
+        async_ld16(ksrd, row * kstride + k_col, 0u, dst + u * BYTES);
+        if (TR) async_ld16(vsrd, row * vstride + v_col, 0u, dst + KC * CH * 16 + u * BYTES);
       }
     }
     if (!TR) {
@@ -725,19 +738,20 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // and that the one before has been left.
   constexpr int RC = 64;                                     // keys per ring stage
   constexpr uint32_t R_V = RC * CH * 16, R_STAGE = 2 * R_V;  // bytes of K in a stage, and of K and V
-  constexpr int R_LOADS = RC * CH / ATT_THREADS;             // per thread, tensor and chunk
+  constexpr int R_LOADS = 2 * RC * CH / ATT_THREADS;         // per thread of the first waves, tensor and chunk
   // (not in the workgroup whose waves share the middle tile of an odd number from the start)
   const bool middle = (n_tiles & 1) && pg == (n_pairs - 1) / 4;
   const int ring_keys = BF16 && RING && fixed && !middle ? (hi0 - lo0) & ~(2 * RC - 1) : 0;
   const int n_ring = ring_keys / RC;
   auto ring_prefetch = [&](int c) {
+    if (upper) return;
     const srd_words ksrd = make_srd_words(k_base0, c_bytes), vsrd = make_srd_words(v_base0, c_bytes);
     const uint32_t r0 = fresh(ld_row) * (uint32_t)p.row_bytes, src = (uint32_t)(lo0 + c * RC) * (uint32_t)p.row_bytes;
     const uint32_t dst = lds0 + (c & 3) * R_STAGE + __builtin_amdgcn_readfirstlane(wave) * 1024;
 #pragma unroll
     for (int u = 0; u < R_LOADS; ++u) {
-      async_ld16(ksrd, r0 + k_col, src + u * ROWS_PER_LOAD * (uint32_t)p.row_bytes, dst + u * (ATT_THREADS * 16));
-      async_ld16(vsrd, r0 + v_col, src + u * ROWS_PER_LOAD * (uint32_t)p.row_bytes, dst + R_V + u * (ATT_THREADS * 16));
+      async_ld16(ksrd, r0 + k_col, src + u * (ROWS_PER_LOAD / 2) * (uint32_t)p.row_bytes, dst + u * (ATT_THREADS * 8));
+      async_ld16(vsrd, r0 + v_col, src + u * (ROWS_PER_LOAD / 2) * (uint32_t)p.row_bytes, dst + R_V + u * (ATT_THREADS * 8));
     }
   };
   auto ring = [&](bool has_ref) {
@@ -872,8 +886,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
           if (!upper) {
             bad = !finite();
             settle();
+            fetch_rows(t_hi);  // in front of the stores, whose way to the memory it would wait for
             if (present) write_tile(t_lo);
-            load_rows(t_hi);
+            rows_landed();
             clear();
             place();
             has_ref = pass != 0;
@@ -892,23 +907,6 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
         }
         // a row without a visible key subtracts nothing: its hidden logits give 2^(NEG_BIG * scale2) = 0
         float m_sub = m_ref > NEG_BIG ? m_ref : 0.0f;
-        auto raise = [&](const f32x16& acc) {  // the reference, to the row's maximum in a tile
-          float mx = acc[0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-          mx = half_pair_max(mx);
-          const float m_new = mx > NEG_BIG ? fmaxf(m_ref, fmaf(mx, p.scale2, HEADROOM)) : m_ref;
-          if (__any(m_new > m_ref && l_sum > 0.0f)) {  // nothing to rescale before the first keys
-            const float f = fast_exp2(m_ref - m_new);
-            l_sum *= f;
-#pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) o[dt][r] *= f;
-          }
-          m_ref = m_new;
-          m_sub = m_new > NEG_BIG ? m_new : 0.0f;
-        };
         auto soft = [&](f32x16& acc) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
@@ -916,6 +914,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
             l_sum += acc[r];
           }
         };
+        uint32_t moved = 0;  // of the LDS addresses within the chunk
         if (BF16) {
           if (!follows) {
             // two key tiles: the exponentials of one run beside the other's products
@@ -941,29 +940,108 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
               weigh(acc1, vb);
             }
           } else {
+            // The products of a tile with the keys beside the exponentials of the tile before, those with the values beside
+            // the maximum and the next exponents; operands are read four matrix instructions ahead (in the compiler's order
+            // every product with the keys waited for its own read; 16k prefill in blocks of 2048 rows 1385 -> 1372 us).
+            // Bound by issue: of some 1450 clocks per wave and two tiles 520 go into rescaling the output, which some row of
+            // 32 asks for at most tiles.
+            constexpr int AHEAD = 4, HALF = NCH / 2;
+            static_assert(NCH == RUNS * NDT || !BF16, "as many products with the values as with the keys");
+            f32x16 x, nxt;
+            uint4 kf[AHEAD], vf[AHEAD];
+            float m_new;
+            int vis = n_vis;
+            auto read_k = [&](int T, int i) { kf[i % AHEAD] = lds_ld16(kx[i] + T * K_TILE); };
+            auto read_v = [&](int T, int i) {
+              // registers 8s .. 8s+3 of the logits are keys 16s + 4kg + (0..3), registers 8s+4 .. 8s+7 the same + 8
+              const uint32_t at = vx[i % NDT] + T * V_TILE + 16 * (i / NDT) * CH * 16;
+              const uint2 lo = ds_read_tr16(at), hi = ds_read_tr16(at + 8 * CH * 16);
+              vf[i % AHEAD] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            };
+            auto reference = [&]() {  // the row's maximum with the next tile
+              float mx = nxt[0];
 #pragma unroll
-            for (int T = 0; T < TPC; T += 2) {
-              if (left <= T) break;
-              f32x16 acc0, acc1;
-              uint4 kf[NCH], vf[RUNS * NDT];
+              for (int r = 1; r < 16; ++r) mx = fmaxf(mx, nxt[r]);
+              mx = half_pair_max(mx);
+              m_new = mx > NEG_BIG ? fmaxf(m_ref, fmaf(mx, p.scale2, HEADROOM)) : m_ref;
+              m_sub = m_new > NEG_BIG ? m_new : 0.0f;
+            };
+            auto rescale = [&]() {
+              if (__any(m_new > m_ref && l_sum > 0.0f)) {  // nothing to rescale before the first keys
+                const float f = fast_exp2(m_ref - m_new);
+                l_sum *= f;
 #pragma unroll
-              for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(kx[i] + T * K_TILE);
-              logits(kf, acc0);
+                for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-              for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(kx[i] + (T + 1) * K_TILE);
-              logits(kf, acc1);
-              if (!whole) {
-                hide(acc0, n_vis - T * 32);
-                hide(acc1, n_vis - T * 32 - 32);
+                  for (int r = 0; r < 16; ++r) o[dt][r] *= f;
               }
-              load_v_tr(vx, T * V_TILE, vf);
-              raise(acc0);
-              soft(acc0);
-              weigh(acc0, vf);
-              load_v_tr(vx, (T + 1) * V_TILE, vf);
-              raise(acc1);
-              soft(acc1);
-              weigh(acc1, vf);
+              m_ref = m_new;
+            };
+            auto unit = [&](int T, bool more) {  // more: another tile follows
+              uint4 pb[2];
+              if (more)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) nxt[r] = 0.0f;
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) {
+                if (more) Mma<DT>::run(nxt, kf[i % AHEAD], a[i]);
+#pragma unroll
+                for (int r = i * (16 / NCH); r < (i + 1) * (16 / NCH); ++r) {
+                  x[r] = fast_exp2(x[r]);
+                  l_sum += x[r];
+                }
+                if (i + AHEAD >= NCH) read_v(T, i + AHEAD - NCH);
+                else if (more) read_k(T + 1, i + AHEAD);
+                if (i == HALF - 1 || i == NCH - 1) {
+                  const int s = i / HALF;
+                  pb[s] = make_uint4(pack_bf16(x[8 * s], x[8 * s + 1]), pack_bf16(x[8 * s + 2], x[8 * s + 3]),
+                                     pack_bf16(x[8 * s + 4], x[8 * s + 5]), pack_bf16(x[8 * s + 6], x[8 * s + 7]));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+              }
+              if (more && !whole) hide(nxt, vis - (T + 1) * 32);
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) {
+                Mma<DT>::run(o[i % NDT], vf[i % AHEAD], pb[i / NDT]);
+                if (i + AHEAD < NCH) read_v(T, i + AHEAD);
+                else if (more) read_k(T + 2, i + AHEAD - NCH);
+                if (more && i == HALF - 1) reference();
+                if (more && i >= HALF)
+#pragma unroll
+                  for (int r = (i - HALF) * (16 / HALF); r < (i - HALF + 1) * (16 / HALF); ++r) x[r] = fmaf(nxt[r], p.scale2, -m_sub);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+              if (more) rescale();
+            };
+            if (left > 0) {
+#pragma unroll
+              for (int r = 0; r < 16; ++r) nxt[r] = 0.0f;
+#pragma unroll
+              for (int i = 0; i < AHEAD; ++i) read_k(0, i);
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) {
+                Mma<DT>::run(nxt, kf[i % AHEAD], a[i]);
+                if (i + AHEAD < NCH) read_k(0, i + AHEAD);
+                else read_k(1, i + AHEAD - NCH);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+              if (!whole) hide(nxt, vis);
+              reference();
+#pragma unroll
+              for (int r = 0; r < 16; ++r) x[r] = fmaf(nxt[r], p.scale2, -m_sub);
+              rescale();
+              unit(0, true);
+              for (; left > 2; left -= 2) {
+                unit(1, true);
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) kx[i] = opaque(kx[i] + 2 * K_TILE);
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) vx[dt] = opaque(vx[dt] + 2 * V_TILE);
+                moved += 2 * K_TILE;
+                vis -= 64;
+                unit(0, true);
+              }
+              unit(1, false);
             }
           }
         } else {
@@ -986,7 +1064,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
         }
         next();
         if (DT == DT_BF16) {
-          const uint32_t move = cur ? STAGE * 16 : -STAGE * 16;
+          const uint32_t move = (cur ? STAGE * 16 : -STAGE * 16) - moved;
 #pragma unroll
           for (int i = 0; i < NCH; ++i) kx[i] = opaque(kx[i] + move);
 #pragma unroll
