@@ -22,7 +22,6 @@ struct KeyRing {
   static constexpr int KC = CH <= 16 ? 128 : 64;     // keys per stage
   static constexpr int STAGE = KC / 32 * TILE;
   static constexpr int STAGES = 4;
-  static constexpr int LOADS = KC * CH / RS_THREADS; // loads per thread and stage
   static constexpr int NA = RPG > 2 ? RPG / 2 : 1;   // different addresses of a lane's operand chunks
 };
 constexpr size_t row_stats_lds(int row_bytes) {
@@ -64,6 +63,12 @@ __device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t 
   constexpr int CH = D * (DT == DT_BF16 ? 2 : 4) / 16, NCH = CH / 2;
   using L = KeyRing<CH>;
   constexpr int KC = L::KC, TPC = KC / 32, S = L::STAGES;
+  // Waves that bring the keys in.  In long ranges the first wave of every SIMD: the address unit takes some five hundred clocks
+  // for a chunk, and the second waves have the SIMDs to themselves meanwhile (512 rows over 63 520 keys 70.0 -> 68.1 us, 128k
+  // layer 477.6 -> 476.6; fp32 likewise: 256 rows over 9000 keys 49.6 -> 48.6).  In short ranges all of them, the first keys are
+  // there sooner (256 rows over 31 681 keys 28.15 us, 28.4 with half of them; over 74 keys 9.6, 9.7).
+  constexpr int LOADERS = LONG || DT == DT_F32 ? RS_WAVES / 2 : RS_WAVES;
+  constexpr int LOADS = KC * CH / (LOADERS * 64);  // each, per stage
   // registers for a second tile's logits (in fp32 matrix instructions take nearly all of the time: twice the code is slower)
   constexpr bool PIPED = DT == DT_BF16 && RT * NCH <= 16;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rl = lane & 31, kg = lane >> 5;
@@ -83,31 +88,32 @@ __device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t 
   const int ahead = roll ? 1 : 0;
 
   const uint32_t lds0 = lds_offset(smem);
-  // loads: wave w brings the w-th of every RS_WAVES groups of a stage
+  // loads: wave w brings the w-th of every LOADERS groups of a stage
   const uint32_t ld_row = lane / CH, ld_col = ((lane % CH) ^ (ld_row % L::RPG)) * 16;
   const uint32_t ld_off = ld_row * kstride + ld_col;
   auto prefetch = [&](int c) {
+    if (LOADERS < RS_WAVES && wave >= LOADERS) return;
     const int row = c * KC + wave * L::RPG;  // of the range: the first group's first
     uint32_t dst = lds0 + (c % S) * L::STAGE + wave * L::GROUP;
     if ((c + 1) * KC <= n_keys) {
       uint32_t src = (uint32_t)(k_lo + row) * kstride;
 #pragma unroll
-      for (int u = 0; u < L::LOADS; ++u, src += RS_WAVES * L::RPG * kstride, dst += RS_WAVES * L::GROUP) async_ld16(ksrd, ld_off, src, dst);
+      for (int u = 0; u < LOADS; ++u, src += LOADERS * L::RPG * kstride, dst += LOADERS * L::GROUP) async_ld16(ksrd, ld_off, src, dst);
     } else if (c < n_chunks) {
       // Rows past the end repeat the last one.  Where everything is waited for at the start, only whole tiles are loaded (256
       // rows over 74 keys 9.5 -> 9.35 us); else every chunk has as many loads as `await` counts.
-      const int n_loads = n_chunks <= span + ahead ? min((n_tiles * 32 - row + RS_WAVES * L::RPG - 1) / (RS_WAVES * L::RPG), L::LOADS) : L::LOADS;
+      const int n_loads = n_chunks <= span + ahead ? min((n_tiles * 32 - row + LOADERS * L::RPG - 1) / (LOADERS * L::RPG), LOADS) : LOADS;
 #pragma unroll 1
-      for (int u = 0; u < n_loads; ++u, dst += RS_WAVES * L::GROUP)
-        async_ld16(ksrd, (uint32_t)(k_lo + min(row + u * RS_WAVES * L::RPG + (int)ld_row, n_keys - 1)) * kstride + ld_col, 0u, dst);
+      for (int u = 0; u < n_loads; ++u, dst += LOADERS * L::GROUP)
+        async_ld16(ksrd, (uint32_t)(k_lo + min(row + u * LOADERS * L::RPG + (int)ld_row, n_keys - 1)) * kstride + ld_col, 0u, dst);
     }
   };
   int open = span - 1, issued = min(span + ahead, n_chunks);
   auto await = [&](int c) {  // chunks up to c
     static_assert(S == 4, "at most two chunks are on their way behind the one waited for");
     const int flying = issued - 1 - c;
-    if (flying >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L::LOADS) : "memory");
-    else if (flying == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::LOADS) : "memory");
+    if (flying >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
+    else if (flying == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   };
   // Opens chunk c with those of its span: they (and the one behind them) have landed for every wave, and every wave has left
@@ -304,7 +310,7 @@ __device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t 
   auto middle_chunks = [&]() {
     if (wk > 2 || !roll || !here || first || pending < 0 || pending >= n_whole || t / TPC <= open) return;
     while ((open + 1 + S) * KC <= n_keys && (open + 2) * TPC <= n_whole) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::LOADS) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
       lds_barrier();
       ++open;
       prefetch(open + S - 1);
