@@ -463,6 +463,7 @@ int select_impl(laserkv_ctx* ctx,
   cp.sig_k = ctx->sig_k;
   cp.sig_q = ctx->sig_q;
   cp.cnt = ctx->cnt;
+  cp.octets = false;
   cp.s_t = cp.key_stride = s_t;
   cp.last_group = c.n_kv_heads;
   cp.last_s_t = 0;
@@ -824,6 +825,7 @@ int laserkv_compress_layer(laserkv_ctx* ctx,
     cp.sig_q = p.sig_q;
     cp.cnt = p.cnt;
     cp.s_t = s_block;
+    cp.octets = lkv::code_octets(c.lsh_tables);
     cp.key_stride = p.s_stride;
     cp.last_group = (n_blocks - 1) * c.n_kv_heads;
     cp.last_s_t = s_last;

@@ -67,7 +67,8 @@ struct PassParams {
 };
 
 struct CountParams {
-  const uint16_t* sig_k;  // [groups, key_stride, L]; a group is a KV head, or a (block, KV head) pair of a layer
+  const uint16_t* sig_k;  // [groups, key_stride, L], or in octets; a group is a KV head, or a (block, KV head) pair of a layer
+  bool octets;            // sig_k is [groups, L / 8, key_stride, 8]
   const uint16_t* sig_q;  // [groups, G * W, L]
   int32_t* cnt;           // [groups, key_stride]
   int group, w, s_t;
@@ -193,7 +194,7 @@ struct LayerParams {
   int s_stride;          // keys per group in score / cnt / sig_k
   float* score;          // [groups, s_stride] pooled probabilities (sum over the rows)
   int32_t* cnt;          // [groups, s_stride]
-  uint16_t* sig_k;       // [groups, s_stride, L] when cells is null
+  uint16_t* sig_k;       // when cells is null: [groups, L / 8, s_stride, 8] where code_octets, else [groups, s_stride, L]
   uint16_t* sig_q;       // [groups, M, L] when cells is null
   // the blocks' protected rows, which the score kernel copies to the cache: this many per key range of a block, and of the
   // last one (0: the selection copies them)
@@ -210,6 +211,9 @@ struct LayerPlan {
   size_t codes_lds, stats_lds, score_lds;
   size_t off_part, off_score, off_cnt, off_cells, off_heavy, off_sig_k, off_sig_q, bytes;  // workspace
 };
+// Whether a layer's key codes are stored eight tables at a time, which is how they are written and read: whole lines both
+// ways, where a key's tables in one place were written two bytes at a time and passed through memory once per eight tables.
+constexpr bool code_octets(int n_tables) { return (n_tables & 7) == 0; }
 bool layer_supports(int dtype, int head_dim, int m_rows);
 void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* plan);  // fills the launch geometry of both
 void layer_plan_copies(LayerParams* p);  // copies and last_copies, of the geometry, v and the parts of the kept rows

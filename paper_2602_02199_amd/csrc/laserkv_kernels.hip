@@ -724,7 +724,8 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
 // register and costs one global atomic.
 // What a table costs is three barriers, 512 atomics and the lookups of a range: long ranges, few tables.  (Key codes
 // staged in LDS were read with a stride of a whole key, sixteen lanes to a bank, and left room for 1024 keys only: 145 us
-// for a layer of 131 072 keys, 8 heads, 32 tables of 16 bits, now 53.)
+// for a layer of 131 072 keys, 8 heads, 32 tables of 16 bits, 53 from registers.)  Octets: the fetches are whole lines; of
+// [keys, tables] every eight tables passed the codes' 67 MB through memory again (277 -> 76 MB read, 53.8 -> 30.0 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int COUNT_THREADS = 1024;
 constexpr int COUNT_KEYS_PER_THREAD = 8;  // keys_per_range <= COUNT_THREADS * COUNT_KEYS_PER_THREAD
@@ -745,14 +746,17 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
   const int n_bin_words = (p.tables_per_group << p.n_bits) >> 1;
   uint16_t* sQ = reinterpret_cast<uint16_t*>(bins + ((n_bin_words + 3) & ~3));  // [ntw][nq]
   const uint16_t* gq = p.sig_q + (size_t)h * nq * p.n_tables + t_first;
-  const uint16_t* gk = p.sig_k + ((size_t)h * p.key_stride + i0) * p.n_tables + t_first;
+  const uint16_t* gk = p.sig_k + (size_t)h * p.key_stride * p.n_tables;
+  const int pitch = p.octets ? 8 : p.n_tables;  // from a key's codes to the next key's
 
   uint4 next[KPT];  // VEC: the codes of eight tables; else .x: of one
   auto fetch = [&](int t) {
+    t += t_first;
+    const uint16_t* gt = gk + (size_t)i0 * pitch + (p.octets ? (size_t)(t >> 3) * p.key_stride * 8 + (t & 7) : (size_t)t);
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
       if (k * COUNT_THREADS >= n_keys) break;  // workgroup-uniform
-      const uint16_t* at = gk + (size_t)min(tid + k * COUNT_THREADS, n_keys - 1) * p.n_tables + t;
+      const uint16_t* at = gt + (size_t)min(tid + k * COUNT_THREADS, n_keys - 1) * pitch;
       if (VEC) next[k] = ld16(at);
       else next[k].x = *at;
     }

@@ -576,12 +576,12 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       for (int w = 1; w < n_sum; ++w) v += col[w * KC];
       p.score[at] = v;
     }
+    auto code_of = [&](int t) {
+      const int bitpos = t * p.n_bits, w0 = bitpos >> 5;
+      return __builtin_amdgcn_alignbit(bits[w0 + 1], bits[w0], bitpos & 31) & code_mask;
+    };
     if (p.cells) {
       uint32_t n = 0u, fullest = 0u;
-      auto code_of = [&](int t) {
-        const int bitpos = t * p.n_bits, w0 = bitpos >> 5;
-        return __builtin_amdgcn_alignbit(bits[w0 + 1], bits[w0], bitpos & 31) & code_mask;
-      };
       auto nibble_of = [&](int t, uint32_t code) {
         return __builtin_amdgcn_ubfe(sCells[t * p.cell_words + (code >> 3)], (code & 7u) << 2, 4u);
       };
@@ -619,10 +619,17 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
       n += lane_xor1(n);
       if (sub == 0 && kidx < k_hi) p.cnt[at] = (int)n;
     } else if (kidx < k_hi) {
-      uint16_t* dst = p.sig_k + ((size_t)gr.g * p.s_stride + kidx) * p.n_tables;
-      for (int t = sub; t < p.n_tables; t += 2) {
-        const int bitpos = t * p.n_bits, w0 = bitpos >> 5;
-        dst[t] = (uint16_t)(__builtin_amdgcn_alignbit(bits[w0 + 1], bits[w0], bitpos & 31) & code_mask);
+      if (code_octets(p.n_tables)) {
+        const int n_oct = p.n_tables >> 3;
+        for (int o = sub; o < n_oct; o += 2) {
+          uint32_t two[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) two[u] = code_of(8 * o + 2 * u) | code_of(8 * o + 2 * u + 1) << 16;
+          *reinterpret_cast<uint4*>(p.sig_k + (((size_t)gr.g * n_oct + o) * p.s_stride + kidx) * 8) = make_uint4(two[0], two[1], two[2], two[3]);
+        }
+      } else {
+        uint16_t* dst = p.sig_k + at * p.n_tables;
+        for (int t = sub; t < p.n_tables; t += 2) dst[t] = (uint16_t)code_of(t);
       }
       if (sub == 1) p.cnt[at] = 0;  // count_kernel accumulates with atomics
     }

@@ -33,3 +33,12 @@ def test_equal_window_rows(tables, bits):
         data["q_win"][:] = data["q_win"][:, :1, :1]
 
     check_layer(workload(8, 64, tables, bits), mutate=mutate)
+
+
+# Key codes in octets of tables: one octet, which half of the lanes write; an odd number of them; through the counting kernel
+# whole octets at a time (32 groups and more share a card) and table by table (two groups).
+@pytest.mark.parametrize("tables,bits", [(8, 16), (24, 14), (24, 13)])
+@pytest.mark.parametrize("heads", [1, 8])
+def test_octets_of_key_codes(tables, bits, heads):
+    check_layer(synth.shrink(workload(4, 24, tables, bits), name=f"octets-{heads}-{tables}x{bits}", n_q_heads=4 * heads, n_kv_heads=heads,
+                             l_ctx=(32 if heads > 1 else 2) * 72 - 5))
