@@ -243,9 +243,9 @@ int laserkv_create(const laserkv_config* cfg, laserkv_ctx** out) {
     return fail_hip(nullptr, e, "create: device query");
   }
   e = lkv::init_kernel_attributes();
-  if (e == hipSuccess) e = lkv::init_attend_attributes();
+  if (e == hipSuccess) e = lkv::init_attend_attributes(c.dtype, c.head_dim);
   if (e == hipSuccess) e = lkv::init_single_attributes();
-  if (e == hipSuccess) e = lkv::init_layer_attributes();
+  if (e == hipSuccess) e = lkv::init_layer_attributes(c.dtype, c.head_dim);
   if (e != hipSuccess) {
     laserkv_destroy(ctx);
     return fail_hip(nullptr, e, "create: kernel attribute");

@@ -1485,12 +1485,10 @@ static hipError_t attend_attr() {
   return e;
 }
 
-hipError_t init_attend_attributes() {
-  hipError_t e = attend_attr<DT_BF16, 128>();
-  if (e == hipSuccess) e = attend_attr<DT_BF16, 64>();
-  if (e == hipSuccess) e = attend_attr<DT_F32, 128>();
-  if (e == hipSuccess) e = attend_attr<DT_F32, 64>();
-  return e;
+// Of the instances that a context can launch (each attribute takes some 4 us, and all types' were set for each)
+hipError_t init_attend_attributes(int dtype, int head_dim) {
+  if (dtype == DT_BF16) return head_dim == 128 ? attend_attr<DT_BF16, 128>() : attend_attr<DT_BF16, 64>();
+  return head_dim == 128 ? attend_attr<DT_F32, 128>() : attend_attr<DT_F32, 64>();
 }
 
 }  // namespace lkv

@@ -212,7 +212,8 @@ struct LayerPlan {
   size_t off_part, off_score, off_cnt, off_cells, off_heavy, off_sig_k, off_sig_q, bytes;  // workspace
 };
 // Whether a layer's key codes are stored eight tables at a time, which is how they are written and read: whole lines both
-// ways, where a key's tables in one place were written two bytes at a time and passed through memory once per eight tables.
+// ways, where a key's tables in one place were written two bytes at a time and passed through memory once per eight tables
+// (groups of eight with 32 tables of 16 bits 567 -> 528 us a layer).  Where the tables are no multiple of eight they stay so.
 constexpr bool code_octets(int n_tables) { return (n_tables & 7) == 0; }
 bool layer_supports(int dtype, int head_dim, int m_rows);
 void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* plan);  // fills the launch geometry of both
@@ -220,7 +221,7 @@ void layer_plan_copies(LayerParams* p);  // copies and last_copies, of the geome
 hipError_t launch_layer_codes(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
 hipError_t launch_layer_stats(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
 hipError_t launch_layer_score(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
-hipError_t init_layer_attributes();
+hipError_t init_layer_attributes(int dtype, int head_dim);
 
 // Attention of n_q queries per query head over the first cache_len rows of each KV head's compacted cache.
 struct AttendParams {
@@ -270,7 +271,7 @@ hipError_t launch_attend(int dtype, int head_dim, const AttendParams& p, hipStre
 // the normaliser alone (out unused): 512 rows per workgroup, keys only
 void attend_lse_plan(int m_rows, int64_t cache_len, int n_kv_heads, int n_cu, AttendPlan* plan);
 hipError_t launch_attend_lse(int dtype, int head_dim, const AttendParams& p, hipStream_t st);
-hipError_t init_attend_attributes();
+hipError_t init_attend_attributes(int dtype, int head_dim);
 
 hipError_t launch_sweep1(int dtype, int head_dim, const PassParams& p, hipStream_t st);
 hipError_t launch_sweep2(int dtype, int head_dim, const PassParams& p, hipStream_t st);

@@ -941,11 +941,9 @@ static hipError_t layer_attrs() {
   if (e == hipSuccess) e = score_attrs<DT, D, 4>();
   return e;
 }
-hipError_t init_layer_attributes() {
-  hipError_t e = layer_attrs<DT_BF16, 128>();
-  if (e == hipSuccess) e = layer_attrs<DT_BF16, 64>();
-  if (e == hipSuccess) e = layer_attrs<DT_F32, 64>();
-  return e;
+hipError_t init_layer_attributes(int dtype, int head_dim) {
+  if (dtype == DT_BF16) return head_dim == 128 ? layer_attrs<DT_BF16, 128>() : layer_attrs<DT_BF16, 64>();
+  return head_dim == 64 ? layer_attrs<DT_F32, 64>() : hipSuccess;  // fp32 with rows of 512 bytes: layer_supports
 }
 
 }  // namespace lkv
