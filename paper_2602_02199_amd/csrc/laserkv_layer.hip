@@ -548,10 +548,17 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     }
   };
   prefetch(k_lo, 0);
+  // One plane tile more than a multiple of the hashing waves: each of them holds it and takes it for one key tile of a chunk.  On
+  // one wave it made that wave's SIMD do a quarter more matrix work than the others, and the barrier waits for it (64k layer,
+  // 160 hyperplanes, 165.2 -> 162.5 us; 16k 57.4 -> 57.3).  Two or three tiles more are not shared out: the copies would cost
+  // registers; nor is the thirteenth (four tiles a wave, where none are left).
+  constexpr bool CAN_SPREAD = PT == 2 || PT == 3;
+  const bool spread = CAN_SPREAD && n_pt == LY_HALF * (PT - 1) + 1;
   uint4 a[PT][NCH];
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
-    const char* ptr = p.planes + (size_t)min((first + LY_HALF * t) * 32 + plane_row(rl), p.n_planes - 1) * (D * ES);
+    const int tile = t == PT - 1 && spread ? n_pt - 1 : first + LY_HALF * t;
+    const char* ptr = p.planes + (size_t)min(tile * 32 + plane_row(rl), p.n_planes - 1) * (D * ES);
 #pragma unroll
     for (int i = 0; i < NCH; ++i) a[t][i] = ld16(ptr + (2 * i + kg) * 16);
   }
@@ -685,25 +692,27 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
     __builtin_amdgcn_s_setprio(0);
     if (active && kstep == 1 && kc0 + KC <= k_hi) {  // a complete chunk
       // The products of a (key tile, plane tile) beside the sign bits of the one before.
-      auto steps = [&](auto tiles) {
+      auto steps = [&](auto tiles, auto more_tiles) {
         constexpr int N = decltype(tiles)::value;  // plane tiles of this wave
+        constexpr int M = TPC * N + decltype(more_tiles)::value;  // products; the last one of the tile that all waves hold
         constexpr int PER = 16 / NCH;
+        static_assert(TPC == LY_HALF, "a key tile of the chunk for each hashing wave");
         uint32_t* bits = sBits + (cur * KC + rl) * bits_pitch + first;
         uint4 kf[NCH];
         f32x16 acc[2];
 #pragma unroll
         for (int i = 0; i < NCH; ++i) kf[i] = key(0, i);
 #pragma unroll
-        for (int s = 0; s <= TPC * N; ++s) {
-          const bool mul = s < TPC * N, newk = mul && s % N == N - 1 && s / N + 1 < TPC;
+        for (int s = 0; s <= M; ++s) {
+          const bool mul = s < M, newk = s < TPC * N && s % N == N - 1 && (s / N + 1 < TPC || M > TPC * N);
           uint32_t neg = 0u;
           if (mul)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[s & 1][e] = 0.0f;
 #pragma unroll
           for (int i = 0; i < NCH; ++i) {
-            if (mul) Mma<DT>::run(acc[s & 1], a[s % N][i], kf[i]);
-            if (newk) kf[i] = key(s / N + 1, i);
+            if (mul) Mma<DT>::run(acc[s & 1], a[s < TPC * N ? s % N : PT - 1][i], kf[i]);
+            if (newk) kf[i] = s / N + 1 < TPC ? key(s / N + 1, i) : lds_ld16(from[i % L::NA] + first * L::TILE, i / L::NA * (L::NA * 32));
             if (s > 0)
 #pragma unroll
               for (int e = i * PER; e < (i + 1) * PER; ++e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[(s + 1) & 1][15 - e]), 31);
@@ -713,12 +722,18 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
             // 16 consecutive planes per lane (see plane_row): their sign bits have been shifted into one word
             const uint32_t pos = ~neg & 0xffffu;
             const uint32_t mask = pos | (half_other(pos, kg) << 16);
-            if (kg == 0) bits[(s - 1) / N * 32 * bits_pitch + LY_HALF * ((s - 1) % N)] = mask;
+            if (kg == 0) {
+              if (s <= TPC * N) bits[(s - 1) / N * 32 * bits_pitch + LY_HALF * ((s - 1) % N)] = mask;
+              else bits[first * 32 * bits_pitch + n_pt - 1 - first] = mask;
+            }
           }
         }
       };
-      if (first + LY_HALF * (PT - 1) < n_pt) steps(std::integral_constant<int, PT>{});
-      else steps(std::integral_constant<int, PT == 1 ? 1 : PT - 1>{});
+      constexpr std::integral_constant<int, PT == 1 ? 1 : PT - 1> fewer;
+      constexpr std::integral_constant<int, 0> none;
+      if (spread) steps(fewer, std::integral_constant<int, CAN_SPREAD>{});
+      else if (first + LY_HALF * (PT - 1) < n_pt) steps(std::integral_constant<int, PT>{}, none);
+      else steps(fewer, none);
     } else if (active) {
 #pragma unroll 1
       for (int vt = k0; vt < TPC; vt += kstep) {
@@ -730,7 +745,7 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
           for (int e = 15; e >= 0; --e) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[e]), 31);
           const uint32_t pos = ~neg & 0xffffu;
           const uint32_t mask = pos | (half_other(pos, kg) << 16);
-          const int tile = first + LY_HALF * t;
+          const int tile = t == PT - 1 && spread ? n_pt - 1 : first + LY_HALF * t;  // (all four write the same)
           if (kg == 0 && tile < n_pt) sBits[(cur * KC + vt * 32 + rl) * bits_pitch + tile] = mask;
         };
         constexpr int HT = PT == 4 ? 2 : PT;  // tiles at a time (registers)

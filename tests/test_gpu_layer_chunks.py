@@ -29,3 +29,12 @@ def test_blocks_around_whole_chunks(beyond, dtype, head_dim):
     check_layer(synth.shrink(synth.WORKLOADS["tiny"], index=52, name=f"chunks{beyond}-{dtype}", n_q_heads=8, n_kv_heads=2,
                              head_dim=head_dim, dtype=dtype, l_ctx=3 * s - 40, s_block=s, window=w, n_div=4, lsh_tables=16,
                              lsh_bits=10, needles_per_block=2, outlier_channels=2))
+
+
+@pytest.mark.parametrize("tables,bits", [(13, 10), (16, 10), (29, 9), (24, 12)])  # 5 and 9 plane tiles, the last with a few planes or 32
+@pytest.mark.parametrize("dtype,head_dim", [("bf16", 128), ("f32", 64)])
+def test_one_plane_tile_more_than_whole_rounds(tables, bits, dtype, head_dim):
+    """The last tile is shared out over the key tiles of a complete chunk."""
+    check_layer(synth.shrink(synth.WORKLOADS["tiny"], index=53, name=f"spread-{tables}x{bits}-{dtype}", n_q_heads=8, n_kv_heads=2,
+                             head_dim=head_dim, dtype=dtype, l_ctx=1664, s_block=640, window=40, n_div=4, lsh_tables=tables,
+                             lsh_bits=bits, needles_per_block=2, outlier_channels=2))
