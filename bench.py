@@ -178,6 +178,11 @@ def measure(wl, args, dev, cpu_seconds):
         work["select"] = ("hbm", work["select"][1] + work["append"][1])
     if len(plan) < wl.n_blocks:  # one call for the layer: the key projection is part of the second sweep
         work["sweep1"], work["sweep2"] = work["sweep2"], work["sweep1"]
+        # the second sweep copies the anchors and the local window where they are a fifth of the kept rows and there are at most
+        # 384 hyperplanes: their rows are not the selection's
+        n_prot = comp.parts[0] + comp.parts[1]
+        if 5 * n_prot >= comp.B and wl.lsh_tables * wl.lsh_bits <= 384:
+            work["select"] = ("hbm", work["select"][1] - wl.n_kv_heads * n_prot * 4 * wl.head_dim * (2 if wl.dtype == "bf16" else 4))
     if args.attend:
         res["attend_cache"] = measure_attend(wl, comp, ddev, dev, cases=args.attend_case.split(","))
     if args.pipeline and args.batch == 1 and args.lse == "own":
