@@ -464,6 +464,12 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   const uint32_t k_col = (ld_pos ^ (ld_row & KX)) * 16, v_col = (ld_pos ^ (2 * v_swz<CH>(ld_row & 3))) * 16;
   const uint32_t v_i = tid % EPC, v_c = (tid / EPC) % CH, v_grp = tid / (EPC * CH);
   uint4 vpre[TR ? 1 : KL];
+  // bf16 rows of 256 bytes: the first waves bring the keys, and tiles against following references pass in a fixed order.
+  // Rows of 128 bytes have half the loads and half the products to put anything beside; both cost there (block of 4096 rows
+  // over 64 cache rows 124.4 us, 122.8 with all waves loading, 122.2 with the compiler's order too; 2048 rows over 3000 85.1,
+  // 84.5, 83.8; 64 rows over 31 681 32.2, 31.7, 31.7).
+  constexpr bool WIDE = TR && CH == 16;
+  constexpr int SHARE = WIDE ? 2 : 1;  // of the loads that a loading wave takes
   // Starts the loads of a chunk into a stage.  Rows past the segment's last one repeat it (they weigh nothing).  The
   // asynchronous loads come from the first wave of every SIMD: 64 KiB keep the address unit busy for a thousand clocks, and
   // while the first waves wait for it the second ones have the SIMDs to themselves.  From all waves, behind the barrier, both
@@ -477,9 +483,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
     const uint32_t rows = (uint32_t)(seg ? p.s_t : p.cache_len);
     const uint32_t dst = lds0 + stage * (STAGE * 16) + __builtin_amdgcn_readfirstlane(wave) * 1024;
     const uint32_t r0 = fresh(ld_row);
-    if (TR && upper) return;
+    if (WIDE && upper) return;
     // (fp32: every thread has its loads of V besides)
-    constexpr int N = TR ? 2 * KL : KL, ROWS = ROWS_PER_LOAD * KL / N, BYTES = ATT_THREADS * 16 * KL / N;
+    constexpr int N = SHARE * KL, ROWS = ROWS_PER_LOAD * KL / N, BYTES = ATT_THREADS * 16 * KL / N;
     if (kc0 + KC <= (int)rows) {
       const uint32_t k_off = r0 * kstride + k_col, v_off = r0 * vstride + v_col;
 #pragma unroll
@@ -738,20 +744,20 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
   // and that the one before has been left.
   constexpr int RC = 64;                                     // keys per ring stage
   constexpr uint32_t R_V = RC * CH * 16, R_STAGE = 2 * R_V;  // bytes of K in a stage, and of K and V
-  constexpr int R_LOADS = 2 * RC * CH / ATT_THREADS;         // per thread of the first waves, tensor and chunk
+  constexpr int R_LOADS = SHARE * RC * CH / ATT_THREADS;     // per loading thread, tensor and chunk
   // (not in the workgroup whose waves share the middle tile of an odd number from the start)
   const bool middle = (n_tiles & 1) && pg == (n_pairs - 1) / 4;
   const int ring_keys = BF16 && RING && fixed && !middle ? (hi0 - lo0) & ~(2 * RC - 1) : 0;
   const int n_ring = ring_keys / RC;
   auto ring_prefetch = [&](int c) {
-    if (upper) return;
+    if (WIDE && upper) return;
     const srd_words ksrd = make_srd_words(k_base0, c_bytes), vsrd = make_srd_words(v_base0, c_bytes);
     const uint32_t r0 = fresh(ld_row) * (uint32_t)p.row_bytes, src = (uint32_t)(lo0 + c * RC) * (uint32_t)p.row_bytes;
     const uint32_t dst = lds0 + (c & 3) * R_STAGE + __builtin_amdgcn_readfirstlane(wave) * 1024;
 #pragma unroll
     for (int u = 0; u < R_LOADS; ++u) {
-      async_ld16(ksrd, r0 + k_col, src + u * (ROWS_PER_LOAD / 2) * (uint32_t)p.row_bytes, dst + u * (ATT_THREADS * 8));
-      async_ld16(vsrd, r0 + v_col, src + u * (ROWS_PER_LOAD / 2) * (uint32_t)p.row_bytes, dst + R_V + u * (ATT_THREADS * 8));
+      async_ld16(ksrd, r0 + k_col, src + u * (ROWS_PER_LOAD / SHARE) * (uint32_t)p.row_bytes, dst + u * (ATT_THREADS * 16 / SHARE));
+      async_ld16(vsrd, r0 + v_col, src + u * (ROWS_PER_LOAD / SHARE) * (uint32_t)p.row_bytes, dst + R_V + u * (ATT_THREADS * 16 / SHARE));
     }
   };
   auto ring = [&](bool has_ref) {
@@ -938,6 +944,48 @@ __global__ __launch_bounds__(ATT_THREADS) void attend_rows_kernel(AttendParams p
               weigh(acc0, va);
               soft(acc1);
               weigh(acc1, vb);
+            }
+          } else if constexpr (!WIDE) {
+            auto raise = [&](const f32x16& acc) {  // the reference, to the row's maximum in a tile
+              float mx = acc[0];
+#pragma unroll
+              for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+              mx = half_pair_max(mx);
+              const float m_new = mx > NEG_BIG ? fmaxf(m_ref, fmaf(mx, p.scale2, HEADROOM)) : m_ref;
+              if (__any(m_new > m_ref && l_sum > 0.0f)) {  // nothing to rescale before the first keys
+                const float f = fast_exp2(m_ref - m_new);
+                l_sum *= f;
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                  for (int r = 0; r < 16; ++r) o[dt][r] *= f;
+              }
+              m_ref = m_new;
+              m_sub = m_new > NEG_BIG ? m_new : 0.0f;
+            };
+#pragma unroll
+            for (int T = 0; T < TPC; T += 2) {
+              if (left <= T) break;
+              f32x16 acc0, acc1;
+              uint4 kf[NCH], vf[RUNS * NDT];
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(kx[i] + T * K_TILE);
+              logits(kf, acc0);
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) kf[i] = lds_ld16(kx[i] + (T + 1) * K_TILE);
+              logits(kf, acc1);
+              if (!whole) {
+                hide(acc0, n_vis - T * 32);
+                hide(acc1, n_vis - T * 32 - 32);
+              }
+              load_v_tr(vx, T * V_TILE, vf);
+              raise(acc0);
+              soft(acc0);
+              weigh(acc0, vf);
+              load_v_tr(vx, (T + 1) * V_TILE, vf);
+              raise(acc1);
+              soft(acc1);
+              weigh(acc1, vf);
             }
           } else {
             // The products of a tile with the keys beside the exponentials of the tile before, those with the values beside
