@@ -729,7 +729,9 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void pass_kernel(PassParams p) {
 // ---------------------------------------------------------------------------------------------
 constexpr int COUNT_THREADS = 1024;
 constexpr int COUNT_KEYS_PER_THREAD = 8;  // keys_per_range <= COUNT_THREADS * COUNT_KEYS_PER_THREAD
-template <bool VEC>
+// OCTETS: the layout of sig_k (asked for at run time it cost a block's call, whose codes never lie so, 22.7 -> 23.0 us: 512 keys,
+// 32 tables of 16 bits)
+template <bool VEC, bool OCTETS>
 __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
   extern __shared__ uint32_t bins[];  // [tables_per_group << n_bits] / 2 words, then the query codes
   constexpr int KPT = COUNT_KEYS_PER_THREAD;
@@ -746,13 +748,12 @@ __global__ __launch_bounds__(COUNT_THREADS) void count_kernel(CountParams p) {
   const int n_bin_words = (p.tables_per_group << p.n_bits) >> 1;
   uint16_t* sQ = reinterpret_cast<uint16_t*>(bins + ((n_bin_words + 3) & ~3));  // [ntw][nq]
   const uint16_t* gq = p.sig_q + (size_t)h * nq * p.n_tables + t_first;
-  const uint16_t* gk = p.sig_k + (size_t)h * p.key_stride * p.n_tables;
-  const int pitch = p.octets ? 8 : p.n_tables;  // from a key's codes to the next key's
+  const int pitch = OCTETS ? 8 : p.n_tables;  // from a key's codes to the next key's
+  const uint16_t* gk = p.sig_k + (size_t)h * p.key_stride * p.n_tables + (size_t)i0 * pitch + (OCTETS ? 0 : t_first);
 
   uint4 next[KPT];  // VEC: the codes of eight tables; else .x: of one
   auto fetch = [&](int t) {
-    t += t_first;
-    const uint16_t* gt = gk + (size_t)i0 * pitch + (p.octets ? (size_t)(t >> 3) * p.key_stride * 8 + (t & 7) : (size_t)t);
+    const uint16_t* gt = gk + (OCTETS ? (size_t)((t_first + t) >> 3) * p.key_stride * 8 + ((t_first + t) & 7) : (size_t)t);
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
       if (k * COUNT_THREADS >= n_keys) break;  // workgroup-uniform
@@ -1334,9 +1335,11 @@ static hipError_t pass_attrs() {
 }
 
 hipError_t init_kernel_attributes() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&count_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&count_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const void* counts[] = {reinterpret_cast<const void*>(&count_kernel<true, true>), reinterpret_cast<const void*>(&count_kernel<true, false>),
+                          reinterpret_cast<const void*>(&count_kernel<false, true>), reinterpret_cast<const void*>(&count_kernel<false, false>)};
+  hipError_t e = hipSuccess;
+  for (const void* f : counts)
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess) e = pass_attrs<DT_BF16, 128>();
   if (e == hipSuccess) e = pass_attrs<DT_BF16, 64>();
   if (e == hipSuccess) e = pass_attrs<DT_F32, 128>();
@@ -1363,8 +1366,10 @@ hipError_t launch_count(const CountParams& p, int n_groups, hipStream_t st) {
   dim3 grid(n_kr, n_wg_t, n_groups);
   // every workgroup's tables are whole aligned groups of eight
   const bool vec = (p.groups_per_wg * p.tables_per_group) % 8 == 0 && p.n_tables % 8 == 0;
-  if (vec) hipLaunchKernelGGL(count_kernel<true>, grid, dim3(COUNT_THREADS), lds, st, p);
-  else hipLaunchKernelGGL(count_kernel<false>, grid, dim3(COUNT_THREADS), lds, st, p);
+  if (vec && p.octets) hipLaunchKernelGGL((count_kernel<true, true>), grid, dim3(COUNT_THREADS), lds, st, p);
+  else if (vec) hipLaunchKernelGGL((count_kernel<true, false>), grid, dim3(COUNT_THREADS), lds, st, p);
+  else if (p.octets) hipLaunchKernelGGL((count_kernel<false, true>), grid, dim3(COUNT_THREADS), lds, st, p);
+  else hipLaunchKernelGGL((count_kernel<false, false>), grid, dim3(COUNT_THREADS), lds, st, p);
   return hipGetLastError();
 }
 
