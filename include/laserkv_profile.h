@@ -42,6 +42,20 @@ int laserkv_profile_end(laserkv_ctx* ctx, double* ms_per_kernel, int64_t* launch
  * Errors: LKV_EINVAL (null context, kernel_id >= LKV_N_KERNELS). */
 int laserkv_profile_isolate(laserkv_ctx* ctx, int32_t kernel_id);
 
+/* How laserkv_compress_layer cuts up a layer of these sizes (host only, nothing is launched).  lse_complete: whether the
+ * window rows' complete log-sum-exp comes from the caller; values are taken as rows that follow each other.  plan: HOST
+ * pointer to LKV_N_LAYER_PLAN entries.  Errors: LKV_EINVAL (null, or sizes that laserkv_compress_layer refuses). */
+typedef enum {
+  LKV_LAYER_STAT_RANGES = 0,  /* key ranges per (block, KV head) of the row statistics (0: complete ones) */
+  LKV_LAYER_STAT_KEYS = 1,    /* and keys in each */
+  LKV_LAYER_SCORE_RANGES = 2, /* the same of the scores */
+  LKV_LAYER_SCORE_KEYS = 3,
+  LKV_LAYER_COPIED_ROWS = 4,  /* protected rows per KV head that the score kernel copies to the cache: all of them, or none */
+  LKV_N_LAYER_PLAN = 5
+} laserkv_layer_plan_id;
+int laserkv_layer_plan(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_block, int32_t w, int32_t B, int32_t n, double alpha,
+                       int32_t lse_complete, int64_t* plan);
+
 #ifdef __cplusplus
 }
 #endif

@@ -20,7 +20,7 @@ LKV_WINDOW_AT_BLOCK_END = -(1 << 63)   # q_pos0 sentinel of laserkv.h
 EXPORTS = (
     "laserkv_create", "laserkv_destroy", "laserkv_last_error", "laserkv_budget",
     "laserkv_partition", "laserkv_select_block", "laserkv_append", "laserkv_compress_block",
-    "laserkv_profile_begin", "laserkv_profile_end", "laserkv_profile_isolate",
+    "laserkv_profile_begin", "laserkv_profile_end", "laserkv_profile_isolate", "laserkv_layer_plan",
     "laserkv_score_block", "laserkv_select_consensus", "laserkv_append_shared", "laserkv_set_row_lse",
     "laserkv_set_row_lse_complete", "laserkv_attend_workspace_bytes", "laserkv_attend_cache",
     "laserkv_attend_block_workspace_bytes", "laserkv_attend_block",
@@ -28,6 +28,7 @@ EXPORTS = (
     "laserkv_static_init", "laserkv_static_workspace_bytes", "laserkv_compress_block_static",
 )
 LKV_STATIC_SCRATCH_BYTES = 32 << 20
+LAYER_PLAN = ("stat_ranges", "stat_keys", "score_ranges", "score_keys", "copied_rows")
 KERNEL_NAMES = ("sweep1", "sweep2", "count", "select", "append", "attend", "single")
 
 
@@ -119,6 +120,8 @@ def load():
     lib.laserkv_profile_end.restype = C.c_int
     lib.laserkv_profile_isolate.argtypes = [vp, i32]
     lib.laserkv_profile_isolate.restype = C.c_int
+    lib.laserkv_layer_plan.argtypes = [vp, i64, i32, i32, i32, i32, C.c_double, i32, C.POINTER(i64)]
+    lib.laserkv_layer_plan.restype = C.c_int
     _lib = lib
     return lib
 
@@ -404,3 +407,11 @@ class LaserKV:
     def laserkv_profile_isolate(self, kernel):
         """kernel: a name from KERNEL_NAMES, or None to launch every kernel again."""
         self._check(self._lib.laserkv_profile_isolate(self._ctx, -1 if kernel is None else KERNEL_NAMES.index(kernel)))
+
+    def laserkv_layer_plan(self, n_tok, s_block, w, B, n, alpha, lse_complete=False):
+        """How laserkv_compress_layer cuts up a layer of these sizes: {name of LAYER_PLAN: value}."""
+        plan = (C.c_int64 * len(LAYER_PLAN))()
+        rc = self._lib.laserkv_layer_plan(self._ctx, n_tok, s_block, w, B, n, alpha, 1 if lse_complete else 0, plan)
+        if rc != LKV_OK:
+            raise LaserKVError(rc, "layer_plan: null, or sizes that compress_layer refuses")
+        return dict(zip(LAYER_PLAN, map(int, plan)))

@@ -1096,6 +1096,27 @@ int laserkv_profile_isolate(laserkv_ctx* ctx, int32_t kernel_id) {
   return LKV_OK;
 }
 
+int laserkv_layer_plan(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_block, int32_t w, int32_t B, int32_t n, double alpha,
+                       int32_t lse_complete, int64_t* plan) {
+  lkv::LayerParams p = {};
+  lkv::LayerPlan lp = {};
+  int32_t ke, kl, ke1, kl1;
+  if (!ctx || !plan || s_block < 1 || laserkv_partition(B, n, alpha, s_block, &p.n_anchor, &p.n_local, &ke, &kl) != LKV_OK) return LKV_EINVAL;
+  if (!layer_geometry(ctx, n_tok, s_block, w, lse_complete ? 0 : p.n_local, p, lp)) return LKV_EINVAL;
+  const int s_last = (int)(n_tok - (int64_t)(p.n_blocks - 1) * s_block);
+  if (s_last < w || laserkv_partition(B, n, alpha, s_last, &p.last_anchor, &p.last_local, &ke1, &kl1) != LKV_OK) return LKV_EINVAL;
+  p.n_kept = p.n_anchor + p.n_local + ke + kl;
+  p.last_kept = p.last_anchor + p.last_local + ke1 + kl1;
+  p.v.stride_row = (int64_t)ctx->cfg.head_dim * ctx->elem_size;
+  lkv::layer_plan_copies(&p);
+  plan[LKV_LAYER_STAT_RANGES] = lse_complete ? 0 : p.stat_splits;
+  plan[LKV_LAYER_STAT_KEYS] = lse_complete ? 0 : p.stat_keys;
+  plan[LKV_LAYER_SCORE_RANGES] = p.score_splits;
+  plan[LKV_LAYER_SCORE_KEYS] = p.score_keys;
+  plan[LKV_LAYER_COPIED_ROWS] = p.copies || p.last_copies ? (int64_t)(p.n_blocks - 1) * (p.n_anchor + p.n_local) + p.last_anchor + p.last_local : 0;
+  return LKV_OK;
+}
+
 int laserkv_profile_begin(laserkv_ctx* ctx) {
   if (!ctx) return fail(nullptr, LKV_EINVAL, "profile_begin: null context");
   ctx->ev_kind->clear();

@@ -38,6 +38,12 @@ def loop_positions(wl, dev, B, nb):
     return comp
 
 
+def layer_plan(wl, complete=False):
+    """How one call of this layer cuts up its keys, and the protected rows that its score kernel copies."""
+    comp = LayerCompressor(wl, DEV, max_blocks=1)
+    return comp.lib.laserkv_layer_plan(wl.l_ctx, wl.s_block, wl.window, comp.B, wl.n_div, wl.alpha, complete)
+
+
 def check_layer(wl, mutate=None, with_oracle=True, tol=2e-3):
     B = O.budget(wl.s_block, wl.l_ctx, wl.r_num, wl.r_den)
     data = synth.make_layer(wl, 1, O.partition(B, wl.n_div, wl.alpha, wl.s_block)[0])
@@ -205,3 +211,20 @@ def test_layer_calls_on_two_streams_and_a_first_call_under_capture():
         assert torch.equal(want, fresh.cache_pos[:, :n])
         comp.run_layer(dev)
         assert torch.equal(want, comp.cache_pos[:, :n])
+
+
+def test_the_plan_of_a_layer_call():
+    wl = synth.WORKLOADS["llama8b-16k"]
+    lib, B = LayerCompressor(wl, DEV, max_blocks=1).lib, O.budget(wl.s_block, wl.l_ctx, wl.r_num, wl.r_den)
+    plan = lib.laserkv_layer_plan(wl.l_ctx, wl.s_block, wl.window, B, wl.n_div, wl.alpha)
+    n_prot = sum(O.partition(B, wl.n_div, wl.alpha, wl.s_block)[:2])
+    assert plan["copied_rows"] in (0, wl.n_blocks * n_prot)
+    for ranges, keys, n in [("stat_ranges", "stat_keys", wl.s_block + n_prot // 2), ("score_ranges", "score_keys", wl.s_block)]:
+        assert plan[keys] % 32 == 0 and (plan[ranges] - 1) * plan[keys] < n <= plan[ranges] * plan[keys]
+    complete = lib.laserkv_layer_plan(wl.l_ctx, wl.s_block, wl.window, B, wl.n_div, wl.alpha, True)
+    assert complete == {**plan, "stat_ranges": 0, "stat_keys": 0}
+    for bad in [dict(n_tok=0), dict(s_block=wl.s_block + 1), dict(w=wl.window + 1), dict(n=1), dict(alpha=1.5), dict(n_tok=wl.l_ctx + 1)]:
+        args = {**dict(n_tok=wl.l_ctx, s_block=wl.s_block, w=wl.window, B=B, n=wl.n_div, alpha=wl.alpha), **bad}
+        with pytest.raises(binding.LaserKVError) as err:
+            lib.laserkv_layer_plan(**args)
+        assert err.value.code == binding.LKV_EINVAL
