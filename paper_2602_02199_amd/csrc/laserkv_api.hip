@@ -803,7 +803,7 @@ int laserkv_compress_layer(laserkv_ctx* ctx,
   p.last_anchor = na1;
   p.last_local = nl1;
   p.last_kept = b_last;
-  lkv::layer_plan_copies(&p);
+  lkv::layer_plan_copies(d * es, ctx->n_cu, &p);
 
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   const int dt = c.dtype, n_groups = n_blocks * c.n_kv_heads;
@@ -1108,7 +1108,7 @@ int laserkv_layer_plan(const laserkv_ctx* ctx, int64_t n_tok, int32_t s_block, i
   p.n_kept = p.n_anchor + p.n_local + ke + kl;
   p.last_kept = p.last_anchor + p.last_local + ke1 + kl1;
   p.v.stride_row = (int64_t)ctx->cfg.head_dim * ctx->elem_size;
-  lkv::layer_plan_copies(&p);
+  lkv::layer_plan_copies(ctx->cfg.head_dim * ctx->elem_size, ctx->n_cu, &p);
   plan[LKV_LAYER_STAT_RANGES] = lse_complete ? 0 : p.stat_splits;
   plan[LKV_LAYER_STAT_KEYS] = lse_complete ? 0 : p.stat_keys;
   plan[LKV_LAYER_SCORE_RANGES] = p.score_splits;

@@ -217,7 +217,7 @@ struct LayerPlan {
 constexpr bool code_octets(int n_tables) { return (n_tables & 7) == 0; }
 bool layer_supports(int dtype, int head_dim, int m_rows);
 void layer_plan(int dtype, int head_dim, int n_cu, LayerParams* p, LayerPlan* plan);  // fills the launch geometry of both
-void layer_plan_copies(LayerParams* p);  // copies and last_copies, of the geometry, v and the parts of the kept rows
+void layer_plan_copies(int row_bytes, int n_cu, LayerParams* p);  // copies and last_copies, of the geometry, v and the parts of the kept rows
 hipError_t launch_layer_codes(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
 hipError_t launch_layer_stats(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);
 hipError_t launch_layer_score(int dtype, int head_dim, const LayerParams& p, const LayerPlan& plan, hipStream_t st);

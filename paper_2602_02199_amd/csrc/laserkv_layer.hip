@@ -791,21 +791,34 @@ static size_t score_lds(int head_dim, int es, int n_planes, int cell_total_words
          (size_t)2 * LY_HALF * LY_KC * 4 + (size_t)LY_ROWS * 8 + (size_t)cell_total_words * 4 + 16;
 }
 
-// Whether the score kernel copies the blocks' protected rows.  Where it has at least three chunks per workgroup to load and
-// store in (64 groups of four ranges of one chunk 34.3 us a layer, 35.3 with; of two chunks 46.0, 46.2; of three 51.1,
-// 48.9); at least a fifth of the kept rows are protected (16 blocks of 4096 at a divisor of 8 250.7, 244.8; of 16 263, 265);
-// and the plane tiles leave registers (four a wave: 60 bytes in scratch memory, groups of eight 577, 600).
-static bool copies_protected(const LayerParams& p) {
-  return p.score_keys >= 3 * LY_KC && 5 * (p.n_anchor + p.n_local) >= p.n_kept && p.n_planes <= 3 * 32 * LY_HALF;
+// Whether the score kernel copies the blocks' protected rows (us a layer: the selection copies them, this kernel does).
+//  - It has at least three chunks per workgroup to load and store in (64 groups of four ranges of one chunk 34.3, 35.3; of two
+//    46.0, 46.2; of three 51.1, 48.9), and at least a fifth of the kept rows are protected (16 blocks of 4096 at a divisor of
+//    8 250.7, 244.8; 32 blocks of 2048 at 10 167.1, 166.6, at 12 166.6, 167.0, at 16 166.4, 168.1).
+//  - Plane tiles leave registers (four a wave: 60 bytes in scratch memory, groups of eight 577, 600).
+//  - Its workgroups fill most of the chip.  Where they do not, neither do the selection's, which are no slower for the rows
+//    (groups of sixteen ranges of 512 keys: two groups 55.1, 56.2, four 55.0, 56.3, eight 56.4, 57.5; ten 59.8, 60.2, and at
+//    twice the budget 76.9, 63.6; twelve 61.1, 60.1).
+//  - A range has enough of them for what each workgroup pays: where a block is one range 48 (ranges of 384 keys with 40 of them
+//    52.2, 52.4, with 93 52.1, 50.8; of 512 with 62 60.2, 59.1), else 16 KiB of each tensor (four ranges of 512 keys, rows of 256
+//    bytes: 57 of them 61.0, 61.8, with 384 hyperplanes 69.9, 72.0; 60 61.5, 62.3; 76 60.2, 59.7; 114 60.9, 59.3, of 128 bytes
+//    43.0, 44.1).
+// There is no line above which it copies too many: at a divisor of 2 and twice the budget, where half of them are left to the
+// loop behind the last chunk, 128k layer 655, 612, 64k 219, 205, 16k 70.7, 69.0.
+static bool copies_protected(const LayerParams& p, int row_bytes, int n_cu, int rows) {
+  const int n_groups = p.n_blocks * p.n_kv_heads;
+  return p.score_keys >= 3 * LY_KC && 5 * (p.n_anchor + p.n_local) >= p.n_kept && p.n_planes <= 3 * 32 * LY_HALF &&
+         8 * n_groups * p.score_splits >= 5 * n_cu && (p.score_splits == 1 ? rows >= 48 : rows * row_bytes >= 16 * 1024);
 }
 
-void layer_plan_copies(LayerParams* p) {
+void layer_plan_copies(int row_bytes, int n_cu, LayerParams* p) {
   auto rows = [&](int s_t, int n_prot) {  // per range with keys
     const int n_rng = (s_t + p->score_keys - 1) / p->score_keys;
     return (n_prot + n_rng - 1) / n_rng;
   };
-  const bool copies = copies_protected(*p) && (int64_t)p->s_block * p->v.stride_row < (int64_t(1) << 31);  // 32-bit offsets
-  p->copies = copies ? rows(p->s_block, p->n_anchor + p->n_local) : 0;
+  const int each = rows(p->s_block, p->n_anchor + p->n_local);
+  const bool copies = copies_protected(*p, row_bytes, n_cu, each) && (int64_t)p->s_block * p->v.stride_row < (int64_t(1) << 31);  // 32-bit offsets
+  p->copies = copies ? each : 0;
   p->last_copies = copies ? rows(p->n_tok - (p->n_blocks - 1) * p->s_block, p->last_anchor + p->last_local) : 0;
 }
 

@@ -8,7 +8,7 @@ import torch
 from oracle import laserkv_oracle as O
 from paper_2602_02199_amd import synth
 from paper_2602_02199_amd.driver import LayerCompressor
-from tests.test_gpu_layer import oracle_positions
+from tests.test_gpu_layer import layer_plan, oracle_positions
 from tests.test_gpu_parity import DEV, f64, say, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -102,6 +102,17 @@ def test_equal_window_rows(tables, bits, heads, n_blocks):
 @pytest.mark.parametrize("s_block,l_ctx", [(640, 1664), (2048, 5000)])
 def test_longer_blocks(s_block, l_ctx):
     check_complete(synth.shrink(workload(4, 40, 16, 10), name=f"long-{s_block}", s_block=s_block, l_ctx=l_ctx))
+
+
+# the score kernel copies the protected rows: ten groups of sixteen ranges with a whole and a short last block, one range a block
+@pytest.mark.parametrize("dtype,head_dim", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("heads,n_blocks,s_block,last", [(2, 5, 6144, 6144), (2, 5, 6144, 385), (8, 32, 512, 500)])
+@pytest.mark.parametrize("tables,bits", [(16, 10), (32, 12)])
+def test_copies_of_protected_rows(heads, n_blocks, s_block, last, dtype, head_dim, tables, bits):
+    wl = synth.shrink(workload(2, 20, tables, bits, head_dim, dtype, heads, n_blocks), name=f"copies-{s_block}-{last}-{dtype}{head_dim}",
+                      s_block=s_block, l_ctx=(n_blocks - 1) * s_block + last, r_num=1, r_den=2)
+    assert layer_plan(wl, complete=True)["copied_rows"] > 0
+    check_complete(wl)
 
 
 def test_the_contexts_setting_holds_for_every_block():
