@@ -43,6 +43,14 @@ def algorithmic_work(wl, B):
     }
 
 
+def layer_work(wl, work, copied_rows):
+    """The same of one call for the layer, still per block: the key projection is part of the second sweep, which copies
+    `copied_rows` of a KV head's kept rows (of the whole layer, as the library says); the selection copies the others."""
+    es = 2 if wl.dtype == "bf16" else 4
+    copied = wl.n_kv_heads * copied_rows / wl.n_blocks * 4 * wl.head_dim * es
+    return {**work, "sweep1": work["sweep2"], "sweep2": work["sweep1"], "select": ("hbm", work["select"][1] - copied)}
+
+
 def measured_traffic(workload, lse, whole_layer, kernel):
     """HBM bytes per launch of a kernel kind as profiled, or None: a launch of the layer call takes all blocks, one of the
     block calls a block."""
@@ -176,13 +184,9 @@ def measure(wl, args, dev, cpu_seconds):
     work = algorithmic_work(wl, comp.B)
     if not args.unfused:  # the last kernel selects and appends
         work["select"] = ("hbm", work["select"][1] + work["append"][1])
-    if len(plan) < wl.n_blocks:  # one call for the layer: the key projection is part of the second sweep
-        work["sweep1"], work["sweep2"] = work["sweep2"], work["sweep1"]
-        # the second sweep copies the anchors and the local window where they are a fifth of the kept rows and there are at most
-        # 384 hyperplanes: their rows are not the selection's
-        n_prot = comp.parts[0] + comp.parts[1]
-        if 5 * n_prot >= comp.B and wl.lsh_tables * wl.lsh_bits <= 384:
-            work["select"] = ("hbm", work["select"][1] - wl.n_kv_heads * n_prot * 4 * wl.head_dim * (2 if wl.dtype == "bf16" else 4))
+    if len(plan) < wl.n_blocks:  # one call for the layer
+        cut = comp.lib.laserkv_layer_plan(wl.l_ctx, wl.s_block, wl.window, comp.B, wl.n_div, wl.alpha, args.lse == "complete")
+        work = layer_work(wl, work, cut["copied_rows"])
     if args.attend:
         res["attend_cache"] = measure_attend(wl, comp, ddev, dev, cases=args.attend_case.split(","))
     if args.pipeline and args.batch == 1 and args.lse == "own":
