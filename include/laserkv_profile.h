@@ -19,15 +19,18 @@ extern "C" {
  * later ones run untimed.  Errors: LKV_EINVAL (null / not begun), LKV_EHIP. */
 typedef enum {
   LKV_KERN_SWEEP1 = 0, /* exact score sweep 1 (row maxima and sums) + SimHash codes of keys and window queries
-                          + histograms of the query codes */
-  LKV_KERN_SWEEP2 = 1, /* exact score sweep 2 (pooled probabilities) + collision counts by histogram lookup */
+                          + histograms of the query codes; of a layer call without the codes of the keys */
+  LKV_KERN_SWEEP2 = 1, /* exact score sweep 2 (pooled probabilities) + collision counts by histogram lookup; of a layer
+                          call with the codes of the keys, and it copies protected rows (laserkv_layer_plan) */
   LKV_KERN_COUNT = 2,  /* collision counts as a kernel of their own (codes wider than 12 bits) */
-  LKV_KERN_SELECT = 3, /* two-stage TopK and compaction (with the gather in laserkv_compress_block); also the
-                          accumulation kernel of laserkv_score_block */
+  LKV_KERN_SELECT = 3, /* two-stage TopK and compaction (with the gather in laserkv_compress_block and of the rows that
+                          are not copied yet in laserkv_compress_layer); also the accumulation kernel of
+                          laserkv_score_block */
   LKV_KERN_APPEND = 4, /* gather-append as a kernel of its own */
   LKV_KERN_ATTEND = 5, /* attention over the compacted cache (both of its kernels) */
   LKV_KERN_SINGLE = 6, /* the one sweep of a block whose rows come with their complete log-sum-exp: SimHash codes,
-                          pooled probabilities and collision counts from one read of the keys */
+                          pooled probabilities and collision counts from one read of the keys (of a layer call the
+                          window rows' codes and the scores, which copy protected rows as above) */
   LKV_N_KERNELS = 7
 } laserkv_kernel_id;
 #define LKV_PROFILE_MAX_LAUNCHES 8192

@@ -196,8 +196,8 @@ struct LayerParams {
   int32_t* cnt;          // [groups, s_stride]
   uint16_t* sig_k;       // when cells is null: [groups, L / 8, s_stride, 8] where code_octets, else [groups, s_stride, L]
   uint16_t* sig_q;       // [groups, M, L] when cells is null
-  // the blocks' protected rows, which the score kernel copies to the cache: this many per key range of a block, and of the
-  // last one (0: the selection copies them)
+  // the blocks' protected rows, where the score kernel copies them to the cache: this many per key range of a block, and of
+  // the last one (both 0: the selection copies them)
   int copies, last_copies;
   RowSrc v;              // [H_kv, n_tok, d]
   char* k_cache;

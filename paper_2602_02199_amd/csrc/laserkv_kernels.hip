@@ -858,8 +858,9 @@ constexpr int SEL_PARTS = 1024;  // 16 per lane
 constexpr int SEL_BUFFERS = 3;
 constexpr uint32_t SEL_SCORES = (16u << 23) - 1u;  // bit patterns of 16 octaves
 
-// LAYER = true (with FUSED): the groups are all (block, KV head) pairs of a layer, whose protected rows layer_score_kernel
-// copies (but for those of huge strides).
+// LAYER = true (with FUSED): the groups are all (block, KV head) pairs of a layer.  Where layer_plan_copies decides so
+// (ly.copied; the conditions stand at copies_protected) layer_score_kernel has copied their protected rows, and only their
+// positions are left to write.
 template <int NT, int EPT, bool FUSED, bool LAYER>
 __global__ __launch_bounds__(NT) void select_kernel(SelectParams p, AppendParams ap, SelectLayer ly, int split) {
   __shared__ __align__(16) uint32_t sHist[SEL_BUFFERS][SEL_PARTS];
@@ -1433,7 +1434,7 @@ hipError_t launch_select_append(const SelectParams& p, const AppendParams& ap, i
 
 hipError_t launch_select_layer(const SelectParams& p, const AppendParams& ap, const SelectLayer& ly, int n_cu, hipStream_t st) {
   const int n_groups = (ly.last + 1) * p.n_kv_heads;
-  // the others are layer_score_kernel's
+  // rows that are copied here: where layer_score_kernel has taken the protected ones, the others
   const int rows = ly.copied ? max(p.k_exact + p.k_lsh, ly.last_exact + ly.last_lsh) : p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
   const int threads = select_threads(p.s_t, true);  // 2048 fit a compute unit
   // Every workgroup of a group selects, and an XCD starts eight workgroups in a microsecond: one chunk per thread made up to

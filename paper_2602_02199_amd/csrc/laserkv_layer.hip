@@ -277,9 +277,9 @@ __global__ __launch_bounds__(LY_THREADS) void layer_stats_kernel(LayerParams p) 
 // hashing wave two of the previous plane tile's signs.  A hashing wave first finishes the chunk before, served before the
 // score wave of its SIMD, and then takes its products on equal terms: what is left at the barrier is then the score waves'
 // (128k layer 227 -> 214-218 us, 64k 74.7 -> 68.5, 16k 23.6 -> 22.7, groups of eight 249 -> 240-245; with the hashing waves
-// served first throughout and finishing last 227, never served first 251).  Keys arrive by asynchronous loads (KeyRing);
-// partials of the statistics are fetched eight at a time.  Earlier, with the order left to the compiler, keys
-// through registers, serial loads at the start, plane tiles past the last one multiplied too).  What the counting needs is
+// served first throughout and finishing last 227, never served first 251; ranges shorter than a chunk, where nothing is
+// interleaved, the same within 1 %: layers in blocks of 72, 128 and 256 keys 37.0 -> 36.5, 32.9 -> 33.0, 39.3 -> 39.0).  Keys
+// arrive by asynchronous loads (KeyRing); partials of the statistics are fetched eight at a time.  What the counting needs is
 // computed from the thread's number chunk by chunk: kept in registers across the loop it went to scratch memory, whose loads
 // wait for the keys on their way (groups of eight 267 us instead of 246, one chunk per workgroup 21.1 instead of 18.9).
 // ---------------------------------------------------------------------------------------------
@@ -644,7 +644,8 @@ __global__ __launch_bounds__(LY_THREADS) void layer_score_kernel(LayerParams p) 
   // Rows that are kept whatever the scores (the block's first n_anchor and last n_local) go to the cache from here: this
   // kernel leaves the memory idle, and the selection behind it, which is bound by it, has so much less to copy (a quarter to
   // a half of the kept rows at divisors of 8 and 4).  A piece is 16 bytes of a key and of its value; each range takes a share
-  // of them, its threads two a chunk, loaded in one chunk and stored in the next.  Offsets are 32-bit ones into descriptors (64-bit addresses took 0.5 us a
+  // of them, its threads two a chunk, loaded in one chunk and stored in the next; what is left then (divisors below 4 and
+  // larger budgets) follows behind the last chunk.  Offsets are 32-bit ones into descriptors (64-bit addresses took 0.5 us a
   // chunk), past whose end nothing is loaded or stored.
   constexpr int PIECES = 2, STEP = LY_HALF * 64 / CH;  // rows from one of a thread's pieces to its next
   const bool last_blk = gr.b == p.n_blocks - 1;
@@ -803,12 +804,13 @@ static size_t score_lds(int head_dim, int es, int n_planes, int cell_total_words
 //    52.2, 52.4, with 93 52.1, 50.8; of 512 with 62 60.2, 59.1), else 16 KiB of each tensor (four ranges of 512 keys, rows of 256
 //    bytes: 57 of them 61.0, 61.8, with 384 hyperplanes 69.9, 72.0; 60 61.5, 62.3; 76 60.2, 59.7; 114 60.9, 59.3, of 128 bytes
 //    43.0, 44.1).
-// There is no line above which it copies too many: at a divisor of 2 and twice the budget, where half of them are left to the
-// loop behind the last chunk, 128k layer 655, 612, 64k 219, 205, 16k 70.7, 69.0.
+// Rows of 128 bytes and fp32 likewise (128k layer of dimension 64 at a divisor of 4 349.5, 334.5, fp32 layer of 32k 224.4,
+// 214.2).  There is no line above which it copies too many: at a divisor of 2 and twice the budget, where half of them are left
+// to the loop behind the last chunk, 128k layer 655, 612, 64k 219, 205, 16k 70.7, 69.0.
 static bool copies_protected(const LayerParams& p, int row_bytes, int n_cu, int rows) {
-  const int n_groups = p.n_blocks * p.n_kv_heads;
+  const int64_t n_wg = (int64_t)p.n_blocks * p.n_kv_heads * p.score_splits;
   return p.score_keys >= 3 * LY_KC && 5 * (p.n_anchor + p.n_local) >= p.n_kept && p.n_planes <= 3 * 32 * LY_HALF &&
-         8 * n_groups * p.score_splits >= 5 * n_cu && (p.score_splits == 1 ? rows >= 48 : rows * row_bytes >= 16 * 1024);
+         8 * n_wg >= 5 * n_cu && (p.score_splits == 1 ? rows >= 48 : rows * row_bytes >= 16 * 1024);
 }
 
 void layer_plan_copies(int row_bytes, int n_cu, LayerParams* p) {

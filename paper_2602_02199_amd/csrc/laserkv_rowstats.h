@@ -65,8 +65,10 @@ __device__ __forceinline__ void row_stats(uint4* smem, srd_words ksrd, uint32_t 
   constexpr int KC = L::KC, TPC = KC / 32, S = L::STAGES;
   // Waves that bring the keys in.  In long ranges the first wave of every SIMD: the address unit takes some five hundred clocks
   // for a chunk, and the second waves have the SIMDs to themselves meanwhile (512 rows over 63 520 keys 70.0 -> 68.1 us, 128k
-  // layer 477.6 -> 476.6; fp32 likewise: 256 rows over 9000 keys 49.6 -> 48.6).  In short ranges all of them, the first keys are
-  // there sooner (256 rows over 31 681 keys 28.15 us, 28.4 with half of them; over 74 keys 9.6, 9.7).
+  // layer 477.6 -> 476.6).  In short ranges all of them, the first keys are there sooner (256 rows over 31 681 keys 28.15 us, 28.4
+  // with half of them; over 74 keys 9.6, 9.7).  In fp32, whose tiles take several times as long, the first ones always: dimension
+  // 128, 32 rows a head over 9000 keys 29.2 -> 28.3, over 4000 17.5 -> 17.2, short ranges the same (over 64, 500 and 2000 keys 10.3,
+  // 10.9 and 13.1 with all waves, 10.4, 11.0 and 13.1).
   constexpr int LOADERS = LONG || DT == DT_F32 ? RS_WAVES / 2 : RS_WAVES;
   constexpr int LOADS = KC * CH / (LOADERS * 64);  // each, per stage
   // registers for a second tile's logits (in fp32 matrix instructions take nearly all of the time: twice the code is slower)
