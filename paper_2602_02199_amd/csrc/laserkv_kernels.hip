@@ -1436,7 +1436,9 @@ hipError_t launch_select_layer(const SelectParams& p, const AppendParams& ap, co
   const int n_groups = (ly.last + 1) * p.n_kv_heads;
   // rows that are copied here: where layer_score_kernel has taken the protected ones, the others
   const int rows = ly.copied ? max(p.k_exact + p.k_lsh, ly.last_exact + ly.last_lsh) : p.n_anchor + p.n_local + p.k_exact + p.k_lsh;
-  const int threads = select_threads(p.s_t, true);  // 2048 fit a compute unit
+  // 2048 threads to a compute unit, of which it takes seven waves a SIMD at a time from four positions per thread on (their
+  // scalar registers)
+  const int threads = select_threads(p.s_t, true);
   // Every workgroup of a group selects, and an XCD starts eight workgroups in a microsecond: one chunk per thread made up to
   // 2048 workgroups of few rows (layer of 16k, 64 groups: 65.3 us; four: 62.8; 12 blocks of 1238 keys, 4 heads: 34.3, 28.7;
   // where all workgroups have more rows anyway the same).
